@@ -36,10 +36,11 @@ extern "C" mrh_status mrh_map_check(mrh_map* map, mrh_check* out) {
     const DevMap& d = map->dm;
     const size_t nh = (size_t)d.hmask + 1;
     const uint32_t nb = c.n_blocks < d.max_blocks ? c.n_blocks : d.max_blocks;
-    std::vector<unsigned long long> hkeys, bkey;
-    std::vector<uint32_t> hvals, binfo;
-    if (st == MRH_OK) st = fetch(map, hkeys, d.hkeys, nh, "check");
-    if (st == MRH_OK) st = fetch(map, hvals, d.hvals, nh, "check");
+    std::vector<HashSlot> table;
+    std::vector<unsigned long long> bkey;
+    std::vector<uint32_t> binfo, bslot;
+    if (st == MRH_OK) st = fetch(map, table, d.table, nh, "check");
+    if (st == MRH_OK) st = fetch(map, bslot, d.bslot, nb, "check");
     if (st == MRH_OK) st = fetch(map, bkey, d.bkey, nb, "check");
     if (st == MRH_OK) st = fetch(map, binfo, d.binfo, nb, "check");
     if (st != MRH_OK) return st;
@@ -49,7 +50,7 @@ extern "C" mrh_status mrh_map_check(mrh_map* map, mrh_check* out) {
     where.reserve(nh / 2);
     double probe_sum = 0.0;
     for (size_t h = 0; h < nh; ++h) {
-        const unsigned long long k = hkeys[h];
+        const unsigned long long k = table[h].key;
         if (k == kEmptyKey) continue;
         if (k == kTombstone) {
             ++out->tombstones;
@@ -64,17 +65,18 @@ extern "C" mrh_status mrh_map_check(mrh_map* map, mrh_check* out) {
         uint32_t dist = ((uint32_t)h - home) & d.hmask;
         bool blocked = false;
         for (uint32_t s = home; s != (uint32_t)h; s = (s + 1) & d.hmask)
-            if (hkeys[s] == kEmptyKey) {
+            if (table[s].key == kEmptyKey) {
                 blocked = true;
                 break;
             }
         if (blocked || (int64_t)dist + 1 > (int64_t)d.max_probe) ++out->unreachable_keys;
         probe_sum += (double)dist + 1.0;
         if ((int32_t)dist + 1 > out->max_probe) out->max_probe = (int32_t)dist + 1;
-        const uint32_t id = hvals[h];
+        const uint32_t id = table[h].id;
         if (id == kInvalidId) {
             ++out->idless_keys;  // a key inserted when the block table was full
-        } else if (id >= nb || bkey[id] != k || (binfo[id] & kGoneBit)) {
+        } else if (id >= nb || bkey[id] != k || (binfo[id] & kGoneBit) || bslot[id] != h ||
+                   ((table[h].info ^ binfo[id]) & ~kNewBit)) {
             ++out->bad_table_entries;
         }
     }
@@ -98,7 +100,7 @@ extern "C" mrh_status mrh_map_check(mrh_map* map, mrh_check* out) {
             continue;
         }
         auto it = where.find(bkey[id]);
-        if (it == where.end() || hvals[it->second] != id) ++out->unreachable_keys;
+        if (it == where.end() || table[it->second].id != id) ++out->unreachable_keys;
         if (info & kNoBlockBit) {
             ++out->slotless_blocks;  // a key that found its level-0 heap empty
             continue;

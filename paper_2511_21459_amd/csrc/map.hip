@@ -49,7 +49,7 @@ bool pose_from(const double* T, Pose& P) {
 __global__ void k_reset(const DevMap* __restrict__ pm, uint32_t n_hash) {
     const DevMap& m = *pm;
     const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
-    for (uint32_t i = tid; i < n_hash; i += stride) m.hkeys[i] = kEmptyKey;
+    for (uint32_t i = tid; i < n_hash; i += stride) m.table[i] = HashSlot{kEmptyKey, kInvalidId, kNoBlockBit};
     for (int n = 0; n < m.levels; ++n) {
         const uint32_t cap = (uint32_t)m.heap_cap[n];
         for (uint32_t i = tid; i < cap; i += stride) m.stack[n][i] = cap - 1 - i;  // pops give 0, 1, 2, ...
@@ -132,7 +132,7 @@ const char* mrh_last_error(const mrh_map* map) { return map ? map->err : "null m
 static void free_all(mrh_map* m) {
     stream_free(m);
     DevMap& d = m->dm;
-    void* ptrs[] = {d.hkeys, d.hvals, d.bkey, d.binfo, d.bvsum, d.bvcnt, m->ctr, m->partials, m->pose_out, m->dmd,
+    void* ptrs[] = {d.table, d.bslot, d.bkey, d.binfo, d.bvsum, d.bvcnt, m->ctr, m->partials, m->pose_out, m->dmd,
                     m->count_dev, m->mesh_order};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -207,8 +207,8 @@ mrh_status mrh_map_create(const mrh_config* cfg, void* stream, mrh_map** out) {
         st = check_hip(m, hipMalloc(p, bytes ? bytes : 16), what);
     };
     const size_t nh = (size_t)c.hash_slots, nb = (size_t)c.max_blocks;
-    alloc((void**)&d.hkeys, nh * 8, "hash keys");
-    alloc((void**)&d.hvals, nh * 4, "hash values");
+    alloc((void**)&d.table, nh * sizeof(HashSlot), "hash table");
+    alloc((void**)&d.bslot, nb * 4, "block hash slots");
     alloc((void**)&d.bkey, nb * 8, "block keys");
     alloc((void**)&d.binfo, nb * 4, "block info");
     alloc((void**)&d.bvsum, nb * 8, "block variance sums");

@@ -553,8 +553,7 @@ __global__ __launch_bounds__(kMeshThreads) void k_mesh(const DevMap* __restrict_
             if (ox == 0 && oy == 0 && oz == 0) {
                 ni = info;
             } else {
-                const uint32_t bid = find_block(m, pack_key(b[0] + ox, b[1] + oy, b[2] + oz));
-                if (bid != kInvalidId) ni = m.binfo[bid];
+                ni = find_slot(m, pack_key(b[0] + ox, b[1] + oy, b[2] + oz)).info;
             }
             nbw[lane] = ni;
         }

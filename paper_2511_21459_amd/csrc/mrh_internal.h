@@ -1,9 +1,11 @@
 // Internal layout and device helpers of the mrhash library (gfx950).
 //
 // Map layout in HBM (all arrays allocated once at map creation):
-//   hash table   hkeys[u64 n_hash] packed block keys (EMPTY = all ones), hvals[u32 n_hash] block id
+//   hash table   table[n_hash] slots of 16 bytes: packed block key (EMPTY = all ones), block id, and
+//                the block's row as in binfo
 //   block table  bkey[u64 max_blocks], binfo[u32] = heap slot | level << 27 | NEW | NOBLOCK,
-//                bvsum[f64] = sum over voxels with W >= min_obs of S2 / W, bvcnt[u32] = their count
+//                bslot[u32] its hash slot, bvsum[f64] = sum over voxels with W >= min_obs of S2 / W,
+//                bvcnt[u32] = their count
 //   heaps        per level n: D, W, S2 planes of heap_blocks[n] blocks x (8 >> n)^3 voxels, voxels
 //                of a block in Morton (Z) order so the 2x2x2 children of a coarse voxel are
 //                contiguous; a free stack of slot indices and a pending-free list per level
@@ -67,10 +69,20 @@ struct alignas(128) DevCounters {
     unsigned long long frame[kStripes][16];  // statistics since the reset, in stripes
 };
 
+// One slot of the hash table: key, block id and the block's row (a copy of binfo[id]; its NEW bit may
+// be stale), so that a lookup ends with one 16-byte read of one line.  With keys, ids and rows in
+// three arrays it took three reads, each waiting for the one before, on three lines (a query has two
+// such chains, its own block's and its corners').
+struct alignas(16) HashSlot {
+    unsigned long long key;
+    uint32_t id;
+    uint32_t info;
+};
+
 // Everything a kernel needs to find the map; passed by value as a kernel argument.
 struct DevMap {
-    unsigned long long* hkeys;
-    uint32_t* hvals;
+    HashSlot* table;
+    uint32_t* bslot;
     uint32_t hmask;
     int32_t max_probe;
     unsigned long long* bkey;
@@ -168,7 +180,7 @@ __device__ inline uint32_t home_slot(unsigned long long key, uint32_t mask) {
 __device__ inline uint32_t probe_find(const DevMap& m, unsigned long long key, uint32_t* stop) {
     uint32_t h = home_slot(key, m.hmask);
     for (int p = 0; p < m.max_probe; ++p) {
-        const unsigned long long k = __hip_atomic_load(&m.hkeys[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long k = __hip_atomic_load(&m.table[h].key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (k == key) return h;
         if (k == kEmptyKey) {
             if (stop) *stop = h;
@@ -180,10 +192,33 @@ __device__ inline uint32_t probe_find(const DevMap& m, unsigned long long key, u
     return kInvalidId;
 }
 
-// Block id of `key`, or kInvalidId when absent (or inserted without a block id).
-__device__ inline uint32_t find_block(const DevMap& m, unsigned long long key) {
-    const uint32_t h = probe_find(m, key, nullptr);
-    return h == kInvalidId ? kInvalidId : m.hvals[h];
+// One slot, in one 16-byte read (launches that insert nothing).
+__device__ inline HashSlot load_slot(const DevMap& m, uint32_t h) {
+    const uint4 v = *reinterpret_cast<const uint4*>(m.table + h);
+    return HashSlot{(unsigned long long)v.x | ((unsigned long long)v.y << 32), v.z, v.w};
+}
+
+// The slot holding `key` given its home slot `h` (content `s`), in launches that insert nothing; an
+// absent key gives id kInvalidId and NOBLOCK.
+__device__ inline HashSlot follow_slot(const DevMap& m, unsigned long long key, uint32_t h, HashSlot s) {
+    for (int p = 1; s.key != key; ++p) {
+        if (s.key == kEmptyKey || p >= m.max_probe) return HashSlot{key, kInvalidId, kNoBlockBit};
+        h = (h + 1) & m.hmask;
+        s = load_slot(m, h);
+    }
+    return s;
+}
+
+__device__ inline HashSlot find_slot(const DevMap& m, unsigned long long key) {
+    const uint32_t h = home_slot(key, m.hmask);
+    return follow_slot(m, key, h, load_slot(m, h));
+}
+
+// A block's row and its copy in the hash table, after a merge (hslot = bslot[id], read by the caller
+// early enough to overlap its other reads).
+__device__ inline void set_row(const DevMap& m, uint32_t id, uint32_t hslot, uint32_t info) {
+    m.binfo[id] = info;
+    m.table[hslot].info = info;
 }
 
 enum InsertResult { INS_FOUND = 0, INS_NEW = 1, INS_FULL = 2 };
@@ -197,13 +232,13 @@ __device__ inline int probe_insert(const DevMap& m, unsigned long long key, uint
     uint32_t h = start;
     for (int p = 0; p < m.max_probe; ++p) {
         const unsigned long long k =
-            p == 0 ? kEmptyKey : __hip_atomic_load(&m.hkeys[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            p == 0 ? kEmptyKey : __hip_atomic_load(&m.table[h].key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (k == key) {
             *slot = h;
             return INS_FOUND;
         }
         if (k == kEmptyKey) {
-            const unsigned long long old = atomicCAS(&m.hkeys[h], kEmptyKey, key);
+            const unsigned long long old = atomicCAS(&m.table[h].key, kEmptyKey, key);
             if (old == kEmptyKey || old == key) {
                 *slot = h;
                 return old == key ? INS_FOUND : INS_NEW;

@@ -254,16 +254,16 @@ struct BoxWalk {
 };
 
 // The observations of one ray (segment a..e, surface point p, direction nn) inside the block
-// `key` (block id `id`, kInvalidId when it has none) that its walk visits: the block walk restricted
-// to the block's own voxel lattice.
+// of hash slot hs (NOBLOCK when its key has none) that its walk visits: the block walk restricted to
+// the block's own voxel lattice.
 template <int ST, bool QUEUE>
 __device__ inline void ray_block(const DevMap& m, const ScanParams& sp, const double a[3], const double e[3],
-                                 const double p[3], const double nn[3], unsigned long long key, uint32_t id,
-                                 unsigned long long* tab) {
+                                 const double p[3], const double nn[3], const HashSlot& hs, unsigned long long* tab) {
+    const unsigned long long key = hs.key;
+    const uint32_t id = hs.id, info = hs.info;
     int32_t bx, by, bz;
     unpack_key(key, bx, by, bz);
     const int64_t b[3] = {bx, by, bz};
-    const uint32_t info = id == kInvalidId ? kNoBlockBit : m.binfo[id];
     const int level = (int)((info >> kLevelShift) & 3u);
     const bool has = !(info & kNoBlockBit);
     unsigned long long groups = 0ull;  // the update's lane groups this ray touches in the block
@@ -401,10 +401,8 @@ __device__ inline void points_ray_chunk(const DevMap& m, const ScanParams& sp, u
                 sn[k] = seg[wv][j][9 + k];
             }
             const uint32_t slot = m.rslots[(size_t)i * K + (q - ej)];
-            const bool ok = slot != kInvalidId;
-            const unsigned long long key = ok ? m.hkeys[slot] : 0ull;
-            const uint32_t id = ok ? m.hvals[slot] : kInvalidId;
-            ray_block<ST, QUEUE>(m, sp, sa, se, sp3, sn, key, id, tab);
+            const HashSlot hs = slot != kInvalidId ? load_slot(m, slot) : HashSlot{0ull, kInvalidId, kNoBlockBit};
+            ray_block<ST, QUEUE>(m, sp, sa, se, sp3, sn, hs, tab);
         }
     }
     if (cnt > K) {
@@ -419,7 +417,7 @@ __device__ inline void points_ray_chunk(const DevMap& m, const ScanParams& sp, u
             const unsigned long long key = pack_key(w.c0, w.c1, w.c2);
             wsave[wv][lane] = w;
             __asm__ volatile("" ::: "memory");
-            ray_block<ST, QUEUE>(m, sp, a, e, p, nn, key, find_block(m, key), tab);
+            ray_block<ST, QUEUE>(m, sp, a, e, p, nn, find_slot(m, key), tab);
             __asm__ volatile("" ::: "memory");
             w = wsave[wv][lane];
             more = w.next();

@@ -102,6 +102,7 @@ template <int ST>
 __device__ inline void merge_fine_into(const DevMap& m, uint32_t id, uint32_t cslot, const float D[8],
                                        const uint32_t W[8], const float S2[8]) {
     const int lane = lane_id();
+    const uint32_t hslot = m.bslot[id];
     uint32_t Wc = 0;
     float sd = 0.f, s2 = 0.f;
     for (int q = 0; q < 8; ++q) {
@@ -119,7 +120,7 @@ __device__ inline void merge_fine_into(const DevMap& m, uint32_t id, uint32_t cs
     if (lane == 0) {
         m.bvsum[id] = csum;
         m.bvcnt[id] = (uint32_t)ccnt;
-        m.binfo[id] = cslot | (1u << kLevelShift);
+        set_row(m, id, hslot, cslot | (1u << kLevelShift));
     }
 }
 
@@ -128,6 +129,7 @@ __device__ inline void merge_fine_into(const DevMap& m, uint32_t id, uint32_t cs
 template <int ST>
 __device__ inline void merge_level1_into(const DevMap& m, uint32_t id, uint32_t cslot, float D, uint32_t W, float S2) {
     const int lane = lane_id();
+    const uint32_t hslot = m.bslot[id];
     uint32_t Wc = W;
     float sd = W ? (float)W * D : 0.f, s2 = W ? S2 : 0.f;
     Wc = group8_sum(Wc);
@@ -143,7 +145,7 @@ __device__ inline void merge_level1_into(const DevMap& m, uint32_t id, uint32_t 
     if (lane == 0) {
         m.bvsum[id] = csum;
         m.bvcnt[id] = (uint32_t)ccnt;
-        m.binfo[id] = cslot | (2u << kLevelShift);
+        set_row(m, id, hslot, cslot | (2u << kLevelShift));
     }
 }
 
@@ -329,6 +331,7 @@ __device__ inline int finish_coarse(const DevMap& m, uint32_t id, uint32_t info,
         }
         return 0;
     }
+    const uint32_t hslot = m.bslot[id];
     uint32_t Wc = W;
     float sd = W ? (float)W * D : 0.f, s2 = W ? S2 : 0.f;
     Wc = group8_sum(Wc);
@@ -344,7 +347,7 @@ __device__ inline int finish_coarse(const DevMap& m, uint32_t id, uint32_t info,
     if (lane == 0) {
         m.bvsum[id] = csum;
         m.bvcnt[id] = (uint32_t)ccnt;
-        m.binfo[id] = (uint32_t)cslot | ((uint32_t)(level + 1) << kLevelShift);
+        set_row(m, id, hslot, (uint32_t)cslot | ((uint32_t)(level + 1) << kLevelShift));
         push_pending(m, level, slot, par);
     }
     return 1;
@@ -385,6 +388,7 @@ __device__ inline int finish_packed(const DevMap& m, bool live, uint32_t id, uin
         return 0;
     }
     // only level 2 (seg = 8) can merge: pool the segment's 8 voxels into the single level-3 voxel
+    const uint32_t hslot = m.bslot[id];
     uint32_t Wc = W;
     float sd = W ? (float)W * D : 0.f, s2 = W ? S2 : 0.f;
     if (seg == 8) {
@@ -399,7 +403,7 @@ __device__ inline int finish_packed(const DevMap& m, bool live, uint32_t id, uin
         Store<ST>::put(m, level + 1, (size_t)cslot, Dc, Wc, Sc);
         m.bvsum[id] = var_term(m, Wc, Sc);
         m.bvcnt[id] = (uint32_t)var_count(m, Wc);
-        m.binfo[id] = (uint32_t)cslot | ((uint32_t)(level + 1) << kLevelShift);
+        set_row(m, id, hslot, (uint32_t)cslot | ((uint32_t)(level + 1) << kLevelShift));
         push_pending_wave(m, level, true, slot, par);
         return 1;
     }
@@ -562,7 +566,8 @@ __device__ inline void queue_block_wg(const DevMap& m, int level, uint32_t id, u
 __device__ inline void register_block(const DevMap& m, unsigned long long key, uint32_t slot, uint32_t id,
                                       uint32_t pop) {
     if (id >= m.max_blocks) {
-        m.hvals[slot] = kInvalidId;
+        m.table[slot].id = kInvalidId;
+        m.table[slot].info = kNoBlockBit;
         atomicOr(&m.ctr->error_flags.v, kErrBlockLimit);
         stat_add(m, S_FAILED, 1ull);
         return;
@@ -580,7 +585,9 @@ __device__ inline void register_block(const DevMap& m, unsigned long long key, u
     m.binfo[id] = info;
     m.bvsum[id] = 0.0;
     m.bvcnt[id] = 0;
-    m.hvals[slot] = id;
+    m.bslot[id] = slot;
+    m.table[slot].id = id;
+    m.table[slot].info = info;
 }
 
 // k new blocks: one atomic on the allocation word; returns the old word (ids and pops start there).

@@ -22,15 +22,6 @@ struct QueryResult {
     double grad[3];  // d sdf / d x (world)
 };
 
-// Block table row of `key` for a query corner: the home slot is read for all corners at once, and
-// only a corner whose home slot holds another key walks the probe sequence.
-__device__ inline uint32_t corner_info(const DevMap& m, unsigned long long key, unsigned long long home_key,
-                                       uint32_t home_slot_id) {
-    if (home_key == key) return m.hvals[home_slot_id];
-    if (home_key == kEmptyKey) return kInvalidId;
-    return find_block(m, key);
-}
-
 template <int ST>
 __device__ inline QueryResult query_point(const DevMap& m, const double x[3], bool strict) {
     QueryResult q;
@@ -44,9 +35,7 @@ __device__ inline QueryResult query_point(const DevMap& m, const double x[3], bo
         b[k] = (int64_t)fb;
     }
     const unsigned long long hkey = pack_key(b[0], b[1], b[2]);
-    const uint32_t id = find_block(m, hkey);
-    if (id == kInvalidId) return q;
-    const uint32_t info = m.binfo[id];
+    const uint32_t info = find_slot(m, hkey).info;
     if (info & kNoBlockBit) return q;
     const int n = (int)((info >> kLevelShift) & 3u);
     const int shift = 3 - n;
@@ -66,26 +55,24 @@ __device__ inline QueryResult query_point(const DevMap& m, const double x[3], bo
         cross[k] = (int)(((i0[k] + 1) >> shift) - blo[k]);
     }
     // rows of the (up to 8) distinct blocks, addressed by (dx, dy, dz) in {0, 1}^3; all home
-    // slots are read before any is examined
-    unsigned long long bkeys[8], hk[8];
-    uint32_t hs[8];
+    // slots are read before any is examined, and only a corner whose home slot holds another key
+    // walks the probe sequence
+    unsigned long long bkeys[8];
+    HashSlot home[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
         const int dx = c & 1, dy = (c >> 1) & 1, dz = (c >> 2) & 1;
         const bool need = (dx <= cross[0]) && (dy <= cross[1]) && (dz <= cross[2]);
         bkeys[c] = pack_key(blo[0] + dx, blo[1] + dy, blo[2] + dz);
-        hs[c] = home_slot(bkeys[c], m.hmask);
-        hk[c] = (!need || bkeys[c] == hkey) ? hkey : __hip_atomic_load(&m.hkeys[hs[c]], __ATOMIC_RELAXED,
-                                                                          __HIP_MEMORY_SCOPE_AGENT);
+        home[c] = HashSlot{bkeys[c], kInvalidId, kNoBlockBit};
+        if (need && bkeys[c] == hkey) home[c].info = info;
+        else if (need) home[c] = load_slot(m, home_slot(bkeys[c], m.hmask));
     }
     uint32_t binfo8[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-        const int dx = c & 1, dy = (c >> 1) & 1, dz = (c >> 2) & 1;
-        const bool need = (dx <= cross[0]) && (dy <= cross[1]) && (dz <= cross[2]);
-        uint32_t cid = kInvalidId;
-        if (need) cid = bkeys[c] == hkey ? id : corner_info(m, bkeys[c], hk[c], hs[c]);
-        binfo8[c] = cid == kInvalidId ? kNoBlockBit : (cid == id ? info : m.binfo[cid]);
+        binfo8[c] = home[c].info;
+        if (home[c].key != bkeys[c]) binfo8[c] = follow_slot(m, bkeys[c], home_slot(bkeys[c], m.hmask), home[c]).info;
     }
     // the 8 corner voxels: heap positions first, then all weight and TSDF reads
     double cw[8], cd[8];

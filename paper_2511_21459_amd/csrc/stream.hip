@@ -126,7 +126,7 @@ __global__ __launch_bounds__(256) void k_stream_out(const DevMap* __restrict__ p
         vsum[e] = m.bvsum[id];
         vcnt[e] = m.bvcnt[id];
         const uint32_t h = probe_find(m, key, nullptr);
-        if (h != kInvalidId) m.hkeys[h] = kTombKey;
+        if (h != kInvalidId) m.table[h].key = kTombKey;
         const int32_t at = atomicAdd(&m.ctr->top[level].v, 1);
         m.stack[level][at] = slot;
         m.binfo[id] = kNoBlockBit | kGoneBit;
@@ -164,7 +164,8 @@ __global__ __launch_bounds__(256) void k_stream_in(const DevMap* __restrict__ pm
                 id = (uint32_t)atomicAdd(reinterpret_cast<unsigned long long*>(&m.ctr->n_blocks), 1ull);
                 const int32_t t = atomicSub(&m.ctr->top[level].v, 1);
                 if (id >= m.max_blocks) {
-                    m.hvals[h] = kInvalidId;
+                    m.table[h].id = kInvalidId;
+                    m.table[h].info = kNoBlockBit;
                     atomicOr(&m.ctr->error_flags.v, kErrBlockLimit);
                     if (t > 0) atomicAdd(&m.ctr->top[level].v, 1);
                     outcome = 4;
@@ -173,14 +174,16 @@ __global__ __launch_bounds__(256) void k_stream_in(const DevMap* __restrict__ pm
                     atomicAdd(&m.ctr->top[level].v, 1);
                     atomicOr(&m.ctr->error_flags.v, kErrHeapFull);
                     m.bkey[id] = key;
-                    m.binfo[id] = kNoBlockBit;
-                    m.hvals[h] = id;
+                    m.bslot[id] = h;
+                    m.table[h].id = id;
+                    set_row(m, id, h, kNoBlockBit);
                     outcome = 5;
                     id = kInvalidId;
                 } else {
                     slot = m.stack[level][t - 1];
                     m.bkey[id] = key;
-                    m.hvals[h] = id;
+                    m.bslot[id] = h;
+                    m.table[h].id = id;
                     if (m.btouch) m.btouch[id] = 0ull;
                     outcome = 1;
                 }
@@ -218,7 +221,7 @@ __global__ __launch_bounds__(256) void k_stream_in(const DevMap* __restrict__ pm
     if (lane == 0) {
         m.bvsum[id] = s;
         m.bvcnt[id] = c;
-        m.binfo[id] = slot | ((uint32_t)level << kLevelShift);
+        set_row(m, id, m.bslot[id], slot | ((uint32_t)level << kLevelShift));
     }
 }
 
