@@ -158,7 +158,6 @@ __host__ __device__ constexpr int edge_c0(int e) {
 __host__ __device__ constexpr int edge_c1(int e) { return edge_c0(e) | (1 << (e >> 2)); }
 
 // Morton position of (i, j, k), coordinates below 8
-__device__ inline int spread3(int x) { return (x & 1) | ((x & 2) << 2) | ((x & 4) << 4); }
 __device__ inline int morton_of(int i, int j, int k) { return spread3(i) | (spread3(j) << 1) | (spread3(k) << 2); }
 
 // Per workgroup: the case table, and per wave the 27 blocks around its block (table row or

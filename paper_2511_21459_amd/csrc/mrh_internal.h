@@ -378,6 +378,10 @@ __host__ __device__ inline int morton3(int i, int j, int k) {
     return p;
 }
 
+// The bits of a coordinate below 8 at every third position: morton3(i, j, k) is
+// spread3(i) | spread3(j) << 1 | spread3(k) << 2.
+__host__ __device__ inline int spread3(int x) { return (x & 1) | ((x & 2) << 2) | ((x & 4) << 4); }
+
 __host__ __device__ inline void demorton3(int p, int& i, int& j, int& k) {
     i = j = k = 0;
     for (int b = 0; b < 3; ++b) {

@@ -1,6 +1,6 @@
 // Multi-resolution trilinear SDF query (Sec. 3.4) and its adjoint for points and a 6-DoF pose.
 //
-// One thread per point.  The point's block fixes the interpolation lattice (its level n); each of
+// Four lanes per point, two corners each.  The point's block fixes the interpolation lattice (its level n); each of
 // the 8 surrounding level-n lattice points takes the TSDF of the voxel, at whatever level its own
 // block has, whose cell contains it; corners without a block or with W = 0 drop out and the
 // remaining trilinear weights are renormalised.  Lattice indices and weights are FP64.
@@ -16,130 +16,118 @@ struct QueryParams {
     int32_t strict;
 };
 
+// The query of one point by 4 consecutive lanes: lane c = lane & 3 takes corners c and c + 4 (the two
+// along z); every lane of the group calls with the same x.  A query is a chain of reads (its block's
+// hash slot, the corners' slots, the voxels) behind about 1100 instructions when one lane does all 8
+// corners, which leaves the chip idle on small batches.  Measured with gradients on a 1 cm room, one / 8 / 4 lanes
+// per point: QUERY_TIMES
 struct QueryResult {
-    bool valid;
+    bool valid;      // the same on the group's lanes, as are the values
     double sdf;
     double grad[3];  // d sdf / d x (world)
 };
 
-template <int ST>
+// Sum over each group of 4 consecutive lanes, on every lane.
+__device__ inline double group4_sum(double v) {
+    v += dpp<kDppXor1>(v);
+    return v + dpp<kDppXor2>(v);
+}
+
+// The hash slot content of block (x, y, z).
+__device__ inline HashSlot block_slot(const DevMap& m, int32_t x, int32_t y, int32_t z) {
+    const unsigned long long key = pack_key(x, y, z);
+    const uint32_t h = spatial_hash(x, y, z) & m.hmask;
+    return follow_slot(m, key, h, load_slot(m, h));
+}
+
+template <int ST, bool GRAD>
 __device__ inline QueryResult query_point(const DevMap& m, const double x[3], bool strict) {
     QueryResult q;
     q.valid = false;
     q.sdf = 0.0;
     q.grad[0] = q.grad[1] = q.grad[2] = 0.0;
-    int64_t b[3];
+    const int c = lane_id() & 3;
+    int32_t b[3];
+    bool in_range = true;
     for (int k = 0; k < 3; ++k) {
         const double fb = __builtin_floor(x[k] * m.invB);
-        if (!(__builtin_fabs(fb) <= (double)kKeyLimit)) return q;
-        b[k] = (int64_t)fb;
+        in_range = in_range && __builtin_fabs(fb) <= (double)kKeyLimit;
+        b[k] = (int32_t)fb;
     }
-    const unsigned long long hkey = pack_key(b[0], b[1], b[2]);
-    const uint32_t info = find_slot(m, hkey).info;
+    // uniform over the group, so its lanes leave together and the sums below see all 4
+    if (!in_range) return q;
+    const uint32_t info = block_slot(m, b[0], b[1], b[2]).info;
     if (info & kNoBlockBit) return q;
-    const int n = (int)((info >> kLevelShift) & 3u);
-    const int shift = 3 - n;
-    int64_t i0[3];
+    const int n = (int)((info >> kLevelShift) & 3u), shift = 3 - n;
+    // lattice cell, fractions, and this lane's corners: lattice points cell + (dx, dy, 0 and 1), each in
+    // block cell >> shift (floor division by the block side)
+    int32_t cell[3];
     double f[3];
     for (int k = 0; k < 3; ++k) {
         const double g = x[k] * m.inv_nu[n] - 0.5;
         const double fl = __builtin_floor(g);
-        i0[k] = (int64_t)fl;
         f[k] = g - fl;
+        cell[k] = (int32_t)fl;
     }
-    // the corners' blocks: along each axis the 2 lattice points lie in block lo or lo + 1
-    int64_t blo[3];
-    int cross[3];
-    for (int k = 0; k < 3; ++k) {
-        blo[k] = i0[k] >> shift;  // floor division by the block side 2^shift
-        cross[k] = (int)(((i0[k] + 1) >> shift) - blo[k]);
+    const bool dx = (c & 1) != 0, dy = (c & 2) != 0;
+    cell[0] += dx ? 1 : 0;
+    cell[1] += dy ? 1 : 0;
+    const int32_t bx = cell[0] >> shift, by = cell[1] >> shift, bz0 = cell[2] >> shift, bz1 = (cell[2] + 1) >> shift;
+    const bool side = bx != b[0] || by != b[1];
+    uint32_t row[2] = {info, info};
+    {
+        // both home slots are read before either is examined
+        const bool need0 = side || bz0 != b[2], need1 = (side || bz1 != b[2]) && bz1 != bz0;
+        const unsigned long long k0 = pack_key(bx, by, bz0), k1 = pack_key(bx, by, bz1);
+        const uint32_t h0 = spatial_hash(bx, by, bz0) & m.hmask, h1 = spatial_hash(bx, by, bz1) & m.hmask;
+        HashSlot s0{k0, 0u, info}, s1{k1, 0u, info};
+        if (need0) s0 = load_slot(m, h0);
+        if (need1) s1 = load_slot(m, h1);
+        row[0] = follow_slot(m, k0, h0, s0).info;
+        row[1] = follow_slot(m, k1, h1, s1).info;
+        if (bz1 == bz0) row[1] = row[0];
     }
-    // rows of the (up to 8) distinct blocks, addressed by (dx, dy, dz) in {0, 1}^3; all home
-    // slots are read before any is examined, and only a corner whose home slot holds another key
-    // walks the probe sequence
-    unsigned long long bkeys[8];
-    HashSlot home[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        const int dx = c & 1, dy = (c >> 1) & 1, dz = (c >> 2) & 1;
-        const bool need = (dx <= cross[0]) && (dy <= cross[1]) && (dz <= cross[2]);
-        bkeys[c] = pack_key(blo[0] + dx, blo[1] + dy, blo[2] + dz);
-        home[c] = HashSlot{bkeys[c], kInvalidId, kNoBlockBit};
-        if (need && bkeys[c] == hkey) home[c].info = info;
-        else if (need) home[c] = load_slot(m, home_slot(bkeys[c], m.hmask));
-    }
-    uint32_t binfo8[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        binfo8[c] = home[c].info;
-        if (home[c].key != bkeys[c]) binfo8[c] = follow_slot(m, bkeys[c], home_slot(bkeys[c], m.hmask), home[c]).info;
-    }
-    // the 8 corner voxels: heap positions first, then all weight and TSDF reads
-    double cw[8], cd[8];
-    size_t at8[8];
-    int lv8[8];
-    uint32_t have = 0;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        const int dl[3] = {c & 1, (c >> 1) & 1, (c >> 2) & 1};
-        int64_t cell[3], cb[3];
-        int sel = 0;
-        for (int k = 0; k < 3; ++k) {
-            cell[k] = i0[k] + dl[k];
-            cb[k] = cell[k] >> shift;
-            sel |= (int)(cb[k] - blo[k]) << k;
-        }
-        cw[c] = ((dl[0] ? f[0] : 1.0 - f[0]) * (dl[1] ? f[1] : 1.0 - f[1])) * (dl[2] ? f[2] : 1.0 - f[2]);
-        const uint32_t binf = binfo8[sel];
-        at8[c] = 0;
-        lv8[c] = 0;
-        if (binf & kNoBlockBit) continue;
-        const int n2 = (int)((binf >> kLevelShift) & 3u);
-        int idx[3];
-        for (int k = 0; k < 3; ++k) {
+    double cd[2] = {0.0, 0.0};
+    bool have[2] = {false, false};
+    {
+        const int base[2] = {bz0, bz1};
+        uint32_t W[2] = {0u, 0u};
+        float D[2] = {0.f, 0.f};
+        for (int z = 0; z < 2; ++z) {
+            if (row[z] & kNoBlockBit) continue;
+            const int n2 = (int)((row[z] >> kLevelShift) & 3u);
             // lattice point (cell + 1/2) nu_n in half finest-voxel units, relative to its block
-            const int64_t p2 = cell[k] * ((int64_t)2 << n) + ((int64_t)1 << n);
-            idx[k] = (int)((p2 - 16 * cb[k]) >> (n2 + 1));
+            const int i = ((2 * (cell[0] - (bx << shift)) + 1) << n) >> (n2 + 1);
+            const int j = ((2 * (cell[1] - (by << shift)) + 1) << n) >> (n2 + 1);
+            const int k = ((2 * (cell[2] + z - (base[z] << shift)) + 1) << n) >> (n2 + 1);
+            const size_t at = ((size_t)(row[z] & kSlotMask) << (3 * (3 - n2))) +
+                              (size_t)(spread3(i) | (spread3(j) << 1) | (spread3(k) << 2));
+            W[z] = Store<ST>::getW(m, n2, at);
+            D[z] = Store<ST>::getD(m, n2, at);
         }
-        const int m2 = 8 >> n2;
-        at8[c] = (size_t)(binf & kSlotMask) * (size_t)(m2 * m2 * m2) + (size_t)morton3(idx[0], idx[1], idx[2]);
-        lv8[c] = n2;
-        have |= 1u << c;
-    }
-    uint32_t W8[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        W8[c] = Store<ST>::getW(m, lv8[c], at8[c]);
-        cd[c] = (double)Store<ST>::getD(m, lv8[c], at8[c]);
-    }
-    uint32_t valid_mask = 0;
-    double wsum = 0.0, num = 0.0;
-    bool any_pos = false;
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        if (!(have & (1u << c)) || W8[c] == 0) {
-            cd[c] = 0.0;
-            continue;
+        for (int z = 0; z < 2; ++z) {
+            have[z] = W[z] != 0u;
+            cd[z] = have[z] ? (double)D[z] : 0.0;
         }
-        valid_mask |= 1u << c;
-        wsum += cw[c];
-        num += cw[c] * cd[c];
-        if (cw[c] > 0.0) any_pos = true;
     }
-    if (strict ? valid_mask != 0xFFu : !any_pos) return q;
+    const double wx = dx ? f[0] : 1.0 - f[0], wy = dy ? f[1] : 1.0 - f[1], wxy = wx * wy;
+    const double cw[2] = {have[0] ? wxy * (1.0 - f[2]) : 0.0, have[1] ? wxy * f[2] : 0.0};
+    const double wsum = group4_sum(cw[0] + cw[1]);
+    const double num = group4_sum(cw[0] * cd[0] + cw[1] * cd[1]);
+    // all 8 corners observed, or one observed with a positive weight, over the group's 4 bits
+    const int sh = lane_id() & 60;
+    const uint32_t seen = (uint32_t)(__ballot(have[0] && have[1]) >> sh) & 15u;
+    const uint32_t pos = (uint32_t)(__ballot(cw[0] > 0.0 || cw[1] > 0.0) >> sh) & 15u;
+    if (strict ? seen != 15u : pos == 0u) return q;
     q.valid = true;
     q.sdf = num / wsum;
-    for (int a = 0; a < 3; ++a) {
-        double s = 0.0;
-        for (int c = 0; c < 8; ++c) {
-            if (!(valid_mask & (1u << c))) continue;
-            const int dl[3] = {c & 1, (c >> 1) & 1, (c >> 2) & 1};
-            double dw = dl[a] ? 1.0 : -1.0;
-            for (int bb = 0; bb < 3; ++bb)
-                if (bb != a) dw *= dl[bb] ? f[bb] : 1.0 - f[bb];
-            s += dw * (cd[c] - q.sdf);
-        }
-        q.grad[a] = s / wsum * m.inv_nu[n];
+    if (GRAD) {
+        const double e0 = have[0] ? cd[0] - q.sdf : 0.0, e1 = have[1] ? cd[1] - q.sdf : 0.0;
+        const double ez = (1.0 - f[2]) * e0 + f[2] * e1;
+        const double r = m.inv_nu[n] / wsum;
+        q.grad[0] = group4_sum((dx ? wy : -wy) * ez) * r;
+        q.grad[1] = group4_sum((dy ? wx : -wx) * ez) * r;
+        q.grad[2] = group4_sum(wxy * (e1 - e0)) * r;
     }
     return q;
 }
@@ -153,63 +141,62 @@ __device__ inline void world_point(const QueryParams& qp, const float* pts, int6
     }
 }
 
-template <int ST>
+constexpr int kQueryPoints = 64;  // points per 256-thread workgroup
+
+template <int ST, bool GRAD>
 __global__ __launch_bounds__(256) void k_query(const DevMap* __restrict__ pm, QueryParams qp, const float* __restrict__ pts,
                                                int64_t n, float* sdf, uint8_t* valid, float* grad) {
     const DevMap& m = *pm;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    const int c = lane_id() & 3;
+    const int64_t stride = (int64_t)gridDim.x * kQueryPoints;
+    for (int64_t i = (int64_t)blockIdx.x * kQueryPoints + (threadIdx.x >> 2); i < n; i += stride) {
         double x[3];
         world_point(qp, pts, i, x);
-        const QueryResult q = query_point<ST>(m, x, qp.strict != 0);
-        sdf[i] = (float)q.sdf;
-        valid[i] = q.valid ? 1 : 0;
-        if (grad) {
-            grad[3 * i] = (float)q.grad[0];
-            grad[3 * i + 1] = (float)q.grad[1];
-            grad[3 * i + 2] = (float)q.grad[2];
+        const QueryResult q = query_point<ST, GRAD>(m, x, qp.strict != 0);
+        if (c == 0) {
+            sdf[i] = (float)q.sdf;
+            valid[i] = q.valid ? 1 : 0;
         }
+        if (GRAD && c < 3) grad[3 * i + c] = (float)(c == 0 ? q.grad[0] : c == 1 ? q.grad[1] : q.grad[2]);
     }
 }
 
-// Backward: per point dL/dx = g_i * d sdf / dx; dL/dp = R^T dL/dx; pose terms (dL/dx, x cross
-// dL/dx) summed per thread, then per workgroup in a fixed order into FP64 partials.
+// Backward: per point dL/dx = g_i * d sdf / dx; dL/dp = R^T dL/dx.  Of a point's pose terms lane 0 of the
+// group sums dL/dx and lane 1 x cross dL/dx; then per workgroup in a fixed order into FP64 partials.
 template <int ST>
 __global__ __launch_bounds__(256) void k_query_backward(const DevMap* __restrict__ pm, QueryParams qp, const float* __restrict__ pts,
                                                         int64_t n, const float* __restrict__ gsdf, float* gpts,
                                                         double* partials) {
     const DevMap& m = *pm;
-    double acc[6] = {0, 0, 0, 0, 0, 0};
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    const int c = lane_id() & 3;
+    double acc[3] = {0.0, 0.0, 0.0};
+    const int64_t stride = (int64_t)gridDim.x * kQueryPoints;
+    for (int64_t i = (int64_t)blockIdx.x * kQueryPoints + (threadIdx.x >> 2); i < n; i += stride) {
         double x[3];
         world_point(qp, pts, i, x);
-        const QueryResult q = query_point<ST>(m, x, qp.strict != 0);
+        const float gi = gsdf[i];
+        const QueryResult q = query_point<ST, true>(m, x, qp.strict != 0);
         double g[3] = {0.0, 0.0, 0.0};
         if (q.valid) {
-            const double gs = (double)gsdf[i];
+            const double gs = (double)gi;
             for (int k = 0; k < 3; ++k) g[k] = gs * q.grad[k];
         }
-        for (int r = 0; r < 3; ++r) {
-            const double v = qp.identity ? g[r] : (qp.P.R[0][r] * g[0] + qp.P.R[1][r] * g[1]) + qp.P.R[2][r] * g[2];
-            gpts[3 * i + r] = (float)v;
+        if (c < 3) {
+            double v = c == 0 ? g[0] : c == 1 ? g[1] : g[2];
+            if (!qp.identity) v = (qp.P.R[0][c] * g[0] + qp.P.R[1][c] * g[1]) + qp.P.R[2][c] * g[2];
+            gpts[3 * i + c] = (float)v;
         }
-        acc[0] += g[0];
-        acc[1] += g[1];
-        acc[2] += g[2];
-        acc[3] += x[1] * g[2] - x[2] * g[1];
-        acc[4] += x[2] * g[0] - x[0] * g[2];
-        acc[5] += x[0] * g[1] - x[1] * g[0];
+        const double t[3] = {x[1] * g[2] - x[2] * g[1], x[2] * g[0] - x[0] * g[2], x[0] * g[1] - x[1] * g[0]};
+        for (int k = 0; k < 3; ++k) acc[k] += c == 0 ? g[k] : t[k];
     }
-    __shared__ double red[4][6];
-    for (int k = 0; k < 6; ++k) acc[k] = wave_sum(acc[k]);
-    const int wave = threadIdx.x >> 6;
-    if (lane_id() == 0)
-        for (int k = 0; k < 6; ++k) red[wave][k] = acc[k];
+    __shared__ double red[kQueryPoints][6];
+    if (c < 2)
+        for (int k = 0; k < 3; ++k) red[threadIdx.x >> 2][3 * c + k] = acc[k];
     __syncthreads();
     if (threadIdx.x < 6) {
-        const int k = threadIdx.x;
-        partials[(size_t)blockIdx.x * 6 + k] = ((red[0][k] + red[1][k]) + red[2][k]) + red[3][k];
+        double s = 0.0;
+        for (int k = 0; k < kQueryPoints; ++k) s += red[k][threadIdx.x];
+        partials[(size_t)blockIdx.x * 6 + threadIdx.x] = s;
     }
 }
 
@@ -255,13 +242,16 @@ extern "C" mrh_status mrh_query_sdf(mrh_map* map, const float* pts_dev, int64_t 
     if (!pts_dev || !sdf_dev || !valid_dev) return MRH_ERR_INVALID_ARG;
     QueryParams qp;
     if (!make_params(T_wq, strict, qp)) return set_error(map, MRH_ERR_INVALID_ARG, "non-finite query pose");
-    const int64_t blocks = (n + 255) / 256;
-    const unsigned grid = (unsigned)(blocks < 16384 ? blocks : 16384);
+    const int64_t blocks = (n + kQueryPoints - 1) / kQueryPoints;
+    const unsigned grid = (unsigned)(blocks < 65536 ? blocks : 65536);
     launch(map, K_QUERY, [&] {
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, map->stream, map->dmd, qp, pts_dev, n, sdf_dev, valid_dev, grad_dev);
+        };
         switch (map->cfg.storage) {
-            case MRH_STORE_F16: hipLaunchKernelGGL(k_query<MRH_STORE_F16>, dim3(grid), dim3(256), 0, map->stream, map->dmd, qp, pts_dev, n, sdf_dev, valid_dev, grad_dev); break;
-            case MRH_STORE_BF16: hipLaunchKernelGGL(k_query<MRH_STORE_BF16>, dim3(grid), dim3(256), 0, map->stream, map->dmd, qp, pts_dev, n, sdf_dev, valid_dev, grad_dev); break;
-            default: hipLaunchKernelGGL(k_query<MRH_STORE_F32>, dim3(grid), dim3(256), 0, map->stream, map->dmd, qp, pts_dev, n, sdf_dev, valid_dev, grad_dev);
+            case MRH_STORE_F16: grad_dev ? go(k_query<MRH_STORE_F16, true>) : go(k_query<MRH_STORE_F16, false>); break;
+            case MRH_STORE_BF16: grad_dev ? go(k_query<MRH_STORE_BF16, true>) : go(k_query<MRH_STORE_BF16, false>); break;
+            default: grad_dev ? go(k_query<MRH_STORE_F32, true>) : go(k_query<MRH_STORE_F32, false>);
         }
     });
     return check_hip(map, hipGetLastError(), "query_sdf");
@@ -276,7 +266,7 @@ extern "C" mrh_status mrh_query_sdf_backward(mrh_map* map, const float* pts_dev,
     if (!make_params(T_wq, strict, qp)) return set_error(map, MRH_ERR_INVALID_ARG, "non-finite query pose");
     for (int k = 0; k < 6; ++k) grad_pose_host[k] = 0.0;
     if (n == 0) return MRH_OK;
-    const int64_t blocks = (n + 255) / 256;
+    const int64_t blocks = (n + kQueryPoints - 1) / kQueryPoints;
     const int grid = (int)(blocks < map->partials_cap ? blocks : map->partials_cap);
     launch(map, K_QUERY_BACKWARD, [&] {
         switch (map->cfg.storage) {
