@@ -145,7 +145,7 @@ static void free_all(mrh_map* m) {
     for (int n = 0; n < 4; ++n)
         if (d.vis[n]) (void)hipFree(d.vis[n]);
     for (int n = 0; n < 4; ++n) {
-        void* lp[] = {d.stack[n], d.pend[n], d.D[n], d.W[n], d.S2[n], d.C[n], d.acc_sat[n], d.acc_band[n], d.acc_s1[n], d.acc_s2[n]};
+        void* lp[] = {d.stack[n], d.pend[n], d.DW[n], d.S2[n], d.C[n], d.acc_sat[n], d.acc_band[n], d.acc_s1[n], d.acc_s2[n]};
         for (void* p : lp)
             if (p) (void)hipFree(p);
     }
@@ -224,8 +224,7 @@ mrh_status mrh_map_create(const mrh_config* cfg, void* stream, mrh_map** out) {
         if (n == 0)
             for (int p = 0; p < 2; ++p) alloc((void**)&d.pend0[p], (size_t)cap * 4, "pending frees");
         const size_t pb = (size_t)plane_bytes(c.storage);
-        alloc((void**)&d.D[n], nv * pb, "TSDF heap");
-        alloc((void**)&d.W[n], nv * pb, "weight heap");
+        alloc((void**)&d.DW[n], nv * 2 * pb, "TSDF and weight heap");
         alloc((void**)&d.S2[n], nv * pb, "variance heap");
         if (c.color) alloc((void**)&d.C[n], nv * 12, "colour heap");
     }

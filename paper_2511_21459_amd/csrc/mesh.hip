@@ -182,9 +182,9 @@ template <int ST>
 __device__ __forceinline__ bool voxel_value(const DevMap& m, uint32_t info, int i, int j, int k, float& v) {
     const int n = (int)((info >> kLevelShift) & 3u);
     const size_t at = ((size_t)(info & kSlotMask) << (3 * (3 - n))) + (size_t)morton_of(i, j, k);
-    // both reads issued together (the TSDF read does not wait for the weight)
-    const uint32_t w = Store<ST>::getW(m, n, at);
-    const float d = Store<ST>::getD(m, n, at);
+    uint32_t w;
+    float d;
+    Store<ST>::getDW(m, n, at, d, w);
     if (w == 0u) return false;
     v = d;
     return true;
@@ -272,10 +272,7 @@ __device__ __forceinline__ bool lattice_value(const DevMap& m, const uint32_t* n
     for (int c = 0; c < 8; ++c) {
         W[c] = 0u;
         D[c] = 0.f;
-        if (live & (1u << c)) {
-            W[c] = Store<ST>::getW(m, lvl[c], at[c]);
-            D[c] = Store<ST>::getD(m, lvl[c], at[c]);
-        }
+        if (live & (1u << c)) Store<ST>::getDW(m, lvl[c], at[c], D[c], W[c]);
     }
     float wsum = 0.f, num = 0.f;
     bool any = false;
@@ -578,10 +575,7 @@ __global__ __launch_bounds__(kMeshThreads) void k_mesh(const DevMap* __restrict_
             const int p = lane + 64 * t;
             dq[t] = 0.f;
             wq[t] = 0u;
-            if (p < nvox) {
-                wq[t] = Store<ST>::getW(m, n, own + (size_t)p);
-                dq[t] = Store<ST>::getD(m, n, own + (size_t)p);
-            }
+            if (p < nvox) Store<ST>::getDW(m, n, own + (size_t)p, dq[t], wq[t]);
         }
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
@@ -640,10 +634,7 @@ __global__ __launch_bounds__(kMeshThreads) void k_mesh(const DevMap* __restrict_
         for (int u = 0; u < 4; ++u) {
             pw[u] = 0u;
             pd[u] = 0.f;
-            if (pk[u] == 2) {
-                pw[u] = Store<ST>::getW(m, plv[u], pat[u]);
-                pd[u] = Store<ST>::getD(m, plv[u], pat[u]);
-            }
+            if (pk[u] == 2) Store<ST>::getDW(m, plv[u], pat[u], pd[u], pw[u]);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {

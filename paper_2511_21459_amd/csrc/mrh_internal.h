@@ -6,7 +6,7 @@
 //   block table  bkey[u64 max_blocks], binfo[u32] = heap slot | level << 27 | NEW | NOBLOCK,
 //                bslot[u32] its hash slot, bvsum[f64] = sum over voxels with W >= min_obs of S2 / W,
 //                bvcnt[u32] = their count
-//   heaps        per level n: D, W, S2 planes of heap_blocks[n] blocks x (8 >> n)^3 voxels, voxels
+//   heaps        per level n: (D, W) pair and S2 planes of heap_blocks[n] blocks x (8 >> n)^3 voxels, voxels
 //                of a block in Morton (Z) order so the 2x2x2 children of a coarse voxel are
 //                contiguous; a free stack of slot indices and a pending-free list per level
 //   counters     DevCounters (block count, stack tops, stats, latched error flags)
@@ -96,8 +96,7 @@ struct DevMap {
     uint32_t* pend[4];      // level n >= 1 frees (entry 0 unused)
     uint32_t* pend0[2];     // level-0 frees, per parity
     int32_t heap_cap[4];
-    void* D[4];   // per level, plane of the storage format (see mrh_store.h)
-    void* W[4];
+    void* DW[4];  // per level, planes of the storage format (see mrh_store.h)
     void* S2[4];
     float* C[4];  // per level, colour RGB float32 x 3 per voxel (maps created with colour; else null)
     // LiDAR per-frame accumulators, parallel to the heaps (zero between frames):

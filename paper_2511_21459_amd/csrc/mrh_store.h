@@ -5,6 +5,10 @@
 //   MRH_STORE_F16   D half of D / tau       W uint16 (satur.) V half of S2 / (W tau^2)  6 B / voxel
 //   MRH_STORE_BF16  D bfloat16 of D / tau   W half (satur.)   V half of S2 / (W tau^2)  6 B / voxel
 //
+// D and W of a voxel lie side by side in one plane, S2 in another: queries and meshing read D and W of
+// scattered voxels, and the pair costs one read of one line (8 corners of a query point in random order
+// met 2.8 lines of the pair plane on average where they met 2.3 of each of two planes).
+//
 // The 16-bit formats keep the per-voxel variance sigma^2 = S2 / W normalised by tau^2 rather than
 // S2 itself: sigma^2 / tau^2 stays in [0, 4] whatever the weight, so it neither overflows half
 // nor needs rescaling after a merge multiplies W.
@@ -64,49 +68,49 @@ struct Store;
 template <>
 struct Store<MRH_STORE_F32> {
     static constexpr int kBytes = 12;
+    __device__ static inline const uint2* dw(const DevMap& m, int lvl) { return static_cast<const uint2*>(m.DW[lvl]); }
+    __device__ static inline void getDW(const DevMap& m, int lvl, size_t i, float& D, uint32_t& W) {
+        const uint2 v = dw(m, lvl)[i];
+        D = __builtin_bit_cast(float, v.x);
+        W = v.y;
+    }
     __device__ static inline void get(const DevMap& m, int lvl, size_t i, float& D, uint32_t& W, float& S2) {
-        D = static_cast<const float*>(m.D[lvl])[i];
-        W = static_cast<const uint32_t*>(m.W[lvl])[i];
+        getDW(m, lvl, i, D, W);
         S2 = static_cast<const float*>(m.S2[lvl])[i];
     }
     __device__ static inline void put(const DevMap& m, int lvl, size_t i, float D, uint32_t W, float S2) {
-        static_cast<float*>(m.D[lvl])[i] = D;
-        static_cast<uint32_t*>(m.W[lvl])[i] = W;
+        static_cast<uint2*>(m.DW[lvl])[i] = make_uint2(__builtin_bit_cast(uint32_t, D), W);
         static_cast<float*>(m.S2[lvl])[i] = S2;
     }
     __device__ static inline void round(const DevMap&, float&, uint32_t&, float&) {}
-    __device__ static inline float getD(const DevMap& m, int lvl, size_t i) {
-        return static_cast<const float*>(m.D[lvl])[i];
-    }
-    __device__ static inline uint32_t getW(const DevMap& m, int lvl, size_t i) {
-        return static_cast<const uint32_t*>(m.W[lvl])[i];
-    }
+    __device__ static inline uint32_t getW(const DevMap& m, int lvl, size_t i) { return dw(m, lvl)[i].y; }
     // the weights of 8 consecutive level-0 voxels starting at base (a multiple of 8)
     __device__ static inline void getW8(const DevMap& m, size_t base, uint32_t W[8]) {
-        const uint4* wp = reinterpret_cast<const uint4*>(static_cast<const uint32_t*>(m.W[0]) + base);
-        const uint4 w0 = wp[0], w1 = wp[1];
-        W[0] = w0.x, W[1] = w0.y, W[2] = w0.z, W[3] = w0.w, W[4] = w1.x, W[5] = w1.y, W[6] = w1.z, W[7] = w1.w;
+        const uint4* p = reinterpret_cast<const uint4*>(dw(m, 0) + base);
+        for (int k = 0; k < 4; ++k) {
+            const uint4 v = p[k];
+            W[2 * k] = v.y, W[2 * k + 1] = v.w;
+        }
     }
     // 8 consecutive level-0 voxels starting at base (a multiple of 8)
     __device__ static inline void get8(const DevMap& m, size_t base, float D[8], uint32_t W[8], float S2[8]) {
-        const float4* dp = reinterpret_cast<const float4*>(static_cast<const float*>(m.D[0]) + base);
-        const uint4* wp = reinterpret_cast<const uint4*>(static_cast<const uint32_t*>(m.W[0]) + base);
+        const uint4* p = reinterpret_cast<const uint4*>(dw(m, 0) + base);
         const float4* sp = reinterpret_cast<const float4*>(static_cast<const float*>(m.S2[0]) + base);
-        const float4 d0 = dp[0], d1 = dp[1], s0 = sp[0], s1 = sp[1];
-        const uint4 w0 = wp[0], w1 = wp[1];
-        D[0] = d0.x, D[1] = d0.y, D[2] = d0.z, D[3] = d0.w, D[4] = d1.x, D[5] = d1.y, D[6] = d1.z, D[7] = d1.w;
+        const uint4 v[4] = {p[0], p[1], p[2], p[3]};
+        const float4 s0 = sp[0], s1 = sp[1];
+        for (int k = 0; k < 4; ++k) {
+            D[2 * k] = __builtin_bit_cast(float, v[k].x), W[2 * k] = v[k].y;
+            D[2 * k + 1] = __builtin_bit_cast(float, v[k].z), W[2 * k + 1] = v[k].w;
+        }
         S2[0] = s0.x, S2[1] = s0.y, S2[2] = s0.z, S2[3] = s0.w, S2[4] = s1.x, S2[5] = s1.y, S2[6] = s1.z, S2[7] = s1.w;
-        W[0] = w0.x, W[1] = w0.y, W[2] = w0.z, W[3] = w0.w, W[4] = w1.x, W[5] = w1.y, W[6] = w1.z, W[7] = w1.w;
     }
     __device__ static inline void put8(const DevMap& m, size_t base, const float D[8], const uint32_t W[8],
                                        const float S2[8]) {
-        float4* dp = reinterpret_cast<float4*>(static_cast<float*>(m.D[0]) + base);
-        uint4* wp = reinterpret_cast<uint4*>(static_cast<uint32_t*>(m.W[0]) + base);
+        uint4* p = reinterpret_cast<uint4*>(static_cast<uint2*>(m.DW[0]) + base);
         float4* sp = reinterpret_cast<float4*>(static_cast<float*>(m.S2[0]) + base);
-        dp[0] = make_float4(D[0], D[1], D[2], D[3]);
-        dp[1] = make_float4(D[4], D[5], D[6], D[7]);
-        wp[0] = make_uint4(W[0], W[1], W[2], W[3]);
-        wp[1] = make_uint4(W[4], W[5], W[6], W[7]);
+        for (int k = 0; k < 4; ++k)
+            p[k] = make_uint4(__builtin_bit_cast(uint32_t, D[2 * k]), W[2 * k], __builtin_bit_cast(uint32_t, D[2 * k + 1]),
+                              W[2 * k + 1]);
         sp[0] = make_float4(S2[0], S2[1], S2[2], S2[3]);
         sp[1] = make_float4(S2[4], S2[5], S2[6], S2[7]);
     }
@@ -151,23 +155,23 @@ struct Store16 {
         D = decD(m, encD(m, D));
         S2 = decS2(m, encS2(m, S2, W), W);
     }
+    // a voxel's D (low half) and W in one word
+    __device__ static inline const uint32_t* dw(const DevMap& m, int lvl) { return static_cast<const uint32_t*>(m.DW[lvl]); }
+    __device__ static inline void getDW(const DevMap& m, int lvl, size_t i, float& D, uint32_t& W) {
+        const uint32_t v = dw(m, lvl)[i];
+        D = decD(m, (uint16_t)v);
+        W = decW((uint16_t)(v >> 16));
+    }
     __device__ static inline void get(const DevMap& m, int lvl, size_t i, float& D, uint32_t& W, float& S2) {
-        W = decW(static_cast<const uint16_t*>(m.W[lvl])[i]);
-        D = decD(m, static_cast<const uint16_t*>(m.D[lvl])[i]);
+        getDW(m, lvl, i, D, W);
         S2 = decS2(m, static_cast<const uint16_t*>(m.S2[lvl])[i], W);
     }
     __device__ static inline void put(const DevMap& m, int lvl, size_t i, float D, uint32_t W, float S2) {
         const uint16_t wb = encW(W);
-        static_cast<uint16_t*>(m.D[lvl])[i] = encD(m, D);
-        static_cast<uint16_t*>(m.W[lvl])[i] = wb;
+        static_cast<uint32_t*>(m.DW[lvl])[i] = (uint32_t)encD(m, D) | ((uint32_t)wb << 16);
         static_cast<uint16_t*>(m.S2[lvl])[i] = encS2(m, S2, decW(wb));
     }
-    __device__ static inline float getD(const DevMap& m, int lvl, size_t i) {
-        return decD(m, static_cast<const uint16_t*>(m.D[lvl])[i]);
-    }
-    __device__ static inline uint32_t getW(const DevMap& m, int lvl, size_t i) {
-        return decW(static_cast<const uint16_t*>(m.W[lvl])[i]);
-    }
+    __device__ static inline uint32_t getW(const DevMap& m, int lvl, size_t i) { return decW((uint16_t)(dw(m, lvl)[i] >> 16)); }
     __device__ static inline void unpack8(uint4 v, uint16_t o[8]) {
         o[0] = (uint16_t)v.x, o[1] = (uint16_t)(v.x >> 16), o[2] = (uint16_t)v.y, o[3] = (uint16_t)(v.y >> 16);
         o[4] = (uint16_t)v.z, o[5] = (uint16_t)(v.z >> 16), o[6] = (uint16_t)v.w, o[7] = (uint16_t)(v.w >> 16);
@@ -177,34 +181,36 @@ struct Store16 {
                           (uint32_t)o[4] | ((uint32_t)o[5] << 16), (uint32_t)o[6] | ((uint32_t)o[7] << 16));
     }
     __device__ static inline void getW8(const DevMap& m, size_t base, uint32_t W[8]) {
-        uint16_t wb[8];
-        unpack8(*reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(m.W[0]) + base), wb);
-        for (int q = 0; q < 8; ++q) W[q] = decW(wb[q]);
+        const uint4* p = reinterpret_cast<const uint4*>(dw(m, 0) + base);
+        const uint4 a = p[0], b = p[1];
+        const uint32_t v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        for (int q = 0; q < 8; ++q) W[q] = decW((uint16_t)(v[q] >> 16));
     }
     __device__ static inline void get8(const DevMap& m, size_t base, float D[8], uint32_t W[8], float S2[8]) {
-        const uint4 d = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(m.D[0]) + base);
-        const uint4 w = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(m.W[0]) + base);
+        const uint4* p = reinterpret_cast<const uint4*>(dw(m, 0) + base);
+        const uint4 a = p[0], b = p[1];
         const uint4 s = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(m.S2[0]) + base);
-        uint16_t db[8], wb[8], sb[8];
-        unpack8(d, db);
-        unpack8(w, wb);
+        const uint32_t v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+        uint16_t sb[8];
         unpack8(s, sb);
         for (int q = 0; q < 8; ++q) {
-            W[q] = decW(wb[q]);
-            D[q] = decD(m, db[q]);
+            W[q] = decW((uint16_t)(v[q] >> 16));
+            D[q] = decD(m, (uint16_t)v[q]);
             S2[q] = decS2(m, sb[q], W[q]);
         }
     }
     __device__ static inline void put8(const DevMap& m, size_t base, const float D[8], const uint32_t W[8],
                                        const float S2[8]) {
-        uint16_t db[8], wb[8], sb[8];
+        uint32_t v[8];
+        uint16_t sb[8];
         for (int q = 0; q < 8; ++q) {
-            wb[q] = encW(W[q]);
-            db[q] = encD(m, D[q]);
-            sb[q] = encS2(m, S2[q], decW(wb[q]));
+            const uint16_t wb = encW(W[q]);
+            v[q] = (uint32_t)encD(m, D[q]) | ((uint32_t)wb << 16);
+            sb[q] = encS2(m, S2[q], decW(wb));
         }
-        *reinterpret_cast<uint4*>(static_cast<uint16_t*>(m.D[0]) + base) = pack8(db);
-        *reinterpret_cast<uint4*>(static_cast<uint16_t*>(m.W[0]) + base) = pack8(wb);
+        uint4* p = reinterpret_cast<uint4*>(static_cast<uint32_t*>(m.DW[0]) + base);
+        p[0] = make_uint4(v[0], v[1], v[2], v[3]);
+        p[1] = make_uint4(v[4], v[5], v[6], v[7]);
         *reinterpret_cast<uint4*>(static_cast<uint16_t*>(m.S2[0]) + base) = pack8(sb);
     }
 };
@@ -214,7 +220,7 @@ struct Store<MRH_STORE_F16> : Store16<MRH_STORE_F16> {};
 template <>
 struct Store<MRH_STORE_BF16> : Store16<MRH_STORE_BF16> {};
 
-// host: bytes per voxel of each plane
+// host: bytes of one element (D, W or S2)
 __host__ __device__ inline int plane_bytes(int storage) { return storage == MRH_STORE_F32 ? 4 : 2; }
 
 }  // namespace mrh

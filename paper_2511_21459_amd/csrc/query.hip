@@ -20,7 +20,9 @@ struct QueryParams {
 // along z); every lane of the group calls with the same x.  A query is a chain of reads (its block's
 // hash slot, the corners' slots, the voxels) behind about 1100 instructions when one lane does all 8
 // corners, which leaves the chip idle on small batches.  Measured with gradients on a 1 cm room, one / 8 / 4 lanes
-// per point: QUERY_TIMES
+// per point: 1000 points 14 / 7 / 8 us, 65536 24 / 15 / 14 us, 1M in
+// random order 151 / 119 / 121 us (bound by the lines met; 78 us once D and W share theirs), 1M in
+// block order 74 / 93 / 60 us (bound by VALU issue, where the work that 8 lanes repeat shows).
 struct QueryResult {
     bool valid;      // the same on the group's lanes, as are the values
     double sdf;
@@ -102,8 +104,7 @@ __device__ inline QueryResult query_point(const DevMap& m, const double x[3], bo
             const int k = ((2 * (cell[2] + z - (base[z] << shift)) + 1) << n) >> (n2 + 1);
             const size_t at = ((size_t)(row[z] & kSlotMask) << (3 * (3 - n2))) +
                               (size_t)(spread3(i) | (spread3(j) << 1) | (spread3(k) << 2));
-            W[z] = Store<ST>::getW(m, n2, at);
-            D[z] = Store<ST>::getD(m, n2, at);
+            Store<ST>::getDW(m, n2, at, D[z], W[z]);
         }
         for (int z = 0; z < 2; ++z) {
             have[z] = W[z] != 0u;

@@ -8,7 +8,7 @@
 // diagonal): it lies inside when the sphere meets the frustum (the conservative test of the
 // update's cull) or the ball.
 //
-// Leaving the GPU: the block's three planes are copied out in the storage format (so a round trip
+// Leaving the GPU: the block's planes are copied out in the storage format (so a round trip
 // is bit exact, variance sums included), its hash entry becomes a tombstone (lookups step over it,
 // inserts never reuse it), its heap slot goes back on its level's free stack, and its table row is
 // marked gone (no kernel reads a gone row).  Block ids are not reused: the block table bounds the
@@ -90,21 +90,21 @@ __global__ __launch_bounds__(256) void k_stream_select(const DevMap* __restrict_
     }
 }
 
-// The three planes of a block between a heap slot and a contiguous buffer, in elements of the
-// storage format (T: 32-bit for FP32, 16-bit otherwise); to_heap selects the direction.
+// A block's planes ((D, W) pairs, then S2) between a heap slot and a contiguous buffer, in elements of
+// the storage format (T: 32-bit for FP32, 16-bit otherwise); to_heap selects the direction.
 template <typename T>
 __device__ inline void copy_planes(const DevMap& m, int level, uint32_t slot, T* buf, bool to_heap) {
     const int nv = 1 << (3 * (3 - level));
-    T* planes[3] = {static_cast<T*>(m.D[level]), static_cast<T*>(m.W[level]), static_cast<T*>(m.S2[level])};
-    for (int p = 0; p < 3; ++p)
-        for (int v = lane_id(); v < nv; v += 64) {
-            T& h = planes[p][(size_t)slot * nv + v];
-            if (to_heap) h = buf[p * nv + v];
-            else buf[p * nv + v] = h;
-        }
+    T* dw = static_cast<T*>(m.DW[level]) + (size_t)slot * (2 * nv);
+    T* s2 = static_cast<T*>(m.S2[level]) + (size_t)slot * nv;
+    for (int v = lane_id(); v < 3 * nv; v += 64) {
+        T& h = v < 2 * nv ? dw[v] : s2[v - 2 * nv];
+        if (to_heap) h = buf[v];
+        else buf[v] = h;
+    }
 }
 
-// Copy one level's selected blocks out (one wave per block: the three planes in the storage
+// Copy one level's selected blocks out (one wave per block: the planes in the storage
 // format, the key and the variance sums), then take them off the GPU.
 __global__ __launch_bounds__(256) void k_stream_out(const DevMap* __restrict__ pm, int level, const uint32_t* __restrict__ ids,
                                                     uint32_t n, uint8_t* payload, unsigned long long* keys,
@@ -234,7 +234,7 @@ struct HostBlock {
     double vsum;
 };
 
-// The stored planes of one level (D plane, W plane, S2 plane of a block, Morton order, storage
+// The stored planes of one level ((D, W) pairs and S2 plane of a block, Morton order, storage
 // format; a fixed size per level), in chunks of about 4 MiB with a free list, so that storing a
 // block costs a copy rather than an allocation and the store grows without moving what it holds.
 // Chunks are anonymous mappings populated when they are made (before the blocks leave the GPU),
@@ -328,18 +328,18 @@ double heap_usage(const mrh_map* map, const DevCounters& h) {
 // decoded only for inspection; blocks loaded from outside are encoded with an exact division in
 // place of the device's reciprocal for the variance, which can differ from a device store by one
 // 16-bit ulp.
-// voxel p of a block of nv voxels held as three planes in `buf`
+// voxel p of a block of nv voxels held in `buf` as nv (D, W) pairs and nv S2 elements
 inline void host_decode(int st, const uint8_t* buf, int nv, int p, float tau_f, float tau2_f, float& D, uint32_t& W,
                         float& S2) {
     if (st == MRH_STORE_F32) {
-        std::memcpy(&D, buf + 4 * (size_t)p, 4);
-        std::memcpy(&W, buf + 4 * ((size_t)nv + p), 4);
+        std::memcpy(&D, buf + 8 * (size_t)p, 4);
+        std::memcpy(&W, buf + 8 * (size_t)p + 4, 4);
         std::memcpy(&S2, buf + 4 * (2 * (size_t)nv + p), 4);
         return;
     }
     uint16_t d, w, v;
-    std::memcpy(&d, buf + 2 * (size_t)p, 2);
-    std::memcpy(&w, buf + 2 * ((size_t)nv + p), 2);
+    std::memcpy(&d, buf + 4 * (size_t)p, 2);
+    std::memcpy(&w, buf + 4 * (size_t)p + 2, 2);
     std::memcpy(&v, buf + 2 * (2 * (size_t)nv + p), 2);
     D = (st == MRH_STORE_F16 ? h_f16(d) : h_bf16(d)) * tau_f;
     W = st == MRH_STORE_F16 ? (uint32_t)w : (uint32_t)h_f16(w);
@@ -350,8 +350,8 @@ inline void host_encode(int st, uint8_t* buf, int nv, int p, float tau_f, float 
                         uint32_t W, float S2) {
     (void)tau_f;
     if (st == MRH_STORE_F32) {
-        std::memcpy(buf + 4 * (size_t)p, &D, 4);
-        std::memcpy(buf + 4 * ((size_t)nv + p), &W, 4);
+        std::memcpy(buf + 8 * (size_t)p, &D, 4);
+        std::memcpy(buf + 8 * (size_t)p + 4, &W, 4);
         std::memcpy(buf + 4 * (2 * (size_t)nv + p), &S2, 4);
         return;
     }
@@ -360,8 +360,8 @@ inline void host_encode(int st, uint8_t* buf, int nv, int p, float tau_f, float 
     const uint16_t w = st == MRH_STORE_F16 ? (uint16_t)(W < 65535u ? W : 65535u) : h_to_f16((float)(W < 65504u ? W : 65504u));
     const uint32_t wd = st == MRH_STORE_F16 ? (uint32_t)w : (uint32_t)h_f16(w);
     const uint16_t v = h_to_f16(wd > 0 ? S2 / ((float)wd * tau2_f) : 0.f);
-    std::memcpy(buf + 2 * (size_t)p, &d, 2);
-    std::memcpy(buf + 2 * ((size_t)nv + p), &w, 2);
+    std::memcpy(buf + 4 * (size_t)p, &d, 2);
+    std::memcpy(buf + 4 * (size_t)p + 2, &w, 2);
     std::memcpy(buf + 2 * (2 * (size_t)nv + p), &v, 2);
 }
 
