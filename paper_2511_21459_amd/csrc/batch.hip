@@ -64,7 +64,8 @@ __global__ __launch_bounds__(256) void k_batch_alloc(const DevMap* __restrict__ 
     const BatchEntry& e = ents[i];
     const DevMap& m = maps[i];
     const uint32_t local = blockIdx.x - e.alloc_begin;
-    if (local == e.alloc_end - e.alloc_begin - 1) alloc_duties(m, e.kind == MRH_FRAME_DEPTH ? e.df.parity : e.sp.parity);
+    const uint32_t count = e.alloc_end - e.alloc_begin, parts = duty_parts(count), part = count - 1u - local;
+    if (part < parts) alloc_duties(m, entry_parity(e), part, parts);
     if (e.kind == MRH_FRAME_DEPTH) {
         if (local < e.tiles) depth_alloc_tile(m, e.df, local, e.tiles_x);
         else depth_cull(m, e.df, local - e.tiles, e.alloc_end - e.alloc_begin - e.tiles);
@@ -73,13 +74,12 @@ __global__ __launch_bounds__(256) void k_batch_alloc(const DevMap* __restrict__ 
     }
 }
 
-template <int ST>
 __global__ __launch_bounds__(256) void k_batch_rays(const DevMap* __restrict__ maps, const BatchEntry* __restrict__ ents,
                                                     int n) {
-    __shared__ unsigned long long tab[kSatSlots];
+    __shared__ RayLds lds;
     const int i = entry_of(ents, n, blockIdx.x, true);
     if (i < 0) return;  // uniform across the workgroup
-    points_ray_chunk<ST, false>(maps[i], ents[i].sp, blockIdx.x - ents[i].ray_begin, tab);
+    points_ray_chunk(maps[i], ents[i].sp, blockIdx.x - ents[i].ray_begin, lds);
 }
 
 // After the ray launch: each LiDAR map's touched blocks onto its update queues, kBatchTouchWgs
@@ -107,8 +107,11 @@ __global__ __launch_bounds__(256) void k_batch_update(const DevMap* __restrict__
     __shared__ TaskCounts cnt[kMaxBatch];
     __shared__ uint32_t pre[kMaxBatch + 1];
     __shared__ unsigned long long wst[kMaxBatch][6];
-    if ((int)blockIdx.x < n && ents[blockIdx.x].kind == KIND)
-        update_duties(maps[blockIdx.x], entry_parity(ents[blockIdx.x]));
+    {
+        // the grid has at least one workgroup per map; each map's hand-off takes an equal share of it
+        const uint32_t parts = duty_parts(gridDim.x / (uint32_t)n), i = blockIdx.x / parts;
+        if (i < (uint32_t)n && ents[i].kind == KIND) update_duties(maps[i], entry_parity(ents[i]), blockIdx.x % parts, parts);
+    }
     for (int i = threadIdx.x; i < n; i += blockDim.x) {
         if (ents[i].kind != KIND) cnt[i] = TaskCounts{{0u, 0u, 0u, 0u}, 0u, 0u};
         else cnt[i] = frame_task_counts(maps[i], KIND == MRH_FRAME_DEPTH, entry_parity(ents[i]));
@@ -210,11 +213,7 @@ static void enqueue_step(mrh_batch* b, hipStream_t s, uint32_t alloc_wgs, uint32
     const int n = b->n;
     if (alloc_wgs) hipLaunchKernelGGL(k_batch_alloc, dim3(alloc_wgs), dim3(256), 0, s, b->d_maps, b->d_ents, n);
     if (ray_wgs) {
-        switch (b->storage) {
-            case MRH_STORE_F16: hipLaunchKernelGGL(k_batch_rays<MRH_STORE_F16>, dim3(ray_wgs), dim3(256), 0, s, b->d_maps, b->d_ents, n); break;
-            case MRH_STORE_BF16: hipLaunchKernelGGL(k_batch_rays<MRH_STORE_BF16>, dim3(ray_wgs), dim3(256), 0, s, b->d_maps, b->d_ents, n); break;
-            default: hipLaunchKernelGGL(k_batch_rays<MRH_STORE_F32>, dim3(ray_wgs), dim3(256), 0, s, b->d_maps, b->d_ents, n);
-        }
+        hipLaunchKernelGGL(k_batch_rays, dim3(ray_wgs), dim3(256), 0, s, b->d_maps, b->d_ents, n);
         hipLaunchKernelGGL(k_batch_touch, dim3((unsigned)n * kBatchTouchWgs), dim3(256), 0, s, b->d_maps, b->d_ents, n);
     }
     // at least one workgroup per map: workgroup i carries map i's update-side hand-off
@@ -364,7 +363,7 @@ mrh_status mrh_batch_integrate(mrh_batch* b, const mrh_frame* frames) {
         } else if (f.kind == MRH_FRAME_POINTS) {
             if (f.n < 0 || (f.n > 0 && !f.data_dev) || !pose_from(f.T_ws, e.sp.P))
                 return batch_err(b, MRH_ERR_INVALID_ARG, "batch: bad point frame");
-            e.sp.xyz = f.data_dev;
+            e.sp.xyz = global(f.data_dev);
             e.sp.n = f.n;
             e.sp.parity = (int32_t)(b->maps[i]->frames & 1u);
             // at least one workgroup: it carries the map's allocation-side hand-off

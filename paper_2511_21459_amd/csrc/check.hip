@@ -39,10 +39,10 @@ extern "C" mrh_status mrh_map_check(mrh_map* map, mrh_check* out) {
     std::vector<HashSlot> table;
     std::vector<unsigned long long> bkey;
     std::vector<uint32_t> binfo, bslot;
-    if (st == MRH_OK) st = fetch(map, table, d.table, nh, "check");
-    if (st == MRH_OK) st = fetch(map, bslot, d.bslot, nb, "check");
-    if (st == MRH_OK) st = fetch(map, bkey, d.bkey, nb, "check");
-    if (st == MRH_OK) st = fetch(map, binfo, d.binfo, nb, "check");
+    if (st == MRH_OK) st = fetch(map, table, plain(d.table), nh, "check");
+    if (st == MRH_OK) st = fetch(map, bslot, plain(d.bslot), nb, "check");
+    if (st == MRH_OK) st = fetch(map, bkey, plain(d.bkey), nb, "check");
+    if (st == MRH_OK) st = fetch(map, binfo, plain(d.binfo), nb, "check");
     if (st != MRH_OK) return st;
 
     // the hash table: every present key once, reachable from its home slot within the probe limit
@@ -118,16 +118,16 @@ extern "C" mrh_status mrh_map_check(mrh_map* map, mrh_check* out) {
             continue;
         }
         std::vector<uint32_t> s;
-        st = fetch(map, s, d.stack[n], (size_t)top, "check");
+        st = fetch(map, s, plain(d.stack[n]), (size_t)top, "check");
         if (st != MRH_OK) return st;
         for (uint32_t v : s) take(n, v, 2);
         out->free_slots[n] = top;
         std::vector<const uint32_t*> lists;
         std::vector<uint32_t> counts;
         if (n == 0) {
-            for (int p = 0; p < 2; ++p) lists.push_back(d.pend0[p]), counts.push_back(c.pending0[p].v);
+            for (int p = 0; p < 2; ++p) lists.push_back(plain(d.pend0[p])), counts.push_back(c.pending0[p].v);
         } else {
-            lists.push_back(d.pend[n]), counts.push_back(c.pending[n].v);
+            lists.push_back(plain(d.pend[n])), counts.push_back(c.pending[n].v);
         }
         for (size_t q = 0; q < lists.size(); ++q) {
             if (counts[q] > cap) {

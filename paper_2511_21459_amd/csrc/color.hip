@@ -49,12 +49,12 @@ __device__ inline void color_fine_block(const DevMap& m, const DepthFrame& f, co
     uint32_t W[8];
     Store<ST>::getW8(m, base, W);
     float c[24];
-    float4* cp = reinterpret_cast<float4*>(m.C[0] + 3 * base);  // 96 B per group, 16 B aligned
+    float MRH_GLOBAL* cp = m.C[0] + 3 * base;  // 96 B per group, 16 B aligned
     if (fresh) {
         for (int k = 0; k < 24; ++k) c[k] = 0.f;
     } else {
         for (int k = 0; k < 6; ++k) {
-            const float4 v = cp[k];
+            const f32x4 v = load_as<f32x4>(cp + 4 * k);
             c[4 * k] = v.x, c[4 * k + 1] = v.y, c[4 * k + 2] = v.z, c[4 * k + 3] = v.w;
         }
     }
@@ -77,18 +77,18 @@ __device__ inline void color_fine_block(const DevMap& m, const DepthFrame& f, co
     if (merged) {
         const size_t at = (size_t)(now & kSlotMask) * 64 + (size_t)lane;
         const float inv = sw > 0.f ? 1.0f / sw : 0.f;
-        float* Cc = m.C[1];
+        float MRH_GLOBAL* Cc = m.C[1];
         Cc[3 * at] = s0 * inv;
         Cc[3 * at + 1] = s1 * inv;
         Cc[3 * at + 2] = s2 * inv;
     } else if (upd || fresh) {
-        for (int k = 0; k < 6; ++k) cp[k] = make_float4(c[4 * k], c[4 * k + 1], c[4 * k + 2], c[4 * k + 3]);
+        for (int k = 0; k < 6; ++k) store_as(cp + 4 * k, f32x4{c[4 * k], c[4 * k + 1], c[4 * k + 2], c[4 * k + 3]});
     }
 }
 
 // One block (one wave): entry e as queued at the frame's start (or a new block of the frame).
 template <int ST>
-__device__ inline void color_block(const DevMap& m, const DepthFrame& f, const uint8_t* __restrict__ rgb, uint4 e,
+__device__ inline void color_block(const DevMap& m, const DepthFrame& f, const uint8_t* __restrict__ rgb, u32x4 e,
                                    bool fresh) {
     const uint32_t id = e.x, info = e.y;
     if (info & kNoBlockBit) return;
@@ -104,7 +104,7 @@ __device__ inline void color_block(const DevMap& m, const DepthFrame& f, const u
         return;
     }
     const int lane = lane_id();
-    float* C = m.C[lvl];
+    float MRH_GLOBAL* C = m.C[lvl];
     for (int r = 0; r < nv; r += 64) {
         const int v = r + lane;
         const bool act = v < nv;
@@ -139,7 +139,7 @@ __device__ inline void color_block(const DevMap& m, const DepthFrame& f, const u
             s2 = group8_sum(s2);
             if (act && (v & 7) == 0) {
                 const size_t at = (size_t)(now & kSlotMask) * (size_t)(nv / 8) + (size_t)(v >> 3);
-                float* Cc = m.C[lvl + 1];
+                float MRH_GLOBAL* Cc = m.C[lvl + 1];
                 const float inv = sw > 0.f ? 1.0f / sw : 0.f;
                 Cc[3 * at] = s0 * inv;
                 Cc[3 * at + 1] = s1 * inv;
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(256) void k_integrate_color(const DevMap* __restric
     const uint32_t wave = uniform((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
     const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
     for (uint32_t t = wave; t < ntask; t += nwaves) {
-        uint4 e;
+        u32x4 e;
         bool fresh = false;
         if (t < c.n[0]) {
             e = m.vis[0][t];
@@ -230,7 +230,7 @@ extern "C" mrh_status mrh_extract_color(mrh_map* map, float* rgb_dev, int64_t vo
     const uint32_t nb = h.n_blocks < map->dm.max_blocks ? h.n_blocks : map->dm.max_blocks;
     std::vector<uint32_t> info(nb);
     if (nb) {
-        st = check_hip(map, hipMemcpy(info.data(), map->dm.binfo, (size_t)nb * 4, hipMemcpyDeviceToHost), "extract colour");
+        st = check_hip(map, hipMemcpy(info.data(), plain(map->dm.binfo), (size_t)nb * 4, hipMemcpyDeviceToHost), "extract colour");
         if (st != MRH_OK) return st;
     }
     // the rows and voxel offsets of mrh_extract_blocks

@@ -35,7 +35,7 @@ mrh_status attach_tiles(mrh_map* map, int32_t width, int32_t height, DepthFrame&
         if (st != MRH_OK) return st;
         map->tile_cap = need;
     }
-    f.tile_max = map->tile_max;
+    f.tile_max = global(map->tile_max);
     return MRH_OK;
 }
 
@@ -53,7 +53,7 @@ bool make_depth_frame(const mrh_config& cfg, const float* depth, int32_t width, 
     f.ify = 1.0 / f.fy;
     f.width = width;
     f.height = height;
-    f.depth = depth;
+    f.depth = global(depth);
     f.fxf = (float)f.fx;
     f.fyf = (float)f.fy;
     f.cxf = (float)f.cx;
@@ -83,7 +83,9 @@ bool make_depth_frame(const mrh_config& cfg, const float* depth, int32_t width, 
 // Workgroups [0, tiles): pixel tiles; [tiles, gridDim): cull.
 __global__ __launch_bounds__(256) void k_alloc_depth(const DevMap* __restrict__ pm, DepthFrame f, uint32_t tiles_x, uint32_t tiles) {
     const DevMap& m = *pm;
-    if (blockIdx.x == gridDim.x - 1) alloc_duties(m, f.parity);
+    // (the last workgroups: at most the cull's)
+    const uint32_t parts = duty_parts(gridDim.x - tiles), part = gridDim.x - 1u - blockIdx.x;
+    if (part < parts) alloc_duties(m, f.parity, part, parts);
     if (blockIdx.x >= tiles) depth_cull(m, f, blockIdx.x - tiles, gridDim.x - tiles);
     else depth_alloc_tile(m, f, blockIdx.x, tiles_x);
 }
@@ -93,7 +95,7 @@ __global__ __launch_bounds__(256) void k_integrate_depth(const DevMap* __restric
     const DevMap& m = *pm;
     const uint32_t wave = uniform((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
     const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
-    if (blockIdx.x == 0) update_duties(m, f.parity);
+    if (blockIdx.x < duty_parts(gridDim.x)) update_duties(m, f.parity, blockIdx.x, duty_parts(gridDim.x));
     const TaskCounts n = frame_task_counts(m, true, f.parity);
     const uint32_t ntask = update_task_count(n);
     TaskStats ts;
@@ -193,7 +195,7 @@ extern "C" mrh_status mrh_integrate_depth_noalloc(mrh_map* map, const float* dep
     if (sa != MRH_OK) return sa;
     f.tiles_x = (width + 15) / 16;
     f.tiles_y = (height + 15) / 16;
-    f.tile_max = tiles_dev;
+    f.tile_max = global(tiles_dev);
     f.parity = (int32_t)(map->frames & 1u);
     map->frames += 1;
     const uint32_t tiles_x = (uint32_t)f.tiles_x, tiles = (uint32_t)tiles_need;

@@ -49,13 +49,13 @@ bool pose_from(const double* T, Pose& P) {
 __global__ void k_reset(const DevMap* __restrict__ pm, uint32_t n_hash) {
     const DevMap& m = *pm;
     const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
-    for (uint32_t i = tid; i < n_hash; i += stride) m.table[i] = HashSlot{kEmptyKey, kInvalidId, kNoBlockBit};
+    for (uint32_t i = tid; i < n_hash; i += stride) store_as(m.table + i, u32x4{0xFFFFFFFFu, 0xFFFFFFFFu, kInvalidId, kNoBlockBit});  // kEmptyKey
     for (int n = 0; n < m.levels; ++n) {
         const uint32_t cap = (uint32_t)m.heap_cap[n];
         for (uint32_t i = tid; i < cap; i += stride) m.stack[n][i] = cap - 1 - i;  // pops give 0, 1, 2, ...
     }
     if (tid == 0) {
-        DevCounters* c = m.ctr;
+        DevCounters MRH_GLOBAL* c = m.ctr;
         c->n_blocks = 0;
         c->pops0 = 0;
         c->error_flags.v = 0;
@@ -63,6 +63,7 @@ __global__ void k_reset(const DevMap* __restrict__ pm, uint32_t n_hash) {
             c->n_prev[p] = 0;
             c->pending0[p].v = 0;
             for (int n = 0; n < 4; ++n) c->vis_n[p][n].v = 0;
+            c->duty[p].v = 0;
         }
         for (int n = 0; n < 4; ++n) {
             c->top[n].v = n < m.levels ? m.heap_cap[n] : 0;
@@ -132,20 +133,20 @@ const char* mrh_last_error(const mrh_map* map) { return map ? map->err : "null m
 static void free_all(mrh_map* m) {
     stream_free(m);
     DevMap& d = m->dm;
-    void* ptrs[] = {d.table, d.bslot, d.bkey, d.binfo, d.bvsum, d.bvcnt, m->ctr, m->partials, m->pose_out, m->dmd,
+    void* ptrs[] = {plain(d.table), plain(d.bslot), plain(d.bkey), plain(d.binfo), plain(d.bvsum), plain(d.bvcnt), m->ctr, m->partials, m->pose_out, m->dmd,
                     m->count_dev, m->mesh_order};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
-    if (d.btouch) (void)hipFree(d.btouch);
+    if (d.btouch) (void)hipFree(plain(d.btouch));
     for (int p = 0; p < 2; ++p)
-        if (d.pend0[p]) (void)hipFree(d.pend0[p]);
-    if (d.rslots) (void)hipFree(d.rslots);
-    if (d.rcount) (void)hipFree(d.rcount);
+        if (d.pend0[p]) (void)hipFree(plain(d.pend0[p]));
+    if (d.rslots) (void)hipFree(plain(d.rslots));
+    if (d.rcount) (void)hipFree(plain(d.rcount));
     if (m->tile_max) (void)hipFree(m->tile_max);
     for (int n = 0; n < 4; ++n)
-        if (d.vis[n]) (void)hipFree(d.vis[n]);
+        if (d.vis[n]) (void)hipFree(plain(d.vis[n]));
     for (int n = 0; n < 4; ++n) {
-        void* lp[] = {d.stack[n], d.pend[n], d.DW[n], d.S2[n], d.C[n], d.acc_sat[n], d.acc_band[n], d.acc_s1[n], d.acc_s2[n]};
+        void* lp[] = {plain(d.stack[n]), plain(d.pend[n]), plain(d.DW[n]), plain(d.S2[n]), plain(d.C[n]), plain(d.acc_sat[n]), plain(d.acc_band[n]), plain(d.acc_s1[n]), plain(d.acc_s2[n])};
         for (void* p : lp)
             if (p) (void)hipFree(p);
     }
@@ -202,38 +203,38 @@ mrh_status mrh_map_create(const mrh_config* cfg, void* stream, mrh_map** out) {
     d.storage = c.storage;
 
     mrh_status st = MRH_OK;
-    auto alloc = [&](void** p, size_t bytes, const char* what) {
+    auto alloc = [&](void* p, size_t bytes, const char* what) {  // p: the address of a pointer
         if (st != MRH_OK) return;
-        st = check_hip(m, hipMalloc(p, bytes ? bytes : 16), what);
+        st = check_hip(m, hipMalloc((void**)p, bytes ? bytes : 16), what);
     };
     const size_t nh = (size_t)c.hash_slots, nb = (size_t)c.max_blocks;
-    alloc((void**)&d.table, nh * sizeof(HashSlot), "hash table");
-    alloc((void**)&d.bslot, nb * 4, "block hash slots");
-    alloc((void**)&d.bkey, nb * 8, "block keys");
-    alloc((void**)&d.binfo, nb * 4, "block info");
-    alloc((void**)&d.bvsum, nb * 8, "block variance sums");
-    alloc((void**)&d.bvcnt, nb * 4, "block variance counts");
-    alloc((void**)&m->ctr, sizeof(DevCounters), "counters");
-    for (int n = 0; n < c.levels; ++n) alloc((void**)&d.vis[n], nb * 16, "visible-block lists");
+    alloc(&d.table, nh * sizeof(HashSlot), "hash table");
+    alloc(&d.bslot, nb * 4, "block hash slots");
+    alloc(&d.bkey, nb * 8, "block keys");
+    alloc(&d.binfo, nb * 4, "block info");
+    alloc(&d.bvsum, nb * 8, "block variance sums");
+    alloc(&d.bvcnt, nb * 4, "block variance counts");
+    alloc(&m->ctr, sizeof(DevCounters), "counters");
+    for (int n = 0; n < c.levels; ++n) alloc(&d.vis[n], nb * 16, "visible-block lists");
     for (int n = 0; n < c.levels; ++n) {
         const int64_t cap = c.heap_blocks[n] > 0 ? c.heap_blocks[n] : c.max_blocks;
         d.heap_cap[n] = (int32_t)cap;
         const size_t nv = (size_t)cap * (size_t)(side_of(n) * side_of(n) * side_of(n));
-        alloc((void**)&d.stack[n], (size_t)cap * 4, "free stack");
-        if (n >= 1) alloc((void**)&d.pend[n], (size_t)cap * 4, "pending frees");
+        alloc(&d.stack[n], (size_t)cap * 4, "free stack");
+        if (n >= 1) alloc(&d.pend[n], (size_t)cap * 4, "pending frees");
         if (n == 0)
-            for (int p = 0; p < 2; ++p) alloc((void**)&d.pend0[p], (size_t)cap * 4, "pending frees");
+            for (int p = 0; p < 2; ++p) alloc(&d.pend0[p], (size_t)cap * 4, "pending frees");
         const size_t pb = (size_t)plane_bytes(c.storage);
-        alloc((void**)&d.DW[n], nv * 2 * pb, "TSDF and weight heap");
-        alloc((void**)&d.S2[n], nv * pb, "variance heap");
-        if (c.color) alloc((void**)&d.C[n], nv * 12, "colour heap");
+        alloc(&d.DW[n], nv * 2 * pb, "TSDF and weight heap");
+        alloc(&d.S2[n], nv * pb, "variance heap");
+        if (c.color) alloc(&d.C[n], nv * 12, "colour heap");
     }
     m->partials_cap = 1024;
-    alloc((void**)&m->partials, (size_t)m->partials_cap * 6 * 8, "reduction partials");
-    alloc((void**)&m->pose_out, 6 * 8, "pose gradient");
-    alloc((void**)&m->count_dev, 8, "extraction counter");
-    alloc((void**)&m->dmd, sizeof(DevMap), "map descriptor");
-    d.ctr = m->ctr;
+    alloc(&m->partials, (size_t)m->partials_cap * 6 * 8, "reduction partials");
+    alloc(&m->pose_out, 6 * 8, "pose gradient");
+    alloc(&m->count_dev, 8, "extraction counter");
+    alloc(&m->dmd, sizeof(DevMap), "map descriptor");
+    d.ctr = global(m->ctr);
     if (st == MRH_OK) st = upload_descriptor(m);
     if (st != MRH_OK) {
         free_all(m);
@@ -336,7 +337,7 @@ mrh_status mrh_extract_blocks(mrh_map* map, int32_t* keys_dev, uint8_t* levels_d
     const uint32_t nb = h.n_blocks < map->dm.max_blocks ? h.n_blocks : map->dm.max_blocks;
     std::vector<uint32_t> info(nb);
     if (nb) {
-        st = check_hip(map, hipMemcpy(info.data(), map->dm.binfo, (size_t)nb * 4, hipMemcpyDeviceToHost), "extract");
+        st = check_hip(map, hipMemcpy(info.data(), plain(map->dm.binfo), (size_t)nb * 4, hipMemcpyDeviceToHost), "extract");
         if (st != MRH_OK) return st;
     }
     // rows of blocks streamed out to the host store are skipped; pos[id] is a row's output index
@@ -365,8 +366,8 @@ mrh_status mrh_extract_blocks(mrh_map* map, int32_t* keys_dev, uint8_t* levels_d
     // block voxel offsets per output row (the caller's buffer when given) and row positions per id
     int64_t* doffs = offsets_dev;
     int32_t* dpos = nullptr;
-    if (!doffs) st = check_hip(map, hipMalloc((void**)&doffs, ((size_t)nout + 1) * 8), "extract offsets");
-    if (st == MRH_OK) st = check_hip(map, hipMalloc((void**)&dpos, (size_t)nb * 4), "extract rows");
+    if (!doffs) st = check_hip(map, hipMalloc(&doffs, ((size_t)nout + 1) * 8), "extract offsets");
+    if (st == MRH_OK) st = check_hip(map, hipMalloc(&dpos, (size_t)nb * 4), "extract rows");
     if (st == MRH_OK) st = check_hip(map, hipMemcpy(doffs, offs.data(), ((size_t)nout + 1) * 8, hipMemcpyHostToDevice), "extract");
     if (st == MRH_OK) st = check_hip(map, hipMemcpy(dpos, pos.data(), (size_t)nb * 4, hipMemcpyHostToDevice), "extract");
     if (st == MRH_OK) {

@@ -20,14 +20,14 @@ struct DepthFrame {
     Pose P;
     double fx, fy, cx, cy, ifx, ify;
     int32_t width, height;
-    const float* depth;  // device z-depth image, row-major
+    const float MRH_GLOBAL* depth;  // device z-depth image, row-major
     float fxf, fyf, cxf, cyf;  // intrinsics rounded to FP32 for the fast projection
     // conservative culling of whole blocks (camera frame): side-plane normals and a range bound
     double plane[4][3];
     double cull_range;
     // largest valid depth per 16 x 16 pixel tile (written by the allocation launch, -1 when the
     // tile holds no valid sample), tiles_x tiles per row
-    float* tile_max;
+    float MRH_GLOBAL* tile_max;
     int32_t tiles_x, tiles_y;
 };
 
@@ -118,7 +118,7 @@ __device__ inline int observe_fast(const DevMap& m, double x2, float lam, float 
 }
 
 // One voxel: pixel decision, depth lookup, observation.
-__device__ inline bool observe(const DevMap& m, const DepthFrame& f, const float* __restrict__ depth, double x0,
+__device__ inline bool observe(const DevMap& m, const DepthFrame& f, const float MRH_GLOBAL* __restrict__ depth, double x0,
                                double x1, double x2, float& obs) {
     float lam;
     int p = pixel_fast(f, x0, x1, x2, lam);
@@ -218,7 +218,7 @@ constexpr int kTileNew = 512;  // new blocks a tile registers with one allocatio
 // workgroup; a key that finds the list full is registered by its wave directly.
 __device__ inline void depth_alloc_tile(const DevMap& m, const DepthFrame& f, uint32_t tile, uint32_t tiles_x) {
     const int lane = lane_id(), wave = threadIdx.x >> 6;
-    const float* __restrict__ depth = f.depth;
+    const float MRH_GLOBAL* __restrict__ depth = f.depth;
     const int u = (int)(tile % tiles_x) * 16 + (lane & 15);
     const int v = (int)(tile / tiles_x) * 16 + wave * 4 + (lane >> 4);
     bool ok = u < f.width && v < f.height;
@@ -315,7 +315,7 @@ __device__ inline void voxel_camera(const DevMap& m, const DepthFrame& f, int64_
 // (-1: none), obs[q] its observation, and the returned mask has bit q set when the frame updates the
 // voxel.  Every launch that needs these decisions (the update, the colour launch) calls this one
 // function, so they agree voxel for voxel.
-__device__ inline uint32_t fine_decisions(const DevMap& m, const DepthFrame& f, const float* __restrict__ depth,
+__device__ inline uint32_t fine_decisions(const DevMap& m, const DepthFrame& f, const float MRH_GLOBAL* __restrict__ depth,
                                           int32_t bx, int32_t by, int32_t bz, int I, int J, int K, int pix[8],
                                           float obs[8]) {
     const double nu = m.nu[0];
@@ -390,10 +390,10 @@ __device__ inline uint32_t fine_decisions(const DevMap& m, const DepthFrame& f, 
 
 // Level-0 block: lane l owns the 2x2x2 group of Morton positions 8l .. 8l+7.
 template <int ST>
-__device__ inline TaskOut integrate_fine_block(const DevMap& m, const DepthFrame& f, const float* __restrict__ depth,
-                                            const uint4 eq) {
+__device__ inline TaskOut integrate_fine_block(const DevMap& m, const DepthFrame& f, const float MRH_GLOBAL* __restrict__ depth,
+                                            const u32x4 eq) {
     const int lane = lane_id();
-    const uint4 e = uniform(eq);  // one block per wave
+    const u32x4 e = uniform(eq);  // one block per wave
     const uint32_t id = e.x, info = e.y;
     if (info & kNoBlockBit) return TaskOut{};
     int32_t bx, by, bz;
@@ -442,10 +442,10 @@ __device__ inline TaskOut integrate_fine_block(const DevMap& m, const DepthFrame
 
 // Level-1 block: lane l owns the voxel at Morton position l.
 template <int ST>
-__device__ inline TaskOut integrate_level1_block(const DevMap& m, const DepthFrame& f, const float* __restrict__ depth,
-                                              const uint4 eq) {
+__device__ inline TaskOut integrate_level1_block(const DevMap& m, const DepthFrame& f, const float MRH_GLOBAL* __restrict__ depth,
+                                              const u32x4 eq) {
     const int lane = lane_id();
-    const uint4 e = uniform(eq);  // one block per wave
+    const u32x4 e = uniform(eq);  // one block per wave
     const uint32_t id = e.x, info = e.y;
     int32_t bx, by, bz;
     unpack_key(entry_key(e), bx, by, bz);
@@ -483,8 +483,8 @@ __device__ inline TaskOut integrate_level1_block(const DevMap& m, const DepthFra
 
 // 64 / seg blocks of `level` (2: seg = 8 voxels, 3: seg = 1 voxel) per wave.
 template <int ST>
-__device__ inline TaskOut integrate_packed_blocks(const DevMap& m, const DepthFrame& f, const float* __restrict__ depth,
-                                               const uint4* list, uint32_t count, uint32_t group, int level) {
+__device__ inline TaskOut integrate_packed_blocks(const DevMap& m, const DepthFrame& f, const float MRH_GLOBAL* __restrict__ depth,
+                                               const u32x4 MRH_GLOBAL* list, uint32_t count, uint32_t group, int level) {
     const int lane = lane_id();
     const int seg = level == 2 ? 8 : 1;
     const uint32_t bi = group * (uint32_t)(64 / seg) + (uint32_t)(lane / seg);
@@ -493,7 +493,7 @@ __device__ inline TaskOut integrate_packed_blocks(const DevMap& m, const DepthFr
     bool upd = false;
     float obs = 0.f;
     if (live) {
-        const uint4 e = list[bi];
+        const u32x4 e = list[bi];
         id = e.x;
         info = e.y;
         int32_t bx, by, bz;
@@ -533,14 +533,19 @@ template <int ST>
 __device__ inline TaskOut depth_update_task(const DevMap& m, const DepthFrame& f, uint32_t t, const TaskCounts& c) {
     const uint32_t n0 = c.n[0] + c.n_new;
     const uint32_t g2 = (c.n[2] + 7) / 8;
-    if (t < c.n[0]) return integrate_fine_block<ST>(m, f, f.depth, m.vis[0][t]);
+    // each work unit is called in one place: its code is inlined there, and a launch of some 30 us pays for
+    // fetching every copy
     if (t < n0) {
         const uint32_t id = c.new_base + (t - c.n[0]);
-        return integrate_fine_block<ST>(m, f, f.depth, make_entry(id, m.binfo[id], m.bkey[id]));
+        u32x4 e;
+        if (t < c.n[0]) e = m.vis[0][t];
+        else e = make_entry(id, m.binfo[id], m.bkey[id]);
+        return integrate_fine_block<ST>(m, f, f.depth, e);
     }
     if (t < n0 + c.n[1]) return integrate_level1_block<ST>(m, f, f.depth, m.vis[1][t - n0]);
-    if (t < n0 + c.n[1] + g2) return integrate_packed_blocks<ST>(m, f, f.depth, m.vis[2], c.n[2], t - n0 - c.n[1], 2);
-    return integrate_packed_blocks<ST>(m, f, f.depth, m.vis[3], c.n[3], t - n0 - c.n[1] - g2, 3);
+    const uint32_t g = t - n0 - c.n[1];
+    const int level = g < g2 ? 2 : 3;
+    return integrate_packed_blocks<ST>(m, f, f.depth, m.vis[level], c.n[level], level == 2 ? g : g - g2, level);
 }
 
 }  // namespace mrh

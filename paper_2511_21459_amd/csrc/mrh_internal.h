@@ -19,7 +19,61 @@
 
 #include "mrhash.h"
 
+// Pointers that kernels read from memory (the map and frame descriptors) are declared as pointers to
+// global memory.  The compiler cannot tell where a plain pointer read from memory points: its
+// accesses become flat ones, which also count as LDS accesses, so that every scalar read of the
+// descriptor between them waits until they have all come back, one after the other.
+#define MRH_GLOBAL __attribute__((address_space(1)))
+
 namespace mrh {
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+
+// The atomics of the HIP headers (relaxed, device scope) on global pointers.
+using ::atomicAdd;
+using ::atomicCAS;
+using ::atomicOr;
+using ::atomicSub;
+template <typename T>
+__device__ inline T atomicAdd(T MRH_GLOBAL* p, T v) {
+    return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ inline T atomicSub(T MRH_GLOBAL* p, T v) {
+    return __hip_atomic_fetch_add(p, (T)-v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ inline T atomicOr(T MRH_GLOBAL* p, T v) {
+    return __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ inline T atomicCAS(T MRH_GLOBAL* p, T expected, T v) {
+    __hip_atomic_compare_exchange_strong(p, &expected, v, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return expected;
+}
+
+// V-sized access at p (aligned to V).
+template <typename V, typename T>
+__device__ inline V load_as(const T MRH_GLOBAL* p) {
+    return *reinterpret_cast<const V MRH_GLOBAL*>(p);
+}
+template <typename V, typename T>
+__device__ inline void store_as(T MRH_GLOBAL* p, V v) {
+    *reinterpret_cast<V MRH_GLOBAL*>(p) = v;
+}
+
+// Between a descriptor's pointer and a plain one (host code).
+template <typename T>
+inline T* plain(T MRH_GLOBAL* p) {
+    return (T*)p;
+}
+template <typename T>
+inline T MRH_GLOBAL* global(T* p) {
+    return (T MRH_GLOBAL*)p;
+}
 
 constexpr unsigned long long kEmptyKey = ~0ull;
 constexpr uint32_t kInvalidId = 0xFFFFFFFFu;
@@ -55,7 +109,8 @@ struct alignas(128) Line {
 // only: per-frame counts are double-buffered by frame parity p (the host alternates it), each
 // launch reads the buffer of its own frame and clears or fills the other one; slots freed at
 // level n >= 1 are returned to their stacks by the next allocation launch (which never pops those
-// levels), level-0 slots by one workgroup of the next update launch (which never pops level 0).
+// levels), level-0 slots by the next update launch (which never pops level 0), in both by a few
+// workgroups, the last of which to finish settles the counts.
 struct alignas(128) DevCounters {
     // allocation word: one 64-bit atomic adds k to both halves for k new blocks
     uint32_t n_blocks;   // block ids handed out (keys inserted), low half
@@ -66,6 +121,7 @@ struct alignas(128) DevCounters {
     Line<uint32_t> pending[4];   // slots freed at level n >= 1 this frame (entry 0 unused)
     Line<uint32_t> pending0[2];  // slots freed at level 0, per parity
     Line<uint32_t> vis_n[2][4];  // per parity: blocks queued for the update, per level
+    Line<uint32_t> duty[2];      // workgroups done with the hand-off of the allocation / update launch
     unsigned long long frame[kStripes][16];  // statistics since the reset, in stripes
 };
 
@@ -81,41 +137,42 @@ struct alignas(16) HashSlot {
 
 // Everything a kernel needs to find the map; passed by value as a kernel argument.
 struct DevMap {
-    HashSlot* table;
-    uint32_t* bslot;
+    HashSlot MRH_GLOBAL* table;
+    uint32_t MRH_GLOBAL* bslot;
     uint32_t hmask;
     int32_t max_probe;
-    unsigned long long* bkey;
-    uint32_t* binfo;
-    double* bvsum;
-    uint32_t* bvcnt;
+    unsigned long long MRH_GLOBAL* bkey;
+    uint32_t MRH_GLOBAL* binfo;
+    double MRH_GLOBAL* bvsum;
+    uint32_t MRH_GLOBAL* bvcnt;
     uint32_t max_blocks;
     int32_t levels;
-    DevCounters* ctr;
-    uint32_t* stack[4];
-    uint32_t* pend[4];      // level n >= 1 frees (entry 0 unused)
-    uint32_t* pend0[2];     // level-0 frees, per parity
+    DevCounters MRH_GLOBAL* ctr;
+    uint32_t MRH_GLOBAL* stack[4];
+    uint32_t MRH_GLOBAL* pend[4];      // level n >= 1 frees (entry 0 unused)
+    uint32_t MRH_GLOBAL* pend0[2];     // level-0 frees, per parity
     int32_t heap_cap[4];
-    void* DW[4];  // per level, planes of the storage format (see mrh_store.h)
-    void* S2[4];
-    float* C[4];  // per level, colour RGB float32 x 3 per voxel (maps created with colour; else null)
+    void MRH_GLOBAL* DW[4];  // per level, planes of the storage format (see mrh_store.h)
+    void MRH_GLOBAL* S2[4];
+    float MRH_GLOBAL* C[4];  // per level, colour RGB float32 x 3 per voxel (maps created with colour; else null)
     // LiDAR per-frame accumulators, parallel to the heaps (zero between frames):
-    // saturated (+tau) observation counts, band observation counts, and the exact integer sums of
-    // the band observations' fixed-point values q = rint(d 2^24) and of q^2
-    uint32_t* acc_sat[4];
-    uint32_t* acc_band[4];
-    unsigned long long* acc_s1[4];
-    unsigned long long* acc_s2[4];
+    // saturated (+tau) observation counts, and the exact integer sums of the band observations'
+    // fixed-point values q = rint(d 2^24), with their count in the same word (see accumulate_band), and
+    // of q^2; acc_band holds the count where that word could overflow (band_wide), else it is null
+    uint32_t MRH_GLOBAL* acc_sat[4];
+    uint32_t MRH_GLOBAL* acc_band[4];
+    unsigned long long MRH_GLOBAL* acc_s1[4];
+    unsigned long long MRH_GLOBAL* acc_s2[4];
     // per block: the lane groups rays touched this frame, bit g = the voxels lane g of the update
     // owns (level 0: Morton positions 8g .. 8g+7, level 1: position g; levels 2, 3: bit 0)
-    unsigned long long* btouch;
+    unsigned long long MRH_GLOBAL* btouch;
     // LiDAR: the hash slots of the block keys each ray's walk visits, in walk order (rcap_k per ray,
     // written by the allocation launch; kInvalidId for a key the full table could not take), and
     // their count per ray (may exceed rcap_k)
-    uint32_t* rslots;
-    uint32_t* rcount;
+    uint32_t MRH_GLOBAL* rslots;
+    uint32_t MRH_GLOBAL* rcount;
     int32_t rcap_k;
-    uint4* vis[4];     // per level: the blocks the update visits this frame, (id, info, key lo, key hi)
+    u32x4 MRH_GLOBAL* vis[4];     // per level: the blocks the update visits this frame, (id, info, key lo, key hi)
     double B, invB;
     double nu[4], inv_nu[4];
     double tau, var_thr;
@@ -123,21 +180,42 @@ struct DevMap {
     float tau_f, inv_tau_f, tau2_f;
     float max_depth_f;  // largest float <= max_depth: (double)d <= max_depth  <=>  d <= max_depth_f
     int32_t min_obs, form, carve, storage;
+    int32_t band_wide;
+    long long band_bias;  // added to each q of a shared word: at least tau 2^24
 };
 
 // An update-queue entry carries the block's table row, so an update task needs no second lookup.
-__device__ inline uint4 make_entry(uint32_t id, uint32_t info, unsigned long long key) {
-    return make_uint4(id, info, (uint32_t)key, (uint32_t)(key >> 32));
+__device__ inline u32x4 make_entry(uint32_t id, uint32_t info, unsigned long long key) {
+    return u32x4{id, info, (uint32_t)key, (uint32_t)(key >> 32)};
 }
 
-__device__ inline unsigned long long entry_key(const uint4& e) {
+__device__ inline unsigned long long entry_key(const u32x4& e) {
     return (unsigned long long)e.z | ((unsigned long long)e.w << 32);
 }
 
 // Values the caller knows to be equal on every active lane, moved to scalar registers (a wave waits
 // for a loaded value here, so loaded values that are needed late are better left alone).
 __device__ inline uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
-__device__ inline uint4 uniform(const uint4& e) { return make_uint4(uniform(e.x), uniform(e.y), uniform(e.z), uniform(e.w)); }
+__device__ inline u32x4 uniform(const u32x4& e) { return u32x4{uniform(e.x), uniform(e.y), uniform(e.z), uniform(e.w)}; }
+
+// p[level] of a descriptor's per-level pointers where the lanes' levels differ: selected among scalar
+// reads.  Indexed, it is a vector read per lane, which waits for every memory operation the wave has
+// in flight (they complete in order), and then the access behind it waits again.  (uniform() keeps the
+// compiler from turning the selection back into an indexed read.)
+template <typename T>
+__device__ inline T MRH_GLOBAL* of_level(T MRH_GLOBAL* const p[4], int level) {
+    unsigned long long v[4];
+    for (int k = 0; k < 4; ++k) {
+        const unsigned long long q = (unsigned long long)p[k];
+        v[k] = (unsigned long long)uniform((uint32_t)q) | ((unsigned long long)uniform((uint32_t)(q >> 32)) << 32);
+    }
+    const unsigned long long a = level & 1 ? v[1] : v[0], b = level & 1 ? v[3] : v[2];
+    return (T MRH_GLOBAL*)(level & 2 ? b : a);
+}
+
+// nu[level] and inv_nu[level], exactly (powers of two times the finest), on lanes of different levels.
+__device__ inline double nu_of(const double nu[4], int level) { return __builtin_ldexp(nu[0], level); }
+__device__ inline double inv_nu_of(const double inv_nu[4], int level) { return __builtin_ldexp(inv_nu[0], -level); }
 
 // world <- sensor rigid transform, FP64
 struct Pose {
@@ -193,7 +271,7 @@ __device__ inline uint32_t probe_find(const DevMap& m, unsigned long long key, u
 
 // One slot, in one 16-byte read (launches that insert nothing).
 __device__ inline HashSlot load_slot(const DevMap& m, uint32_t h) {
-    const uint4 v = *reinterpret_cast<const uint4*>(m.table + h);
+    const u32x4 v = load_as<u32x4>(m.table + h);
     return HashSlot{(unsigned long long)v.x | ((unsigned long long)v.y << 32), v.z, v.w};
 }
 
@@ -420,13 +498,14 @@ __device__ inline bool segment_in_range(const double a[3], const double e[3], do
 // parameters are recomputed from the cell index at every step.
 // One axis of a walk: position A (in cell units), cell c, step direction, inverse extent and the
 // parameter of the next boundary.
-__device__ inline void walk_axis(double a, double e, double inv_cell, double& A, int64_t& c, int& st, double& iD,
-                                 double& t, int64_t& guard) {
+// (Cells fit 32 bits: segment_in_range holds before a walk starts.)
+__device__ inline void walk_axis(double a, double e, double inv_cell, double& A, int32_t& c, int& st, double& iD,
+                                 double& t, int32_t& guard) {
     A = a * inv_cell;
     const double E = e * inv_cell;
-    c = (int64_t)__builtin_floor(A);
+    c = (int32_t)__builtin_floor(A);
     const double dv = E - A;
-    const int64_t fe = (int64_t)__builtin_floor(E);
+    const int32_t fe = (int32_t)__builtin_floor(E);
     guard += fe > c ? fe - c : c - fe;
     if (dv > 0.0) {
         st = 1;
@@ -449,9 +528,9 @@ __device__ inline void walk_axis(double a, double e, double inv_cell, double& A,
 // arrays) so the walk state lives in registers.
 struct Walk {
     double A0, A1, A2, iD0, iD1, iD2, t0, t1, t2;
-    int64_t c0, c1, c2;
+    int32_t c0, c1, c2;
     int s0, s1, s2;
-    int64_t guard;
+    int32_t guard;
 
     __device__ inline void init(const double a[3], const double e[3], double inv_cell) {
         guard = 3;

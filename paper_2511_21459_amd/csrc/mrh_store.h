@@ -68,51 +68,54 @@ struct Store;
 template <>
 struct Store<MRH_STORE_F32> {
     static constexpr int kBytes = 12;
-    __device__ static inline const uint2* dw(const DevMap& m, int lvl) { return static_cast<const uint2*>(m.DW[lvl]); }
+    __device__ static inline u32x2 MRH_GLOBAL* dw(const DevMap& m, int lvl) { return (u32x2 MRH_GLOBAL*)m.DW[lvl]; }
+    __device__ static inline float MRH_GLOBAL* s2(const DevMap& m, int lvl) { return (float MRH_GLOBAL*)m.S2[lvl]; }
+    // (the lanes' levels may differ)
     __device__ static inline void getDW(const DevMap& m, int lvl, size_t i, float& D, uint32_t& W) {
-        const uint2 v = dw(m, lvl)[i];
-        D = __builtin_bit_cast(float, v.x);
+        const u32x2 v = ((u32x2 MRH_GLOBAL*)of_level(m.DW, lvl))[i];
+        const uint32_t d = v.x;
+        D = __builtin_bit_cast(float, d);
         W = v.y;
     }
     __device__ static inline void get(const DevMap& m, int lvl, size_t i, float& D, uint32_t& W, float& S2) {
-        getDW(m, lvl, i, D, W);
-        S2 = static_cast<const float*>(m.S2[lvl])[i];
+        const u32x2 v = dw(m, lvl)[i];
+        const uint32_t d = v.x;
+        D = __builtin_bit_cast(float, d);
+        W = v.y;
+        S2 = s2(m, lvl)[i];
     }
     __device__ static inline void put(const DevMap& m, int lvl, size_t i, float D, uint32_t W, float S2) {
-        static_cast<uint2*>(m.DW[lvl])[i] = make_uint2(__builtin_bit_cast(uint32_t, D), W);
-        static_cast<float*>(m.S2[lvl])[i] = S2;
+        dw(m, lvl)[i] = u32x2{__builtin_bit_cast(uint32_t, D), W};
+        s2(m, lvl)[i] = S2;
     }
     __device__ static inline void round(const DevMap&, float&, uint32_t&, float&) {}
     __device__ static inline uint32_t getW(const DevMap& m, int lvl, size_t i) { return dw(m, lvl)[i].y; }
     // the weights of 8 consecutive level-0 voxels starting at base (a multiple of 8)
     __device__ static inline void getW8(const DevMap& m, size_t base, uint32_t W[8]) {
-        const uint4* p = reinterpret_cast<const uint4*>(dw(m, 0) + base);
         for (int k = 0; k < 4; ++k) {
-            const uint4 v = p[k];
+            const u32x4 v = load_as<u32x4>(dw(m, 0) + base + 2 * k);
             W[2 * k] = v.y, W[2 * k + 1] = v.w;
         }
     }
     // 8 consecutive level-0 voxels starting at base (a multiple of 8)
     __device__ static inline void get8(const DevMap& m, size_t base, float D[8], uint32_t W[8], float S2[8]) {
-        const uint4* p = reinterpret_cast<const uint4*>(dw(m, 0) + base);
-        const float4* sp = reinterpret_cast<const float4*>(static_cast<const float*>(m.S2[0]) + base);
-        const uint4 v[4] = {p[0], p[1], p[2], p[3]};
-        const float4 s0 = sp[0], s1 = sp[1];
+        u32x4 v[4];
+        for (int k = 0; k < 4; ++k) v[k] = load_as<u32x4>(dw(m, 0) + base + 2 * k);
+        const f32x4 s0 = load_as<f32x4>(s2(m, 0) + base), s1 = load_as<f32x4>(s2(m, 0) + base + 4);
         for (int k = 0; k < 4; ++k) {
-            D[2 * k] = __builtin_bit_cast(float, v[k].x), W[2 * k] = v[k].y;
-            D[2 * k + 1] = __builtin_bit_cast(float, v[k].z), W[2 * k + 1] = v[k].w;
+            const uint32_t d0 = v[k].x, d1 = v[k].z;  // (a bit cast of a vector's component takes the first one)
+            D[2 * k] = __builtin_bit_cast(float, d0), W[2 * k] = v[k].y;
+            D[2 * k + 1] = __builtin_bit_cast(float, d1), W[2 * k + 1] = v[k].w;
         }
         S2[0] = s0.x, S2[1] = s0.y, S2[2] = s0.z, S2[3] = s0.w, S2[4] = s1.x, S2[5] = s1.y, S2[6] = s1.z, S2[7] = s1.w;
     }
     __device__ static inline void put8(const DevMap& m, size_t base, const float D[8], const uint32_t W[8],
                                        const float S2[8]) {
-        uint4* p = reinterpret_cast<uint4*>(static_cast<uint2*>(m.DW[0]) + base);
-        float4* sp = reinterpret_cast<float4*>(static_cast<float*>(m.S2[0]) + base);
         for (int k = 0; k < 4; ++k)
-            p[k] = make_uint4(__builtin_bit_cast(uint32_t, D[2 * k]), W[2 * k], __builtin_bit_cast(uint32_t, D[2 * k + 1]),
-                              W[2 * k + 1]);
-        sp[0] = make_float4(S2[0], S2[1], S2[2], S2[3]);
-        sp[1] = make_float4(S2[4], S2[5], S2[6], S2[7]);
+            store_as(dw(m, 0) + base + 2 * k, u32x4{__builtin_bit_cast(uint32_t, D[2 * k]), W[2 * k],
+                                                    __builtin_bit_cast(uint32_t, D[2 * k + 1]), W[2 * k + 1]});
+        store_as(s2(m, 0) + base, f32x4{S2[0], S2[1], S2[2], S2[3]});
+        store_as(s2(m, 0) + base + 4, f32x4{S2[4], S2[5], S2[6], S2[7]});
     }
 };
 
@@ -156,40 +159,42 @@ struct Store16 {
         S2 = decS2(m, encS2(m, S2, W), W);
     }
     // a voxel's D (low half) and W in one word
-    __device__ static inline const uint32_t* dw(const DevMap& m, int lvl) { return static_cast<const uint32_t*>(m.DW[lvl]); }
+    __device__ static inline uint32_t MRH_GLOBAL* dw(const DevMap& m, int lvl) { return (uint32_t MRH_GLOBAL*)m.DW[lvl]; }
+    __device__ static inline uint16_t MRH_GLOBAL* s2(const DevMap& m, int lvl) { return (uint16_t MRH_GLOBAL*)m.S2[lvl]; }
+    // (the lanes' levels may differ)
     __device__ static inline void getDW(const DevMap& m, int lvl, size_t i, float& D, uint32_t& W) {
-        const uint32_t v = dw(m, lvl)[i];
+        const uint32_t v = ((uint32_t MRH_GLOBAL*)of_level(m.DW, lvl))[i];
         D = decD(m, (uint16_t)v);
         W = decW((uint16_t)(v >> 16));
     }
     __device__ static inline void get(const DevMap& m, int lvl, size_t i, float& D, uint32_t& W, float& S2) {
-        getDW(m, lvl, i, D, W);
-        S2 = decS2(m, static_cast<const uint16_t*>(m.S2[lvl])[i], W);
+        const uint32_t v = dw(m, lvl)[i];
+        D = decD(m, (uint16_t)v);
+        W = decW((uint16_t)(v >> 16));
+        S2 = decS2(m, s2(m, lvl)[i], W);
     }
     __device__ static inline void put(const DevMap& m, int lvl, size_t i, float D, uint32_t W, float S2) {
         const uint16_t wb = encW(W);
-        static_cast<uint32_t*>(m.DW[lvl])[i] = (uint32_t)encD(m, D) | ((uint32_t)wb << 16);
-        static_cast<uint16_t*>(m.S2[lvl])[i] = encS2(m, S2, decW(wb));
+        dw(m, lvl)[i] = (uint32_t)encD(m, D) | ((uint32_t)wb << 16);
+        s2(m, lvl)[i] = encS2(m, S2, decW(wb));
     }
     __device__ static inline uint32_t getW(const DevMap& m, int lvl, size_t i) { return decW((uint16_t)(dw(m, lvl)[i] >> 16)); }
-    __device__ static inline void unpack8(uint4 v, uint16_t o[8]) {
+    __device__ static inline void unpack8(u32x4 v, uint16_t o[8]) {
         o[0] = (uint16_t)v.x, o[1] = (uint16_t)(v.x >> 16), o[2] = (uint16_t)v.y, o[3] = (uint16_t)(v.y >> 16);
         o[4] = (uint16_t)v.z, o[5] = (uint16_t)(v.z >> 16), o[6] = (uint16_t)v.w, o[7] = (uint16_t)(v.w >> 16);
     }
-    __device__ static inline uint4 pack8(const uint16_t o[8]) {
-        return make_uint4((uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16),
-                          (uint32_t)o[4] | ((uint32_t)o[5] << 16), (uint32_t)o[6] | ((uint32_t)o[7] << 16));
+    __device__ static inline u32x4 pack8(const uint16_t o[8]) {
+        return u32x4{(uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16),
+                          (uint32_t)o[4] | ((uint32_t)o[5] << 16), (uint32_t)o[6] | ((uint32_t)o[7] << 16)};
     }
     __device__ static inline void getW8(const DevMap& m, size_t base, uint32_t W[8]) {
-        const uint4* p = reinterpret_cast<const uint4*>(dw(m, 0) + base);
-        const uint4 a = p[0], b = p[1];
+        const u32x4 a = load_as<u32x4>(dw(m, 0) + base), b = load_as<u32x4>(dw(m, 0) + base + 4);
         const uint32_t v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
         for (int q = 0; q < 8; ++q) W[q] = decW((uint16_t)(v[q] >> 16));
     }
     __device__ static inline void get8(const DevMap& m, size_t base, float D[8], uint32_t W[8], float S2[8]) {
-        const uint4* p = reinterpret_cast<const uint4*>(dw(m, 0) + base);
-        const uint4 a = p[0], b = p[1];
-        const uint4 s = *reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(m.S2[0]) + base);
+        const u32x4 a = load_as<u32x4>(dw(m, 0) + base), b = load_as<u32x4>(dw(m, 0) + base + 4);
+        const u32x4 s = load_as<u32x4>(s2(m, 0) + base);
         const uint32_t v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
         uint16_t sb[8];
         unpack8(s, sb);
@@ -208,10 +213,9 @@ struct Store16 {
             v[q] = (uint32_t)encD(m, D[q]) | ((uint32_t)wb << 16);
             sb[q] = encS2(m, S2[q], decW(wb));
         }
-        uint4* p = reinterpret_cast<uint4*>(static_cast<uint32_t*>(m.DW[0]) + base);
-        p[0] = make_uint4(v[0], v[1], v[2], v[3]);
-        p[1] = make_uint4(v[4], v[5], v[6], v[7]);
-        *reinterpret_cast<uint4*>(static_cast<uint16_t*>(m.S2[0]) + base) = pack8(sb);
+        store_as(dw(m, 0) + base, u32x4{v[0], v[1], v[2], v[3]});
+        store_as(dw(m, 0) + base + 4, u32x4{v[4], v[5], v[6], v[7]});
+        store_as(s2(m, 0) + base, pack8(sb));
     }
 };
 

@@ -492,35 +492,62 @@ __device__ inline void queue_block(const DevMap& m, int level, uint32_t id, uint
     }
 }
 
-// Frame hand-off, part 1: run by one workgroup of a frame's allocation launch (frame parity par).
-// Clears the other parity's update-queue counts (the previous frame's, used by the next one) and
-// returns the slots freed at levels >= 1 by the previous frame's merges to their stacks; nothing
+// Workgroups that share a launch's hand-off.  A LiDAR scan frees up to 140 k slots per level, which one
+// workgroup moved in a loop of dependent reads and writes that outlasted the launch (the update of a
+// street's second scan 666 -> 514 us).
+constexpr uint32_t kDutyParts = 32;
+
+// Move n freed slots onto a stack: part `part` of `nparts` workgroups, four in flight per thread.
+__device__ inline void return_slots(const uint32_t MRH_GLOBAL* from, uint32_t MRH_GLOBAL* to, uint32_t n, uint32_t part,
+                                    uint32_t nparts) {
+    const uint32_t step = nparts * blockDim.x;
+    uint32_t i = part * blockDim.x + threadIdx.x;
+    for (; i + 3 * step < n; i += 4 * step) {
+        uint32_t v[4];
+        for (int k = 0; k < 4; ++k) v[k] = from[i + (uint32_t)k * step];
+        for (int k = 0; k < 4; ++k) to[i + (uint32_t)k * step] = v[k];
+    }
+    for (; i < n; i += step) to[i] = from[i];
+}
+
+// Every thread of a sharing workgroup calls, with its reads of the counts done: true on the first
+// thread of the workgroup that finishes last (the counts may then be rewritten).
+__device__ inline bool duty_done(const DevMap& m, int which, uint32_t nparts) {
+    __syncthreads();
+    if (threadIdx.x != 0 || atomicAdd(&m.ctr->duty[which].v, 1u) != nparts - 1u) return false;
+    m.ctr->duty[which].v = 0u;
+    return true;
+}
+
+// Frame hand-off, part 1: run by `nparts` workgroups of a frame's allocation launch (frame parity
+// par).  Clears the other parity's update-queue counts (the previous frame's, used by the next one)
+// and returns the slots freed at levels >= 1 by the previous frame's merges to their stacks; nothing
 // else in the allocation launch touches those counts or stacks.
-__device__ inline void alloc_duties(const DevMap& m, int par) {
-    DevCounters* c = m.ctr;
+__device__ inline void alloc_duties(const DevMap& m, int par, uint32_t part, uint32_t nparts) {
+    DevCounters MRH_GLOBAL* c = m.ctr;
     __shared__ int32_t s_top[4];
     __shared__ uint32_t s_pend[4];
     if (threadIdx.x < 4) {
         const int n = threadIdx.x;
-        c->vis_n[par ^ 1][n].v = 0;
+        if (part == 0) c->vis_n[par ^ 1][n].v = 0;
         s_top[n] = n >= 1 && n < m.levels ? c->top[n].v : 0;
         s_pend[n] = n >= 1 && n < m.levels ? c->pending[n].v : 0u;
     }
     __syncthreads();
-    for (int n = 1; n < m.levels; ++n)
-        for (uint32_t i = threadIdx.x; i < s_pend[n]; i += blockDim.x) m.stack[n][s_top[n] + i] = m.pend[n][i];
-    if (threadIdx.x >= 1 && threadIdx.x < 4 && (int)threadIdx.x < m.levels && s_pend[threadIdx.x]) {
-        c->top[threadIdx.x].v = s_top[threadIdx.x] + (int32_t)s_pend[threadIdx.x];
-        c->pending[threadIdx.x].v = 0;
-    }
+    for (int n = 1; n < m.levels; ++n) return_slots(m.pend[n], m.stack[n] + s_top[n], s_pend[n], part, nparts);
+    if (duty_done(m, 0, nparts))
+        for (int n = 1; n < m.levels; ++n) {
+            c->top[n].v = s_top[n] + (int32_t)s_pend[n];
+            c->pending[n].v = 0;
+        }
 }
 
-// Frame hand-off, part 2: run by one workgroup of a frame's update launch (frame parity par).
+// Frame hand-off, part 2: run by `nparts` workgroups of a frame's update launch (frame parity par).
 // Takes the frame's level-0 pops off the stack, returns the level-0 slots freed by the previous
 // frame's merges, and records where the next frame's new block ids start.  Nothing else in the
 // update launch pops level 0 or reads the other parity.
-__device__ inline void update_duties(const DevMap& m, int par) {
-    DevCounters* c = m.ctr;
+__device__ inline void update_duties(const DevMap& m, int par, uint32_t part, uint32_t nparts) {
+    DevCounters MRH_GLOBAL* c = m.ctr;
     __shared__ int32_t s_t0;
     __shared__ uint32_t s_p;
     if (threadIdx.x == 0) {
@@ -529,19 +556,24 @@ __device__ inline void update_duties(const DevMap& m, int par) {
         const uint32_t pops = c->pops0;
         s_t0 = t0 - (int32_t)(pops < avail ? pops : avail);
         s_p = c->pending0[par ^ 1].v;
-        unsigned long long q = 0;  // blocks the frame queued for this launch (all levels)
-        for (int l = 0; l < 4; ++l) q += c->vis_n[par][l].v;
-        stat_add(m, S_QUEUED, q);
-        c->pops0 = 0;
-        c->n_prev[par ^ 1] = c->n_blocks < m.max_blocks ? c->n_blocks : m.max_blocks;
+        if (part == 0) {
+            unsigned long long q = 0;  // blocks the frame queued for this launch (all levels)
+            for (int l = 0; l < 4; ++l) q += c->vis_n[par][l].v;
+            stat_add(m, S_QUEUED, q);
+        }
     }
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < s_p; i += blockDim.x) m.stack[0][s_t0 + i] = m.pend0[par ^ 1][i];
-    if (threadIdx.x == 0) {
+    return_slots(m.pend0[par ^ 1], m.stack[0] + s_t0, s_p, part, nparts);
+    if (duty_done(m, 1, nparts)) {
+        c->pops0 = 0;
+        c->n_prev[par ^ 1] = c->n_blocks < m.max_blocks ? c->n_blocks : m.max_blocks;
         c->top[0].v = s_t0 + (int32_t)s_p;
         c->pending0[par ^ 1].v = 0;
     }
 }
+
+// The part of a launch's hand-off that workgroup `local` of `count` runs, among the last kDutyParts.
+__device__ inline uint32_t duty_parts(uint32_t count) { return count < kDutyParts ? count : kDutyParts; }
 
 // Queue block `id` on the update list of `level` (level < 0 queues nothing).  Called by every
 // thread of the workgroup (a barrier inside): positions come from LDS counters and one global
@@ -593,7 +625,7 @@ __device__ inline void register_block(const DevMap& m, unsigned long long key, u
 // k new blocks: one atomic on the allocation word; returns the old word (ids and pops start there).
 __device__ inline unsigned long long take_new_blocks(const DevMap& m, uint32_t k) {
     stat_add(m, S_NEW, (unsigned long long)k);
-    return atomicAdd(reinterpret_cast<unsigned long long*>(&m.ctr->n_blocks),
+    return atomicAdd(reinterpret_cast<unsigned long long MRH_GLOBAL*>(&m.ctr->n_blocks),
                      (unsigned long long)k | ((unsigned long long)k << 32));
 }
 

@@ -12,14 +12,14 @@ namespace mrh {
 
 
 __global__ __launch_bounds__(256) void k_alloc_points(const DevMap* __restrict__ pm, ScanParams sp) {
-    if (blockIdx.x == gridDim.x - 1) alloc_duties(*pm, sp.parity);
+    const uint32_t parts = duty_parts(gridDim.x), part = gridDim.x - 1u - blockIdx.x;
+    if (part < parts) alloc_duties(*pm, sp.parity, part, parts);
     points_alloc_chunk(*pm, sp, blockIdx.x);
 }
 
-template <int ST>
 __global__ __launch_bounds__(256) void k_rays(const DevMap* __restrict__ pm, ScanParams sp) {
-    __shared__ unsigned long long tab[kSatSlots];
-    points_ray_chunk<ST, false>(*pm, sp, blockIdx.x, tab);
+    __shared__ RayLds lds;
+    points_ray_chunk(*pm, sp, blockIdx.x, lds);
 }
 
 // After the ray launch: the touched blocks onto the update queues (workgroup w takes block ids
@@ -35,7 +35,7 @@ __global__ __launch_bounds__(256) void k_touch_queue(const DevMap* __restrict__ 
 template <int ST>
 __global__ __launch_bounds__(256) void k_apply_points(const DevMap* __restrict__ pm, int par) {
     const DevMap& m = *pm;
-    if (blockIdx.x == 0) update_duties(m, par);
+    if (blockIdx.x < duty_parts(gridDim.x)) update_duties(m, par, blockIdx.x, duty_parts(gridDim.x));
     const uint32_t wave = uniform((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
     const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
     const TaskCounts n = frame_task_counts(m, false, par);
@@ -63,38 +63,49 @@ static int32_t ray_block_cap(const mrh_config& c) {
     return cells < 1024.0 ? (int32_t)cells : 1024;
 }
 
+// Observations one voxel can take from one ray: a walk enters each cell of its lattice once.
+constexpr double kMaxObsPerRay = 1.0;
+
 // LiDAR state of a map: accumulators (first scan) and per-ray block-key buffers for n rays.
 mrh_status ensure_lidar(mrh_map* map, int64_t n) {
     DevMap& d = map->dm;
     mrh_status st = MRH_OK;
     bool changed = false;
-    auto alloc = [&](void** p, size_t bytes, const char* what) {
+    auto alloc = [&](void* p, size_t bytes, const char* what) {  // p: the address of a pointer
         if (st != MRH_OK) return;
-        st = check_hip(map, hipMalloc(p, bytes), what);
-        if (st == MRH_OK) st = check_hip(map, hipMemsetAsync(*p, 0, bytes, map->stream), what);
+        st = check_hip(map, hipMalloc((void**)p, bytes), what);
+        if (st == MRH_OK) st = check_hip(map, hipMemsetAsync(*(void**)p, 0, bytes, map->stream), what);
         changed = true;
     };
     if (!map->lidar_ready) {
-        alloc((void**)&d.btouch, (size_t)d.max_blocks * 8, "touch masks");
+        alloc(&d.btouch, (size_t)d.max_blocks * 8, "touch masks");
         for (int l = 0; l < map->cfg.levels; ++l) {
             const size_t nv = (size_t)d.heap_cap[l] * (size_t)(side_of(l) * side_of(l) * side_of(l));
-            alloc((void**)&d.acc_sat[l], nv * 4, "scan accumulators");
-            alloc((void**)&d.acc_band[l], nv * 4, "scan accumulators");
-            alloc((void**)&d.acc_s1[l], nv * 8, "scan accumulators");
-            alloc((void**)&d.acc_s2[l], nv * 8, "scan accumulators");
+            alloc(&d.acc_sat[l], nv * 4, "scan accumulators");
+            alloc(&d.acc_s1[l], nv * 8, "scan accumulators");
+            alloc(&d.acc_s2[l], nv * 8, "scan accumulators");
         }
+        d.band_bias = (long long)std::ceil(map->cfg.tau * kS1Scale) + 1;
         d.rcap_k = ray_block_cap(map->cfg);
         if (st == MRH_OK) map->lidar_ready = true;
     }
+    // a voxel takes at most a few observations from each ray: with 2^20 of them its count and its sum of
+    // up to 2 bias each fit the shared word; larger scans and truncations keep their counts apart
+    if (st == MRH_OK && !d.band_wide &&
+        ((double)n * kMaxObsPerRay >= 1048576.0 || (double)n * kMaxObsPerRay * 2.0 * (double)d.band_bias >= 0x1p44)) {
+        for (int l = 0; l < map->cfg.levels; ++l)
+            alloc(&d.acc_band[l], (size_t)d.heap_cap[l] * (size_t)(side_of(l) * side_of(l) * side_of(l)) * 4, "scan accumulators");
+        if (st == MRH_OK) d.band_wide = 1;
+    }
     if (st == MRH_OK && n > map->rcap_n) {
         st = check_hip(map, hipStreamSynchronize(map->stream), "ray buffers");
-        if (d.rslots) (void)hipFree(d.rslots);
-        if (d.rcount) (void)hipFree(d.rcount);
+        if (d.rslots) (void)hipFree(plain(d.rslots));
+        if (d.rcount) (void)hipFree(plain(d.rcount));
         d.rslots = nullptr;
         d.rcount = nullptr;
         map->rcap_n = 0;
-        alloc((void**)&d.rslots, (size_t)n * (size_t)d.rcap_k * 4, "ray block slots");
-        alloc((void**)&d.rcount, (size_t)n * 4, "ray block counts");
+        alloc(&d.rslots, (size_t)n * (size_t)d.rcap_k * 4, "ray block slots");
+        alloc(&d.rcount, (size_t)n * 4, "ray block counts");
         if (st == MRH_OK) map->rcap_n = n;
     }
     if (st == MRH_OK && changed) st = upload_descriptor(map);
@@ -110,7 +121,7 @@ extern "C" mrh_status mrh_integrate_points(mrh_map* map, const float* xyz_dev, i
     if (map->cfg.color) return set_error(map, MRH_ERR_INVALID_ARG, "a map with colour fuses RGB-D frames only");
     ScanParams sp;
     if (!pose_from(T_ws, sp.P)) return set_error(map, MRH_ERR_INVALID_ARG, "non-finite pose");
-    sp.xyz = xyz_dev;
+    sp.xyz = global(xyz_dev);
     sp.n = n;
     mrh_status st = ensure_lidar(map, n);
     if (st != MRH_OK) return st;
@@ -124,11 +135,7 @@ extern "C" mrh_status mrh_integrate_points(mrh_map* map, const float* xyz_dev, i
     if (n > 0) {
         const unsigned rgrid = (unsigned)((n + kRaysPerGroup - 1) / kRaysPerGroup);
         launch(map, K_RAYS, [&] {
-            switch (map->cfg.storage) {
-                case MRH_STORE_F16: hipLaunchKernelGGL(k_rays<MRH_STORE_F16>, dim3(rgrid), dim3(256), 0, map->stream, map->dmd, sp); break;
-                case MRH_STORE_BF16: hipLaunchKernelGGL(k_rays<MRH_STORE_BF16>, dim3(rgrid), dim3(256), 0, map->stream, map->dmd, sp); break;
-                default: hipLaunchKernelGGL(k_rays<MRH_STORE_F32>, dim3(rgrid), dim3(256), 0, map->stream, map->dmd, sp);
-            }
+            hipLaunchKernelGGL(k_rays, dim3(rgrid), dim3(256), 0, map->stream, map->dmd, sp);
             hipLaunchKernelGGL(k_touch_queue, dim3(1024), dim3(256), 0, map->stream, map->dmd, par);
         });
     }

@@ -65,8 +65,9 @@ __device__ inline QueryResult query_point(const DevMap& m, const double x[3], bo
     // block cell >> shift (floor division by the block side)
     int32_t cell[3];
     double f[3];
+    const double inv_nu = inv_nu_of(m.inv_nu, n);
     for (int k = 0; k < 3; ++k) {
-        const double g = x[k] * m.inv_nu[n] - 0.5;
+        const double g = x[k] * inv_nu - 0.5;
         const double fl = __builtin_floor(g);
         f[k] = g - fl;
         cell[k] = (int32_t)fl;
@@ -125,7 +126,7 @@ __device__ inline QueryResult query_point(const DevMap& m, const double x[3], bo
     if (GRAD) {
         const double e0 = have[0] ? cd[0] - q.sdf : 0.0, e1 = have[1] ? cd[1] - q.sdf : 0.0;
         const double ez = (1.0 - f[2]) * e0 + f[2] * e1;
-        const double r = m.inv_nu[n] / wsum;
+        const double r = inv_nu / wsum;
         q.grad[0] = group4_sum((dx ? wy : -wy) * ez) * r;
         q.grad[1] = group4_sum((dy ? wx : -wx) * ez) * r;
         q.grad[2] = group4_sum(wxy * (e1 - e0)) * r;

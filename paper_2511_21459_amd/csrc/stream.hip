@@ -95,10 +95,10 @@ __global__ __launch_bounds__(256) void k_stream_select(const DevMap* __restrict_
 template <typename T>
 __device__ inline void copy_planes(const DevMap& m, int level, uint32_t slot, T* buf, bool to_heap) {
     const int nv = 1 << (3 * (3 - level));
-    T* dw = static_cast<T*>(m.DW[level]) + (size_t)slot * (2 * nv);
-    T* s2 = static_cast<T*>(m.S2[level]) + (size_t)slot * nv;
+    T MRH_GLOBAL* dw = (T MRH_GLOBAL*)m.DW[level] + (size_t)slot * (2 * nv);
+    T MRH_GLOBAL* s2 = (T MRH_GLOBAL*)m.S2[level] + (size_t)slot * nv;
     for (int v = lane_id(); v < 3 * nv; v += 64) {
-        T& h = v < 2 * nv ? dw[v] : s2[v - 2 * nv];
+        T MRH_GLOBAL& h = v < 2 * nv ? dw[v] : s2[v - 2 * nv];
         if (to_heap) h = buf[v];
         else buf[v] = h;
     }
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(256) void k_stream_in(const DevMap* __restrict__ pm
                 outcome = 3;
                 atomicOr(&m.ctr->error_flags.v, kErrTableFull);
             } else {
-                id = (uint32_t)atomicAdd(reinterpret_cast<unsigned long long*>(&m.ctr->n_blocks), 1ull);
+                id = (uint32_t)atomicAdd(reinterpret_cast<unsigned long long MRH_GLOBAL*>(&m.ctr->n_blocks), 1ull);
                 const int32_t t = atomicSub(&m.ctr->top[level].v, 1);
                 if (id >= m.max_blocks) {
                     m.table[h].id = kInvalidId;
