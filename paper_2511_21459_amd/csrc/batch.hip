@@ -120,7 +120,7 @@ __global__ __launch_bounds__(256) void k_batch_update(const DevMap* __restrict__
     __syncthreads();
     if (threadIdx.x == 0) {
         pre[0] = 0;
-        for (int i = 0; i < n; ++i) pre[i + 1] = pre[i] + update_task_count(cnt[i]);
+        for (int i = 0; i < n; ++i) pre[i + 1] = pre[i] + (KIND == MRH_FRAME_DEPTH ? update_task_count(cnt[i]) : points_task_count(cnt[i]));
     }
     __syncthreads();
     const uint32_t total = pre[n];
@@ -130,6 +130,19 @@ __global__ __launch_bounds__(256) void k_batch_update(const DevMap* __restrict__
     // the expensive runs); a wave's statistics go to per-map LDS sums, flushed once per workgroup
     int cur = -1;
     TaskStats ts;
+    // LiDAR: a wave's recorded merges are done before it goes on to another map
+    __shared__ uint32_t dbuf[4][4 * kDefer];
+    __shared__ ApplyLds alds[4];
+    const uint32_t wv = uniform(threadIdx.x >> 6);
+    DeferList dl{dbuf[wv], 0u};
+    auto merges = [&](int i) {
+        if constexpr (KIND == MRH_FRAME_POINTS) {
+            unsigned long long m0 = 0, m1 = 0;
+            run_deferred<ST>(maps[i], dl, entry_parity(ents[i]), m0, m1);
+            ts.merge0 += m0;
+            ts.merge1 += m1;
+        }
+    };
     auto flush = [&](int i) {
         if (lane_id() == 0) {
             atomicAdd(&wst[i][0], ts.obs);
@@ -149,6 +162,9 @@ __global__ __launch_bounds__(256) void k_batch_update(const DevMap* __restrict__
             else hi = mid;
         }
         lo = (int)uniform((uint32_t)lo);
+        if (lo != cur || !dl.ready(kApplyBlocks)) {
+            if (cur >= 0) merges(cur);
+        }
         if (lo != cur) {
             if (cur >= 0) flush(cur);
             ts = TaskStats();
@@ -163,10 +179,13 @@ __global__ __launch_bounds__(256) void k_batch_update(const DevMap* __restrict__
             const DepthFrame fr = *(const DepthFrame*)&ce[lo].df;
             ts.add(depth_update_task<ST>(maps[lo], fr, local, c));
         } else {
-            ts.add_uniform(points_update_task<ST, false>(maps[lo], local, c, ((const BatchEntry*)&ce[lo])->sp.parity, nullptr));
+            ts.add_uniform(points_update_task<ST>(maps[lo], local, c, ((const BatchEntry*)&ce[lo])->sp.parity, &dl, alds[wv]));
         }
     }
-    if (cur >= 0) flush(cur);
+    if (cur >= 0) {
+        merges(cur);
+        flush(cur);
+    }
     __syncthreads();
     const int sid[6] = {S_OBS, S_OBS_FRESH, S_MERGE0, S_MERGE1, S_MERGE2, S_DISTINCT};
     for (int k = threadIdx.x; k < 6 * n; k += blockDim.x)

@@ -13,8 +13,7 @@
 //                       voxel's state; the update forms the sums of (d - D) and (d - D)^2 from them.
 //                       The touched lane groups of each block are marked
 //   queue_touched       the touched blocks onto their levels' update queues
-//   points_update_task  one queued level-0 or level-1 block (a wave), or 8 level-2 / 64 level-3
-//                       blocks per wave: each voxel's scan statistics merge into its state (W' =
+//   points_update_task  8 queued blocks of level 0, 1 or 2, or 64 of level 3, per wave: each voxel's scan statistics merge into its state (W' =
 //                       W + n, D' = D + s1 / W', S2' = S2 + s2 - s1^2 / W', the batch form of Eq. 3
 //                       and Eq. 5), then the block variance bookkeeping and the merging criterion
 #pragma once
@@ -729,77 +728,58 @@ __device__ inline void take_accumulators(const DevMap& m, int level, size_t at, 
     }
 }
 
-template <int ST, bool DEFER>
-__device__ inline TaskOut apply_fine(const DevMap& m, const u32x4 eq, int par, DeferList* dl) {
-    const int lane = lane_id();
-    const u32x4 e = uniform(eq);  // one block per wave
-    const uint32_t id = e.x, info = e.y;
-    const double bvs = m.bvsum[id];
-    const uint32_t bvc = m.bvcnt[id];
-    const bool fresh = (info & kNewBit) != 0;
-    const size_t base = (size_t)(info & kSlotMask) * 512 + (size_t)lane * 8;
-    // lanes whose group no ray touched have zero accumulators: they read nothing
-    const unsigned long long touched = m.btouch[id];
-    uint32_t ns[8] = {0, 0, 0, 0, 0, 0, 0, 0}, nb[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    unsigned long long s1[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if ((touched >> lane) & 1ull) {
-        const u32x4 a0 = load_as<u32x4>(m.acc_sat[0] + base), a1 = load_as<u32x4>(m.acc_sat[0] + base + 4);
-        u64x2 w[4];
-        for (int k = 0; k < 4; ++k) w[k] = load_as<u64x2>(m.acc_s1[0] + base + 2 * k);
-        ns[0] = a0.x, ns[1] = a0.y, ns[2] = a0.z, ns[3] = a0.w, ns[4] = a1.x, ns[5] = a1.y, ns[6] = a1.z, ns[7] = a1.w;
-        u32x4 b0{0, 0, 0, 0}, b1{0, 0, 0, 0};
-        if (m.band_wide) b0 = load_as<u32x4>(m.acc_band[0] + base), b1 = load_as<u32x4>(m.acc_band[0] + base + 4);
-        const uint32_t wide[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-        for (int k = 0; k < 4; ++k) {
-            band_sums(m, wide[2 * k], w[k].x, nb[2 * k], s1[2 * k]);
-            band_sums(m, wide[2 * k + 1], w[k].y, nb[2 * k + 1], s1[2 * k + 1]);
-        }
+// Scan accumulators of the 8 voxels of a level-0 lane group, read (counts and sums of q).
+__device__ inline void group_accumulators(const DevMap& m, size_t base, uint32_t ns[8], uint32_t nb[8],
+                                          unsigned long long s1[8]) {
+    const u32x4 a0 = load_as<u32x4>(m.acc_sat[0] + base), a1 = load_as<u32x4>(m.acc_sat[0] + base + 4);
+    u64x2 w[4];
+    for (int k = 0; k < 4; ++k) w[k] = load_as<u64x2>(m.acc_s1[0] + base + 2 * k);
+    u32x4 b0{0, 0, 0, 0}, b1{0, 0, 0, 0};
+    if (m.band_wide) b0 = load_as<u32x4>(m.acc_band[0] + base), b1 = load_as<u32x4>(m.acc_band[0] + base + 4);
+    ns[0] = a0.x, ns[1] = a0.y, ns[2] = a0.z, ns[3] = a0.w, ns[4] = a1.x, ns[5] = a1.y, ns[6] = a1.z, ns[7] = a1.w;
+    const uint32_t wide[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+    for (int k = 0; k < 4; ++k) {
+        band_sums(m, wide[2 * k], w[k].x, nb[2 * k], s1[2 * k]);
+        band_sums(m, wide[2 * k + 1], w[k].y, nb[2 * k + 1], s1[2 * k + 1]);
     }
-    uint32_t upd = 0;
-    int nobs = 0;
-    for (int q = 0; q < 8; ++q) {
-        if (ns[q] + nb[q]) upd |= 1u << q;
-        nobs += (int)(ns[q] + nb[q]);
-    }
-    bool any_band = false;
-    for (int q = 0; q < 8; ++q) any_band |= nb[q] != 0;
-    const int wobs = wave_sum(nobs);
-    TaskOut out;
-    out.obs = (uint32_t)wobs;
-    out.fresh = fresh ? (uint32_t)wobs : 0u;
-    out.distinct = (uint32_t)wave_sum((int)__popc(upd));
-    if (lane == 0) m.btouch[id] = 0ull;
-    float D[8], S2[8];
-    uint32_t W[8];
-    bool have = false;
-    if (fresh) {
-        for (int q = 0; q < 8; ++q) D[q] = 0.f, S2[q] = 0.f, W[q] = 0u;
-        have = true;
-    } else if (upd) {
-        Store<ST>::get8(m, base, D, W, S2);
-        have = true;
-    }
+}
+
+// What one lane's voxels add to their block: the change of its variance sum and count, observations
+// and distinct voxels.
+struct UnitOut {
     double dsum = 0.0;
-    int dcnt = 0;
-    if (upd) {
-        for (int h = 0; h < 2; ++h) {
-            unsigned long long s2[4] = {0, 0, 0, 0};
-            if (any_band) {
-                const u64x2 v0 = load_as<u64x2>(m.acc_s2[0] + base + 4 * h), v1 = load_as<u64x2>(m.acc_s2[0] + base + 4 * h + 2);
-                s2[0] = v0.x, s2[1] = v0.y, s2[2] = v1.x, s2[3] = v1.y;
-            }
-            for (int qq = 0; qq < 4; ++qq) {
-                const int q = 4 * h + qq;
-                if (!(upd & (1u << q))) continue;
-                const double before = var_term(m, W[q], S2[q]);
-                const int cb = var_count(m, W[q]);
-                apply_stats(m, ns[q], nb[q], s1[q], s2[qq], D[q], W[q], S2[q]);
-                Store<ST>::round(m, D[q], W[q], S2[q]);
-                dsum += var_term(m, W[q], S2[q]) - before;
-                dcnt += var_count(m, W[q]) - cb;
-            }
+    int dcnt = 0, nobs = 0, distinct = 0;
+};
+
+// The scan's observations of a level-0 lane group into its state, the accumulators left at zero.
+template <int ST>
+__device__ inline UnitOut apply_group(const DevMap& m, size_t base, const uint32_t ns[8], const uint32_t nb[8],
+                                      const unsigned long long s1[8], float D[8], uint32_t W[8], float S2[8]) {
+    UnitOut u;
+    bool any_band = false;
+    for (int q = 0; q < 8; ++q) {
+        any_band |= nb[q] != 0;
+        u.nobs += (int)(ns[q] + nb[q]);
+        u.distinct += ns[q] + nb[q] ? 1 : 0;
+    }
+    for (int h = 0; h < 2; ++h) {
+        unsigned long long s2[4] = {0, 0, 0, 0};
+        if (any_band) {
+            const u64x2 v0 = load_as<u64x2>(m.acc_s2[0] + base + 4 * h), v1 = load_as<u64x2>(m.acc_s2[0] + base + 4 * h + 2);
+            s2[0] = v0.x, s2[1] = v0.y, s2[2] = v1.x, s2[3] = v1.y;
         }
-        // leave the accumulators at zero for the next scan
+        for (int k = 0; k < 4; ++k) {
+            const int q = 4 * h + k;
+            if (ns[q] + nb[q] == 0u) continue;
+            const double before = var_term(m, W[q], S2[q]);
+            const int cb = var_count(m, W[q]);
+            apply_stats(m, ns[q], nb[q], s1[q], s2[k], D[q], W[q], S2[q]);
+            Store<ST>::round(m, D[q], W[q], S2[q]);
+            u.dsum += var_term(m, W[q], S2[q]) - before;
+            u.dcnt += var_count(m, W[q]) - cb;
+        }
+    }
+    if (u.nobs) {
         const u32x4 z{0, 0, 0, 0};
         store_as(m.acc_sat[0] + base, z);
         store_as(m.acc_sat[0] + base + 4, z);
@@ -814,43 +794,173 @@ __device__ inline TaskOut apply_fine(const DevMap& m, const u32x4 eq, int par, D
             }
         }
     }
-    out.merge0 = (uint32_t)finish_fine<ST, DEFER>(m, id, info, D, W, S2, have, upd != 0 || fresh, wobs, dsum, dcnt,
-                                                        bvs, bvc, par, dl);
+    return u;
+}
+
+// A block of the scan itself (level 0, one wave, lane l the group of Morton positions 8l .. 8l+7): every
+// group is written, with zeros where no ray touched it.
+template <int ST>
+__device__ inline TaskOut apply_new(const DevMap& m, uint32_t id, uint32_t info, unsigned long long touched, double bvs,
+                                    uint32_t bvc, int par, DeferList* dl) {
+    const int lane = lane_id();
+    const size_t base = (size_t)(info & kSlotMask) * 512 + (size_t)lane * 8;
+    uint32_t ns[8] = {0, 0, 0, 0, 0, 0, 0, 0}, nb[8] = {0, 0, 0, 0, 0, 0, 0, 0}, W[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    unsigned long long s1[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    float D[8] = {0, 0, 0, 0, 0, 0, 0, 0}, S2[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    // lanes whose group no ray touched have zero accumulators: they read nothing
+    if ((touched >> lane) & 1ull) group_accumulators(m, base, ns, nb, s1);
+    const UnitOut u = apply_group<ST>(m, base, ns, nb, s1, D, W, S2);
+    TaskOut out;
+    out.obs = out.fresh = (uint32_t)wave_sum(u.nobs);
+    out.distinct = (uint32_t)wave_sum(u.distinct);
+    (void)finish_fine<ST, true>(m, id, info, D, W, S2, true, true, (int)out.obs, u.dsum, u.dcnt, bvs, bvc, par, dl);
     return out;
 }
 
-// Level-1 block: lane l owns the voxel at Morton position l.
-template <int ST, bool DEFER>
-__device__ inline TaskOut apply_level1(const DevMap& m, const u32x4 eq, int par, DeferList* dl) {
-    const int lane = lane_id();
-    const u32x4 e = uniform(eq);  // one block per wave
-    const uint32_t id = e.x, info = e.y;
-    const double bvs = m.bvsum[id];
-    const uint32_t bvc = m.bvcnt[id];
-    const size_t at = (size_t)(info & kSlotMask) * 64 + lane;
-    uint32_t ns = 0, nb = 0;
-    unsigned long long s1 = 0ull, s2 = 0ull;
-    if ((m.btouch[id] >> lane) & 1ull) take_accumulators(m, 1, at, ns, nb, s1, s2);
-    if (lane == 0) m.btouch[id] = 0ull;
-    const bool upd = ns + nb > 0;
-    const int wobs = wave_sum((int)(ns + nb));
-    TaskOut out;
-    out.obs = (uint32_t)wobs;
-    out.distinct = (uint32_t)wave_sum(upd ? 1 : 0);
-    float D, S2;
-    uint32_t W;
-    Store<ST>::get(m, 1, at, D, W, S2);
-    double dsum = 0.0;
-    int dcnt = 0;
-    if (upd) {
-        const double before = var_term(m, W, S2);
-        const int cb = var_count(m, W);
-        apply_stats(m, ns, nb, s1, s2, D, W, S2);
-        Store<ST>::round(m, D, W, S2);
-        dsum = var_term(m, W, S2) - before;
-        dcnt = var_count(m, W) - cb;
+// Blocks a task of level 0 or 1 holds.  A scan touches few of a block's lane groups (a ray about 5 of 64),
+// so a wave takes kApplyBlocks blocks and gives each touched group (level 1: voxel) a lane: the chain of
+// reads (queue entry, touch mask and sums, accumulators and state) is walked once for them all, where a
+// wave per block walked it for every block with most of its lanes idle (131072 points on a settled map:
+// APPLY_TIMES).
+constexpr int kApplyBlocks = 8;
+
+struct ApplyLds {  // one wave's
+    unsigned long long touched[kApplyBlocks];
+    double dsum[kApplyBlocks];
+    uint32_t slot[kApplyBlocks];
+    int dcnt[kApplyBlocks], nobs[kApplyBlocks];
+    uint32_t first[kApplyBlocks + 1];
+};
+
+// The position of the k-th set bit of x (k below its bit count).
+__device__ inline int nth_bit(unsigned long long x, int k) {
+    uint32_t lo = (uint32_t)x;
+    int pos = 0;
+    const int c = __popc(lo);
+    if (k >= c) k -= c, lo = (uint32_t)(x >> 32), pos = 32;
+    for (int w = 16; w > 0; w >>= 1) {
+        const int n = __popc(lo & ((1u << w) - 1u));
+        if (k >= n) k -= n, lo >>= w, pos += w;
     }
-    out.merge1 = (uint32_t)finish_coarse<ST, DEFER>(m, id, info, 1, D, W, S2, upd, wobs, dsum, dcnt, bvs, bvc, par, dl);
+    return pos;
+}
+
+template <int ST, int LEVEL>
+__device__ inline TaskOut apply_blocks(const DevMap& m, const u32x4 MRH_GLOBAL* list, uint32_t count, uint32_t group,
+                                       int par, DeferList* dl, ApplyLds& A) {
+    const int lane = lane_id();
+    const uint32_t bi = group * (uint32_t)kApplyBlocks + (uint32_t)lane;
+    const bool live = lane < kApplyBlocks && bi < count;
+    uint32_t id = 0, info = 0, bvc = 0;
+    unsigned long long touched = 0ull;
+    double bvs = 0.0;
+    if (live) {
+        const u32x4 e = list[bi];
+        id = e.x;
+        info = e.y;
+        touched = m.btouch[id];
+        bvs = m.bvsum[id];
+        bvc = m.bvcnt[id];
+        m.btouch[id] = 0ull;
+    }
+    TaskOut out;
+    const bool fresh = LEVEL == 0 && live && (info & kNewBit);
+    if (LEVEL == 0) {
+        for (unsigned long long left = __ballot(fresh); left; left &= left - 1ull) {
+            const int j = __ffsll((long long)left) - 1;
+            const TaskOut o = apply_new<ST>(m, (uint32_t)lane_value((int)id, j), (uint32_t)lane_value((int)info, j),
+                                            lane_value(touched, j), lane_value(bvs, j), (uint32_t)lane_value((int)bvc, j), par, dl);
+            out.obs += o.obs;
+            out.fresh += o.fresh;
+            out.distinct += o.distinct;
+        }
+    }
+    // the touched groups of the other blocks, block after block
+    const bool mine = live && !fresh;
+    const uint32_t n = mine ? (uint32_t)__popcll(touched) : 0u;
+    uint32_t incl = n;
+    for (int o = 1; o < kApplyBlocks; o <<= 1) {
+        const uint32_t v = (uint32_t)__shfl_up((int)incl, o);
+        if (lane >= o) incl += v;
+    }
+    const uint32_t total = (uint32_t)lane_value((int)incl, kApplyBlocks - 1);
+    if (total == 0) return out;
+    if (lane < kApplyBlocks) {
+        A.touched[lane] = touched;
+        A.dsum[lane] = 0.0;
+        A.slot[lane] = info & kSlotMask;
+        A.dcnt[lane] = A.nobs[lane] = 0;
+        A.first[lane + 1] = incl;
+        if (lane == 0) A.first[0] = 0u;
+    }
+    DeferList::sync();
+    int nobs = 0, distinct = 0;
+    for (uint32_t base = 0; base < total; base += 64) {
+        const uint32_t q = base + (uint32_t)lane;
+        const bool act = q < total;
+        int j = kApplyBlocks;  // (no block)
+        UnitOut u;
+        if (act) {
+            j = 0;
+            for (int step = kApplyBlocks / 2; step > 0; step >>= 1)
+                if (q >= A.first[j + step]) j += step;
+            const int g = nth_bit(A.touched[j], (int)(q - A.first[j]));
+            if (LEVEL == 0) {
+                const size_t at = (size_t)A.slot[j] * 512 + (size_t)g * 8;
+                uint32_t ns[8], nb[8], W[8];
+                unsigned long long s1[8];
+                float D[8], S2[8];
+                group_accumulators(m, at, ns, nb, s1);
+                Store<ST>::get8(m, at, D, W, S2);
+                u = apply_group<ST>(m, at, ns, nb, s1, D, W, S2);
+                Store<ST>::put8(m, at, D, W, S2);
+            } else {
+                const size_t at = (size_t)A.slot[j] * 64 + (size_t)g;
+                uint32_t ns, nb, W;
+                unsigned long long s1, s2;
+                float D, S2;
+                Store<ST>::get(m, 1, at, D, W, S2);
+                take_accumulators(m, 1, at, ns, nb, s1, s2);
+                u.nobs = (int)(ns + nb);
+                if (u.nobs) {
+                    u.distinct = 1;
+                    const double before = var_term(m, W, S2);
+                    const int cb = var_count(m, W);
+                    apply_stats(m, ns, nb, s1, s2, D, W, S2);
+                    Store<ST>::round(m, D, W, S2);
+                    u.dsum = var_term(m, W, S2) - before;
+                    u.dcnt = var_count(m, W) - cb;
+                    Store<ST>::put(m, 1, at, D, W, S2);
+                }
+            }
+            atomicAdd(&A.dcnt[j], u.dcnt);
+            atomicAdd(&A.nobs[j], u.nobs);
+        }
+        nobs += u.nobs;
+        distinct += u.distinct;
+        // sums within each block's run of lanes (in lane order), added by the run's last lane
+        double d = u.dsum;
+        for (int o = 1; o < 64; o <<= 1) {
+            const double v = __shfl_up(d, o);
+            const int jo = __shfl_up(j, o);
+            if (lane >= o && jo == j) d += v;
+        }
+        const int next = __shfl_down(j, 1);
+        if (act && (lane == 63 || next != j)) A.dsum[j] += d;
+        DeferList::sync();
+    }
+    out.obs += (uint32_t)wave_sum(nobs);
+    out.distinct += (uint32_t)wave_sum(distinct);
+    bool merge = false;
+    if (mine) {
+        const double vsum = bvs + A.dsum[lane];
+        const uint32_t vcnt = bvc + (uint32_t)A.dcnt[lane];
+        merge = A.nobs[lane] > 0 && LEVEL < m.levels - 1 && vcnt > 0 && vsum / (double)vcnt < m.var_thr;
+        m.bvsum[id] = vsum;
+        m.bvcnt[id] = vcnt;
+    }
+    dl->add_lanes(merge, id, info);
+    DeferList::sync();
     return out;
 }
 
@@ -892,18 +1002,27 @@ __device__ inline TaskOut apply_packed(const DevMap& m, const u32x4 MRH_GLOBAL* 
     return out;
 }
 
-// One update task t of a scan whose queues hold n0..n3 blocks per level.
-// DEFER: merges of level-0 / level-1 blocks are recorded in *dl and done in batches (run_deferred);
-// the single-map update does this (a scan's merges all hit one map's stack tops and pending
-// counts), the batched update does not (its merges are spread over the maps' counters).
-template <int ST, bool DEFER>
-__device__ inline TaskOut points_update_task(const DevMap& m, uint32_t t, const TaskCounts& c, int par, DeferList* dl) {
-    const uint32_t* n = c.n;  // LiDAR frames queue their new blocks like the others (n_new = 0)
+// A scan's update task space: [queued level-0 blocks | level-1 blocks, both in groups of kApplyBlocks |
+// level-2 blocks in groups of 8 | level-3 blocks in groups of 64] (new blocks are queued like the others).
+__device__ inline uint32_t points_task_count(const TaskCounts& c) {
+    return (c.n[0] + kApplyBlocks - 1) / kApplyBlocks + (c.n[1] + kApplyBlocks - 1) / kApplyBlocks + (c.n[2] + 7) / 8 +
+           (c.n[3] + 63) / 64;
+}
+
+// One of its tasks.  Merges of level-0 / level-1 blocks are recorded in *dl, which has room for those of one
+// task (DeferList::ready), and done by run_deferred.
+template <int ST>
+__device__ inline TaskOut points_update_task(const DevMap& m, uint32_t t, const TaskCounts& c, int par, DeferList* dl,
+                                             ApplyLds& A) {
+    const uint32_t* n = c.n;
+    const uint32_t g0 = (n[0] + kApplyBlocks - 1) / kApplyBlocks, g1 = (n[1] + kApplyBlocks - 1) / kApplyBlocks;
+    if (t < g0) return apply_blocks<ST, 0>(m, m.vis[0], n[0], t, par, dl, A);
+    t -= g0;
+    if (t < g1) return apply_blocks<ST, 1>(m, m.vis[1], n[1], t, par, dl, A);
+    t -= g1;
     const uint32_t g2 = (n[2] + 7) / 8;
-    if (t < n[0]) return apply_fine<ST, DEFER>(m, m.vis[0][t], par, dl);
-    if (t < n[0] + n[1]) return apply_level1<ST, DEFER>(m, m.vis[1][t - n[0]], par, dl);
-    if (t < n[0] + n[1] + g2) return apply_packed<ST>(m, m.vis[2], n[2], t - n[0] - n[1], 2);
-    return apply_packed<ST>(m, m.vis[3], n[3], t - n[0] - n[1] - g2, 3);
+    const int level = t < g2 ? 2 : 3;
+    return apply_packed<ST>(m, m.vis[level], n[level], level == 2 ? t : t - g2, level);
 }
 
 }  // namespace mrh

@@ -175,7 +175,17 @@ struct DeferList {
         }
         n += 1;
     }
-    __device__ inline bool full() const { return n >= (uint32_t)kDefer; }
+    // the same for the lanes with `want` (every lane calls)
+    __device__ inline void add_lanes(bool want, uint32_t id, uint32_t info) {
+        const unsigned long long mask = __ballot(want);
+        if (want) {
+            const uint32_t at = n + (uint32_t)rank_in_mask(mask);
+            e[at] = id;
+            e[kDefer + at] = info;
+        }
+        n += (uint32_t)__popcll(mask);
+    }
+    __device__ inline bool ready(uint32_t room) const { return n + room <= (uint32_t)kDefer; }
 };
 
 // count pops from stack[level] by lane 0 with the semantics of count single pops: returns the old
