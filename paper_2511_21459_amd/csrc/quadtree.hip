@@ -7,12 +7,16 @@
 // top-left, bottom-left, top-right and bottom-right children (children without pixels dropped);
 // every other node is a leaf.
 //
-// The paper reduces each node's pixels in shared memory.  Here one pass builds summed-area tables
-// of the channel values and of their squares (exact integers: 32-bit sums, 64-bit sums of
-// squares), after which every node's sums come from four table reads, so each level of the tree
-// costs a launch over its nodes rather than a pass over the image.  With S_c and Q_c the node's
-// sums over its n pixels, n^2 times the channel variance is n Q_c - S_c^2, exact in 64 bits for
-// images of up to 2^23 pixels; the contrast is then formed in FP64.
+// The paper reduces each node's pixels in shared memory, a launch per level.  Here a workgroup owns a
+// node at the depth where nodes fit LDS (at most kTileSide pixels a side): it builds summed-area tables of
+// its own pixels there, after which every node below costs four table reads, and it walks its subtree
+// in LDS.  Which of its ancestors are split follows from their sums, which a first launch over the
+// image leaves per subtree: two launches and two reads of the image whatever the depth, where tables of
+// the whole image (36 B a pixel written twice and read by every level) took three and one per level.
+// Long thin images keep those tables (mrh_quadtree_build has the rule).
+// With S_c and Q_c a node's sums of channel values and of their squares over its n pixels (exact
+// integers), n^2 times the channel variance is n Q_c - S_c^2, exact in 64 bits for images of up to
+// 2^23 pixels; the contrast is then formed in FP64.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -157,22 +161,29 @@ __global__ __launch_bounds__(64) void k_sat_cols_apply(int32_t W, int32_t H, uin
     }
 }
 
+// Eq. 10 from the exact sums of a node's n pixels.
+__device__ inline double contrast_of(unsigned long long n, const unsigned long long sum[3], const unsigned long long sq[3]) {
+    const double l[3] = {0.2989, 0.5870, 0.1140};
+    double con = 0.0;
+    for (int k = 0; k < 3; ++k) {
+        const unsigned long long v = n * sq[k] - sum[k] * sum[k];  // n^2 times the channel variance, exact
+        con += l[k] * (double)v;
+    }
+    return con / ((double)n * (double)n);
+}
+
 __device__ inline double node_contrast(const uint32_t* S, const unsigned long long* Q, int32_t W, int32_t H,
                                        const QtNode& nd) {
     const size_t pitch = (size_t)W + 1, plane = pitch * ((size_t)H + 1);
     const size_t a = (size_t)nd.y * pitch + nd.x, b = a + nd.w, c = ((size_t)nd.y + nd.h) * pitch + nd.x, d = c + nd.w;
-    const unsigned long long n = (unsigned long long)nd.w * (unsigned long long)nd.h;
-    const double l[3] = {0.2989, 0.5870, 0.1140};
-    double con = 0.0;
+    unsigned long long sum[3], sq[3];
     for (int k = 0; k < 3; ++k) {
         const uint32_t* s = S + k * plane;
         const unsigned long long* q = Q + k * plane;
-        const unsigned long long sum = (unsigned long long)(s[d] - s[b] - s[c] + s[a]);
-        const unsigned long long sq = q[d] - q[b] - q[c] + q[a];
-        const unsigned long long v = n * sq - sum * sum;  // n^2 times the channel variance, exact
-        con += l[k] * (double)v;
+        sum[k] = (unsigned long long)(s[d] - s[b] - s[c] + s[a]);
+        sq[k] = q[d] - q[b] - q[c] + q[a];
     }
-    return con / ((double)n * (double)n);
+    return contrast_of((unsigned long long)nd.w * (unsigned long long)nd.h, sum, sq);
 }
 
 // One breadth-first level: every node of the input queue is split into the output queue or written
@@ -237,6 +248,304 @@ __global__ __launch_bounds__(256) void k_qt_level(const uint32_t* __restrict__ S
     }
 }
 
+// ---- subtrees in LDS --------------------------------------------------------------------------
+
+constexpr int kTileSide = 40;    // longest side of a subtree's root (640 x 480: 256 workgroups of 40 x 30)
+constexpr int kTilePitch = kTileSide + 1;
+constexpr int kTilePixels = kTileSide * kTileSide;
+constexpr int kTileDepth = 8;    // deepest subtree root
+constexpr int kTileThreads = 512;
+
+// Sums of a node's channel values and squares.
+struct QtSums {
+    unsigned long long q[3];
+    uint32_t s[3], unused;
+};
+
+// Node `path` (two bits per level, the split's order: bit 1 right, bit 0 bottom) of depth d.
+__device__ inline QtNode node_at(int32_t W, int32_t H, int d, uint32_t path) {
+    QtNode nd{0, 0, W, H};
+    for (int k = d - 1; k >= 0; --k) {
+        const uint32_t b = path >> (2 * k);
+        const int32_t wl = nd.w / 2, ht = nd.h / 2;
+        if (b & 2u) nd.x += wl, nd.w -= wl;
+        else nd.w = wl;
+        if (b & 1u) nd.y += ht, nd.h -= ht;
+        else nd.h = ht;
+    }
+    return nd;
+}
+
+__host__ __device__ inline size_t sums_at(int d) { return ((size_t(1) << (2 * d)) - 1) / 3; }  // nodes above depth d
+
+__device__ inline void add_xor(QtSums& v, int lane) {
+    for (int c = 0; c < 3; ++c) {
+        v.s[c] += (uint32_t)__shfl_xor((int)v.s[c], lane);
+        const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v.q[c], lane);
+        const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v.q[c] >> 32), lane);
+        v.q[c] += ((unsigned long long)hi << 32) | lo;
+    }
+}
+
+// Sums of the subtree roots, one workgroup each: a read of the image, 4 us at 640 x 480.  Workgroup 0
+// clears the leaf count.
+__global__ __launch_bounds__(256) void k_qt_sums(const uint8_t* __restrict__ rgb, int32_t W, int32_t H, int depth,
+                                                 QtSums* __restrict__ sums, unsigned long long* __restrict__ n_leaves) {
+    const uint32_t path = blockIdx.x;
+    if (path == 0 && threadIdx.x == 0) *n_leaves = 0ull;
+    const QtNode nd = node_at(W, H, depth, path);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t s[3] = {0, 0, 0}, q[3] = {0, 0, 0};  // (a subtree's squares fit 32 bits: kTilePixels x 255^2)
+    static_assert((uint64_t)kTilePixels * 255 * 255 < (uint64_t(1) << 32), "subtree sums in 32 bits");
+    if (lane < nd.w) {
+        const uint8_t* p = rgb + 3 * ((size_t)nd.y * W + nd.x + lane);
+        uint32_t v[3][kTileSide / 4];  // every row's reads in flight together
+#pragma unroll
+        for (int i = 0; i < kTileSide / 4; ++i)
+            for (int c = 0; c < 3; ++c) v[c][i] = wave + 4 * i < nd.h ? p[3 * (size_t)(wave + 4 * i) * W + c] : 0u;
+#pragma unroll
+        for (int i = 0; i < kTileSide / 4; ++i)
+            for (int c = 0; c < 3; ++c) s[c] += v[c][i], q[c] += v[c][i] * v[c][i];
+    }
+    for (int o = 1; o < 64; o <<= 1)
+        for (int c = 0; c < 3; ++c) {
+            s[c] += (uint32_t)__shfl_xor((int)s[c], o);
+            q[c] += (uint32_t)__shfl_xor((int)q[c], o);
+        }
+    __shared__ uint32_t part[4][6];
+    if (lane == 0)
+        for (int c = 0; c < 3; ++c) part[wave][c] = s[c], part[wave][3 + c] = q[c];
+    __syncthreads();
+    if (threadIdx.x) return;
+    QtSums o{};
+    for (int w = 0; w < 4; ++w)
+        for (int c = 0; c < 3; ++c) o.s[c] += part[w][c], o.q[c] += part[w][3 + c];
+    sums[sums_at(depth) + path] = o;
+}
+
+// Sums of the nodes at depths depth - 4 .. depth - 1 (subtree roots deeper than 4 only): a workgroup per
+// node of depth - 4, a thread per subtree root below it.
+__global__ __launch_bounds__(256) void k_qt_reduce(int depth, QtSums* __restrict__ sums) {
+    const uint32_t t = threadIdx.x, path = blockIdx.x * 256 + t;
+    QtSums v = sums[sums_at(depth) + path];
+    for (int j = 1; j <= 3; ++j) {
+        add_xor(v, 1 << (2 * j - 2));
+        add_xor(v, 2 << (2 * j - 2));
+        if ((t & ((1u << (2 * j)) - 1u)) == 0) sums[sums_at(depth - j) + (path >> (2 * j))] = v;
+    }
+    __shared__ QtSums part[4];
+    if ((t & 63u) == 0) part[t >> 6] = v;
+    __syncthreads();
+    if (t) return;
+    for (int w = 1; w < 4; ++w)
+        for (int c = 0; c < 3; ++c) v.s[c] += part[w].s[c], v.q[c] += part[w].q[c];
+    sums[sums_at(depth - 4) + blockIdx.x] = v;
+}
+
+struct QtLds {
+    uint32_t table[6][kTilePitch * kTilePitch];  // sums of the subtree's channels, then of their squares
+    uint32_t queue[2][kTilePixels];              // nodes of a level (x, y, w, h in six bits each)
+    uint32_t leaf[kTilePixels];
+    float contrast[kTilePixels];
+    QtSums above[kTileDepth];                    // the subtree root's ancestors
+    QtSums part[4];
+    int first_leaf;                              // depth of the first ancestor that is a leaf (depth: none)
+    uint32_t n[3], n_leaf;                       // queue lengths by level modulo 3
+    unsigned long long base;
+};
+
+// Leaves of the subtree below node blockIdx.x of `depth`.  The levels are a chain of table reads and
+// barriers in LDS, and one append to the leaf list per workgroup (its order is free).  An ancestor
+// that is a leaf is written by the last of the workgroups below it.  640 x 480, 34957 leaves, a build with
+// its read-back: 176 -> 43 us, of which half is the host's.
+__global__ __launch_bounds__(kTileThreads) void k_qt_tree(const uint8_t* __restrict__ rgb, int32_t W, int32_t H, int depth,
+                                                          const QtSums* __restrict__ sums, double threshold,
+                                                          int32_t min_size, int32_t* leaves, float* contrast,
+                                                          unsigned long long* n_leaves, long long cap) {
+    __shared__ QtLds L;
+    const uint32_t path = blockIdx.x;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    constexpr int kWaves = kTileThreads / 64, kRows = kTileSide / kWaves;
+    static_assert(kTileSide % kWaves == 0 && kTileSide < 64, "a wave takes whole rows");
+    const QtNode nd = node_at(W, H, depth, path);
+
+    // the subtree's pixels (used after the ancestors' sums: in flight meanwhile)
+    uint32_t v[kRows][3];
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) {
+        const int y = wave + i * kWaves;
+        const bool in = lane < nd.w && y < nd.h;
+        const uint8_t* p = rgb + (in ? 3 * ((size_t)(nd.y + y) * W + nd.x + lane) : 0);
+        for (int c = 0; c < 3; ++c) v[i][c] = in ? p[c] : 0u;
+    }
+
+    // ancestors: those below depth `top` read, the others summed from the nodes of depth `top`
+    const int top = depth > 4 ? depth - 4 : depth;
+    if (t < 256) {
+        QtSums a{};
+        if (t < 1 << (2 * top)) a = sums[sums_at(top) + t];
+        for (int j = 1; j <= 3; ++j) {
+            add_xor(a, 1 << (2 * j - 2));
+            add_xor(a, 2 << (2 * j - 2));
+            const int d = top - j;
+            if (d >= 0 && (uint32_t)t == (path >> (2 * (depth - d))) << (2 * j)) L.above[d] = a;
+        }
+        if (lane == 0) L.part[wave] = a;
+    } else if (t - 256 < depth - top) {
+        const int d = top + t - 256;
+        L.above[d] = sums[sums_at(d) + (path >> (2 * (depth - d)))];
+    }
+    if (t < 3) L.n[t] = t == 0 ? 1u : 0u;
+    if (t == 3) L.n_leaf = 0u;
+    if (t == 4) L.queue[0][0] = (uint32_t)nd.w << 12 | (uint32_t)nd.h << 18;
+    __syncthreads();
+    if (wave == 0) {
+        bool leaf = false;
+        double con = 0.0;
+        QtNode an{};
+        if (lane < depth) {
+            QtSums a = L.above[lane];
+            if (top == 4 && lane == 0) {
+                a = L.part[0];
+                for (int w = 1; w < 4; ++w)
+                    for (int c = 0; c < 3; ++c) a.s[c] += L.part[w].s[c], a.q[c] += L.part[w].q[c];
+            }
+            an = node_at(W, H, lane, path >> (2 * (depth - lane)));
+            const unsigned long long sum[3] = {a.s[0], a.s[1], a.s[2]};
+            if (an.w > 0 && an.h > 0) con = contrast_of((unsigned long long)an.w * (unsigned long long)an.h, sum, a.q);
+            leaf = !(con > threshold && min(an.w, an.h) > min_size);
+        }
+        const unsigned long long m = __ballot(leaf);
+        const int f = m ? __ffsll((long long)m) - 1 : depth;
+        if (lane == 0) L.first_leaf = f;
+        const uint32_t below = (1u << (2 * (depth - f))) - 1u;
+        if (lane == f && f < depth && (path & below) == below) {
+            const long long at = (long long)atomicAdd(n_leaves, 1ull);
+            if (at < cap) {
+                if (leaves) {
+                    leaves[4 * at] = an.x;
+                    leaves[4 * at + 1] = an.y;
+                    leaves[4 * at + 2] = an.w;
+                    leaves[4 * at + 3] = an.h;
+                }
+                if (contrast) contrast[at] = (float)con;
+            }
+        }
+    }
+    __syncthreads();
+    if (L.first_leaf < depth) return;
+
+    // summed-area tables: rows by shuffles (sums of a row of 40 fit 16 bits, two packed), then columns
+#pragma unroll
+    for (int i = 0; i < kRows; ++i) {
+        const int y = wave + i * kWaves;
+        uint32_t s01 = v[i][0] | v[i][1] << 16, s2 = v[i][2];
+        uint32_t q0 = v[i][0] * v[i][0], q1 = v[i][1] * v[i][1], q2 = v[i][2] * v[i][2];
+        for (int o = 1; o < kTileSide; o <<= 1) {
+            const uint32_t a = (uint32_t)__shfl_up((int)s01, o), b = (uint32_t)__shfl_up((int)s2, o);
+            const uint32_t e = (uint32_t)__shfl_up((int)q0, o), f = (uint32_t)__shfl_up((int)q1, o);
+            const uint32_t g = (uint32_t)__shfl_up((int)q2, o);
+            if (lane >= o) s01 += a, s2 += b, q0 += e, q1 += f, q2 += g;
+        }
+        if (lane < nd.w && y < nd.h) {
+            const int at = (y + 1) * kTilePitch + lane + 1;
+            L.table[0][at] = s01 & 0xffffu;
+            L.table[1][at] = s01 >> 16;
+            L.table[2][at] = s2;
+            L.table[3][at] = q0;
+            L.table[4][at] = q1;
+            L.table[5][at] = q2;
+        }
+    }
+    static_assert(kTileSide * 255 < 1 << 16, "packed row sums");
+    __syncthreads();
+    if (t < 6 * kTilePitch) {
+        const int plane = t / kTilePitch, x = t % kTilePitch;
+        if (x <= nd.w) {
+            uint32_t* col = L.table[plane] + x;
+            uint32_t sum = 0;
+            col[0] = 0u;
+            for (int y = 1; y <= nd.h; ++y) {
+                sum += x ? col[y * kTilePitch] : 0u;
+                col[y * kTilePitch] = sum;
+            }
+        }
+    }
+    static_assert(6 * kTilePitch <= kTileThreads, "a thread per column and plane");
+    __syncthreads();
+
+    // (split sides are above min_size >= 1, so every child has pixels)
+    for (int d = 0;; ++d) {
+        const uint32_t count = L.n[d % 3];
+        if (!count) break;
+        const uint32_t* in = L.queue[d & 1];
+        uint32_t* out = L.queue[(d & 1) ^ 1];
+        if (t == 0) L.n[(d + 2) % 3] = 0u;
+        for (uint32_t i0 = (uint32_t)wave * 64u; i0 < count; i0 += kTileThreads) {
+            const uint32_t i = i0 + lane;
+            bool leaf = false, split = false;
+            uint32_t x = 0, y = 0, w = 0, h = 0;
+            double con = 0.0;
+            if (i < count) {
+                const uint32_t k = in[i];
+                x = k & 63u, y = k >> 6 & 63u, w = k >> 12 & 63u, h = k >> 18;
+                const uint32_t a = y * kTilePitch + x, c = (y + h) * kTilePitch + x;
+                unsigned long long sum[6];
+                for (int p = 0; p < 6; ++p) {
+                    const uint32_t* s = L.table[p];
+                    sum[p] = s[c + w] - s[a + w] - s[c] + s[a];
+                }
+                con = contrast_of((unsigned long long)(w * h), sum, sum + 3);
+                split = con > threshold && (int32_t)min(w, h) > min_size;
+                leaf = !split;
+            }
+            const unsigned long long below = (1ull << lane) - 1ull, ml = __ballot(leaf), ms = __ballot(split);
+            uint32_t bl = 0, bs = 0;
+            if (lane == 0) {
+                if (ml) bl = atomicAdd(&L.n_leaf, (uint32_t)__popcll(ml));
+                if (ms) bs = atomicAdd(&L.n[(d + 1) % 3], 4u * (uint32_t)__popcll(ms));
+            }
+            bl = (uint32_t)__builtin_amdgcn_readfirstlane((int)bl);
+            bs = (uint32_t)__builtin_amdgcn_readfirstlane((int)bs);
+            if (leaf) {
+                const uint32_t at = bl + (uint32_t)__popcll(ml & below);
+                L.leaf[at] = x | y << 6 | w << 12 | h << 18;
+                L.contrast[at] = (float)con;
+            }
+            if (split) {
+                const uint32_t at = bs + 4u * (uint32_t)__popcll(ms & below), wl = w / 2, ht = h / 2;
+                out[at] = x | y << 6 | wl << 12 | ht << 18;
+                out[at + 1] = x | (y + ht) << 6 | wl << 12 | (h - ht) << 18;
+                out[at + 2] = (x + wl) | y << 6 | (w - wl) << 12 | ht << 18;
+                out[at + 3] = (x + wl) | (y + ht) << 6 | (w - wl) << 12 | (h - ht) << 18;
+            }
+        }
+        __syncthreads();
+    }
+    const uint32_t n = L.n_leaf;
+    if (t == 0) L.base = atomicAdd(n_leaves, (unsigned long long)n);
+    __syncthreads();
+    for (uint32_t i = t; i < n; i += kTileThreads) {
+        const long long at = (long long)(L.base + i);
+        if (at >= cap) break;
+        const uint32_t k = L.leaf[i];
+        if (leaves) {
+            leaves[4 * at] = nd.x + (int32_t)(k & 63u);
+            leaves[4 * at + 1] = nd.y + (int32_t)(k >> 6 & 63u);
+            leaves[4 * at + 2] = (int32_t)(k >> 12 & 63u);
+            leaves[4 * at + 3] = (int32_t)(k >> 18);
+        }
+        if (contrast) contrast[at] = L.contrast[i];
+    }
+}
+
+// Depth of the subtree roots: the shallowest whose sides are at most kTileSide (halves round up).
+int tile_depth(int32_t longer) {
+    int d = 0;
+    for (; longer > kTileSide; longer = (longer + 1) / 2) ++d;
+    return d;
+}
+
 }  // namespace
 
 struct mrh_quadtree {
@@ -250,6 +559,7 @@ struct mrh_quadtree {
     size_t queue_cap = 0;
     uint32_t* TS = nullptr;      // column pass: per chunk of rows, channel and column
     unsigned long long* TQ = nullptr;
+    QtSums* sums = nullptr;      // nodes of depths 0 .. the subtree roots'
 };
 
 extern "C" {
@@ -270,7 +580,9 @@ mrh_status mrh_quadtree_create(int32_t max_width, int32_t max_height, void* stre
               hipMalloc((void**)&q->queue[1], q->queue_cap * sizeof(QtNode)) == hipSuccess &&
               hipMalloc((void**)&q->counts, kMaxLevels * 4 + 8) == hipSuccess &&
               hipMalloc((void**)&q->TS, chunks * 3 * ((size_t)max_width + 1) * 4) == hipSuccess &&
-              hipMalloc((void**)&q->TQ, chunks * 3 * ((size_t)max_width + 1) * 8) == hipSuccess;
+              hipMalloc((void**)&q->TQ, chunks * 3 * ((size_t)max_width + 1) * 8) == hipSuccess &&
+              hipMalloc((void**)&q->sums, sums_at(std::min(kTileDepth, tile_depth(std::max(max_width, max_height))) + 1) *
+                                              sizeof(QtSums)) == hipSuccess;
     if (ok) q->n_leaves = reinterpret_cast<unsigned long long*>(q->counts + kMaxLevels);
     if (!ok) {
         mrh_quadtree_destroy(q);
@@ -284,7 +596,7 @@ void mrh_quadtree_destroy(mrh_quadtree* q) {
     if (!q) return;
     if (q->stream) (void)hipStreamSynchronize(q->stream);
     else (void)hipDeviceSynchronize();
-    void* ptrs[] = {q->S, q->Q, q->queue[0], q->queue[1], q->counts, q->TS, q->TQ};
+    void* ptrs[] = {q->S, q->Q, q->queue[0], q->queue[1], q->counts, q->TS, q->TQ, q->sums};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     delete q;
@@ -296,26 +608,41 @@ mrh_status mrh_quadtree_build(mrh_quadtree* q, const uint8_t* rgb_dev, int32_t w
         cap < 0 || !(threshold == threshold))
         return MRH_ERR_INVALID_ARG;
     hipStream_t s = q->stream;
-    // the summed-area tables; the row pass also puts the root in the first queue and clears the counts
-    hipLaunchKernelGGL(k_sat_rows, dim3(height), dim3(256), 0, s, rgb_dev, width, height, q->S, q->Q, q->queue[0],
-                       q->counts);
-    const int32_t chunks = (height + kColChunk - 1) / kColChunk;
-    const dim3 cg((unsigned)((width + 1 + 63) / 64), (unsigned)chunks);
-    hipLaunchKernelGGL(k_sat_cols_part, cg, dim3(64), 0, s, width, height, q->S, q->Q, q->TS, q->TQ);
-    hipLaunchKernelGGL(k_sat_cols_apply, cg, dim3(64), 0, s, width, height, q->S, q->Q, q->TS, q->TQ);
-    // levels: a node's shorter side halves at each split, so the tree is at most
-    // log2(min(width, height)) + 2 levels deep
-    int depth = 1;
-    for (int32_t side = std::min(width, height); side > 1; side = (side + 1) / 2) ++depth;
-    const int64_t pixels = (int64_t)width * height;
-    int64_t bound = 1;
-    for (int d = 0; d <= depth; ++d) {
-        const int cur = d & 1;
-        const unsigned grid = (unsigned)((std::min(bound, pixels) + 255) / 256);
-        hipLaunchKernelGGL(k_qt_level, dim3(grid), dim3(256), 0, s, q->S, q->Q, width, height, threshold, min_size,
-                           q->queue[cur], q->counts + d, q->queue[cur ^ 1], q->counts + d + 1, leaves_dev,
-                           contrast_dev, q->n_leaves, (long long)(leaves_dev || contrast_dev ? cap : 0));
-        bound *= 4;
+    const long long room = leaves_dev || contrast_dev ? cap : 0;
+    const int32_t longer = std::max(width, height), shorter = std::min(width, height);
+    const int tiles = tile_depth(longer);
+    // Subtrees in LDS, unless the longer side asks for more subtree roots than the chip holds at once
+    // (256 at depth 4) and the shorter one leaves most of them nearly empty.  Whole builds, against the
+    // tables of the whole image: 640 x 480 43 us to 176, 640 x 10 33 to 80, 5120 x 640 431 to 564, but
+    // 5120 x 320 399 to 338 and 5120 x 160 384 to 241.
+    if (tiles <= 4 || (tiles <= kTileDepth && longer <= 8ll * shorter)) {
+        hipLaunchKernelGGL(k_qt_sums, dim3(1u << (2 * tiles)), dim3(256), 0, s, rgb_dev, width, height, tiles, q->sums,
+                           q->n_leaves);
+        if (tiles > 4) hipLaunchKernelGGL(k_qt_reduce, dim3(1u << (2 * (tiles - 4))), dim3(256), 0, s, tiles, q->sums);
+        hipLaunchKernelGGL(k_qt_tree, dim3(1u << (2 * tiles)), dim3(kTileThreads), 0, s, rgb_dev, width, height, tiles,
+                           q->sums, threshold, min_size, leaves_dev, contrast_dev, q->n_leaves, room);
+    } else {
+        // the summed-area tables; the row pass also puts the root in the first queue and clears the counts
+        hipLaunchKernelGGL(k_sat_rows, dim3(height), dim3(256), 0, s, rgb_dev, width, height, q->S, q->Q, q->queue[0],
+                           q->counts);
+        const int32_t chunks = (height + kColChunk - 1) / kColChunk;
+        const dim3 cg((unsigned)((width + 1 + 63) / 64), (unsigned)chunks);
+        hipLaunchKernelGGL(k_sat_cols_part, cg, dim3(64), 0, s, width, height, q->S, q->Q, q->TS, q->TQ);
+        hipLaunchKernelGGL(k_sat_cols_apply, cg, dim3(64), 0, s, width, height, q->S, q->Q, q->TS, q->TQ);
+        // levels: a node's shorter side halves at each split, so the tree is at most
+        // log2(min(width, height)) + 2 levels deep
+        int depth = 1;
+        for (int32_t side = std::min(width, height); side > 1; side = (side + 1) / 2) ++depth;
+        const int64_t pixels = (int64_t)width * height;
+        int64_t bound = 1;
+        for (int d = 0; d <= depth; ++d) {
+            const int cur = d & 1;
+            const unsigned grid = (unsigned)((std::min(bound, pixels) + 255) / 256);
+            hipLaunchKernelGGL(k_qt_level, dim3(grid), dim3(256), 0, s, q->S, q->Q, width, height, threshold, min_size,
+                               q->queue[cur], q->counts + d, q->queue[cur ^ 1], q->counts + d + 1, leaves_dev,
+                               contrast_dev, q->n_leaves, room);
+            bound *= 4;
+        }
     }
     if (hipGetLastError() != hipSuccess) return MRH_ERR_HIP;
     unsigned long long n = 0;

@@ -62,3 +62,27 @@ def test_quadtree_small_buffer(mrh):
     assert L.mrh_quadtree_build(qt._h, ctypes.c_void_p(img.data_ptr()), 65, 64, 100.0, 2, None, None, 0, ctypes.byref(n)) == -1
     assert L.mrh_quadtree_build(qt._h, ctypes.c_void_p(img.data_ptr()), 64, 64, 100.0, 0, None, None, 0, ctypes.byref(n)) == -1
     qt.close()
+
+
+# (height, width, min size): sides of 40 and 41, subtree roots at every depth (0 .. 8) and without
+# pixels, and both sides of the line beyond which tables of the whole image are used
+SUBTREES = [(1, 1, 1), (1, 8, 1), (40, 40, 1), (41, 40, 1), (5, 40, 1), (80, 81, 1), (161, 33, 2), (321, 319, 1), (10, 640, 1),
+            (640, 1, 1), (81, 641, 1), (80, 641, 1), (641, 200, 3), (170, 1300, 2), (2600, 330, 5), (700, 5200, 9)]
+
+
+@pytest.mark.parametrize("h,w,mn", SUBTREES)
+def test_quadtree_subtrees(mrh, h, w, mn):
+    announce(f"quadtree subtrees {w}x{h}")
+    img = _image(np.random.default_rng(h * 7919 + w), h, w, 8 if h * w < 100000 else 64, 12.0)
+    qt = mrh.Quadtree(w, h)
+    dev = torch.from_numpy(img).cuda()
+    for thr in (0.0, 200.0) if h * w < 300000 else (300.0,):
+        want, wc, near = oracle.quadtree(img, thr, mn)
+        assert near == 0
+        leaves, con = qt.build(dev, thr, mn)
+        got, gc = leaves.cpu().numpy(), con.cpu().numpy()
+        go, oo = np.lexsort(got.T[::-1]), np.lexsort(want.T[::-1])
+        assert np.array_equal(got[go], want[oo]), (thr, len(got), len(want))
+        # the contrast is an FP64 quotient of exact sums, rounded once to FP32
+        assert np.allclose(gc[go], wc[oo], rtol=1e-6, atol=1e-6)
+    qt.close()
