@@ -10,7 +10,6 @@
 // frames) with the weights from before the frame: the colour is updated there with W + 1 and
 // pooled into the coarse block as the weighted mean of the observed children, as the TSDF was.
 // New blocks cannot merge in their first frame (no voxel reaches min_obs >= 2 observations).
-#include <vector>
 
 #include "mrh_depth.h"
 
@@ -177,24 +176,49 @@ __global__ __launch_bounds__(256) void k_integrate_color(const DevMap* __restric
     }
 }
 
-// Colours out, in the voxel order of mrh_extract_blocks (x fastest per block).
-__global__ void k_extract_color(const DevMap* __restrict__ pm, uint32_t nb, const int32_t* __restrict__ pos,
-                                const int64_t* __restrict__ offsets, float* out) {
+// Colours out, in the voxel order of mrh_extract_blocks (x fastest per block) and its manner: lanes
+// follow the output's floats, so that the stores fill whole lines (room map at 1 cm: 75 -> 38 us).
+__global__ __launch_bounds__(256) void k_extract_color(const DevMap* __restrict__ pm, const ExtractRow* __restrict__ rows,
+                                                       uint32_t nrows, float* __restrict__ out) {
     const DevMap& m = *pm;
-    const int lane = threadIdx.x & 63;
-    const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const uint32_t nwaves = (gridDim.x * blockDim.x) >> 6;
-    for (uint32_t id = wave; id < nb; id += nwaves) {
-        const int32_t row = pos[id];
-        const uint32_t info = m.binfo[id];
-        if (row < 0 || (info & kNoBlockBit)) continue;
-        const int lvl = (int)((info >> kLevelShift) & 3u), ms = 8 >> lvl, nv = ms * ms * ms;
-        const size_t base = (size_t)(info & kSlotMask) * nv;
-        for (int p = lane; p < nv; p += 64) {
-            int i, j, k;
-            demorton3(p, i, j, k);
-            const int64_t o = offsets[row] + i + ms * (j + ms * k);
-            for (int ch = 0; ch < 3; ++ch) out[3 * o + ch] = m.C[lvl][3 * (base + p) + ch];
+    const int lane = threadIdx.x & 63, v = lane & 7, wave = (int)uniform(threadIdx.x >> 6);
+    const uint32_t row = blockIdx.x * kExtractRows + (lane >> 3);
+    ExtractRow e{0, 0u, kNoBlockBit};
+    if (row < nrows) e = rows[row];
+    const bool block = !(e.info & kNoBlockBit);
+    const int lvl = (int)((e.info >> kLevelShift) & 3u);
+    // (the order of the eight voxels of a level-2 block is the same in both)
+    if (wave == 0 && block && (lvl == 2 || (lvl == 3 && v == 0))) {
+        const float MRH_GLOBAL* c = lvl == 2 ? m.C[2] + 24 * (size_t)(e.info & kSlotMask) : m.C[3] + 3 * (size_t)(e.info & kSlotMask);
+        for (int ch = 0; ch < 3; ++ch) out[3 * (e.off + v) + ch] = c[3 * v + ch];
+    }
+    unsigned long long large = __ballot(block && lvl < 2 && v == 0);
+    for (int turn = 0; large; ++turn) {
+        const int src = __ffsll((long long)large) - 1;
+        large &= large - 1;
+        if ((turn & 3) != wave) continue;
+        const uint32_t info = (uint32_t)uniform(__shfl((int)e.info, src));
+        const int64_t off = (int64_t)((unsigned long long)(uint32_t)uniform(__shfl((int)(uint32_t)((unsigned long long)e.off >> 32), src)) << 32 |
+                                      (uint32_t)uniform(__shfl((int)(uint32_t)(unsigned long long)e.off, src)));
+        float* o = out + 3 * off + lane;
+        if (((info >> kLevelShift) & 3u) == 1u) {
+            const float MRH_GLOBAL* c = m.C[1] + 192 * (size_t)(info & kSlotMask);
+            for (int k = 0; k < 3; ++k) {
+                const int q = lane + 64 * k, x = q / 3;
+                const uint32_t p = spread3(x & 3) | spread3((x >> 2) & 3) << 1 | spread3(x >> 4) << 2;
+                o[64 * k] = c[3 * p + (uint32_t)(q - 3 * x)];
+            }
+        } else {
+            const float MRH_GLOBAL* c = m.C[0] + 1536 * (size_t)(info & kSlotMask);
+            float f[24];
+#pragma unroll
+            for (int k = 0; k < 24; ++k) {
+                const int q = lane + 64 * k, x = q / 3;
+                const uint32_t p = spread3(x & 7) | spread3((x >> 3) & 7) << 1 | spread3(x >> 6) << 2;
+                f[k] = c[3 * p + (uint32_t)(q - 3 * x)];
+            }
+#pragma unroll
+            for (int k = 0; k < 24; ++k) o[64 * k] = f[k];
         }
     }
 }
@@ -223,44 +247,17 @@ extern "C" mrh_status mrh_integrate_rgbd(mrh_map* map, const float* depth_dev, c
 extern "C" mrh_status mrh_extract_color(mrh_map* map, float* rgb_dev, int64_t voxel_cap, int64_t* n_voxels) {
     if (!map || !n_voxels) return MRH_ERR_INVALID_ARG;
     if (!map->cfg.color) return set_error(map, MRH_ERR_INVALID_ARG, "the map was created without colour");
-    DevCounters h;
-    mrh_status st = check_hip(map, hipMemcpyAsync(&h, map->ctr, sizeof(h), hipMemcpyDeviceToHost, map->stream), "extract colour");
-    if (st == MRH_OK) st = check_hip(map, hipStreamSynchronize(map->stream), "extract colour");
-    if (st != MRH_OK) return st;
-    const uint32_t nb = h.n_blocks < map->dm.max_blocks ? h.n_blocks : map->dm.max_blocks;
-    std::vector<uint32_t> info(nb);
-    if (nb) {
-        st = check_hip(map, hipMemcpy(info.data(), plain(map->dm.binfo), (size_t)nb * 4, hipMemcpyDeviceToHost), "extract colour");
-        if (st != MRH_OK) return st;
-    }
-    // the rows and voxel offsets of mrh_extract_blocks
-    std::vector<int32_t> pos(nb, -1);
-    std::vector<int64_t> offs(1, 0);
     uint32_t nout = 0;
-    for (uint32_t i = 0; i < nb; ++i) {
-        if (info[i] & kGoneBit) continue;
-        const int lvl = (int)((info[i] >> kLevelShift) & 3u);
-        const int64_t nv = (info[i] & kNoBlockBit) ? 0 : (int64_t)side_of(lvl) * side_of(lvl) * side_of(lvl);
-        pos[i] = (int32_t)nout++;
-        offs.push_back(offs.back() + nv);
-    }
-    *n_voxels = offs[nout];
+    int64_t nvox = 0;
+    mrh_status st = scan_rows(map, "extract colour", nout, nvox);
+    if (st != MRH_OK) return st;
+    *n_voxels = nvox;
     if (!rgb_dev) return MRH_OK;
-    if (voxel_cap < offs[nout]) return set_error(map, MRH_ERR_BUFFER_TOO_SMALL, "colour needs %lld voxels", (long long)offs[nout]);
+    if (voxel_cap < nvox) return set_error(map, MRH_ERR_BUFFER_TOO_SMALL, "colour needs %lld voxels", (long long)nvox);
     if (nout == 0) return MRH_OK;
-    int64_t* doffs = nullptr;
-    int32_t* dpos = nullptr;
-    st = check_hip(map, hipMalloc((void**)&doffs, ((size_t)nout + 1) * 8), "extract colour");
-    if (st == MRH_OK) st = check_hip(map, hipMalloc((void**)&dpos, (size_t)nb * 4), "extract colour");
-    if (st == MRH_OK) st = check_hip(map, hipMemcpy(doffs, offs.data(), ((size_t)nout + 1) * 8, hipMemcpyHostToDevice), "extract colour");
-    if (st == MRH_OK) st = check_hip(map, hipMemcpy(dpos, pos.data(), (size_t)nb * 4, hipMemcpyHostToDevice), "extract colour");
-    if (st == MRH_OK) {
-        const uint32_t grid = nb / 4 + 1 < 4096 ? nb / 4 + 1 : 4096;
-        hipLaunchKernelGGL(k_extract_color, dim3(grid), dim3(256), 0, map->stream, map->dmd, nb, dpos, doffs, rgb_dev);
-        st = check_hip(map, hipGetLastError(), "extract colour");
-        if (st == MRH_OK) st = check_hip(map, hipStreamSynchronize(map->stream), "extract colour");
-    }
-    if (doffs) (void)hipFree(doffs);
-    if (dpos) (void)hipFree(dpos);
+    hipLaunchKernelGGL(k_extract_color, dim3((nout + kExtractRows - 1) / kExtractRows), dim3(256), 0, map->stream,
+                       map->dmd, map->extract_rows, nout, rgb_dev);
+    st = check_hip(map, hipGetLastError(), "extract colour");
+    if (st == MRH_OK) st = check_hip(map, hipStreamSynchronize(map->stream), "extract colour");
     return st;
 }

@@ -575,6 +575,14 @@ enum KernelId { K_RESET = MRH_KERNEL_RESET, K_ALLOC_DEPTH = MRH_KERNEL_ALLOC_DEP
                 K_BATCH_UPDATE = MRH_KERNEL_BATCH_UPDATE, K_BATCH_FINALIZE = MRH_KERNEL_BATCH_FINALIZE,
                 K_BATCH_GRAPH = MRH_KERNEL_BATCH_GRAPH, K_MESH = MRH_KERNEL_MESH, K_COLOR = MRH_KERNEL_COLOR };
 
+// A block of an extraction: its output row's first voxel, id and descriptor.
+struct ExtractRow {
+    int64_t off;
+    uint32_t id, info;
+};
+constexpr uint32_t kExtractChunk = 2048;  // block ids per workgroup of the row scan
+constexpr uint32_t kExtractRows = 8;      // rows per workgroup of the copies
+
 // one profiled launch: kernel id and its bracketing events on the map's stream
 struct ProfRec {
     int kernel;
@@ -597,6 +605,7 @@ struct mrh_map {
     unsigned long long* count_dev = nullptr;  // one device counter for the extraction calls
     uint32_t* mesh_order = nullptr;  // the mesh launch's block ids by level (4 regions) and 4 counts
     size_t mesh_order_cap = 0;
+    mrh::ExtractRow* extract_rows = nullptr;  // extraction: rows (max_blocks), sums per chunk of ids, total
     int32_t partials_cap = 0;
     bool lidar_ready = false;    // accumulators allocated
     int64_t rcap_n = 0;          // rays the per-ray block-key buffers hold
@@ -619,6 +628,8 @@ mrh_status set_error(mrh_map* m, mrh_status code, const char* fmt, ...);
 mrh_status check_hip(mrh_map* m, hipError_t e, const char* what);
 bool pose_from(const double* T, Pose& P);
 mrh_status upload_descriptor(mrh_map* m);
+// Rows of an extraction (map->extract_rows), their number and the number of voxels.
+mrh_status scan_rows(mrh_map* m, const char* what, uint32_t& rows, int64_t& voxels);
 void stream_free(mrh_map* m);   // release the host store and the streaming staging buffers
 void stream_clear(mrh_map* m);  // empty the host store (map reset)
 

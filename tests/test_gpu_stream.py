@@ -182,3 +182,30 @@ def test_load_blocks(mrh):
     assert h.load_blocks(s["keys"], s["levels"], s["D"], s["W"], s["S2"]) == len(s["keys"])
     assert h.load_blocks(s["keys"][:10], s["levels"][:10], s["D"], s["W"], s["S2"]) == 0  # present already
     _same(gpu_sorted(h), _store_sorted(g))
+
+
+@pytest.mark.parametrize("n", [1, 7, 8, 9, 2047, 2048, 2049, 6151])
+def test_extract_rows(mrh, n):
+    """Extraction of maps whose block count lies at the edges of a workgroup's rows (8) and of the row
+    scan's chunks (2048), all levels mixed: every loaded block comes back with its voxels."""
+    announce(f"extract {n} blocks")
+    rng = np.random.default_rng(n)
+    cells = rng.permutation(32 ** 3)[:n]
+    keys = np.stack([cells % 32, cells // 32 % 32, cells // 1024], 1).astype(np.int32) - 16
+    levels = rng.integers(0, 4, n).astype(np.uint8)
+    offs = np.concatenate([[0], np.cumsum((8 >> levels.astype(int)) ** 3)])
+    D = rng.normal(size=offs[-1]).astype(np.float32)
+    W = rng.integers(1, 50, offs[-1]).astype(np.uint32)
+    S2 = rng.random(offs[-1]).astype(np.float32)
+    m = mrh.Map(voxel=0.05, levels=4, tau=0.15, max_blocks=8192)
+    assert m.load_blocks(keys, levels, D, W, S2) == n
+    assert m.counts() == (n, offs[-1])
+    e = {k: v.cpu().numpy() for k, v in m.extract().items()}
+    go, wo = np.lexsort(e["keys"].T), np.lexsort(keys.T)
+    assert np.array_equal(e["keys"][go], keys[wo])
+    assert np.array_equal(e["levels"][go], levels[wo])
+    assert np.array_equal(np.diff(e["offsets"])[go], np.diff(offs)[wo]) and e["offsets"][0] == 0
+    for g, w in zip(go, wo):
+        a, b = slice(*e["offsets"][g:g + 2]), slice(*offs[w:w + 2])
+        assert np.array_equal(e["D"][a], D[b]) and np.array_equal(e["W"][a].view(np.uint32), W[b])
+        assert np.array_equal(e["S2"][a], S2[b])
