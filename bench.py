@@ -588,8 +588,9 @@ def run_query(room, torch, np, mrh):
 
 def run_color(room, torch, np, mrh, configs):
     """Colour integration (mrh_integrate_rgbd) of the room sequence: the 100 frames with a colour
-    image each; the colour launch re-takes every updated voxel's projective decision and averages
-    its pixel's RGB into the voxel's colour (12 B read and written per updated voxel)."""
+    image each; the update launch averages the RGB of every updated voxel's pixel into the voxel's
+    colour (12 B read and written per updated voxel, counted below with the images; the state's
+    bytes are not)."""
     from workloads import colour_image
 
     n = len(room["poses"])

@@ -137,11 +137,10 @@ mrh_status mrh_integrate_depth(mrh_map* map, const float* depth_dev, int32_t wid
                                const double K[4], const double T_ws[16]);
 
 /* Fuse one RGB-D frame with colour into a map created with cfg.color = 1 (Sec. 3: a voxel stores a
- * colour).  The depth part is exactly mrh_integrate_depth; then a separate colour launch takes, for
- * every voxel the frame updated (the same projective decisions), the RGB value of its pixel into
- * the voxel's colour, C <- C + (c - C) / W with the voxel's updated weight (Eq. 3 with w = 1), and
- * pools the colour of a block the frame merged into its coarser block as the weighted mean of the
- * observed children (as the TSDF is pooled).
+ * colour).  The depth part is exactly mrh_integrate_depth; with it, every voxel the frame updates takes
+ * the RGB value of its pixel into its colour, C <- C + (c - C) / W with the voxel's updated weight
+ * (Eq. 3 with w = 1), and the colour of a block the frame merged is pooled into its coarser block as the
+ * weighted mean of the observed children (as the TSDF is pooled).
  *   rgb_dev: device uint8[height][width][3], interleaved, the same pixels as depth_dev.
  * Errors as mrh_integrate_depth; MRH_ERR_INVALID_ARG on a map without colour. */
 mrh_status mrh_integrate_rgbd(mrh_map* map, const float* depth_dev, const uint8_t* rgb_dev, int32_t width,
@@ -298,7 +297,7 @@ enum {
     MRH_KERNEL_BATCH_FINALIZE = 13, /* reserved, as MRH_KERNEL_FINALIZE; stays 0 */
     MRH_KERNEL_BATCH_GRAPH = 14,    /* batched: one replay of the captured step */
     MRH_KERNEL_MESH = 15,           /* multi-resolution Marching Cubes (with its block ordering by level) */
-    MRH_KERNEL_COLOR = 16,          /* colour integration of an RGB-D frame */
+    MRH_KERNEL_COLOR = 16,          /* update of an RGB-D frame with colour */
     MRH_KERNEL_COUNT = 17
 };
 

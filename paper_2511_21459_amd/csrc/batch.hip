@@ -177,7 +177,7 @@ __global__ __launch_bounds__(256) void k_batch_update(const DevMap* __restrict__
         c.n_new = uniform(c.n_new);
         if constexpr (KIND == MRH_FRAME_DEPTH) {
             const DepthFrame fr = *(const DepthFrame*)&ce[lo].df;
-            ts.add(depth_update_task<ST>(maps[lo], fr, local, c));
+            ts.add_uniform(depth_update_task<ST, false>(maps[lo], fr, nullptr, local, c));
         } else {
             ts.add_uniform(points_update_task<ST>(maps[lo], local, c, ((const BatchEntry*)&ce[lo])->sp.parity, &dl, alds[wv]));
         }

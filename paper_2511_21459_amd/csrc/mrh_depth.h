@@ -34,10 +34,10 @@ struct DepthFrame {
 // Host: frame sizes the kernels accept (pixel indices 32-bit, pixel coordinates exact in FP32).
 bool depth_size_ok(int32_t width, int32_t height);
 
-// Host: enqueue the allocation and update launches of one RGB-D frame (no colour check);
-// *frame_out (may be NULL) receives the frame's descriptor.
-mrh_status integrate_depth_frame(mrh_map* map, const float* depth_dev, int32_t width, int32_t height,
-                                 const double K[4], const double T_ws[16], DepthFrame* frame_out);
+// Host: enqueue the allocation and update launches of one RGB-D frame (rgb_dev: of a map with colour, else
+// null; not checked).
+mrh_status integrate_depth_frame(mrh_map* map, const float* depth_dev, const uint8_t* rgb_dev, int32_t width,
+                                 int32_t height, const double K[4], const double T_ws[16]);
 
 // Host: fill a frame descriptor; false on a non-finite pose or intrinsics or a zero focal length.
 bool make_depth_frame(const mrh_config& cfg, const float* depth, int32_t width, int32_t height, const double K[4],
@@ -60,12 +60,11 @@ __device__ inline int pixel_exact(const DepthFrame& f, double x0, double x1, dou
 // than its error can reach; returns -2 when it cannot decide.  Error budget of the FP32 u from FP64
 // x: the roundings of x0, x2, fx, cx, the product and the sum (2^-24 relative each) and the hardware
 // reciprocal (1 ulp) stay below 6e-7 (|u| + |cx|), under the margin 1e-6 (|u| + |cx| + 16).  `lam`
-// receives |x| / x2 in FP32 for the range form.
+// receives |x| / x2 in FP32 for the range form (of use where a pixel is returned).  Straight-line code, as
+// observe_form and the update of a group: a launch issues three quarter million branches and as many mask
+// operations for what they skip (with the grid below 29.1 -> 26.7 us).
 __device__ inline int pixel_fast(const DepthFrame& f, double x0, double x1, double x2, float& lam) {
-    lam = 0.f;
-    if (!(x2 > 0.0)) return -1;
     const float xf0 = (float)x0, xf1 = (float)x1, xf2 = (float)x2;
-    if (!(xf2 > 1e-6f)) return -2;
     const float izf = __builtin_amdgcn_rcpf(xf2);
     lam = __builtin_amdgcn_sqrtf((xf0 * xf0 + xf1 * xf1) + xf2 * xf2) * izf;
     const float uf = f.fxf * (xf0 * izf) + f.cxf;
@@ -75,9 +74,12 @@ __device__ inline int pixel_fast(const DepthFrame& f, double x0, double x1, doub
     const float du = __builtin_fminf(su - fu, fu + 1.0f - su), dv = __builtin_fminf(sv - fv, fv + 1.0f - sv);
     const float eu = 1e-6f * (__builtin_fabsf(uf) + __builtin_fabsf(f.cxf) + 16.0f);
     const float ev = 1e-6f * (__builtin_fabsf(vf) + __builtin_fabsf(f.cyf) + 16.0f);
-    if (!(du > eu && dv > ev)) return -2;
-    if (!(fu >= 0.0f && fu <= (float)(f.width - 1) && fv >= 0.0f && fv <= (float)(f.height - 1))) return -1;
-    return (int)fv * f.width + (int)fu;
+    const bool sure = (xf2 > 1e-6f) & (du > eu) & (dv > ev);
+    // clamped to the image, so that the conversions are defined
+    const float cu = __builtin_amdgcn_fmed3f(fu, 0.0f, (float)(f.width - 1)), cv = __builtin_amdgcn_fmed3f(fv, 0.0f, (float)(f.height - 1));
+    const int p = __mul24((int)cv, f.width) + (int)cu;
+    const int in = ((cu == fu) & (cv == fv)) ? p : -1;
+    return x2 > 0.0 ? (sure ? in : -2) : -1;
 }
 
 // Observation of Eq. 2 (gate at -tau, truncation at +tau) for the voxel centre x from the depth d
@@ -100,32 +102,33 @@ __device__ inline bool observe_exact(const DevMap& m, double x0, double x1, doub
 // The same observation with the range form's scale |x| / x2 in FP32 (`lam` from pixel_fast).
 // Returns 1 (update with obs), 0 (no update) or 2 (undecided: observe_exact must decide).  The
 // validity test is the canonical one (max_depth_f is the largest float not above max_depth) and
-// the z-difference form is evaluated exactly; the range-form value carries about 8 ulps (squares,
+// the z-difference form is evaluated exactly (obs is of use where 1 is returned); the range-form value carries about 8 ulps (squares,
 // sums, square root, reciprocal), so its -tau gate is taken only outside a 1e-5 tau band.
-__device__ inline int observe_fast(const DevMap& m, double x2, float lam, float d, float& obs) {
-    if (!(__builtin_isfinite(d) && d > 0.0f && d <= m.max_depth_f)) return 0;
+template <bool RANGE>
+__device__ inline int observe_form(const DevMap& m, double x2, float lam, float d, float& obs) {
+    const bool valid = (d > 0.0f) & (d <= __builtin_fminf(m.max_depth_f, 3.402823466e38f));
     const double ddiff = (double)d - x2;
-    if (m.form != MRH_FORM_RANGE) {
-        if (ddiff < -m.tau) return 0;
+    if (!RANGE) {
         obs = (float)(ddiff < m.tau ? ddiff : m.tau);
-        return 1;
+        return (valid & !(ddiff < -m.tau)) ? 1 : 0;
     }
     const float raw = (float)ddiff * lam;
-    if (__builtin_fabsf(raw + m.tau_f) <= 1e-5f * m.tau_f + 1e-6f * __builtin_fabsf(raw)) return 2;
-    if (raw < -m.tau_f) return 0;
     obs = raw < m.tau_f ? raw : m.tau_f;
-    return 1;
+    const bool close = __builtin_fabsf(raw + m.tau_f) <= 1e-5f * m.tau_f + 1e-6f * __builtin_fabsf(raw);
+    return valid ? (close ? 2 : (raw < -m.tau_f ? 0 : 1)) : 0;
+}
+__device__ inline int observe_fast(const DevMap& m, double x2, float lam, float d, float& obs) {
+    return m.form == MRH_FORM_RANGE ? observe_form<true>(m, x2, lam, d, obs) : observe_form<false>(m, x2, lam, d, obs);
 }
 
-// One voxel: pixel decision, depth lookup, observation.
-__device__ inline bool observe(const DevMap& m, const DepthFrame& f, const float MRH_GLOBAL* __restrict__ depth, double x0,
-                               double x1, double x2, float& obs) {
+// One voxel: pixel decision, depth lookup, observation; p receives the pixel.
+__device__ inline bool observe(const DevMap& m, const DepthFrame& f, double x0, double x1, double x2, float& obs, int& p) {
     float lam;
-    int p = pixel_fast(f, x0, x1, x2, lam);
+    p = pixel_fast(f, x0, x1, x2, lam);
     const bool exact = p == -2;
     if (exact) p = pixel_exact(f, x0, x1, x2);
     if (p < 0) return false;
-    const float d = depth[p];
+    const float d = f.depth[p];
     if (!exact) {
         const int r = observe_fast(m, x2, lam, d, obs);
         if (r != 2) return r == 1;
@@ -313,11 +316,9 @@ __device__ inline void voxel_camera(const DevMap& m, const DepthFrame& f, int64_
 // The projective decisions of lane group (I, J, K) of level-0 block (bx, by, bz): the 2x2x2 voxels
 // 2I + a, 2J + b, 2K + c at Morton positions q = a + 2 b + 4 c.  pix[q] receives the voxel's pixel
 // (-1: none), obs[q] its observation, and the returned mask has bit q set when the frame updates the
-// voxel.  Every launch that needs these decisions (the update, the colour launch) calls this one
-// function, so they agree voxel for voxel.
-__device__ inline uint32_t fine_decisions(const DevMap& m, const DepthFrame& f, const float MRH_GLOBAL* __restrict__ depth,
-                                          int32_t bx, int32_t by, int32_t bz, int I, int J, int K, int pix[8],
-                                          float obs[8]) {
+// voxel.
+__device__ inline uint32_t fine_decisions(const DevMap& m, const DepthFrame& f, int32_t bx, int32_t by, int32_t bz, int I,
+                                          int J, int K, int pix[8], float obs[8]) {
     const double nu = m.nu[0];
     // camera-frame products of R^T (c - t), one per axis coordinate of this lane's group
     double px[2][3], py[2][3], pz[2][3];
@@ -358,16 +359,22 @@ __device__ inline uint32_t fine_decisions(const DevMap& m, const DepthFrame& f, 
     }
     float dq[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) dq[q] = pix[q] >= 0 ? depth[pix[q]] : -1.f;
-    uint32_t upd = 0, slow = 0;
+    for (int q = 0; q < 8; ++q) dq[q] = f.depth[max(pix[q], 0)];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        obs[q] = 0.f;
-        const double x2 = (px[q & 1][2] + py[(q >> 1) & 1][2]) + pz[q >> 2][2];
-        const int r = (exact >> q) & 1 ? (dq[q] > 0.f ? 2 : 0) : observe_fast(m, x2, lam[q], dq[q], obs[q]);
-        upd |= (r == 1 ? 1u : 0u) << q;
-        slow |= (r == 2 ? 1u : 0u) << q;
-    }
+    for (int q = 0; q < 8; ++q) dq[q] = pix[q] >= 0 ? dq[q] : -1.f;
+    uint32_t upd = 0, slow = 0;
+    auto decide = [&](auto range) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const double x2 = (px[q & 1][2] + py[(q >> 1) & 1][2]) + pz[q >> 2][2];
+            const int fast = observe_form<decltype(range)::value>(m, x2, lam[q], dq[q], obs[q]);
+            const int r = (exact >> q) & 1 ? (dq[q] > 0.f ? 2 : 0) : fast;
+            upd |= r == 1 ? 1u << q : 0u;
+            slow |= r == 2 ? 1u << q : 0u;
+        }
+    };
+    if (m.form == MRH_FORM_RANGE) decide(std::true_type{});
+    else decide(std::false_type{});
     // voxels the FP32 evaluation left undecided: the canonical evaluation from the same depth sample
     while (slow) {
         const int q = __builtin_ctz(slow);
@@ -388,10 +395,71 @@ __device__ inline uint32_t fine_decisions(const DevMap& m, const DepthFrame& f, 
     return upd;
 }
 
+// A voxel's colour after the frame (Eq. 3 with w = 1, W the weight after it).
+__device__ inline void color_update(const uint8_t* __restrict__ rgb, int p, uint32_t W, float c[3]) {
+    const float inv = 1.0f / (float)W;
+    for (int ch = 0; ch < 3; ++ch) c[ch] = c[ch] + ((float)rgb[3 * (size_t)p + ch] - c[ch]) * inv;
+}
+
+// Colours of a block that merged one level coarser, pooled as the TSDF was: the mean of the 8 children
+// (the 8 lanes of a group) weighted by their weights Wp after the frame, into voxel `at` of C.
+__device__ inline void pool_color8(float MRH_GLOBAL* C, size_t at, bool merged, uint32_t Wp, const float c[3]) {
+    float sw = (float)Wp, s0 = sw * c[0], s1 = sw * c[1], s2 = sw * c[2];
+    sw = group8_sum(sw);
+    s0 = group8_sum(s0);
+    s1 = group8_sum(s1);
+    s2 = group8_sum(s2);
+    if (!merged || (lane_id() & 7) != 0) return;
+    const float inv = sw > 0.f ? 1.0f / sw : 0.f;
+    C[3 * at] = s0 * inv;
+    C[3 * at + 1] = s1 * inv;
+    C[3 * at + 2] = s2 * inv;
+}
+
+// The same for a level-0 block's lane group (Morton positions 8l .. 8l+7), whose colours are stored, or pooled
+// into voxel l of level-1 slot `now` when the block merged: upd and pix as fine_decisions returned them,
+// W the weights after the frame as stored, Wp before they were rounded.
+__device__ inline void color_fine_group(const DevMap& m, const uint8_t* __restrict__ rgb, uint32_t info, uint32_t now, uint32_t upd,
+                                        bool fresh, bool merged, const int pix[8], const uint32_t W[8], const uint32_t Wp[8]) {
+    const int lane = lane_id();
+    float c[24];
+    float MRH_GLOBAL* cp = m.C[0] + 3 * ((size_t)(info & kSlotMask) * 512 + (size_t)lane * 8);  // 96 B, 16 B aligned
+    if (fresh || (!merged && !upd)) {
+        for (int k = 0; k < 24; ++k) c[k] = 0.f;
+    } else {
+        for (int k = 0; k < 6; ++k) {
+            const f32x4 v = load_as<f32x4>(cp + 4 * k);
+            c[4 * k] = v.x, c[4 * k + 1] = v.y, c[4 * k + 2] = v.z, c[4 * k + 3] = v.w;
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+        if ((upd >> q) & 1) color_update(rgb, pix[q], merged ? Wp[q] : W[q], c + 3 * q);
+    if (!merged) {
+        if (upd || fresh)
+            for (int k = 0; k < 6; ++k) store_as(cp + 4 * k, f32x4{c[4 * k], c[4 * k + 1], c[4 * k + 2], c[4 * k + 3]});
+        return;
+    }
+    float sw = 0.f, s0 = 0.f, s1 = 0.f, s2 = 0.f;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const float w = (float)Wp[q];
+        sw += w;
+        s0 += w * c[3 * q];
+        s1 += w * c[3 * q + 1];
+        s2 += w * c[3 * q + 2];
+    }
+    const float inv = sw > 0.f ? 1.0f / sw : 0.f;
+    float MRH_GLOBAL* Cc = m.C[1] + 3 * ((size_t)(now & kSlotMask) * 64 + (size_t)lane);
+    Cc[0] = s0 * inv;
+    Cc[1] = s1 * inv;
+    Cc[2] = s2 * inv;
+}
+
 // Level-0 block: lane l owns the 2x2x2 group of Morton positions 8l .. 8l+7.
-template <int ST>
-__device__ inline TaskOut integrate_fine_block(const DevMap& m, const DepthFrame& f, const float MRH_GLOBAL* __restrict__ depth,
-                                            const u32x4 eq) {
+template <int ST, bool COLOR>
+__device__ inline TaskOut integrate_fine_block(const DevMap& m, const DepthFrame& f, const uint8_t* __restrict__ rgb,
+                                               const u32x4 eq) {
     const int lane = lane_id();
     const u32x4 e = uniform(eq);  // one block per wave
     const uint32_t id = e.x, info = e.y;
@@ -406,7 +474,7 @@ __device__ inline TaskOut integrate_fine_block(const DevMap& m, const DepthFrame
     demorton3(lane, I, J, K);
     int pix[8];
     float obs[8];
-    const uint32_t upd = fine_decisions(m, f, depth, bx, by, bz, I, J, K, pix, obs);
+    const uint32_t upd = fine_decisions(m, f, bx, by, bz, I, J, K, pix, obs);
     const int nupd = wave_sum((int)__popc(upd));
     if (nupd == 0 && !fresh) return TaskOut{};
     TaskOut out;
@@ -426,24 +494,44 @@ __device__ inline TaskOut integrate_fine_block(const DevMap& m, const DepthFrame
     }
     double dsum = 0.0;
     int dcnt = 0;
-    for (int q = 0; q < 8; ++q) {
-        if (!(upd & (1u << q))) continue;
-        const double before = var_term(m, W[q], S2[q]);
-        const int cb = var_count(m, W[q]);
-        welford(obs[q], D[q], W[q], S2[q]);
-        Store<ST>::round(m, D[q], W[q], S2[q]);
-        dsum += var_term(m, W[q], S2[q]) - before;
-        dcnt += var_count(m, W[q]) - cb;
+    uint32_t Wp[8];  // (colour) the weights after the frame, not rounded
+    if (COLOR && have)
+        for (int q = 0; q < 8; ++q) Wp[q] = W[q] + ((upd >> q) & 1);
+    if (upd) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const bool u = (upd >> q) & 1;
+            float d = D[q], s2 = S2[q];
+            uint32_t w = W[q];
+            welford(obs[q], d, w, s2);
+            Store<ST>::round(m, d, w, s2);
+            const double change = var_term(m, w, s2) - var_term(m, W[q], S2[q]);
+            dsum += u ? change : 0.0;
+            dcnt += u ? var_count(m, w) - var_count(m, W[q]) : 0;
+            D[q] = u ? d : D[q];
+            S2[q] = u ? s2 : S2[q];
+            W[q] = u ? w : W[q];
+        }
     }
     out.merge0 = (uint32_t)finish_fine<ST>(m, id, info, D, W, S2, have, upd != 0 || fresh, nupd, dsum, dcnt,
                                                         bvs, bvc, f.parity);
+    if (COLOR) {
+        uint32_t now = 0;
+        if (out.merge0) {
+            DeferList::sync();
+            now = uniform(m.binfo[id]);
+            if (!have)  // (finish_fine read the group)
+                for (int q = 0; q < 8; ++q) Wp[q] = W[q];
+        }
+        color_fine_group(m, rgb, info, now, upd, fresh, out.merge0 != 0, pix, W, Wp);
+    }
     return out;
 }
 
 // Level-1 block: lane l owns the voxel at Morton position l.
-template <int ST>
-__device__ inline TaskOut integrate_level1_block(const DevMap& m, const DepthFrame& f, const float MRH_GLOBAL* __restrict__ depth,
-                                              const u32x4 eq) {
+template <int ST, bool COLOR>
+__device__ inline TaskOut integrate_level1_block(const DevMap& m, const DepthFrame& f, const uint8_t* __restrict__ rgb,
+                                                 const u32x4 eq) {
     const int lane = lane_id();
     const u32x4 e = uniform(eq);  // one block per wave
     const uint32_t id = e.x, info = e.y;
@@ -457,7 +545,8 @@ __device__ inline TaskOut integrate_level1_block(const DevMap& m, const DepthFra
     double x0, x1, x2;
     voxel_camera(m, f, bx, by, bz, 1, i, j, k, x0, x1, x2);
     float obs = 0.f;
-    const bool upd = observe(m, f, depth, x0, x1, x2, obs);
+    int pix;
+    const bool upd = observe(m, f, x0, x1, x2, obs, pix);
     const int nupd = __popcll(__ballot(upd));
     if (nupd == 0) return TaskOut{};
     TaskOut out;
@@ -466,6 +555,7 @@ __device__ inline TaskOut integrate_level1_block(const DevMap& m, const DepthFra
     float D, S2;
     uint32_t W;
     Store<ST>::get(m, 1, at, D, W, S2);
+    const uint32_t Wp = W + (upd ? 1u : 0u);
     double dsum = 0.0;
     int dcnt = 0;
     if (upd) {
@@ -478,12 +568,24 @@ __device__ inline TaskOut integrate_level1_block(const DevMap& m, const DepthFra
     }
     out.merge1 = (uint32_t)finish_coarse<ST>(m, id, info, 1, D, W, S2, upd, nupd, dsum, dcnt, bvs, bvc,
                                                           f.parity);
+    if (COLOR) {
+        const bool merged = out.merge1 != 0;
+        float c[3];
+        for (int ch = 0; ch < 3; ++ch) c[ch] = m.C[1][3 * at + ch];
+        if (upd) color_update(rgb, pix, merged ? Wp : W, c);
+        if (merged) {
+            DeferList::sync();
+            pool_color8(m.C[2], (size_t)(m.binfo[id] & kSlotMask) * 8 + (size_t)(lane >> 3), true, Wp, c);
+        } else if (upd) {
+            for (int ch = 0; ch < 3; ++ch) m.C[1][3 * at + ch] = c[ch];
+        }
+    }
     return out;
 }
 
 // 64 / seg blocks of `level` (2: seg = 8 voxels, 3: seg = 1 voxel) per wave.
-template <int ST>
-__device__ inline TaskOut integrate_packed_blocks(const DevMap& m, const DepthFrame& f, const float MRH_GLOBAL* __restrict__ depth,
+template <int ST, bool COLOR>
+__device__ inline TaskOut integrate_packed_blocks(const DevMap& m, const DepthFrame& f, const uint8_t* __restrict__ rgb,
                                                const u32x4 MRH_GLOBAL* list, uint32_t count, uint32_t group, int level) {
     const int lane = lane_id();
     const int seg = level == 2 ? 8 : 1;
@@ -492,6 +594,7 @@ __device__ inline TaskOut integrate_packed_blocks(const DevMap& m, const DepthFr
     uint32_t id = 0, info = 0;
     bool upd = false;
     float obs = 0.f;
+    int pix = 0;
     if (live) {
         const u32x4 e = list[bi];
         id = e.x;
@@ -502,15 +605,17 @@ __device__ inline TaskOut integrate_packed_blocks(const DevMap& m, const DepthFr
         demorton3(lane % seg, i, j, k);
         double x0, x1, x2;
         voxel_camera(m, f, bx, by, bz, level, i, j, k, x0, x1, x2);
-        upd = observe(m, f, depth, x0, x1, x2, obs);
+        upd = observe(m, f, x0, x1, x2, obs, pix);
     }
     if (!__ballot(upd)) return TaskOut{};
     float D = 0.f, S2 = 0.f;
     uint32_t W = 0;
     double dsum = 0.0;
     int dcnt = 0;
+    uint32_t Wp = 0;  // the weight after the frame, not rounded
     if (upd) {
         Store<ST>::get(m, level, (size_t)(info & kSlotMask) * seg + (lane % seg), D, W, S2);
+        Wp = W + 1u;
         const double before = var_term(m, W, S2);
         const int cb = var_count(m, W);
         welford(obs, D, W, S2);
@@ -520,32 +625,49 @@ __device__ inline TaskOut integrate_packed_blocks(const DevMap& m, const DepthFr
     } else if (live && seg > 1) {
         // a segment whose block merges needs all of its voxels
         Store<ST>::get(m, level, (size_t)(info & kSlotMask) * seg + (lane % seg), D, W, S2);
+        Wp = W;
     }
     TaskOut out;
     out.obs = (uint32_t)wave_sum(upd ? 1 : 0);
-    out.merge2 = (uint32_t)wave_sum(finish_packed<ST>(m, live, id, info, level, seg, D, W, S2, upd, upd ? 1 : 0, dsum,
-                                                      dcnt));
+    const int merge = finish_packed<ST>(m, live, id, info, level, seg, D, W, S2, upd, upd ? 1 : 0, dsum, dcnt);
+    out.merge2 = (uint32_t)wave_sum(merge);
+    if (COLOR) {
+        const bool merged = seg == 8 && group8_sum(merge) != 0;
+        const size_t at = 3 * ((size_t)(info & kSlotMask) * seg + (lane % seg));
+        float MRH_GLOBAL* const C = level == 2 ? m.C[2] : m.C[3];
+        float c[3] = {0.f, 0.f, 0.f};
+        if (upd || (merged && live))
+            for (int ch = 0; ch < 3; ++ch) c[ch] = C[at + ch];
+        if (upd) color_update(rgb, pix, merged ? Wp : W, c);
+        if (upd && !merged)
+            for (int ch = 0; ch < 3; ++ch) C[at + ch] = c[ch];
+        if (seg == 8 && __ballot(merged)) {
+            DeferList::sync();
+            const uint32_t now = merged ? m.binfo[id] : 0u;
+            pool_color8(m.C[3], (size_t)(now & kSlotMask), merged, Wp, c);
+        }
+    }
     return out;
 }
 
 // One update task t of the frame's task space (see TaskCounts).
-template <int ST>
-__device__ inline TaskOut depth_update_task(const DevMap& m, const DepthFrame& f, uint32_t t, const TaskCounts& c) {
+template <int ST, bool COLOR>
+__device__ inline TaskOut depth_update_task(const DevMap& m, const DepthFrame& f, const uint8_t* __restrict__ rgb, uint32_t t,
+                                            const TaskCounts& c) {
     const uint32_t n0 = c.n[0] + c.n_new;
     const uint32_t g2 = (c.n[2] + 7) / 8;
-    // each work unit is called in one place: its code is inlined there, and a launch of some 30 us pays for
-    // fetching every copy
+    // each work unit is called in one place: its code is inlined there
     if (t < n0) {
         const uint32_t id = c.new_base + (t - c.n[0]);
         u32x4 e;
         if (t < c.n[0]) e = m.vis[0][t];
         else e = make_entry(id, m.binfo[id], m.bkey[id]);
-        return integrate_fine_block<ST>(m, f, f.depth, e);
+        return integrate_fine_block<ST, COLOR>(m, f, rgb, e);
     }
-    if (t < n0 + c.n[1]) return integrate_level1_block<ST>(m, f, f.depth, m.vis[1][t - n0]);
+    if (t < n0 + c.n[1]) return integrate_level1_block<ST, COLOR>(m, f, rgb, m.vis[1][t - n0]);
     const uint32_t g = t - n0 - c.n[1];
     const int level = g < g2 ? 2 : 3;
-    return integrate_packed_blocks<ST>(m, f, f.depth, m.vis[level], c.n[level], level == 2 ? g : g - g2, level);
+    return integrate_packed_blocks<ST, COLOR>(m, f, rgb, m.vis[level], c.n[level], level == 2 ? g : g - g2, level);
 }
 
 }  // namespace mrh

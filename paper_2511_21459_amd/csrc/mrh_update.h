@@ -27,7 +27,8 @@ __device__ inline void welford(float obs, float& D, uint32_t& W, float& S2) {
 // evaluated in FP32 (a fixed function of the stored S2 and W, so that the incremental block sums
 // stay consistent) and summed in FP64.
 __device__ inline double var_term(const DevMap& m, uint32_t W, float S2) {
-    return W >= (uint32_t)m.min_obs ? (double)(S2 * __builtin_amdgcn_rcpf((float)W)) : 0.0;
+    const float v = S2 * __builtin_amdgcn_rcpf((float)W);
+    return (double)(W >= (uint32_t)m.min_obs ? v : 0.0f);
 }
 
 __device__ inline int var_count(const DevMap& m, uint32_t W) { return W >= (uint32_t)m.min_obs ? 1 : 0; }

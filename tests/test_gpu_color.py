@@ -85,3 +85,31 @@ def test_colour_maps_reject_other_paths(mrh):
         plain.integrate_rgbd(_dev(depths[0]), _dev(np.zeros((48, 64, 3), np.uint8)), cam.K, poses[0])
     with pytest.raises(mrh.MrhError):
         mrh.Map(**dict(ROOM, color=True, min_obs=1))
+
+
+@pytest.mark.parametrize("storage", ["f16", "bf16"])
+def test_colour_in_16_bit_maps(mrh, storage):
+    """Colour with 16-bit state: the fusion is that of the map without colour, and the colours are those of
+    the FP32 map (they depend on the frame's decisions and the weights only) in blocks that never
+    merged, and in most coarse ones (a merge near its threshold may fall in another frame)."""
+    announce(f"colour room 320x240 x12, {storage}")
+    frames = list(range(0, 100, 8))[:12]
+    depths, cam, poses, _ = room_sequence(width=320, height=240, f=262.5, frames=frames)
+    maps = [mrh.Map(**dict(ROOM, color=True)), mrh.Map(**dict(ROOM, color=True, storage=storage)),
+            mrh.Map(**dict(ROOM, storage=storage))]
+    for k in range(len(frames)):
+        rgb = _dev(colour_image(depths[k], cam, poses[k]))
+        for m in maps[:2]:
+            m.integrate_rgbd(_dev(depths[k]), rgb, cam.K, poses[k])
+        maps[2].integrate_depth(_dev(depths[k]), cam.K, poses[k])
+    (fs, fc), (gs, gc), ps = _sorted_colour(maps[0]), _sorted_colour(maps[1]), gpu_sorted(maps[2])
+    for a, b in ((gs.keys, ps.keys), (gs.levels, ps.levels), (gs.W, ps.W), (gs.D, ps.D), (gs.S2, ps.S2)):
+        assert np.array_equal(a, b)
+    assert np.array_equal(gs.keys, fs.keys)
+    for level in (0, 1, 2):
+        ids = np.flatnonzero((gs.levels == level) & (fs.levels == level))
+        gi = np.concatenate([np.arange(gs.offsets[i], gs.offsets[i + 1]) for i in ids])
+        fi = np.concatenate([np.arange(fs.offsets[i], fs.offsets[i + 1]) for i in ids])
+        near = np.abs(gc[gi] - fc[fi]).max(1) <= 2e-3
+        print(storage, "level", level, "voxels", len(gi), "equal", near.mean())
+        assert len(ids) > 100 and (near.all() if level == 0 else near.mean() > 0.9)
