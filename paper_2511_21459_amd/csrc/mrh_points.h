@@ -730,22 +730,6 @@ __device__ inline void take_accumulators(const DevMap& m, int level, size_t at, 
     }
 }
 
-// Scan accumulators of the 8 voxels of a level-0 lane group, read (counts and sums of q).
-__device__ inline void group_accumulators(const DevMap& m, size_t base, uint32_t ns[8], uint32_t nb[8],
-                                          unsigned long long s1[8]) {
-    const u32x4 a0 = load_as<u32x4>(m.acc_sat[0] + base), a1 = load_as<u32x4>(m.acc_sat[0] + base + 4);
-    u64x2 w[4];
-    for (int k = 0; k < 4; ++k) w[k] = load_as<u64x2>(m.acc_s1[0] + base + 2 * k);
-    u32x4 b0{0, 0, 0, 0}, b1{0, 0, 0, 0};
-    if (m.band_wide) b0 = load_as<u32x4>(m.acc_band[0] + base), b1 = load_as<u32x4>(m.acc_band[0] + base + 4);
-    ns[0] = a0.x, ns[1] = a0.y, ns[2] = a0.z, ns[3] = a0.w, ns[4] = a1.x, ns[5] = a1.y, ns[6] = a1.z, ns[7] = a1.w;
-    const uint32_t wide[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-    for (int k = 0; k < 4; ++k) {
-        band_sums(m, wide[2 * k], w[k].x, nb[2 * k], s1[2 * k]);
-        band_sums(m, wide[2 * k + 1], w[k].y, nb[2 * k + 1], s1[2 * k + 1]);
-    }
-}
-
 // What one lane's voxels add to their block: the change of its variance sum and count, observations
 // and distinct voxels.
 struct UnitOut {
@@ -753,69 +737,85 @@ struct UnitOut {
     int dcnt = 0, nobs = 0, distinct = 0;
 };
 
-// The scan's observations of a level-0 lane group into its state, the accumulators left at zero.
+// The scan's observations of four voxels of level-0 blocks per lane (at[k], where on[k]) into their state, the
+// accumulators left at zero.  fresh: the state is empty and is written where no observation fell, too.  A
+// lane owns voxels, not groups of eight, so that the lanes of a group read and write its 32 and 64 bytes
+// together: with 16 bytes per lane and access the launch was bound by the L2's requests (100 M of them, 2.9 GB
+// of misses, for 131072 points into an empty map: 860 us, now 702 or 4.1 TB/s).  All reads of a step are
+// issued before any is used.
+constexpr int kVoxelStep = 4;
 template <int ST>
-__device__ inline UnitOut apply_group(const DevMap& m, size_t base, const uint32_t ns[8], const uint32_t nb[8],
-                                      const unsigned long long s1[8], float D[8], uint32_t W[8], float S2[8]) {
-    UnitOut u;
-    bool any_band = false;
-    for (int q = 0; q < 8; ++q) {
-        any_band |= nb[q] != 0;
-        u.nobs += (int)(ns[q] + nb[q]);
-        u.distinct += ns[q] + nb[q] ? 1 : 0;
-    }
-    for (int h = 0; h < 2; ++h) {
-        unsigned long long s2[4] = {0, 0, 0, 0};
-        if (any_band) {
-            const u64x2 v0 = load_as<u64x2>(m.acc_s2[0] + base + 4 * h), v1 = load_as<u64x2>(m.acc_s2[0] + base + 4 * h + 2);
-            s2[0] = v0.x, s2[1] = v0.y, s2[2] = v1.x, s2[3] = v1.y;
-        }
-        for (int k = 0; k < 4; ++k) {
-            const int q = 4 * h + k;
-            if (ns[q] + nb[q] == 0u) continue;
-            const double before = var_term(m, W[q], S2[q]);
-            const int cb = var_count(m, W[q]);
-            apply_stats(m, ns[q], nb[q], s1[q], s2[k], D[q], W[q], S2[q]);
-            Store<ST>::round(m, D[q], W[q], S2[q]);
-            u.dsum += var_term(m, W[q], S2[q]) - before;
-            u.dcnt += var_count(m, W[q]) - cb;
+__device__ inline void apply_voxels(const DevMap& m, const size_t at[kVoxelStep], const bool on[kVoxelStep], bool fresh,
+                                    UnitOut u[kVoxelStep]) {
+    uint32_t ns[kVoxelStep], nb[kVoxelStep], W[kVoxelStep], wide[kVoxelStep];
+    unsigned long long word[kVoxelStep], s1[kVoxelStep], s2[kVoxelStep];
+    float D[kVoxelStep], S2[kVoxelStep];
+#pragma unroll
+    for (int k = 0; k < kVoxelStep; ++k) {
+        ns[k] = wide[k] = W[k] = 0u, word[k] = 0ull, D[k] = S2[k] = 0.f;
+        if (on[k]) {
+            ns[k] = m.acc_sat[0][at[k]];
+            word[k] = m.acc_s1[0][at[k]];
+            if (m.band_wide) wide[k] = m.acc_band[0][at[k]];
+            if (!fresh) Store<ST>::get(m, 0, at[k], D[k], W[k], S2[k]);
         }
     }
-    if (u.nobs) {
-        const u32x4 z{0, 0, 0, 0};
-        store_as(m.acc_sat[0] + base, z);
-        store_as(m.acc_sat[0] + base + 4, z);
-        if (any_band) {
-            if (m.band_wide) {
-                store_as(m.acc_band[0] + base, z);
-                store_as(m.acc_band[0] + base + 4, z);
+#pragma unroll
+    for (int k = 0; k < kVoxelStep; ++k) {
+        band_sums(m, wide[k], word[k], nb[k], s1[k]);
+        s2[k] = 0ull;
+        if (nb[k]) s2[k] = m.acc_s2[0][at[k]];
+    }
+#pragma unroll
+    for (int k = 0; k < kVoxelStep; ++k) {
+        u[k] = UnitOut();
+        if (ns[k] + nb[k]) {
+            u[k].nobs = (int)(ns[k] + nb[k]);
+            u[k].distinct = 1;
+            const double before = var_term(m, W[k], S2[k]);
+            const int cb = var_count(m, W[k]);
+            apply_stats(m, ns[k], nb[k], s1[k], s2[k], D[k], W[k], S2[k]);
+            Store<ST>::round(m, D[k], W[k], S2[k]);
+            u[k].dsum = var_term(m, W[k], S2[k]) - before;
+            u[k].dcnt = var_count(m, W[k]) - cb;
+            if (ns[k]) m.acc_sat[0][at[k]] = 0u;
+            if (nb[k]) {
+                m.acc_s1[0][at[k]] = 0ull;
+                m.acc_s2[0][at[k]] = 0ull;
+                if (wide[k]) m.acc_band[0][at[k]] = 0u;
             }
-            for (int h = 0; h < 4; ++h) {
-                store_as(m.acc_s1[0] + base + 2 * h, z);
-                store_as(m.acc_s2[0] + base + 2 * h, z);
-            }
         }
+        if (fresh || u[k].distinct) Store<ST>::put(m, 0, at[k], D[k], W[k], S2[k]);
     }
-    return u;
 }
 
-// A block of the scan itself (level 0, one wave, lane l the group of Morton positions 8l .. 8l+7): every
-// group is written, with zeros where no ray touched it.
+// A block of the scan itself (level 0, one wave, lane l voxel l of each run of 64): every voxel is written,
+// with zeros where no ray touched its group.
 template <int ST>
 __device__ inline TaskOut apply_new(const DevMap& m, uint32_t id, uint32_t info, unsigned long long touched, double bvs,
                                     uint32_t bvc, int par, DeferList* dl) {
     const int lane = lane_id();
-    const size_t base = (size_t)(info & kSlotMask) * 512 + (size_t)lane * 8;
-    uint32_t ns[8] = {0, 0, 0, 0, 0, 0, 0, 0}, nb[8] = {0, 0, 0, 0, 0, 0, 0, 0}, W[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    unsigned long long s1[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    float D[8] = {0, 0, 0, 0, 0, 0, 0, 0}, S2[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    // lanes whose group no ray touched have zero accumulators: they read nothing
-    if ((touched >> lane) & 1ull) group_accumulators(m, base, ns, nb, s1);
-    const UnitOut u = apply_group<ST>(m, base, ns, nb, s1, D, W, S2);
+    const size_t base = (size_t)(info & kSlotMask) * 512 + (size_t)lane;
+    double dsum = 0.0;
+    int dcnt = 0, nobs = 0, distinct = 0;
+#pragma unroll 1
+    for (int r = 0; r < 8; r += kVoxelStep) {
+        size_t at[kVoxelStep];
+        bool on[kVoxelStep];
+        UnitOut u[kVoxelStep];
+        for (int k = 0; k < kVoxelStep; ++k) {
+            at[k] = base + (size_t)(r + k) * 64;
+            on[k] = (touched >> (8 * (r + k) + (lane >> 3))) & 1ull;
+        }
+        apply_voxels<ST>(m, at, on, true, u);
+        for (int k = 0; k < kVoxelStep; ++k) dsum += u[k].dsum, dcnt += u[k].dcnt, nobs += u[k].nobs, distinct += u[k].distinct;
+    }
     TaskOut out;
-    out.obs = out.fresh = (uint32_t)wave_sum(u.nobs);
-    out.distinct = (uint32_t)wave_sum(u.distinct);
-    (void)finish_fine<ST, true>(m, id, info, D, W, S2, true, true, (int)out.obs, u.dsum, u.dcnt, bvs, bvc, par, dl);
+    out.obs = out.fresh = (uint32_t)wave_sum(nobs);
+    out.distinct = (uint32_t)wave_sum(distinct);
+    float D[8], S2[8];  // (stored above)
+    uint32_t W[8];
+    (void)finish_fine<ST, true>(m, id, info, D, W, S2, true, false, (int)out.obs, dsum, dcnt, bvs, bvc, par, dl);
     return out;
 }
 
@@ -901,6 +901,7 @@ __device__ inline TaskOut apply_blocks(const DevMap& m, const u32x4 MRH_GLOBAL* 
         const uint32_t q = base + (uint32_t)lane;
         const bool act = q < total;
         int j = kApplyBlocks;  // (no block)
+        uint32_t own = kInvalidId;  // (level 0) the lane's group, in the heap (of fewer than 2^26 slots by its size)
         UnitOut u;
         if (act) {
             j = 0;
@@ -908,14 +909,7 @@ __device__ inline TaskOut apply_blocks(const DevMap& m, const u32x4 MRH_GLOBAL* 
                 if (q >= A.first[j + step]) j += step;
             const int g = nth_bit(A.touched[j], (int)(q - A.first[j]));
             if (LEVEL == 0) {
-                const size_t at = (size_t)A.slot[j] * 512 + (size_t)g * 8;
-                uint32_t ns[8], nb[8], W[8];
-                unsigned long long s1[8];
-                float D[8], S2[8];
-                group_accumulators(m, at, ns, nb, s1);
-                Store<ST>::get8(m, at, D, W, S2);
-                u = apply_group<ST>(m, at, ns, nb, s1, D, W, S2);
-                Store<ST>::put8(m, at, D, W, S2);
+                own = A.slot[j] * 64u + (uint32_t)g;
             } else {
                 const size_t at = (size_t)A.slot[j] * 64 + (size_t)g;
                 uint32_t ns, nb, W;
@@ -935,6 +929,31 @@ __device__ inline TaskOut apply_blocks(const DevMap& m, const u32x4 MRH_GLOBAL* 
                     Store<ST>::put(m, 1, at, D, W, S2);
                 }
             }
+        }
+        if (LEVEL == 0) {
+            // the lanes' groups, eight at a time with a lane per voxel; a group's sums back to its lane
+#pragma unroll 1
+            for (int r = 0; r < 8; r += kVoxelStep) {
+                if (base + 8u * (uint32_t)r >= total) break;
+                size_t at[kVoxelStep];
+                bool on[kVoxelStep];
+                UnitOut v[kVoxelStep];
+                for (int k = 0; k < kVoxelStep; ++k) {
+                    const uint32_t g = (uint32_t)__shfl((int)own, 8 * (r + k) + (lane >> 3));
+                    on[k] = g != kInvalidId;
+                    at[k] = (size_t)g * 8 + (size_t)(lane & 7);
+                }
+                apply_voxels<ST>(m, at, on, false, v);
+                for (int k = 0; k < kVoxelStep; ++k) {
+                    const int from = (lane & 7) * 8;
+                    const double d = __shfl(group8_sum(v[k].dsum), from);
+                    const int c = __shfl(group8_sum(v[k].dcnt), from), o = __shfl(group8_sum(v[k].nobs), from);
+                    const int e = __shfl(group8_sum(v[k].distinct), from);
+                    if ((lane >> 3) == r + k) u.dsum = d, u.dcnt = c, u.nobs = o, u.distinct = e;
+                }
+            }
+        }
+        if (act) {
             atomicAdd(&A.dcnt[j], u.dcnt);
             atomicAdd(&A.nobs[j], u.nobs);
         }
