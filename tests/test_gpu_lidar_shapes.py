@@ -1,0 +1,136 @@
+"""LiDAR fusion and queries where their kernels split the work: rays along and exactly on the block
+lattice, scans at the edges of a workgroup's rays, scans whose band counts need words of their own,
+queries and frames at the edges of a workgroup.  Against the oracle, exactly for counts and
+discrete decisions (both sides decide them in FP64 by the same expressions)."""
+import numpy as np
+import pytest
+import torch
+
+from parity_util import announce, compare_maps, excused_keys, gpu_sorted
+from workloads import configs, room_sequence
+
+pytestmark = pytest.mark.gpu
+
+CFG = dict(voxel=0.05, levels=4, tau=0.15, var_thr=0.025 ** 2, min_obs=2, min_range=0.5, max_range=80.0, carve=True,
+           max_blocks=1 << 16, hash_slots=1 << 17)
+
+
+@pytest.fixture(scope="module")
+def mrh():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2511_21459_amd as mrh
+
+    return mrh
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _scans_match(mrh, orc, cfg, scans):
+    g = mrh.Map(**cfg)
+    o = orc.OracleMap(**configs.oracle_kwargs(cfg))
+    merges = 0
+    for k, (pts, T) in enumerate(scans):
+        g.integrate_points(_dev(pts), T)
+        last, _ = g.sync()
+        st = o.integrate_points(pts, T)
+        for a, b in (("valid_points", "valid_points"), ("new_blocks", "new_blocks"), ("observations", "observations"),
+                     ("distinct_voxels", "distinct_voxels"), ("candidate_keys", "candidate_keys"),
+                     ("queued_blocks", "touched_blocks")):
+            assert last[a] == st[b], (k, a)
+        merges += sum(st["merges"])
+    print(compare_maps(gpu_sorted(g), o.extract(), excused=excused_keys(o), tau=cfg["tau"]), "merges", merges)
+    return merges
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33, 129])
+@pytest.mark.parametrize("origin", [0.0, 0.4, 0.025])
+def test_rays_on_the_lattice(mrh, orc, n, origin):
+    """Axis-parallel and diagonal rays from an origin on a block corner (0, 0.4: ties on every step) and
+    on a voxel centre, with ends on corners and off them; four scans, so that blocks merge."""
+    announce(f"lattice rays n={n} origin={origin}")
+    dirs = np.array([[1, 0, 0], [0, -1, 0], [0, 0, 1], [1, 1, 0], [-1, 0, 1], [0, 1, -1], [1, 1, 1], [-1, -1, 1], [1, -2, 3],
+                     [0.3, 0.7, -0.2], [-1, 0, 0], [0, 1, 0], [0, 0, -1]])
+    reach = np.array([0.8, 1.2, 2.0, 4.4, 0.9375, 3.1])
+    k = np.arange(n)
+    pts = (dirs[k % len(dirs)] * reach[k // 3 % len(reach)][:, None]).astype(np.float32)
+    T = np.eye(4)
+    T[:3, 3] = origin
+    _scans_match(mrh, orc, CFG, [(pts, T)] * 4)
+
+
+@pytest.mark.parametrize("n", [0, 1, 255, 4099])
+def test_scan_sizes(mrh, orc, n):
+    """Scans in general position of few and many rays, the table and touched lists of their workgroups
+    full and nearly empty; moving, so that new, merging and merged blocks are updated together."""
+    announce(f"scan of {n} rays")
+    rng = np.random.default_rng(n)
+    d = rng.normal(size=(n, 3))
+    pts = (d / np.maximum(np.linalg.norm(d, axis=1, keepdims=True), 1e-9) * rng.uniform(1.0, 12.0, (n, 1))).astype(np.float32)
+    scans = []
+    for k in range(5):
+        T = np.eye(4)
+        T[:3, 3] = [0.03 + 0.11 * k, 0.02, -0.01]
+        scans.append((pts, T))
+    merges = _scans_match(mrh, orc, CFG, scans)
+    assert n < 1000 or merges > 50
+
+
+def test_counts_apart(mrh, orc):
+    """A scan whose sums could outgrow the word they share with the count (rays x truncation), between
+    scans that fit it, on one map."""
+    announce("wide band counts")
+    cfg = dict(CFG, voxel=0.5, tau=4.0, min_range=1.0, max_range=400.0, var_thr=0.01, carve=False)
+    rng = np.random.default_rng(3)
+    scans = []
+    for k, n in enumerate((500, 140000, 700)):  # 140000 x 2 x 4 m x 2^24 > 2^44
+        d = rng.normal(size=(n, 3))
+        pts = (d / np.linalg.norm(d, axis=1, keepdims=True) * rng.uniform(20.0, 30.0, (n, 1))).astype(np.float32)
+        T = np.eye(4)
+        T[:3, 3] = [0.1, 0.2 * k, 0.3]
+        scans.append((pts, T))
+    _scans_match(mrh, orc, cfg, scans)
+
+
+@pytest.mark.parametrize("size", [(1, 1), (16, 16), (17, 33)])
+def test_frames_of_few_workgroups(mrh, orc, size):
+    """Frames of one and a few tiles: the hand-off between frames is shared by few workgroups."""
+    w, h = size
+    announce(f"room {w}x{h} x6 frames")
+    depths, cam, poses, _ = room_sequence(width=w, height=h, f=0.82 * w, frames=[0, 1, 2, 3, 4, 5])
+    cfg = dict(configs.ROOM, max_blocks=1 << 14, hash_slots=1 << 15)
+    g = mrh.Map(**cfg)
+    o = orc.OracleMap(**configs.oracle_kwargs(cfg))
+    for k in range(len(depths)):
+        g.integrate_depth(_dev(depths[k]), cam.K, poses[k])
+        last, _ = g.sync()
+        st = o.integrate_depth(depths[k], cam.K, poses[k])
+        for a in ("valid_points", "new_blocks", "observations", "distinct_voxels", "candidate_keys"):
+            assert last[a] == st[a], (k, a)
+    print(compare_maps(gpu_sorted(g), o.extract(), excused=excused_keys(o), tau=cfg["tau"]))
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("strict", [False, True])
+def test_query_group_edges(mrh, storage, strict):
+    """Queries of n points equal the first n of a long one, for n at the edges of a workgroup's 64 points."""
+    announce(f"query edges {storage} strict={strict}")
+    depths, cam, poses, _ = room_sequence(width=160, height=120, f=131.0, frames=[0, 5, 10, 15])
+    m = mrh.Map(**dict(configs.ROOM, max_blocks=1 << 15, hash_slots=1 << 16, storage=storage))
+    for k in range(len(depths)):
+        m.integrate_depth(_dev(depths[k]), cam.K, poses[k])
+    e = m.extract(voxels=False)
+    keys = e["keys"].cpu().numpy()
+    rng = np.random.default_rng(2)
+    pts = _dev(((keys[rng.integers(0, len(keys), 700)] + rng.random((700, 3))) * 8 * configs.ROOM["voxel"]).astype(np.float32))
+    T = np.eye(4)
+    T[:3, 3] = [0.003, -0.002, 0.001]
+    for grad in (False, True):
+        full = m.query(pts, T=T, strict=strict, with_grad=grad)
+        assert 20 < int(full[1].sum()) < 700
+        for n in (0, 1, 63, 64, 65, 129):
+            part = m.query(pts[:n].contiguous(), T=T, strict=strict, with_grad=grad)
+            for a, b in zip(part, full):
+                if a is not None:
+                    assert torch.equal(a, b[:n]), (n, grad)
