@@ -89,14 +89,6 @@ struct Store<MRH_STORE_F32> {
         s2(m, lvl)[i] = S2;
     }
     __device__ static inline void round(const DevMap&, float&, uint32_t&, float&) {}
-    __device__ static inline uint32_t getW(const DevMap& m, int lvl, size_t i) { return dw(m, lvl)[i].y; }
-    // the weights of 8 consecutive level-0 voxels starting at base (a multiple of 8)
-    __device__ static inline void getW8(const DevMap& m, size_t base, uint32_t W[8]) {
-        for (int k = 0; k < 4; ++k) {
-            const u32x4 v = load_as<u32x4>(dw(m, 0) + base + 2 * k);
-            W[2 * k] = v.y, W[2 * k + 1] = v.w;
-        }
-    }
     // 8 consecutive level-0 voxels starting at base (a multiple of 8)
     __device__ static inline void get8(const DevMap& m, size_t base, float D[8], uint32_t W[8], float S2[8]) {
         u32x4 v[4];
@@ -178,7 +170,6 @@ struct Store16 {
         dw(m, lvl)[i] = (uint32_t)encD(m, D) | ((uint32_t)wb << 16);
         s2(m, lvl)[i] = encS2(m, S2, decW(wb));
     }
-    __device__ static inline uint32_t getW(const DevMap& m, int lvl, size_t i) { return decW((uint16_t)(dw(m, lvl)[i] >> 16)); }
     __device__ static inline void unpack8(u32x4 v, uint16_t o[8]) {
         o[0] = (uint16_t)v.x, o[1] = (uint16_t)(v.x >> 16), o[2] = (uint16_t)v.y, o[3] = (uint16_t)(v.y >> 16);
         o[4] = (uint16_t)v.z, o[5] = (uint16_t)(v.z >> 16), o[6] = (uint16_t)v.w, o[7] = (uint16_t)(v.w >> 16);
@@ -186,11 +177,6 @@ struct Store16 {
     __device__ static inline u32x4 pack8(const uint16_t o[8]) {
         return u32x4{(uint32_t)o[0] | ((uint32_t)o[1] << 16), (uint32_t)o[2] | ((uint32_t)o[3] << 16),
                           (uint32_t)o[4] | ((uint32_t)o[5] << 16), (uint32_t)o[6] | ((uint32_t)o[7] << 16)};
-    }
-    __device__ static inline void getW8(const DevMap& m, size_t base, uint32_t W[8]) {
-        const u32x4 a = load_as<u32x4>(dw(m, 0) + base), b = load_as<u32x4>(dw(m, 0) + base + 4);
-        const uint32_t v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-        for (int q = 0; q < 8; ++q) W[q] = decW((uint16_t)(v[q] >> 16));
     }
     __device__ static inline void get8(const DevMap& m, size_t base, float D[8], uint32_t W[8], float S2[8]) {
         const u32x4 a = load_as<u32x4>(dw(m, 0) + base), b = load_as<u32x4>(dw(m, 0) + base + 4);

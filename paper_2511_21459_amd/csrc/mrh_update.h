@@ -311,10 +311,10 @@ __device__ inline int finish_fine(const DevMap& m, uint32_t id, uint32_t info, f
 
 // End of a level-1 block's update (lane = Morton position).  The 8 children of a coarse voxel are
 // 8 consecutive lanes.  Returns 1 when the block merged.
-template <int ST, bool DEFER = false>
+template <int ST>
 __device__ inline int finish_coarse(const DevMap& m, uint32_t id, uint32_t info, int level, float D, uint32_t W,
-                                     float S2, bool dirty, int nupd, double dsum, int dcnt, double bvs, uint32_t bvc,
-                                     int par, DeferList* dl = nullptr) {
+                                    float S2, bool dirty, int nupd, double dsum, int dcnt, double bvs, uint32_t bvc,
+                                    int par) {
     const int lane = lane_id();
     const int side = 8 >> level, nv = side * side * side;
     const uint32_t slot = info & kSlotMask;
@@ -324,10 +324,6 @@ __device__ inline int finish_coarse(const DevMap& m, uint32_t id, uint32_t info,
     const double vsum = bvs + dsum;
     const uint32_t vcnt = bvc + (uint32_t)dcnt;
     bool merge = nupd > 0 && level < m.levels - 1 && vcnt > 0 && vsum / (double)vcnt < m.var_thr;
-    if (DEFER && merge) {  // level 1 only: run_deferred pools level-1 blocks
-        dl->add(id, info);
-        merge = false;
-    }
     int64_t cslot = -1;
     if (merge) {
         if (lane == 0) cslot = pop_slot(m, level + 1);
@@ -484,22 +480,6 @@ __device__ inline void flush_task_stats(const DevMap& m, const TaskStats& ts, bo
         stat_add(m, S_MERGE0, ts.merge0);
         stat_add(m, S_MERGE1, ts.merge1);
         stat_add(m, S_MERGE2, ts.merge2);
-    }
-}
-
-// Queue block `id` for this frame's update on the list of its level (lanes with level < 0 queue
-// nothing).  Called by every lane of the wave; one atomic per level per wave.
-__device__ inline void queue_block(const DevMap& m, int level, uint32_t id, uint32_t info, unsigned long long key,
-                                   int par) {
-    const int lane = lane_id();
-    for (int lv = 0; lv < 4; ++lv) {
-        const unsigned long long msk = __ballot(level == lv);
-        if (!msk) continue;
-        const int f0 = __ffsll((long long)msk) - 1;
-        uint32_t vb = 0;
-        if (lane == f0) vb = atomicAdd(&m.ctr->vis_n[par][lv].v, (uint32_t)__popcll(msk));
-        vb = (uint32_t)__shfl((int)vb, f0);
-        if (level == lv) m.vis[lv][vb + rank_in_mask(msk)] = make_entry(id, info, key);
     }
 }
 

@@ -97,11 +97,15 @@ __device__ inline void copy_planes(const DevMap& m, int level, uint32_t slot, T*
     const int nv = 1 << (3 * (3 - level));
     T MRH_GLOBAL* dw = (T MRH_GLOBAL*)m.DW[level] + (size_t)slot * (2 * nv);
     T MRH_GLOBAL* s2 = (T MRH_GLOBAL*)m.S2[level] + (size_t)slot * nv;
-    for (int v = lane_id(); v < 3 * nv; v += 64) {
-        T MRH_GLOBAL& h = v < 2 * nv ? dw[v] : s2[v - 2 * nv];
-        if (to_heap) h = buf[v];
-        else buf[v] = h;
-    }
+    auto copy = [&](T MRH_GLOBAL* heap, T* at, int n) {
+#pragma unroll 8
+        for (int v = lane_id(); v < n; v += 64) {
+            if (to_heap) heap[v] = at[v];
+            else at[v] = heap[v];
+        }
+    };
+    copy(dw, buf, 2 * nv);
+    copy(s2, buf + 2 * nv, nv);
 }
 
 // Copy one level's selected blocks out (one wave per block: the planes in the storage
@@ -142,18 +146,20 @@ __global__ __launch_bounds__(256) void k_stream_in(const DevMap* __restrict__ pm
                                                    const uint8_t* __restrict__ payload, const double* __restrict__ vsum,
                                                    const uint32_t* __restrict__ vcnt, int sums, uint32_t* result) {
     const DevMap& m = *pm;
+    __shared__ uint32_t taken, first_id;
+    __shared__ int32_t first_top;
     const uint32_t e = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    if (e >= n) return;
     const int lane = lane_id();
-    const unsigned long long key = keys[e];
-    uint32_t id = kInvalidId, slot = 0;
-    if (lane == 0) {
+    uint32_t id = kInvalidId, slot = 0, h = 0, rank = 0;
+    uint32_t outcome = 0;  // 1 restored, 2 key present, 3 table full, 4 block limit, 5 heap full
+    if (threadIdx.x == 0) taken = 0u;
+    __syncthreads();
+    const unsigned long long key = e < n ? keys[e] : 0ull;
+    if (lane == 0 && e < n) {
         uint32_t stop = kInvalidId;
-        uint32_t outcome = 0;  // 1 restored, 2 key present, 3 table full, 4 block limit, 5 heap full
         if (probe_find(m, key, &stop) != kInvalidId) {
             outcome = 2;
         } else {
-            uint32_t h = 0;
             const int ins = stop == kInvalidId ? INS_FULL : probe_insert(m, key, stop, &h);
             if (ins == INS_FOUND) {
                 outcome = 2;
@@ -161,31 +167,43 @@ __global__ __launch_bounds__(256) void k_stream_in(const DevMap* __restrict__ pm
                 outcome = 3;
                 atomicOr(&m.ctr->error_flags.v, kErrTableFull);
             } else {
-                id = (uint32_t)atomicAdd(reinterpret_cast<unsigned long long MRH_GLOBAL*>(&m.ctr->n_blocks), 1ull);
-                const int32_t t = atomicSub(&m.ctr->top[level].v, 1);
-                if (id >= m.max_blocks) {
-                    m.table[h].id = kInvalidId;
-                    m.table[h].info = kNoBlockBit;
-                    atomicOr(&m.ctr->error_flags.v, kErrBlockLimit);
-                    if (t > 0) atomicAdd(&m.ctr->top[level].v, 1);
-                    outcome = 4;
-                    id = kInvalidId;
-                } else if (t <= 0) {
+                outcome = 1;
+                rank = atomicAdd(&taken, 1u);
+            }
+        }
+    }
+    // ids and slots for the workgroup's new keys with one atomic each: the counters are two addresses
+    __syncthreads();
+    if (threadIdx.x == 0 && taken) {
+        first_id = (uint32_t)atomicAdd(reinterpret_cast<unsigned long long MRH_GLOBAL*>(&m.ctr->n_blocks), (unsigned long long)taken);
+        first_top = atomicSub(&m.ctr->top[level].v, (int32_t)taken);
+    }
+    __syncthreads();
+    if (e >= n) return;
+    if (lane == 0) {
+        if (outcome == 1) {
+            id = first_id + rank;
+            const int32_t t = first_top - (int32_t)rank;
+            if (id >= m.max_blocks) {
+                m.table[h].id = kInvalidId;
+                m.table[h].info = kNoBlockBit;
+                atomicOr(&m.ctr->error_flags.v, kErrBlockLimit);
+                if (t > 0) atomicAdd(&m.ctr->top[level].v, 1);
+                outcome = 4;
+                id = kInvalidId;
+            } else {
+                m.bkey[id] = key;
+                m.bslot[id] = h;
+                m.table[h].id = id;
+                if (t <= 0) {
                     atomicAdd(&m.ctr->top[level].v, 1);
                     atomicOr(&m.ctr->error_flags.v, kErrHeapFull);
-                    m.bkey[id] = key;
-                    m.bslot[id] = h;
-                    m.table[h].id = id;
                     set_row(m, id, h, kNoBlockBit);
                     outcome = 5;
                     id = kInvalidId;
                 } else {
                     slot = m.stack[level][t - 1];
-                    m.bkey[id] = key;
-                    m.bslot[id] = h;
-                    m.table[h].id = id;
                     if (m.btouch) m.btouch[id] = 0ull;
-                    outcome = 1;
                 }
             }
         }
@@ -221,7 +239,7 @@ __global__ __launch_bounds__(256) void k_stream_in(const DevMap* __restrict__ pm
     if (lane == 0) {
         m.bvsum[id] = s;
         m.bvcnt[id] = c;
-        set_row(m, id, m.bslot[id], slot | ((uint32_t)level << kLevelShift));
+        set_row(m, id, h, slot | ((uint32_t)level << kLevelShift));
     }
 }
 
