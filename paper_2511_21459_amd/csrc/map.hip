@@ -281,6 +281,8 @@ static void free_all(mrh_map* m) {
     if (m->tile_max) (void)hipFree(m->tile_max);
     for (int n = 0; n < 4; ++n)
         if (d.vis[n]) (void)hipFree(plain(d.vis[n]));
+    for (int n = 0; n < 2; ++n)
+        if (d.vrect[n]) (void)hipFree(plain(d.vrect[n]));
     for (int n = 0; n < 4; ++n) {
         void* lp[] = {plain(d.stack[n]), plain(d.pend[n]), plain(d.DW[n]), plain(d.S2[n]), plain(d.C[n]), plain(d.acc_sat[n]), plain(d.acc_band[n]), plain(d.acc_s1[n]), plain(d.acc_s2[n])};
         for (void* p : lp)
@@ -352,6 +354,7 @@ mrh_status mrh_map_create(const mrh_config* cfg, void* stream, mrh_map** out) {
     alloc(&d.bvcnt, nb * 4, "block variance counts");
     alloc(&m->ctr, sizeof(DevCounters), "counters");
     for (int n = 0; n < c.levels; ++n) alloc(&d.vis[n], nb * 16, "visible-block lists");
+    for (int n = 0; n < c.levels && n < 2; ++n) alloc(&d.vrect[n], nb * 16, "visible-block lists");
     for (int n = 0; n < c.levels; ++n) {
         const int64_t cap = c.heap_blocks[n] > 0 ? c.heap_blocks[n] : c.max_blocks;
         d.heap_cap[n] = (int32_t)cap;

@@ -173,6 +173,7 @@ struct DevMap {
     uint32_t MRH_GLOBAL* rcount;
     int32_t rcap_k;
     u32x4 MRH_GLOBAL* vis[4];     // per level: the blocks the update visits this frame, (id, info, key lo, key hi)
+    u32x4 MRH_GLOBAL* vrect[2];   // levels 0 and 1, RGB-D: the queued blocks' screen rectangles
     double B, invB;
     double nu[4], inv_nu[4];
     double tau, var_thr;

@@ -570,7 +570,7 @@ __device__ inline uint32_t duty_parts(uint32_t count) { return count < kDutyPart
 // thread of the workgroup (a barrier inside): positions come from LDS counters and one global
 // atomic per level per workgroup, since same-address device atomics serialise chip-wide.
 __device__ inline void queue_block_wg(const DevMap& m, int level, uint32_t id, uint32_t info, unsigned long long key,
-                                      int par) {
+                                      const u32x4& rect, int par) {
     __shared__ uint32_t lcnt[4], lbase[4];
     if (threadIdx.x < 4) lcnt[threadIdx.x] = 0;
     __syncthreads();
@@ -580,7 +580,10 @@ __device__ inline void queue_block_wg(const DevMap& m, int level, uint32_t id, u
     if (threadIdx.x < 4 && lcnt[threadIdx.x])
         lbase[threadIdx.x] = atomicAdd(&m.ctr->vis_n[par][threadIdx.x].v, lcnt[threadIdx.x]);
     __syncthreads();
-    if (level >= 0) m.vis[level][lbase[level] + local] = make_entry(id, info, key);
+    if (level < 0) return;
+    const uint32_t at = lbase[level] + local;
+    m.vis[level][at] = make_entry(id, info, key);
+    if (level < 2) m.vrect[level][at] = rect;
 }
 
 // The block table entry of a new key that took hash slot `slot`: block id `id` and, as the
