@@ -54,10 +54,7 @@ bool make_depth_frame(const mrh_config& cfg, const float* depth, int32_t width, 
     f.width = width;
     f.height = height;
     f.depth = global(depth);
-    f.fxf = (float)f.fx;
-    f.fyf = (float)f.fy;
-    f.cxf = (float)f.cx;
-    f.cyf = (float)f.cy;
+    f.pixel_lim = 0.5 - 1e-12 * ((double)std::max(width, height) + std::fabs(f.cx) + std::fabs(f.cy) + 16.0);
     // side planes of the pixel frustum u in [-1/2, W - 1/2), v in [-1/2, H - 1/2) (camera frame),
     // and the largest ray length factor over the image for the range bound
     const double al = (-0.5 - f.cx) / f.fx, ar = ((double)width - 0.5 - f.cx) / f.fx;

@@ -21,7 +21,7 @@ struct DepthFrame {
     double fx, fy, cx, cy, ifx, ify;
     int32_t width, height;
     const float MRH_GLOBAL* depth;  // device z-depth image, row-major
-    float fxf, fyf, cxf, cyf;  // intrinsics rounded to FP32 for the fast projection
+    double pixel_lim;  // 1/2 less the fast projection's margin
     // conservative culling of whole blocks (camera frame): side-plane normals and a range bound
     double plane[4][3];
     double cull_range;
@@ -56,26 +56,28 @@ __device__ inline int pixel_exact(const DepthFrame& f, double x0, double x1, dou
     return (int)fv * f.width + (int)fu;
 }
 
-// The same decision from the FP32 evaluation, taken only when it lies farther from a pixel boundary
-// than its error can reach; returns -2 when it cannot decide.  Error budget of the FP32 u from FP64
-// x: the roundings of x0, x2, fx, cx, the product and the sum (2^-24 relative each) and the hardware
-// reciprocal (1 ulp) stay below 6e-7 (|u| + |cx|), under the margin 1e-6 (|u| + |cx| + 16).  `lam`
-// receives |x| / x2 in FP32 for the range form (of use where a pixel is returned).  Straight-line code, as
-// observe_form and the update of a group: a launch issues three quarter million branches and as many mask
-// operations for what they skip (with the grid below 29.1 -> 26.7 us).
+// The same decision with the division replaced: the hardware's FP32 reciprocal and one Newton step in FP64
+// (relative error below 2^-44; FP64 issues at the FP32 rate here), taken only when u and v lie farther from
+// a pixel boundary than the error can reach.  Returns -2 when it cannot decide.  The products, sums and the
+// rounding of uu + 1/2 in the exact form stay below 1e-13 (|u| + |cx|) together with it, under the margin
+// 1e-12 (larger side + |cx| + |cy| + 16) for every pixel of the image; a voxel beyond it whose error is larger is
+// beyond it either way.  An FP32 evaluation left a voxel in 250 undecided, two per block, each
+// with the exact form's divisions for the whole wave, and took more instructions for its margins (640 x 480
+// room frames: update 24.8 -> 23.3 us).  `lam` receives |x| / x2 in FP32 for the range form (of use where a
+// pixel is returned).  Straight-line code, as
+// observe_form and the update of a group: a launch issued three quarter million branches and as many mask
+// operations for what they skipped (with the grid below 29.1 -> 26.7 us).
 __device__ inline int pixel_fast(const DepthFrame& f, double x0, double x1, double x2, float& lam) {
     const float xf0 = (float)x0, xf1 = (float)x1, xf2 = (float)x2;
     const float izf = __builtin_amdgcn_rcpf(xf2);
     lam = __builtin_amdgcn_sqrtf((xf0 * xf0 + xf1 * xf1) + xf2 * xf2) * izf;
-    const float uf = f.fxf * (xf0 * izf) + f.cxf;
-    const float vf = f.fyf * (xf1 * izf) + f.cyf;
-    const float su = uf + 0.5f, sv = vf + 0.5f;
-    const float fu = __builtin_floorf(su), fv = __builtin_floorf(sv);
-    const float du = __builtin_fminf(su - fu, fu + 1.0f - su), dv = __builtin_fminf(sv - fv, fv + 1.0f - sv);
-    const float eu = 1e-6f * (__builtin_fabsf(uf) + __builtin_fabsf(f.cxf) + 16.0f);
-    const float ev = 1e-6f * (__builtin_fabsf(vf) + __builtin_fabsf(f.cyf) + 16.0f);
-    const bool sure = (xf2 > 1e-6f) & (du > eu) & (dv > ev);
+    const double r = (double)izf;
+    const double iz = __builtin_fma(r, __builtin_fma(-x2, r, 1.0), r);
+    const double u = __builtin_fma(f.fx, x0 * iz, f.cx), v = __builtin_fma(f.fy, x1 * iz, f.cy);
+    const double ru = __builtin_rint(u), rv = __builtin_rint(v);  // (ties are within the margin)
+    const bool sure = (xf2 > 1e-6f) & (__builtin_fabs(u - ru) < f.pixel_lim) & (__builtin_fabs(v - rv) < f.pixel_lim);
     // clamped to the image, so that the conversions are defined
+    const float fu = (float)ru, fv = (float)rv;
     const float cu = __builtin_amdgcn_fmed3f(fu, 0.0f, (float)(f.width - 1)), cv = __builtin_amdgcn_fmed3f(fv, 0.0f, (float)(f.height - 1));
     const int p = __mul24((int)cv, f.width) + (int)cu;
     const int in = ((cu == fu) & (cv == fv)) ? p : -1;
@@ -350,19 +352,22 @@ __device__ inline uint32_t fine_decisions(const DevMap& m, const DepthFrame& f, 
             pz[s][r] = f.P.R[2][r] * dz;
         }
     }
-    // pixels first (FP64 only where FP32 cannot decide), then all depth loads at once, then the
-    // observations; x recomputed by voxel_camera equals these sums bit for bit (same products, same
+    // pixels first (the exact form only where the fast one cannot decide), then all depth loads at once, then
+    // the observations; x recomputed by voxel_camera equals these sums bit for bit (same products, same
     // order, no contraction)
     float lam[8];
     uint32_t exact = 0;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int a = q & 1, b = (q >> 1) & 1, c = (q >> 2) & 1;
-        const double x0 = (px[a][0] + py[b][0]) + pz[c][0];
-        const double x1 = (px[a][1] + py[b][1]) + pz[c][1];
-        const double x2 = (px[a][2] + py[b][2]) + pz[c][2];
-        pix[q] = pixel_fast(f, x0, x1, x2, lam[q]);
-        exact |= (pix[q] == -2 ? 1u : 0u) << q;
+    for (int ab = 0; ab < 4; ++ab) {  // (a pair of voxels shares the sum of two of its axes)
+        const int a = ab & 1, b = ab >> 1;
+        const double s0 = px[a][0] + py[b][0], s1 = px[a][1] + py[b][1], s2 = px[a][2] + py[b][2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int q = ab + 4 * c;
+            pix[q] = pixel_fast(f, s0 + pz[c][0], s1 + pz[c][1], s2 + pz[c][2], lam[q]);
+            exact |= (pix[q] == -2 ? 1u : 0u) << q;
+            asm volatile("" : "+v"(lam[q]));  // here, not where it is used: it holds one register, its operands four
+        }
     }
     for (uint32_t amb = exact; amb;) {
         const int q = __builtin_ctz(amb);

@@ -536,3 +536,29 @@ def test_sequence_entry_points_equal_frame_calls(mrh):
     e.integrate_points_sequence(x, np.ascontiguousarray(sposes))
     gc, ge = gpu_sorted(c), gpu_sorted(e)
     assert np.array_equal(gc.keys, ge.keys) and np.array_equal(gc.D, ge.D) and np.array_equal(gc.W, ge.W)
+
+
+@pytest.mark.parametrize("form", ["range", "zdiff"])
+@pytest.mark.parametrize("shift", [0.5, 0.5 - 2.0 ** -40, 0.25])
+def test_pixel_boundaries(mrh, orc, form, shift):
+    """Voxel centres that project exactly on pixel boundaries (dyadic sizes and pose), next to them by less
+    than the fast projection's margin, and off them: every decision is the canonical one."""
+    announce(f"pixel boundaries {form} shift {shift}")
+    cfg = dict(voxel=1.0 / 32, levels=2, tau=3.0 / 32, var_thr=1e-6, min_obs=2, max_depth=5.0, form=form,
+               max_blocks=1 << 13, hash_slots=1 << 14)
+    g = mrh.Map(**cfg)
+    o = orc.OracleMap(**configs.oracle_kwargs(cfg))
+    K = (32.0, 32.0, 15.5, 11.5)
+    T = np.eye(4)
+    T[:3, 3] = shift / 32
+    rng = np.random.default_rng(5)
+    depth = np.where(rng.random((24, 32)) < 0.5, 1.0, 2.0).astype(np.float32)
+    depth[3:6, 4:9] = 0.0
+    for k in range(3):
+        g.integrate_depth(_dev(depth), K, T)
+        last, _ = g.sync()
+        st = o.integrate_depth(depth, K, T)
+        for a in ("valid_points", "new_blocks", "observations", "distinct_voxels", "candidate_keys"):
+            assert last[a] == st[a], (k, a)
+    assert o.num_blocks > 50
+    print(compare_maps(gpu_sorted(g), o.extract(), excused=excused_keys(o), tau=cfg["tau"]))
