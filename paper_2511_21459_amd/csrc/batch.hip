@@ -5,14 +5,14 @@
 //
 //   k_batch_alloc     workgroup ranges per map: depth maps get their pixel tiles then their cull
 //                     workgroups, LiDAR maps one workgroup per kAllocRaysPerGroup rays; a map's
-//                     last workgroup also runs its allocation-side hand-off
+//                     last workgroups also run its allocation-side hand-off
 //   k_batch_rays      LiDAR maps: one workgroup per kRaysPerGroup rays (their recorded (ray, block)
 //                     pairs in parallel: traversal and accumulation)
 //   k_batch_touch     LiDAR maps: the blocks the rays touched onto the map's update queues
 //   k_batch_update    the update tasks of every map of one frame kind (RGB-D or LiDAR: one launch
 //                     per kind present, so that each gets the registers of its own path), strided
-//                     over the concatenated task space; workgroup i also runs the update-side
-//                     hand-off of map i when map i is of that kind
+//                     over the concatenated task space; the workgroups also share the update-side
+//                     hand-offs of the maps of that kind
 #include <algorithm>
 #include <cmath>
 #include <cstring>

@@ -1,8 +1,9 @@
 // RGB-D fusion of one map (Sec. 3.1 "Cameras", Eq. 2; Eq. 3, Eq. 5; Sec. 3.2.1).
 //
 // One frame is two launches on the map's stream: k_alloc_depth (pixel tiles, then cull
-// workgroups; the last one also runs the allocation-side frame hand-off) and k_integrate_depth
-// (update tasks over the per-level queues; workgroup 0 also runs the update-side hand-off).
+// workgroups; the last ones also run the allocation-side frame hand-off) and k_integrate_depth
+// (update tasks over the per-level queues, colours included; the first workgroups also run the
+// update-side hand-off).
 #include <algorithm>
 #include <cmath>
 #include <mutex>
@@ -10,7 +11,6 @@
 #include "mrh_depth.h"
 
 namespace mrh {
-
 
 // Frame sizes the kernels accept: pixel indices are 32-bit and pixel coordinates exact in FP32.
 bool depth_size_ok(int32_t width, int32_t height) {

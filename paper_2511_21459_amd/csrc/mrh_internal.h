@@ -9,6 +9,8 @@
 //   heaps        per level n: (D, W) pair and S2 planes of heap_blocks[n] blocks x (8 >> n)^3 voxels, voxels
 //                of a block in Morton (Z) order so the 2x2x2 children of a coarse voxel are
 //                contiguous; a free stack of slot indices and a pending-free list per level
+//   queues       per level the blocks a frame's update visits (vis), and for levels 0 and 1 of RGB-D
+//                frames their screen rectangles (vrect)
 //   counters     DevCounters (block count, stack tops, stats, latched error flags)
 #pragma once
 

@@ -4,7 +4,7 @@
 //   points_alloc_chunk  16 rays: validity, segment [o, p + tau n] (carving) or the band
 //                       [p - tau n, p + tau n], walk over the block lattice,
 //                       insert, and the record of the hash slots of each ray's blocks in walk order
-//   points_ray_chunk    32 rays: their recorded (ray, block) pairs in parallel; inside each block a
+//   points_ray_chunk    16 rays: their recorded (ray, block) pairs in parallel; inside each block a
 //                       walk over the block's own voxel lattice; each crossed voxel gets
 //                       clip((p - x) . n, -tau, tau).
 //                       Saturated observations (+tau) only bump an integer count; the others add
@@ -13,9 +13,10 @@
 //                       voxel's state; the update forms the sums of (d - D) and (d - D)^2 from them.
 //                       The touched lane groups of each block are marked
 //   queue_touched       the touched blocks onto their levels' update queues
-//   points_update_task  8 queued blocks of level 0, 1 or 2, or 64 of level 3, per wave: each voxel's scan statistics merge into its state (W' =
-//                       W + n, D' = D + s1 / W', S2' = S2 + s2 - s1^2 / W', the batch form of Eq. 3
-//                       and Eq. 5), then the block variance bookkeeping and the merging criterion
+//   points_update_task  8 queued blocks of level 0, 1 or 2, or 64 of level 3, per wave: each voxel's
+//                       scan statistics merge into its state (W' = W + n, D' = D + s1 / W',
+//                       S2' = S2 + s2 - s1^2 / W', the batch form of Eq. 3 and Eq. 5), then the
+//                       block variance bookkeeping and the merging criterion
 #pragma once
 
 #include "mrh_update.h"
@@ -583,7 +584,7 @@ __device__ inline void ray_fine_block(const DevMap& m, const double o[3], const 
 // blocks.  Reads and atomics are kept apart because a wave's memory operations complete in order: a
 // read issued behind the walk's atomics, performed beyond the L2, waits for them (which is also why
 // the touched groups are gathered in LDS).  131072 points, with the queueing launch: 493 -> 335 us on a
-// settled map, 1718 -> 1266 us into an empty one (34 M atomics at 27 G/s, the rate that bounds it).
+// settled map, 1718 -> 1220 us into an empty one (27 M atomics at 22 G/s, the rate that bounds it).
 // The blocks of a ray beyond the recorded rcap_k are walked afterwards by one thread per ray, through
 // the same two steps.
 __device__ inline void points_ray_chunk(const DevMap& m, const ScanParams& sp, uint32_t chunk, RayLds& L) {

@@ -1,15 +1,14 @@
 // LiDAR fusion of one map (Sec. 3.1 "3D Point Cloud", Eq. 1; Eq. 3, Eq. 5; Sec. 3.2.1).
 //
-// One scan is four launches on the map's stream: k_alloc_points (its last workgroup also runs the
+// One scan is four launches on the map's stream: k_alloc_points (its last workgroups also run the
 // allocation-side frame hand-off), k_rays, k_touch_queue (the touched blocks onto the per-level
-// update queues) and k_apply_points (update tasks over those queues; workgroup 0 also runs the
-// update-side hand-off).
+// update queues) and k_apply_points (update tasks over those queues; the first workgroups also run
+// the update-side hand-off).
 #include <cmath>
 
 #include "mrh_points.h"
 
 namespace mrh {
-
 
 __global__ __launch_bounds__(256) void k_alloc_points(const DevMap* __restrict__ pm, ScanParams sp) {
     const uint32_t parts = duty_parts(gridDim.x), part = gridDim.x - 1u - blockIdx.x;
