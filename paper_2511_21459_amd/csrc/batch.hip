@@ -384,6 +384,7 @@ mrh_status mrh_batch_integrate(mrh_batch* b, const mrh_frame* frames) {
                 return batch_err(b, MRH_ERR_INVALID_ARG, "batch: bad point frame");
             e.sp.xyz = global(f.data_dev);
             e.sp.n = f.n;
+            e.sp.rays = kRaysPerGroup;
             e.sp.parity = (int32_t)(b->maps[i]->frames & 1u);
             // at least one workgroup: it carries the map's allocation-side hand-off
             alloc_wgs += f.n > 0 ? (uint32_t)((f.n + kAllocRaysPerGroup - 1) / kAllocRaysPerGroup) : 1u;

@@ -4,7 +4,7 @@
 //   points_alloc_chunk  16 rays: validity, segment [o, p + tau n] (carving) or the band
 //                       [p - tau n, p + tau n], walk over the block lattice,
 //                       insert, and the record of the hash slots of each ray's blocks in walk order
-//   points_ray_chunk    16 rays: their recorded (ray, block) pairs in parallel; inside each block a
+//   points_ray_chunk    4 to 16 rays: their recorded (ray, block) pairs in parallel; inside each block a
 //                       walk over the block's own voxel lattice; each crossed voxel gets
 //                       clip((p - x) . n, -tau, tau).
 //                       Saturated observations (+tau) only bump an integer count; the others add
@@ -28,6 +28,7 @@ constexpr double kS2Scale = 281474976710656.0;  // 2^48 per square metre: the su
 
 struct ScanParams {
     int32_t parity;  // the frame's parity (selects the double-buffered per-frame counts)
+    int32_t rays;    // rays per workgroup of the ray launch (at most kGroupRays)
     Pose P;
     const float MRH_GLOBAL* xyz;  // device points, sensor frame, [n][3]
     int64_t n;
@@ -493,7 +494,7 @@ __device__ inline void touch_table_flush(const DevMap& m, const TouchTable& t) {
         if (t.id[k]) touch_block(m, t.id[k] - 1u, t.groups[k]);
 }
 
-// Rays per 256-thread workgroup of the ray launch, and the pairs it takes at a time.
+// Rays per 256-thread workgroup of the ray launch at most, and the pairs it takes at a time.
 constexpr int kRaysPerGroup = kGroupRays;
 constexpr int kRayUnroll = 3;
 constexpr int kRayRound = 256 * kRayUnroll;
@@ -575,7 +576,7 @@ __device__ inline void ray_fine_block(const DevMap& m, const double o[3], const 
     touch_table_add(m, L.touch, id, groups);
 }
 
-// Traversal and accumulation for rays chunk * kRaysPerGroup .. (all threads of the workgroup).  A
+// Traversal and accumulation for rays chunk * sp.rays .. (all threads of the workgroup).  A
 // ray's block walk is a serial chain of lookups, so the (ray, block) pairs that the allocation launch
 // recorded are processed in parallel instead, kRayRound at a time by the whole workgroup, in two
 // steps.  First each thread reads the hash slots of its pairs, all reads of a step together; a pair in a
@@ -589,9 +590,9 @@ __device__ inline void ray_fine_block(const DevMap& m, const double o[3], const 
 // the same two steps.
 __device__ inline void points_ray_chunk(const DevMap& m, const ScanParams& sp, uint32_t chunk, RayLds& L) {
     const int lane = lane_id(), tid = (int)threadIdx.x, wv = (int)uniform(threadIdx.x >> 6);
-    const int64_t r0 = (int64_t)chunk * kRaysPerGroup;
+    const int64_t r0 = (int64_t)chunk * sp.rays;
     const uint32_t K = (uint32_t)m.rcap_k;
-    const uint32_t cnt = (tid < kRaysPerGroup && r0 + tid < sp.n) ? m.rcount[r0 + tid] : 0u;
+    const uint32_t cnt = (tid < sp.rays && r0 + tid < sp.n) ? m.rcount[r0 + tid] : 0u;
     if (cnt > 0) {
         RaySegment s;
         point_segment(m, sp, r0 + tid, s.a, s.e, s.p, s.n);  // valid: the ray has recorded blocks

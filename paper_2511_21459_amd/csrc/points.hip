@@ -56,6 +56,12 @@ __global__ __launch_bounds__(256) void k_apply_points(const DevMap* __restrict__
     flush_task_stats(m, as, false);
 }
 
+// Rays per workgroup of a scan's ray launch.  The LDS tables gain from many rays, but below some eight
+// workgroups per CU the launch lasts as long as one of them: 8000 rays 190 us by 16, 146 by 4, 162 by 2; 31713
+// rays 366 by 16, 324 by 8, 349 by 4; 131072 rays 508 by 16, 522 by 8.  (A batch's scans share the chip:
+// always kRaysPerGroup.)
+static int32_t rays_per_group(int64_t n) { return n < (1 << 14) ? 4 : (n < (1 << 16) ? 8 : kRaysPerGroup); }
+
 // Blocks a ray's walk can visit: the guard of the block walk bounds it by 4 + the sum over the
 // axes of the cells the segment spans (carving: up to max_range + tau long; otherwise 2 tau).
 static int32_t ray_block_cap(const mrh_config& c) {
@@ -124,6 +130,7 @@ extern "C" mrh_status mrh_integrate_points(mrh_map* map, const float* xyz_dev, i
     if (!pose_from(T_ws, sp.P)) return set_error(map, MRH_ERR_INVALID_ARG, "non-finite pose");
     sp.xyz = global(xyz_dev);
     sp.n = n;
+    sp.rays = rays_per_group(n);
     mrh_status st = ensure_lidar(map, n);
     if (st != MRH_OK) return st;
     sp.parity = (int32_t)(map->frames & 1u);
@@ -134,7 +141,7 @@ extern "C" mrh_status mrh_integrate_points(mrh_map* map, const float* xyz_dev, i
     launch(map, K_ALLOC_POINTS,
            [&] { hipLaunchKernelGGL(k_alloc_points, dim3(agrid), dim3(256), 0, map->stream, map->dmd, sp); });
     if (n > 0) {
-        const unsigned rgrid = (unsigned)((n + kRaysPerGroup - 1) / kRaysPerGroup);
+        const unsigned rgrid = (unsigned)((n + sp.rays - 1) / sp.rays);
         launch(map, K_RAYS, [&] {
             hipLaunchKernelGGL(k_rays, dim3(rgrid), dim3(256), 0, map->stream, map->dmd, sp);
             hipLaunchKernelGGL(k_touch_queue, dim3(1024), dim3(256), 0, map->stream, map->dmd, par);

@@ -60,7 +60,7 @@ def test_rays_on_the_lattice(mrh, orc, n, origin):
     _scans_match(mrh, orc, CFG, [(pts, T)] * 4)
 
 
-@pytest.mark.parametrize("n", [0, 1, 255, 4099])
+@pytest.mark.parametrize("n", [0, 1, 255, 4099, 16385])
 def test_scan_sizes(mrh, orc, n):
     """Scans in general position of few and many rays, the table and touched lists of their workgroups
     full and nearly empty; moving, so that new, merging and merged blocks are updated together."""
@@ -73,7 +73,7 @@ def test_scan_sizes(mrh, orc, n):
         T = np.eye(4)
         T[:3, 3] = [0.03 + 0.11 * k, 0.02, -0.01]
         scans.append((pts, T))
-    merges = _scans_match(mrh, orc, CFG, scans)
+    merges = _scans_match(mrh, orc, dict(CFG, max_blocks=1 << 18, hash_slots=1 << 19), scans)
     assert n < 1000 or merges > 50
 
 
