@@ -28,7 +28,7 @@ constexpr double kS2Scale = 281474976710656.0;  // 2^48 per square metre: the su
 
 struct ScanParams {
     int32_t parity;  // the frame's parity (selects the double-buffered per-frame counts)
-    int32_t rays;    // rays per workgroup of the ray launch (at most kGroupRays)
+    int32_t rays;    // rays per workgroup (at most kGroupRays)
     Pose P;
     const float MRH_GLOBAL* xyz;  // device points, sensor frame, [n][3]
     int64_t n;
@@ -102,7 +102,7 @@ constexpr int kAllocUnroll = 2;
 constexpr int kAllocRound = 256 * kAllocUnroll;
 constexpr int kAllocNew = 512;  // new blocks a workgroup registers together
 
-// Allocation for rays chunk * kAllocRaysPerGroup ..: the blocks of each ray's walk, their
+// Allocation for rays chunk * sp.rays ..: the blocks of each ray's walk, their
 // insert, and the record of the hash slots of each ray's blocks in walk order.  The walk
 // takes the boundaries of the three axes in the order of their parameters, lowest axis on ties, so the
 // place of a boundary in it is its index plus the boundaries of the other two axes before it, and the
@@ -117,10 +117,10 @@ __device__ inline void points_alloc_chunk(const DevMap& m, const ScanParams& sp,
     __shared__ unsigned long long nkey[kAllocNew], nold;
     __shared__ uint32_t nslot[kAllocNew], ncount;
     const int lane = lane_id(), tid = (int)threadIdx.x;
-    const int64_t r0 = (int64_t)chunk * kAllocRaysPerGroup;
+    const int64_t r0 = (int64_t)chunk * sp.rays;
     if (tid < 64) {
         const int64_t i = r0 + lane;
-        const bool mine = lane < kAllocRaysPerGroup && i < sp.n;
+        const bool mine = lane < sp.rays && i < sp.n;
         double a[3], e[3], p[3], nn[3];
         const bool ok = mine && point_segment(m, sp, i, a, e, p, nn);
         const unsigned long long vmask = __ballot(ok);

@@ -56,10 +56,11 @@ __global__ __launch_bounds__(256) void k_apply_points(const DevMap* __restrict__
     flush_task_stats(m, as, false);
 }
 
-// Rays per workgroup of a scan's ray launch.  The LDS tables gain from many rays, but below some eight
-// workgroups per CU the launch lasts as long as one of them: 8000 rays 190 us by 16, 146 by 4, 162 by 2; 31713
-// rays 366 by 16, 324 by 8, 349 by 4; 131072 rays 508 by 16, 522 by 8.  (A batch's scans share the chip:
-// always kRaysPerGroup.)
+// Rays per workgroup of a scan's allocation and ray launches.  The ray launch's LDS tables gain from many rays,
+// but below some eight workgroups per CU a launch lasts as long as one of them.  Ray launch: 8000 rays 190 us by
+// 16, 146 by 4, 162 by 2; 31713 rays 366 by 16, 324 by 8, 349 by 4; 131072 rays 508 by 16, 522 by 8.
+// Allocation, mean of three scans: 8000 rays 63 us by 16, 49 by 4; 31713 rays 93 by 16, 85 by 8.  (A batch's
+// scans share the chip: always kRaysPerGroup.)
 static int32_t rays_per_group(int64_t n) { return n < (1 << 14) ? 4 : (n < (1 << 16) ? 8 : kRaysPerGroup); }
 
 // Blocks a ray's walk can visit: the guard of the block walk bounds it by 4 + the sum over the
@@ -137,7 +138,7 @@ extern "C" mrh_status mrh_integrate_points(mrh_map* map, const float* xyz_dev, i
     map->frames += 1;
     const int par = sp.parity;
     // the allocation and update launches always run (they carry the frame hand-off)
-    const unsigned agrid = n > 0 ? (unsigned)((n + kAllocRaysPerGroup - 1) / kAllocRaysPerGroup) : 1u;
+    const unsigned agrid = n > 0 ? (unsigned)((n + sp.rays - 1) / sp.rays) : 1u;
     launch(map, K_ALLOC_POINTS,
            [&] { hipLaunchKernelGGL(k_alloc_points, dim3(agrid), dim3(256), 0, map->stream, map->dmd, sp); });
     if (n > 0) {
