@@ -79,7 +79,7 @@ __device__ inline int pixel_fast(const DepthFrame& f, double x0, double x1, doub
     // clamped to the image, so that the conversions are defined
     const float fu = (float)ru, fv = (float)rv;
     const float cu = __builtin_amdgcn_fmed3f(fu, 0.0f, (float)(f.width - 1)), cv = __builtin_amdgcn_fmed3f(fv, 0.0f, (float)(f.height - 1));
-    const int p = __mul24((int)cv, f.width) + (int)cu;
+    const int p = (int)(__umul24((uint32_t)cv, (uint32_t)f.width) + (uint32_t)cu);  // (sides are below 2^24)
     const int in = ((cu == fu) & (cv == fv)) ? p : -1;
     return x2 > 0.0 ? (sure ? in : -2) : -1;
 }

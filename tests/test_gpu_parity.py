@@ -562,3 +562,30 @@ def test_pixel_boundaries(mrh, orc, form, shift):
             assert last[a] == st[a], (k, a)
     assert o.num_blocks > 50
     print(compare_maps(gpu_sorted(g), o.extract(), excused=excused_keys(o), tau=cfg["tau"]))
+
+
+@pytest.mark.parametrize("size", [((1 << 23) + 1, 2), ((1 << 24) - 1, 2), (2, (1 << 23) + 300)])
+def test_sides_from_2_to_the_23(mrh, orc, size):
+    """Frames with a side of 2^23 pixels and more (sides below 2^24 are accepted): valid depths in 140 pixels
+    near the far end of the long side, in both lines of the short one."""
+    w, h = size
+    announce(f"flat frame {w}x{h} x2")
+    cfg = dict(voxel=0.005, levels=3, tau=0.02, var_thr=0.004 ** 2, min_obs=2, max_depth=5.0, max_blocks=1 << 14,
+               hash_slots=1 << 15)
+    depth = np.zeros((h, w), np.float32)
+    rng = np.random.default_rng(4)
+    long = max(w, h)
+    sel = np.s_[:, long - 160:long - 20] if w > h else np.s_[long - 160:long - 20, :]
+    depth[sel] = rng.uniform(0.98, 1.02, depth[sel].shape)
+    K = (100.0, 100.0, long - 90.0 if w > h else 0.5, 0.5 if w > h else long - 90.0)
+    g = mrh.Map(**cfg)
+    o = orc.OracleMap(**configs.oracle_kwargs(cfg))
+    dev = _dev(depth)
+    for k in range(2):
+        g.integrate_depth(dev, K, np.eye(4))
+        last, _ = g.sync()
+        st = o.integrate_depth(depth, K, np.eye(4))
+        for a in ("valid_points", "new_blocks", "observations", "distinct_voxels", "candidate_keys"):
+            assert last[a] == st[a], (k, a)
+    assert st["valid_points"] == 280 and st["observations"] > 10000
+    print(compare_maps(gpu_sorted(g), o.extract(), excused=excused_keys(o), tau=cfg["tau"]))
