@@ -83,13 +83,14 @@ __global__ __launch_bounds__(256) void k_batch_rays(const DevMap* __restrict__ m
 }
 
 // After the ray launch: each LiDAR map's touched blocks onto its update queues, kBatchTouchWgs
-// workgroups per table entry (those of RGB-D entries return at once).
+// workgroups per table entry (those of RGB-D entries and of empty scans return at once: an empty scan
+// touches nothing, and its map may not have touch masks yet).
 constexpr uint32_t kBatchTouchWgs = 64;
 
 __global__ __launch_bounds__(256) void k_batch_touch(const DevMap* __restrict__ maps, const BatchEntry* __restrict__ ents,
                                                      int n) {
     const int i = (int)(blockIdx.x / kBatchTouchWgs);
-    if (i >= n || ents[i].kind != MRH_FRAME_POINTS) return;  // uniform across the workgroup
+    if (i >= n || ents[i].kind != MRH_FRAME_POINTS || ents[i].sp.n == 0) return;  // uniform across the workgroup
     const DevMap& m = maps[i];
     const uint32_t nb = min(m.ctr->n_blocks, m.max_blocks);
     const uint32_t per = blockDim.x * (uint32_t)kTouchPerThread;

@@ -267,3 +267,41 @@ def test_batch_full_size_streams(mrh):
             assert torch.equal(a, w)
         s.close()
         m.close()
+
+
+@pytest.mark.parametrize("graph", [True, False])
+def test_empty_scan_beside_a_full_one(mrh, graph):
+    """An empty scan of a map that holds blocks and never had a scan, in one step with another map's rays: the
+    first map stays as it is, the other equals its own fusion, with and without a graph."""
+    announce(f"batch: empty scan of a map without scans, graph={graph}")
+    cfg = dict(configs.STREET, max_blocks=1 << 14, hash_slots=1 << 15)
+    a, b, alone = mrh.Map(**cfg), mrh.Map(**cfg), mrh.Map(**cfg)
+    keys = np.stack(np.meshgrid(*[np.arange(13)] * 3), -1).reshape(-1, 3).astype(np.int32)
+    levels = (np.arange(len(keys)) % 4).astype(np.uint8)
+    nv = int(((8 >> levels.astype(int)) ** 3).sum())
+    assert a.load_blocks(keys, levels, np.full(nv, 0.1, np.float32), np.full(nv, 2, np.uint32), np.zeros(nv, np.float32)) == len(keys)
+    before = gpu_sorted(a)
+    rng = np.random.default_rng(2)
+    d = rng.normal(size=(700, 3))
+    pts = _dev((d / np.linalg.norm(d, axis=1, keepdims=True) * rng.uniform(2.0, 9.0, (700, 1))).astype(np.float32))
+    none = torch.zeros((0, 3), device="cuda")
+    T = np.eye(4)
+    batch = mrh.Batch([a, b])
+    batch.set_launch(256, 16, graph=graph)
+    for _ in range(3):
+        batch.integrate([("points", none, T), ("points", pts, T)])
+        alone.integrate_points(pts, T)
+    la, _ = a.sync()
+    assert la["valid_points"] == la["observations"] == la["queued_blocks"] == 0
+    for x, y in ((before, gpu_sorted(a)), (gpu_sorted(alone), gpu_sorted(b))):
+        for f in ("keys", "levels", "D", "W", "S2"):
+            assert np.array_equal(getattr(x, f), getattr(y, f)), f
+    # and with rays of its own afterwards
+    single = mrh.Map(**cfg)
+    single.load_blocks(keys, levels, np.full(nv, 0.1, np.float32), np.full(nv, 2, np.uint32), np.zeros(nv, np.float32))
+    batch.integrate([("points", pts, T), ("points", none, T)])
+    single.integrate_points(pts, T)
+    x, y = gpu_sorted(single), gpu_sorted(a)
+    for f in ("keys", "levels", "D", "W", "S2"):
+        assert np.array_equal(getattr(x, f), getattr(y, f)), f
+    batch.close()
