@@ -74,12 +74,13 @@ __global__ __launch_bounds__(256) void k_batch_alloc(const DevMap* __restrict__ 
     }
 }
 
+template <bool WIDE>
 __global__ __launch_bounds__(256) void k_batch_rays(const DevMap* __restrict__ maps, const BatchEntry* __restrict__ ents,
                                                     int n) {
     __shared__ RayLds lds;
     const int i = entry_of(ents, n, blockIdx.x, true);
     if (i < 0) return;  // uniform across the workgroup
-    points_ray_chunk(maps[i], ents[i].sp, blockIdx.x - ents[i].ray_begin, lds);
+    points_ray_chunk<WIDE>(maps[i], ents[i].sp, blockIdx.x - ents[i].ray_begin, lds);
 }
 
 // After the ray launch: each LiDAR map's touched blocks onto its update queues, kBatchTouchWgs
@@ -98,7 +99,8 @@ __global__ __launch_bounds__(256) void k_batch_touch(const DevMap* __restrict__ 
         queue_touched(m, first, min(per, nb - first), ents[i].sp.parity);
 }
 
-template <int ST, int KIND>
+// WIDE: one of the LiDAR maps keeps the halves of its squares apart (square_wide).
+template <int ST, int KIND, bool WIDE>
 __global__ __launch_bounds__(256) void k_batch_update(const DevMap* __restrict__ maps, const BatchEntry* __restrict__ ents,
                                                       int n) {
     // the entry table is written by the host before the launch: read through the constant address
@@ -180,7 +182,7 @@ __global__ __launch_bounds__(256) void k_batch_update(const DevMap* __restrict__
             const DepthFrame fr = *(const DepthFrame*)&ce[lo].df;
             ts.add_uniform(depth_update_task<ST, false>(maps[lo], fr, nullptr, local, c));
         } else {
-            ts.add_uniform(points_update_task<ST>(maps[lo], local, c, ((const BatchEntry*)&ce[lo])->sp.parity, &dl, alds[wv]));
+            ts.add_uniform(points_update_task<ST, WIDE>(maps[lo], local, c, ((const BatchEntry*)&ce[lo])->sp.parity, &dl, alds[wv]));
         }
     }
     if (cur >= 0) {
@@ -229,25 +231,29 @@ static void drop_graph(mrh_batch* b) {
 
 // Enqueue the batched launches on stream s for the launch geometry of the current table.
 static void enqueue_step(mrh_batch* b, hipStream_t s, uint32_t alloc_wgs, uint32_t ray_wgs, int depth_maps,
-                         int point_maps) {
+                         int point_maps, bool wide) {
     const int n = b->n;
     if (alloc_wgs) hipLaunchKernelGGL(k_batch_alloc, dim3(alloc_wgs), dim3(256), 0, s, b->d_maps, b->d_ents, n);
     if (ray_wgs) {
-        hipLaunchKernelGGL(k_batch_rays, dim3(ray_wgs), dim3(256), 0, s, b->d_maps, b->d_ents, n);
+        if (wide) hipLaunchKernelGGL(k_batch_rays<true>, dim3(ray_wgs), dim3(256), 0, s, b->d_maps, b->d_ents, n);
+        else hipLaunchKernelGGL(k_batch_rays<false>, dim3(ray_wgs), dim3(256), 0, s, b->d_maps, b->d_ents, n);
         hipLaunchKernelGGL(k_batch_touch, dim3((unsigned)n * kBatchTouchWgs), dim3(256), 0, s, b->d_maps, b->d_ents, n);
     }
     // at least one workgroup per map: workgroup i carries map i's update-side hand-off
     const dim3 ug((unsigned)(b->update_wgs > n ? b->update_wgs : n)), ub((unsigned)(64 * b->update_waves));
-    auto update = [&](auto kind) {
+    auto update = [&](auto kind, auto w) {
         constexpr int K = decltype(kind)::value;
+        constexpr bool WIDE = decltype(w)::value;
         switch (b->storage) {
-            case MRH_STORE_F16: hipLaunchKernelGGL((k_batch_update<MRH_STORE_F16, K>), ug, ub, 0, s, b->d_maps, b->d_ents, n); break;
-            case MRH_STORE_BF16: hipLaunchKernelGGL((k_batch_update<MRH_STORE_BF16, K>), ug, ub, 0, s, b->d_maps, b->d_ents, n); break;
-            default: hipLaunchKernelGGL((k_batch_update<MRH_STORE_F32, K>), ug, ub, 0, s, b->d_maps, b->d_ents, n);
+            case MRH_STORE_F16: hipLaunchKernelGGL((k_batch_update<MRH_STORE_F16, K, WIDE>), ug, ub, 0, s, b->d_maps, b->d_ents, n); break;
+            case MRH_STORE_BF16: hipLaunchKernelGGL((k_batch_update<MRH_STORE_BF16, K, WIDE>), ug, ub, 0, s, b->d_maps, b->d_ents, n); break;
+            default: hipLaunchKernelGGL((k_batch_update<MRH_STORE_F32, K, WIDE>), ug, ub, 0, s, b->d_maps, b->d_ents, n);
         }
     };
-    if (depth_maps) update(std::integral_constant<int, MRH_FRAME_DEPTH>());
-    if (point_maps) update(std::integral_constant<int, MRH_FRAME_POINTS>());
+    const std::integral_constant<int, MRH_FRAME_POINTS> points;
+    if (depth_maps) update(std::integral_constant<int, MRH_FRAME_DEPTH>(), std::false_type());
+    if (point_maps && wide) update(points, std::true_type());
+    if (point_maps && !wide) update(points, std::false_type());
 }
 
 }  // namespace mrh
@@ -364,6 +370,7 @@ mrh_status mrh_batch_integrate(mrh_batch* b, const mrh_frame* frames) {
     sig.push_back(b->update_waves);
     uint32_t alloc_wgs = 0, ray_wgs = 0;
     int depth_maps = 0, point_maps = 0;
+    bool wide = false;
     for (int i = 0; i < n; ++i) {
         const mrh_frame& f = frames[i];
         BatchEntry& e = h[i];
@@ -395,10 +402,12 @@ mrh_status mrh_batch_integrate(mrh_batch* b, const mrh_frame* frames) {
         e.ray_end = ray_wgs;
         depth_maps += f.kind == MRH_FRAME_DEPTH ? 1 : 0;
         point_maps += f.kind == MRH_FRAME_POINTS ? 1 : 0;
+        wide = wide || (f.kind == MRH_FRAME_POINTS && b->maps[i]->dm.square_wide);
         sig.push_back(f.kind);
         sig.push_back((int64_t)e.alloc_end);
         sig.push_back((int64_t)e.ray_end);
     }
+    sig.push_back(wide);
     if (hipMemcpyAsync(b->d_ents, h, sizeof(BatchEntry) * n, hipMemcpyHostToDevice, b->stream) != hipSuccess ||
         hipEventRecord(b->copied[k], b->stream) != hipSuccess)
         return batch_err(b, MRH_ERR_HIP, "batch: descriptor upload");
@@ -409,7 +418,7 @@ mrh_status mrh_batch_integrate(mrh_batch* b, const mrh_frame* frames) {
             if (frames[i].kind != MRH_FRAME_NONE) b->maps[i]->frames += 1;
     };
     if (!b->use_graph) {
-        launch(m0, K_BATCH_GRAPH, [&] { enqueue_step(b, b->stream, alloc_wgs, ray_wgs, depth_maps, point_maps); });
+        launch(m0, K_BATCH_GRAPH, [&] { enqueue_step(b, b->stream, alloc_wgs, ray_wgs, depth_maps, point_maps, wide); });
         const mrh_status st = check_hip(m0, hipGetLastError(), "batch_integrate");
         if (st == MRH_OK) advance();
         return st;
@@ -419,7 +428,7 @@ mrh_status mrh_batch_integrate(mrh_batch* b, const mrh_frame* frames) {
         hipGraph_t g = nullptr;
         if (hipStreamBeginCapture(b->capture_stream, hipStreamCaptureModeThreadLocal) != hipSuccess)
             return batch_err(b, MRH_ERR_HIP, "batch: begin capture");
-        enqueue_step(b, b->capture_stream, alloc_wgs, ray_wgs, depth_maps, point_maps);
+        enqueue_step(b, b->capture_stream, alloc_wgs, ray_wgs, depth_maps, point_maps, wide);
         const hipError_t ce = hipStreamEndCapture(b->capture_stream, &g);
         if (ce != hipSuccess || !g) return batch_err(b, MRH_ERR_HIP, "batch: end capture");
         const hipError_t ie = hipGraphInstantiate(&b->exec, g, nullptr, nullptr, 0);

@@ -284,7 +284,7 @@ static void free_all(mrh_map* m) {
     for (int n = 0; n < 2; ++n)
         if (d.vrect[n]) (void)hipFree(plain(d.vrect[n]));
     for (int n = 0; n < 4; ++n) {
-        void* lp[] = {plain(d.stack[n]), plain(d.pend[n]), plain(d.DW[n]), plain(d.S2[n]), plain(d.C[n]), plain(d.acc_sat[n]), plain(d.acc_band[n]), plain(d.acc_s1[n]), plain(d.acc_s2[n])};
+        void* lp[] = {plain(d.stack[n]), plain(d.pend[n]), plain(d.DW[n]), plain(d.S2[n]), plain(d.C[n]), plain(d.acc_sat[n]), plain(d.acc_band[n]), plain(d.acc_s1[n]), plain(d.acc_s2[n]), plain(d.acc_s2h[n])};
         for (void* p : lp)
             if (p) (void)hipFree(p);
     }

@@ -160,7 +160,9 @@ struct DevMap {
     // LiDAR per-frame accumulators, parallel to the heaps (zero between frames):
     // saturated (+tau) observation counts, and the exact integer sums of the band observations'
     // fixed-point values q = rint(d 2^24), with their count in the same word (see accumulate_band), and
-    // of q^2; acc_band holds the count where that word could overflow (band_wide), else it is null
+    // of q^2; acc_band holds the count where that word could overflow (band_wide), else it is null, and
+    // acc_s2h the sums of q^2 >> 32 (acc_s2 then those of the low halves) where the sum of q^2 could outgrow
+    // 64 bits (square_wide), else it is null
     uint32_t MRH_GLOBAL* acc_sat[4];
     uint32_t MRH_GLOBAL* acc_band[4];
     unsigned long long MRH_GLOBAL* acc_s1[4];
@@ -185,6 +187,8 @@ struct DevMap {
     int32_t min_obs, form, carve, storage;
     int32_t band_wide;
     long long band_bias;  // added to each q of a shared word: at least tau 2^24
+    int32_t square_wide;
+    unsigned long long MRH_GLOBAL* acc_s2h[4];
 };
 
 // An update-queue entry carries the block's table row, so an update task needs no second lookup.

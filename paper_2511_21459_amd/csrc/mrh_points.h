@@ -325,16 +325,21 @@ __device__ inline void sat_table_flush(const DevMap& m, SatTable& tab) {
 // value) are added, exact integers, fire-and-forget atomics with no dependent load.  The count rides on
 // the sum of q, made non-negative by band_bias: two atomics per observation instead of three (band
 // observations were two thirds of a scan's atomics).  A scan whose sums could outgrow the shared
-// word (m.band_wide) keeps the count in a word of its own.
+// word (m.band_wide) keeps the count in a word of its own, and one whose squares could outgrow theirs
+// (m.square_wide) the halves of each square in two: scans of such a map run the WIDE kernels (with that test
+// in the common ones a pass of three scans of 31 x 1023 rays, with its extraction, took 3.96 -> 4.07 ms).
 constexpr int kBandShift = 44;  // count << 44 | sum of q + bias
 
-// Where a block's words are (count: where it is kept apart, else null).
+// Where a block's words are (count: where it is kept apart, else null): from word `base` of its level.
 struct BandAcc {
     unsigned long long MRH_GLOBAL* s1;
     unsigned long long MRH_GLOBAL* s2;
     uint32_t MRH_GLOBAL* count;
+    int level;
+    size_t base;
 };
 
+template <bool WIDE>
 __device__ inline void accumulate_band(const DevMap& m, const BandAcc& a, uint32_t at, double d) {
     const long long q = (long long)__builtin_rint(d * kS1Scale);
     if (a.count) {
@@ -343,7 +348,13 @@ __device__ inline void accumulate_band(const DevMap& m, const BandAcc& a, uint32
     } else {
         atomicAdd(a.s1 + at, (1ull << kBandShift) + (unsigned long long)(q + m.band_bias));
     }
-    atomicAdd(a.s2 + at, (unsigned long long)(q * q));
+    if (WIDE && m.square_wide) {
+        const unsigned long long u = (unsigned long long)(q < 0 ? -q : q), low = u * u;
+        atomicAdd(a.s2 + at, low & 0xFFFFFFFFull);
+        atomicAdd(of_level(m.acc_s2h, a.level) + a.base + at, __umul64hi(u, u) << 32 | low >> 32);
+    } else {
+        atomicAdd(a.s2 + at, (unsigned long long)(q * q));
+    }
 }
 
 // The count and the sum of q of a voxel from its words.
@@ -356,6 +367,17 @@ __device__ inline void band_sums(const DevMap& m, uint32_t wide_count, unsigned 
         n = (uint32_t)(word >> kBandShift);
         s1 = (word & ((1ull << kBandShift) - 1ull)) - (unsigned long long)n * (unsigned long long)m.band_bias;
     }
+}
+
+// The sum of a voxel's squares, in square metres: `low` is its word of acc_s2, and the other word is read
+// and left at zero.
+template <bool WIDE>
+__device__ inline double take_squares(const DevMap& m, int level, size_t at, unsigned long long low) {
+    if (!WIDE || !m.square_wide) return (double)low / kS2Scale;
+    const unsigned long long high = m.acc_s2h[level][at] + (low >> 32);
+    m.acc_s2h[level][at] = 0ull;
+    low &= 0xFFFFFFFFull;
+    return (high >> 32 ? (double)high * 0x1p32 + (double)low : (double)(high << 32 | low)) / kS2Scale;
 }
 
 // The block walk restricted to one block: the segment is clipped to the block's box, the walk
@@ -513,6 +535,7 @@ struct RayLds {
 static_assert(sizeof(Walk) * kRaysPerGroup <= sizeof(u32x4) * (kRayRound - 256), "room for the walks");
 
 // The ray's one observation in a level-3 block: the centre of its only voxel (Eq. 1).
+template <bool WIDE>
 __device__ inline void ray_coarse_block(const DevMap& m, const RaySegment& r, const HashSlot& hs, RayLds& L) {
     int32_t b[3];
     unpack_key(hs.key, b[0], b[1], b[2]);
@@ -526,7 +549,7 @@ __device__ inline void ray_coarse_block(const DevMap& m, const RaySegment& r, co
         counted = sat_table_add(L.tab, 3, at);
         if (!counted) atomicAdd(&m.acc_sat[3][at], 1u);
     } else {
-        accumulate_band(m, BandAcc{m.acc_s1[3] + at, m.acc_s2[3] + at, m.band_wide ? m.acc_band[3] + at : nullptr}, 0u, d);
+        accumulate_band<WIDE>(m, BandAcc{m.acc_s1[3] + at, m.acc_s2[3] + at, m.band_wide ? m.acc_band[3] + at : nullptr, 3, at}, 0u, d);
     }
     if (counted != 1) touch_table_add(m, L.touch, hs.id, 1ull);  // (1: marked with the voxel's first)
 }
@@ -534,6 +557,7 @@ __device__ inline void ray_coarse_block(const DevMap& m, const RaySegment& r, co
 // The observations of one ray inside a block of level 0 .. 2 (slot and level in `info`): the block walk
 // restricted to the block's own voxel lattice.  The terms of Eq. 1's product are kept per axis and
 // re-evaluated (the whole expression) on the axis that stepped.
+template <bool WIDE>
 __device__ inline void ray_fine_block(const DevMap& m, const double o[3], const RaySegment& r, unsigned long long key,
                                       uint32_t id, uint32_t info, RayLds& L) {
     int32_t b[3];
@@ -543,7 +567,7 @@ __device__ inline void ray_fine_block(const DevMap& m, const double o[3], const 
     const double nu = nu_of(m.nu, level);
     uint32_t MRH_GLOBAL* const sat = of_level(m.acc_sat, level) + base;
     const BandAcc acc{of_level(m.acc_s1, level) + base, of_level(m.acc_s2, level) + base,
-                      m.band_wide ? of_level(m.acc_band, level) + base : nullptr};
+                      m.band_wide ? of_level(m.acc_band, level) + base : nullptr, level, base};
     BoxWalk bw;
     bw.init(r.a, r.e, b, m.B, inv_nu_of(m.inv_nu, level), side);
     const double ob[3] = {(double)b[0] * m.B, (double)b[1] * m.B, (double)b[2] * m.B};
@@ -564,7 +588,7 @@ __device__ inline void ray_fine_block(const DevMap& m, const double o[3], const 
         if (d >= m.tau) {
             if (!(shared && sat_table_add(L.tab, level, base + (size_t)mo))) atomicAdd(sat + mo, 1u);
         } else {
-            accumulate_band(m, acc, mo, d);
+            accumulate_band<WIDE>(m, acc, mo, d);
         }
         if (s == 3 * side) break;
         const int k = bw.next();
@@ -588,6 +612,7 @@ __device__ inline void ray_fine_block(const DevMap& m, const double o[3], const 
 // settled map, 1718 -> 1220 us into an empty one (27 M atomics at 22 G/s, the rate that bounds it).
 // The blocks of a ray beyond the recorded rcap_k are walked afterwards by one thread per ray, through
 // the same two steps.
+template <bool WIDE>
 __device__ inline void points_ray_chunk(const DevMap& m, const ScanParams& sp, uint32_t chunk, RayLds& L) {
     const int lane = lane_id(), tid = (int)threadIdx.x, wv = (int)uniform(threadIdx.x >> 6);
     const int64_t r0 = (int64_t)chunk * sp.rays;
@@ -676,7 +701,7 @@ __device__ inline void points_ray_chunk(const DevMap& m, const ScanParams& sp, u
                 if (mid) L.wait[(uint32_t)kRayRound - 1u - a1 - (uint32_t)rank_in_mask(g)] = (uint16_t)k;
             }
             if (level == 3)
-                ray_coarse_block(m, L.seg[L.ray[k]], HashSlot{(unsigned long long)q.x | ((unsigned long long)q.y << 32), q.z, q.w}, L);
+                ray_coarse_block<WIDE>(m, L.seg[L.ray[k]], HashSlot{(unsigned long long)q.x | ((unsigned long long)q.y << 32), q.z, q.w}, L);
         }
         __syncthreads();
         const uint32_t n0 = uniform(L.n[0]), n1 = uniform(L.n[1]), b0 = (n0 + 63) / 64, nb = b0 + (n1 + 63) / 64;
@@ -686,7 +711,7 @@ __device__ inline void points_ray_chunk(const DevMap& m, const ScanParams& sp, u
             if (k < (fine ? n0 : n1)) {
                 const uint32_t at = L.wait[fine ? k : (uint32_t)kRayRound - 1u - k];
                 const u32x4 q = L.pair[at];
-                ray_fine_block(m, sp.P.t, L.seg[L.ray[at]], (unsigned long long)q.x | ((unsigned long long)q.y << 32), q.z, q.w, L);
+                ray_fine_block<WIDE>(m, sp.P.t, L.seg[L.ray[at]], (unsigned long long)q.x | ((unsigned long long)q.y << 32), q.z, q.w, L);
             }
         }
         __syncthreads();
@@ -696,15 +721,15 @@ __device__ inline void points_ray_chunk(const DevMap& m, const ScanParams& sp, u
 }
 
 // Batch form of Eq. 3 and Eq. 5 for the scan's observations of one voxel: nsat at +tau, and nband
-// in the band with sums s1q of q and s2q of q^2 (q = rint(d 2^24)).  With T and Q those sums in
+// in the band with sums s1q of q = rint(d 2^24) and Q of its squares, in square metres.  With T the former in
 // metres, the band's sums of (d - D) and (d - D)^2 are T - n D and Q - 2 D T + n D^2.
-__device__ inline void apply_stats(const DevMap& m, uint32_t nsat, uint32_t nband, unsigned long long s1q,
-                                   unsigned long long s2q, float& D, uint32_t& W, float& S2) {
+__device__ inline void apply_stats(const DevMap& m, uint32_t nsat, uint32_t nband, unsigned long long s1q, double Q,
+                                   float& D, uint32_t& W, float& S2) {
     const uint32_t nobs = nsat + nband;
     const double Dp = (double)D;
     const double ts = m.tau - Dp;
     const double nb = (double)nband;
-    const double T = (double)(long long)s1q / kS1Scale, Q = (double)s2q / kS2Scale;
+    const double T = (double)(long long)s1q / kS1Scale;
     const double b2 = (Q - 2.0 * Dp * T) + nb * (Dp * Dp);
     const double s1 = (double)nsat * ts + (T - nb * Dp);
     const double s2 = (double)nsat * (ts * ts) + (b2 > 0.0 ? b2 : 0.0);
@@ -716,16 +741,17 @@ __device__ inline void apply_stats(const DevMap& m, uint32_t nsat, uint32_t nban
 }
 
 // Read and clear one voxel's scan accumulators.
+template <bool WIDE>
 __device__ inline void take_accumulators(const DevMap& m, int level, size_t at, uint32_t& ns, uint32_t& nb,
-                                         unsigned long long& s1, unsigned long long& s2) {
+                                         unsigned long long& s1, double& Q) {
     ns = m.acc_sat[level][at];
     const unsigned long long word = m.acc_s1[level][at];
     const uint32_t wide = m.band_wide ? m.acc_band[level][at] : 0u;
     band_sums(m, wide, word, nb, s1);
-    s2 = 0ull;
+    Q = 0.0;
     if (ns) m.acc_sat[level][at] = 0u;
     if (nb) {
-        s2 = m.acc_s2[level][at];
+        Q = take_squares<WIDE>(m, level, at, m.acc_s2[level][at]);
         m.acc_s1[level][at] = 0ull;
         m.acc_s2[level][at] = 0ull;
         if (wide) m.acc_band[level][at] = 0u;
@@ -746,7 +772,7 @@ struct UnitOut {
 // of misses, for 131072 points into an empty map: 860 us, now 702 or 4.1 TB/s).  All reads of a step are
 // issued before any is used.
 constexpr int kVoxelStep = 4;
-template <int ST>
+template <int ST, bool WIDE>
 __device__ inline void apply_voxels(const DevMap& m, const size_t at[kVoxelStep], const bool on[kVoxelStep], bool fresh,
                                     UnitOut u[kVoxelStep]) {
     uint32_t ns[kVoxelStep], nb[kVoxelStep], W[kVoxelStep], wide[kVoxelStep];
@@ -776,7 +802,8 @@ __device__ inline void apply_voxels(const DevMap& m, const size_t at[kVoxelStep]
             u[k].distinct = 1;
             const double before = var_term(m, W[k], S2[k]);
             const int cb = var_count(m, W[k]);
-            apply_stats(m, ns[k], nb[k], s1[k], s2[k], D[k], W[k], S2[k]);
+            const double Q = nb[k] ? take_squares<WIDE>(m, 0, at[k], s2[k]) : 0.0;
+            apply_stats(m, ns[k], nb[k], s1[k], Q, D[k], W[k], S2[k]);
             Store<ST>::round(m, D[k], W[k], S2[k]);
             u[k].dsum = var_term(m, W[k], S2[k]) - before;
             u[k].dcnt = var_count(m, W[k]) - cb;
@@ -793,7 +820,7 @@ __device__ inline void apply_voxels(const DevMap& m, const size_t at[kVoxelStep]
 
 // A block of the scan itself (level 0, one wave, lane l voxel l of each run of 64): every voxel is written,
 // with zeros where no ray touched its group.
-template <int ST>
+template <int ST, bool WIDE>
 __device__ inline TaskOut apply_new(const DevMap& m, uint32_t id, uint32_t info, unsigned long long touched, double bvs,
                                     uint32_t bvc, int par, DeferList* dl) {
     const int lane = lane_id();
@@ -809,7 +836,7 @@ __device__ inline TaskOut apply_new(const DevMap& m, uint32_t id, uint32_t info,
             at[k] = base + (size_t)(r + k) * 64;
             on[k] = (touched >> (8 * (r + k) + (lane >> 3))) & 1ull;
         }
-        apply_voxels<ST>(m, at, on, true, u);
+        apply_voxels<ST, WIDE>(m, at, on, true, u);
         for (int k = 0; k < kVoxelStep; ++k) dsum += u[k].dsum, dcnt += u[k].dcnt, nobs += u[k].nobs, distinct += u[k].distinct;
     }
     TaskOut out;
@@ -849,7 +876,7 @@ __device__ inline int nth_bit(unsigned long long x, int k) {
     return pos;
 }
 
-template <int ST, int LEVEL>
+template <int ST, int LEVEL, bool WIDE>
 __device__ inline TaskOut apply_blocks(const DevMap& m, const u32x4 MRH_GLOBAL* list, uint32_t count, uint32_t group,
                                        int par, DeferList* dl, ApplyLds& A) {
     const int lane = lane_id();
@@ -872,7 +899,7 @@ __device__ inline TaskOut apply_blocks(const DevMap& m, const u32x4 MRH_GLOBAL* 
     if (LEVEL == 0) {
         for (unsigned long long left = __ballot(fresh); left; left &= left - 1ull) {
             const int j = __ffsll((long long)left) - 1;
-            const TaskOut o = apply_new<ST>(m, (uint32_t)lane_value((int)id, j), (uint32_t)lane_value((int)info, j),
+            const TaskOut o = apply_new<ST, WIDE>(m, (uint32_t)lane_value((int)id, j), (uint32_t)lane_value((int)info, j),
                                             lane_value(touched, j), lane_value(bvs, j), (uint32_t)lane_value((int)bvc, j), par, dl);
             out.obs += o.obs;
             out.fresh += o.fresh;
@@ -915,16 +942,17 @@ __device__ inline TaskOut apply_blocks(const DevMap& m, const u32x4 MRH_GLOBAL* 
             } else {
                 const size_t at = (size_t)A.slot[j] * 64 + (size_t)g;
                 uint32_t ns, nb, W;
-                unsigned long long s1, s2;
+                unsigned long long s1;
+                double Q;
                 float D, S2;
                 Store<ST>::get(m, 1, at, D, W, S2);
-                take_accumulators(m, 1, at, ns, nb, s1, s2);
+                take_accumulators<WIDE>(m, 1, at, ns, nb, s1, Q);
                 u.nobs = (int)(ns + nb);
                 if (u.nobs) {
                     u.distinct = 1;
                     const double before = var_term(m, W, S2);
                     const int cb = var_count(m, W);
-                    apply_stats(m, ns, nb, s1, s2, D, W, S2);
+                    apply_stats(m, ns, nb, s1, Q, D, W, S2);
                     Store<ST>::round(m, D, W, S2);
                     u.dsum = var_term(m, W, S2) - before;
                     u.dcnt = var_count(m, W) - cb;
@@ -945,7 +973,7 @@ __device__ inline TaskOut apply_blocks(const DevMap& m, const u32x4 MRH_GLOBAL* 
                     on[k] = g != kInvalidId;
                     at[k] = (size_t)g * 8 + (size_t)(lane & 7);
                 }
-                apply_voxels<ST>(m, at, on, false, v);
+                apply_voxels<ST, WIDE>(m, at, on, false, v);
                 for (int k = 0; k < kVoxelStep; ++k) {
                     const int from = (lane & 7) * 8;
                     const double d = __shfl(group8_sum(v[k].dsum), from);
@@ -988,14 +1016,15 @@ __device__ inline TaskOut apply_blocks(const DevMap& m, const u32x4 MRH_GLOBAL* 
 }
 
 // 64 / seg blocks of `level` (2: seg = 8 voxels, 3: seg = 1 voxel) per wave.
-template <int ST>
+template <int ST, bool WIDE>
 __device__ inline TaskOut apply_packed(const DevMap& m, const u32x4 MRH_GLOBAL* list, uint32_t count, uint32_t group, int level) {
     const int lane = lane_id();
     const int seg = level == 2 ? 8 : 1;
     const uint32_t bi = group * (uint32_t)(64 / seg) + (uint32_t)(lane / seg);
     const bool live = bi < count;
     uint32_t id = 0, info = 0, ns = 0, nb = 0;
-    unsigned long long s1 = 0ull, s2 = 0ull;
+    unsigned long long s1 = 0ull;
+    double Q = 0.0;
     float D = 0.f, S2 = 0.f;
     uint32_t W = 0;
     if (live) {
@@ -1003,7 +1032,7 @@ __device__ inline TaskOut apply_packed(const DevMap& m, const u32x4 MRH_GLOBAL* 
         id = e.x;
         info = e.y;
         const size_t at = (size_t)(info & kSlotMask) * seg + (lane % seg);
-        take_accumulators(m, level, at, ns, nb, s1, s2);
+        take_accumulators<WIDE>(m, level, at, ns, nb, s1, Q);
         if (lane % seg == 0) m.btouch[id] = 0ull;
         Store<ST>::get(m, level, at, D, W, S2);
     }
@@ -1013,7 +1042,7 @@ __device__ inline TaskOut apply_packed(const DevMap& m, const u32x4 MRH_GLOBAL* 
     if (upd) {
         const double before = var_term(m, W, S2);
         const int cb = var_count(m, W);
-        apply_stats(m, ns, nb, s1, s2, D, W, S2);
+        apply_stats(m, ns, nb, s1, Q, D, W, S2);
         Store<ST>::round(m, D, W, S2);
         dsum = var_term(m, W, S2) - before;
         dcnt = var_count(m, W) - cb;
@@ -1034,18 +1063,18 @@ __device__ inline uint32_t points_task_count(const TaskCounts& c) {
 
 // One of its tasks.  Merges of level-0 / level-1 blocks are recorded in *dl, which has room for those of one
 // task (DeferList::ready), and done by run_deferred.
-template <int ST>
+template <int ST, bool WIDE>
 __device__ inline TaskOut points_update_task(const DevMap& m, uint32_t t, const TaskCounts& c, int par, DeferList* dl,
                                              ApplyLds& A) {
     const uint32_t* n = c.n;
     const uint32_t g0 = (n[0] + kApplyBlocks - 1) / kApplyBlocks, g1 = (n[1] + kApplyBlocks - 1) / kApplyBlocks;
-    if (t < g0) return apply_blocks<ST, 0>(m, m.vis[0], n[0], t, par, dl, A);
+    if (t < g0) return apply_blocks<ST, 0, WIDE>(m, m.vis[0], n[0], t, par, dl, A);
     t -= g0;
-    if (t < g1) return apply_blocks<ST, 1>(m, m.vis[1], n[1], t, par, dl, A);
+    if (t < g1) return apply_blocks<ST, 1, WIDE>(m, m.vis[1], n[1], t, par, dl, A);
     t -= g1;
     const uint32_t g2 = (n[2] + 7) / 8;
     const int level = t < g2 ? 2 : 3;
-    return apply_packed<ST>(m, m.vis[level], n[level], level == 2 ? t : t - g2, level);
+    return apply_packed<ST, WIDE>(m, m.vis[level], n[level], level == 2 ? t : t - g2, level);
 }
 
 }  // namespace mrh

@@ -5,6 +5,7 @@
 // update queues) and k_apply_points (update tasks over those queues; the first workgroups also run
 // the update-side hand-off).
 #include <cmath>
+#include <type_traits>
 
 #include "mrh_points.h"
 
@@ -16,9 +17,10 @@ __global__ __launch_bounds__(256) void k_alloc_points(const DevMap* __restrict__
     points_alloc_chunk(*pm, sp, blockIdx.x);
 }
 
+template <bool WIDE>
 __global__ __launch_bounds__(256) void k_rays(const DevMap* __restrict__ pm, ScanParams sp) {
     __shared__ RayLds lds;
-    points_ray_chunk(*pm, sp, blockIdx.x, lds);
+    points_ray_chunk<WIDE>(*pm, sp, blockIdx.x, lds);
 }
 
 // After the ray launch: the touched blocks onto the update queues (workgroup w takes block ids
@@ -31,7 +33,7 @@ __global__ __launch_bounds__(256) void k_touch_queue(const DevMap* __restrict__ 
         queue_touched(m, first, min(per, nb - first), par);
 }
 
-template <int ST>
+template <int ST, bool WIDE>
 __global__ __launch_bounds__(256) void k_apply_points(const DevMap* __restrict__ pm, int par) {
     const DevMap& m = *pm;
     if (blockIdx.x < duty_parts(gridDim.x)) update_duties(m, par, blockIdx.x, duty_parts(gridDim.x));
@@ -47,7 +49,7 @@ __global__ __launch_bounds__(256) void k_apply_points(const DevMap* __restrict__
     unsigned long long m0 = 0, m1 = 0;
     TaskStats as;
     for (uint32_t t = wave; t < ntask; t += nwaves) {
-        as.add_uniform(points_update_task<ST>(m, t, n, par, &dl, lds[wv]));
+        as.add_uniform(points_update_task<ST, WIDE>(m, t, n, par, &dl, lds[wv]));
         if (!dl.ready(kApplyBlocks)) run_deferred<ST>(m, dl, par, m0, m1);
     }
     run_deferred<ST>(m, dl, par, m0, m1);
@@ -70,9 +72,6 @@ static int32_t ray_block_cap(const mrh_config& c) {
     const double cells = 1.7320508075688772 * len / (8.0 * c.voxel) + 8.0;
     return cells < 1024.0 ? (int32_t)cells : 1024;
 }
-
-// Observations one voxel can take from one ray: a walk enters each cell of its lattice once.
-constexpr double kMaxObsPerRay = 1.0;
 
 // LiDAR state of a map: accumulators (first scan) and per-ray block-key buffers for n rays.
 mrh_status ensure_lidar(mrh_map* map, int64_t n) {
@@ -97,14 +96,18 @@ mrh_status ensure_lidar(mrh_map* map, int64_t n) {
         d.rcap_k = ray_block_cap(map->cfg);
         if (st == MRH_OK) map->lidar_ready = true;
     }
-    // a voxel takes at most a few observations from each ray: with 2^20 of them its count and its sum of
-    // up to 2 bias each fit the shared word; larger scans and truncations keep their counts apart
-    if (st == MRH_OK && !d.band_wide &&
-        ((double)n * kMaxObsPerRay >= 1048576.0 || (double)n * kMaxObsPerRay * 2.0 * (double)d.band_bias >= 0x1p44)) {
+    // A ray's walk enters each cell of its lattice once, so a voxel takes at most n observations, each of up to
+    // 2 bias in the shared word and bias^2 in the squares: with fewer than 2^20 of them, and their sums below
+    // 2^44 and 2^64 (n tau < 2^19 m, n tau^2 < 2^16 m^2), every voxel's words hold.  Larger scans and
+    // truncations keep their counts, or the squares' halves, apart.
+    auto words = [&](auto planes, size_t size) {
         for (int l = 0; l < map->cfg.levels; ++l)
-            alloc(&d.acc_band[l], (size_t)d.heap_cap[l] * (size_t)(side_of(l) * side_of(l) * side_of(l)) * 4, "scan accumulators");
-        if (st == MRH_OK) d.band_wide = 1;
-    }
+            alloc(&planes[l], (size_t)d.heap_cap[l] * (size_t)(side_of(l) * side_of(l) * side_of(l)) * size, "scan accumulators");
+        return st == MRH_OK ? 1 : 0;
+    };
+    const double bias = (double)d.band_bias;
+    if (st == MRH_OK && !d.band_wide && ((double)n >= 0x1p20 || (double)n * 2.0 * bias >= 0x1p44)) d.band_wide = words(d.acc_band, 4);
+    if (st == MRH_OK && !d.square_wide && (double)n * bias * bias >= 0x1p64) d.square_wide = words(d.acc_s2h, 8);
     if (st == MRH_OK && n > map->rcap_n) {
         st = check_hip(map, hipStreamSynchronize(map->stream), "ray buffers");
         if (d.rslots) (void)hipFree(plain(d.rslots));
@@ -137,25 +140,30 @@ extern "C" mrh_status mrh_integrate_points(mrh_map* map, const float* xyz_dev, i
     sp.parity = (int32_t)(map->frames & 1u);
     map->frames += 1;
     const int par = sp.parity;
-    // the allocation and update launches always run (they carry the frame hand-off)
+    // the allocation and update launches always run (they carry the frame hand-off); the ray launch has the
+    // allocation's workgroups
     const unsigned agrid = n > 0 ? (unsigned)((n + sp.rays - 1) / sp.rays) : 1u;
     launch(map, K_ALLOC_POINTS,
            [&] { hipLaunchKernelGGL(k_alloc_points, dim3(agrid), dim3(256), 0, map->stream, map->dmd, sp); });
-    if (n > 0) {
-        const unsigned rgrid = (unsigned)((n + sp.rays - 1) / sp.rays);
-        launch(map, K_RAYS, [&] {
-            hipLaunchKernelGGL(k_rays, dim3(rgrid), dim3(256), 0, map->stream, map->dmd, sp);
-            hipLaunchKernelGGL(k_touch_queue, dim3(1024), dim3(256), 0, map->stream, map->dmd, par);
-        });
-    }
-    launch(map, K_APPLY_POINTS, [&] {
-        const dim3 g(1024), b(256);
-        switch (map->cfg.storage) {
-            case MRH_STORE_F16: hipLaunchKernelGGL(k_apply_points<MRH_STORE_F16>, g, b, 0, map->stream, map->dmd, par); break;
-            case MRH_STORE_BF16: hipLaunchKernelGGL(k_apply_points<MRH_STORE_BF16>, g, b, 0, map->stream, map->dmd, par); break;
-            default: hipLaunchKernelGGL(k_apply_points<MRH_STORE_F32>, g, b, 0, map->stream, map->dmd, par);
+    auto rest = [&](auto w) {
+        constexpr bool WIDE = decltype(w)::value;
+        if (n > 0) {
+            launch(map, K_RAYS, [&] {
+                hipLaunchKernelGGL(k_rays<WIDE>, dim3(agrid), dim3(256), 0, map->stream, map->dmd, sp);
+                hipLaunchKernelGGL(k_touch_queue, dim3(1024), dim3(256), 0, map->stream, map->dmd, par);
+            });
         }
-    });
+        launch(map, K_APPLY_POINTS, [&] {
+            const dim3 g(1024), b(256);
+            switch (map->cfg.storage) {
+                case MRH_STORE_F16: hipLaunchKernelGGL(HIP_KERNEL_NAME(k_apply_points<MRH_STORE_F16, WIDE>), g, b, 0, map->stream, map->dmd, par); break;
+                case MRH_STORE_BF16: hipLaunchKernelGGL(HIP_KERNEL_NAME(k_apply_points<MRH_STORE_BF16, WIDE>), g, b, 0, map->stream, map->dmd, par); break;
+                default: hipLaunchKernelGGL(HIP_KERNEL_NAME(k_apply_points<MRH_STORE_F32, WIDE>), g, b, 0, map->stream, map->dmd, par);
+            }
+        });
+    };
+    if (map->dm.square_wide) rest(std::true_type());
+    else rest(std::false_type());
     return check_hip(map, hipGetLastError(), "integrate_points");
 }
 

@@ -305,3 +305,29 @@ def test_empty_scan_beside_a_full_one(mrh, graph):
     for f in ("keys", "levels", "D", "W", "S2"):
         assert np.array_equal(getattr(x, f), getattr(y, f)), f
     batch.close()
+
+
+def test_batch_with_sums_apart(mrh):
+    """A map whose scan is too large for the shared sums beside one whose scan is not, replayed as one graph
+    after steps without either: each equals its own fusion."""
+    announce("batch: wide sums in one map")
+    cfg = dict(configs.STREET, voxel=0.5, tau=4.0, max_range=400.0, var_thr=0.01, carve=False, max_blocks=1 << 14, hash_slots=1 << 15)
+    rng = np.random.default_rng(9)
+
+    def scan(n):
+        d = rng.normal(size=(n, 3)) * [1.0, 1.0, 0.02]
+        return _dev((d / np.linalg.norm(d, axis=1, keepdims=True) * rng.uniform(18.0, 20.0, (n, 1))).astype(np.float32))
+
+    T = np.eye(4)
+    maps = [mrh.Map(**cfg) for _ in range(4)]
+    batch = mrh.Batch(maps[:2])
+    small, wide = [scan(900), scan(1200)], [scan(900), scan(150000)]
+    for pts in (small, small, wide, wide, small):
+        batch.integrate([("points", p, T) for p in pts])
+        for m, p in zip(maps[2:], pts):
+            m.integrate_points(p, T)
+    for m, alone in zip(maps[:2], maps[2:]):
+        x, y = gpu_sorted(m), gpu_sorted(alone)
+        for f in ("keys", "levels", "D", "W", "S2"):
+            assert np.array_equal(getattr(x, f), getattr(y, f)), f
+    batch.close()

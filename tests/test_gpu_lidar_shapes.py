@@ -134,3 +134,32 @@ def test_query_group_edges(mrh, storage, strict):
             for a, b in zip(part, full):
                 if a is not None:
                     assert torch.equal(a, b[:n]), (n, grad)
+
+
+def _one_line(rng, n, lo, hi):
+    """n points along one direction: every ray crosses the same voxels."""
+    d = np.array([0.48, 0.6, 0.64])
+    return (d * rng.uniform(lo, hi, (n, 1))).astype(np.float32)
+
+
+@pytest.mark.parametrize("n", [20000, 140000])
+def test_squares_apart(mrh, orc, n):
+    """A scan whose observations of one voxel have squares that sum to more than 2^16 m^2 (what 64 bits hold
+    in units of 2^-48 m^2), with counts beside the sums (20000 rays) and apart (140000), between scans that
+    stay below it, on one map."""
+    announce(f"wide sums of squares, {n} rays through the same voxels")
+    cfg = dict(CFG, voxel=0.5, tau=4.0, min_range=1.0, max_range=400.0, var_thr=0.01, carve=False)
+    rng = np.random.default_rng(n)
+    T = np.eye(4)
+    T[:3, 3] = [0.1, 0.2, 0.3]
+    _scans_match(mrh, orc, cfg, [(_one_line(rng, k, 19.0, 21.0), T) for k in (500, n, 700)])
+
+
+def test_more_rays_than_the_shared_count(mrh, orc):
+    """2^20 and more observations of one voxel in one scan."""
+    n = (1 << 20) + 40000
+    announce(f"{n} rays through the same voxels")
+    rng = np.random.default_rng(8)
+    T = np.eye(4)
+    T[:3, 3] = [0.01, 0.02, 0.03]
+    _scans_match(mrh, orc, dict(CFG, carve=False), [(_one_line(rng, k, 4.0, 4.1), T) for k in (300, n, 400)])
