@@ -86,7 +86,8 @@ typedef struct mrh_stats {
     int64_t new_blocks;     /* blocks inserted */
     int64_t observations;   /* voxel updates applied (one per voxel per observation) */
     int64_t merges[4];      /* merges out of level n */
-    int64_t failed_inserts; /* inserts lost to a full table / heap / block limit */
+    int64_t failed_inserts; /* inserts lost to a full table / heap / block limit (a full table: one for the
+                               pixels or rays of a wave that ask for the same key together) */
     int64_t fresh_observations; /* of `observations`, those applied to blocks created this frame */
     int64_t blocks;         /* distinct blocks in the map after the frame */
     uint32_t error_flags;   /* bit 0 table full, bit 1 heap full, bit 2 block limit */

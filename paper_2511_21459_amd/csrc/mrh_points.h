@@ -232,7 +232,6 @@ __device__ inline void points_alloc_chunk(const DevMap& m, const ScanParams& sp,
                     open &= ~(1u << u);
                     slot[u] = kInvalidId;
                     atomicOr(&m.ctr->error_flags.v, kErrTableFull);
-                    stat_add(m, S_FAILED, 1ull);
                 } else {
                     slot[u] = (slot[u] + 1) & m.hmask;
                 }
@@ -251,8 +250,15 @@ __device__ inline void points_alloc_chunk(const DevMap& m, const ScanParams& sp,
             register_new(m, spill, key[u], slot[u]);
         }
 #pragma unroll
-        for (int u = 0; u < kAllocUnroll; ++u)
+        for (int u = 0; u < kAllocUnroll; ++u) {
             if (((valid >> u) & 1u) && place[u] < K) m.rslots[(size_t)(r0 + ray[u]) * K + place[u]] = slot[u];
+            // a key that lanes of the wave ask for together is one lost insert
+            unsigned long long left = __ballot(((valid >> u) & 1u) && slot[u] == kInvalidId);
+            while (left) {
+                left &= ~__ballot(key[u] == shfl_u64(key[u], __ffsll((long long)left) - 1));
+                if (lane == 0) stat_add(m, S_FAILED, 1ull);
+            }
+        }
     }
     __syncthreads();
     const uint32_t nnew = ncount < (uint32_t)kAllocNew ? ncount : (uint32_t)kAllocNew;

@@ -163,3 +163,25 @@ def test_more_rays_than_the_shared_count(mrh, orc):
     T = np.eye(4)
     T[:3, 3] = [0.01, 0.02, 0.03]
     _scans_match(mrh, orc, dict(CFG, carve=False), [(_one_line(rng, k, 4.0, 4.1), T) for k in (300, n, 400)])
+
+
+@pytest.mark.parametrize("n", [1, 2, 4])
+def test_failed_inserts_count_keys(mrh, orc, n):
+    """Inserts lost to a full table are counted once for the rays of a wave that ask for the same key: with a
+    probe limit of one slot, the keys of a ray that find their home slot taken, however many rays walk along
+    with it."""
+    announce(f"full table, {n} rays")
+    cfg = dict(CFG, max_blocks=16, hash_slots=32, max_probe=1)
+    pts = np.repeat(np.array([[1.9, 1.3, 0.7]], np.float32), n, 0)
+    o = orc.OracleMap(**configs.oracle_kwargs(cfg))
+    o.integrate_points(pts, np.eye(4))
+    homes = [mrh.block_hash(*map(int, k), 32) for k in o.extract().keys]
+    assert len(homes) <= 12 and len(set(homes)) < len(homes)
+    g = mrh.Map(**cfg)
+    g.integrate_points(_dev(pts), np.eye(4))
+    with pytest.raises(mrh.MrhError) as ei:
+        g.sync()
+    assert ei.value.code == -3
+    _, tot = g.sync()
+    assert tot["new_blocks"] == len(set(homes))
+    assert tot["failed_inserts"] == len(homes) - len(set(homes))
