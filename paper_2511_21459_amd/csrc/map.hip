@@ -329,6 +329,7 @@ mrh_status mrh_map_create(const mrh_config* cfg, void* stream, mrh_map** out) {
     {
         float mf = (float)c.max_depth;
         if ((double)mf > c.max_depth) mf = std::nextafter(mf, -INFINITY);
+        if (std::isnan(c.max_depth)) mf = -1.f;  // no depth is <= a maximum that is not a number
         d.max_depth_f = mf;
     }
     d.var_thr = c.var_thr;

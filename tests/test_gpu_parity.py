@@ -589,3 +589,21 @@ def test_sides_from_2_to_the_23(mrh, orc, size):
             assert last[a] == st[a], (k, a)
     assert st["valid_points"] == 280 and st["observations"] > 10000
     print(compare_maps(gpu_sorted(g), o.extract(), excused=excused_keys(o), tau=cfg["tau"]))
+
+
+@pytest.mark.parametrize("form", ["range", "zdiff"])
+def test_max_depth_nan_takes_no_sample(mrh, form):
+    """No depth is <= a maximum depth that is not a number: a frame changes nothing, also not the blocks
+    that are there."""
+    announce(f"maximum depth NaN, {form}")
+    g = mrh.Map(voxel=0.05, levels=4, tau=0.15, max_depth=float("nan"), form=form, max_blocks=64)
+    keys = np.array([[0, 0, 2], [-1, 0, 2], [0, -1, 2], [-1, -1, 2]], np.int32)
+    nv = 512 + 64 + 8 + 1
+    assert g.load_blocks(keys, np.arange(4), np.full(nv, 0.1, np.float32), np.full(nv, 3, np.uint32), np.zeros(nv, np.float32)) == 4
+    before = gpu_sorted(g)
+    g.integrate_depth(torch.full((48, 64), 0.9, device="cuda"), [60.0, 60.0, 31.5, 23.5], np.eye(4))
+    last, _ = g.sync()
+    assert last["valid_points"] == last["observations"] == last["new_blocks"] == 0
+    after = gpu_sorted(g)
+    for a in ("keys", "levels", "D", "W", "S2"):
+        assert np.array_equal(getattr(before, a), getattr(after, a)), a
