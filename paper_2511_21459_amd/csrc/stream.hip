@@ -218,6 +218,8 @@ __global__ __launch_bounds__(256) void k_stream_in(const DevMap* __restrict__ pm
     uint8_t* in = const_cast<uint8_t*>(payload) + e * bytes;
     if (pb == 4) copy_planes(m, level, slot, reinterpret_cast<uint32_t*>(in), true);
     else copy_planes(m, level, slot, reinterpret_cast<uint16_t*>(in), true);
+    // a voxel's pair, read below, was written by other lanes and as elements of another type
+    DeferList::sync();
     double s = 0.0;
     uint32_t c = 0;
     if (sums) {

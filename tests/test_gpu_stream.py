@@ -209,3 +209,30 @@ def test_extract_rows(mrh, n):
         a, b = slice(*e["offsets"][g:g + 2]), slice(*offs[w:w + 2])
         assert np.array_equal(e["D"][a], D[b]) and np.array_equal(e["W"][a].view(np.uint32), W[b])
         assert np.array_equal(e["S2"][a], S2[b])
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16", "bf16"])
+def test_loaded_blocks_merge_by_their_variance(mrh, storage):
+    """The variance sums of loaded blocks are taken from the voxels as stored: touched once each by a ray that
+    ends in them, the blocks whose mean variance lies below the threshold merge and the others stay (both
+    by a factor of four), at levels 0, 1 and 2."""
+    announce(f"load_blocks, merges by variance, {storage}")
+    tau, thr = 0.15, 0.04 ** 2
+    m = mrh.Map(voxel=0.05, levels=4, tau=tau, var_thr=thr, min_obs=2, max_blocks=4096, min_range=0.1, max_range=50.0, storage=storage)
+    n = 600
+    k = np.arange(n)
+    keys = np.stack([k % 10, k // 10 % 10, 4 + k // 100], 1).astype(np.int32) - np.array([5, 5, 0], np.int32)
+    levels = (k % 3).astype(np.uint8)
+    low = (k // 3) % 2 == 0
+    size = (8 >> levels.astype(int)) ** 3
+    rng = np.random.default_rng(1)
+    W = rng.integers(40, 60, size.sum()).astype(np.uint32)
+    var = np.repeat(np.where(low, thr / 4, thr * 4), size)
+    assert m.load_blocks(keys, levels, np.zeros(size.sum(), np.float32), W, (var * W).astype(np.float32)) == n
+    pts = ((keys + 0.5 + rng.uniform(-0.2, 0.2, (n, 3))) * 0.4).astype(np.float32)
+    m.integrate_points(_dev(pts), np.eye(4))
+    m.sync()
+    g = gpu_sorted(m)
+    got = {tuple(q): int(l) for q, l in zip(g.keys.tolist(), g.levels.tolist())}
+    for q, l, lo in zip(keys.tolist(), levels.tolist(), low.tolist()):
+        assert got[tuple(q)] == l + (1 if lo else 0), (q, l, lo)
