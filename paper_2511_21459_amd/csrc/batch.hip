@@ -290,6 +290,7 @@ mrh_status mrh_batch_create(mrh_map* const* maps, int32_t n_maps, mrh_batch** ou
         ok = hipMemcpy(b->d_maps, dm.data(), sizeof(DevMap) * n_maps, hipMemcpyHostToDevice) == hipSuccess;
     }
     if (!ok) {
+        (void)hipGetLastError();
         mrh_batch_destroy(b);
         return MRH_ERR_HIP;
     }

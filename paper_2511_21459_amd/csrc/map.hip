@@ -20,6 +20,7 @@ mrh_status set_error(mrh_map* m, mrh_status code, const char* fmt, ...) {
 
 mrh_status check_hip(mrh_map* m, hipError_t e, const char* what) {
     if (e == hipSuccess) return MRH_OK;
+    (void)hipGetLastError();  // reported here: the next launch's check would find it again
     return set_error(m, e == hipErrorOutOfMemory ? MRH_ERR_OOM : MRH_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
 }
 

@@ -585,6 +585,7 @@ mrh_status mrh_quadtree_create(int32_t max_width, int32_t max_height, void* stre
                                               sizeof(QtSums)) == hipSuccess;
     if (ok) q->n_leaves = reinterpret_cast<unsigned long long*>(q->counts + kMaxLevels);
     if (!ok) {
+        (void)hipGetLastError();
         mrh_quadtree_destroy(q);
         return MRH_ERR_OOM;
     }

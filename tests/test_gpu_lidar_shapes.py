@@ -185,3 +185,26 @@ def test_failed_inserts_count_keys(mrh, orc, n):
     _, tot = g.sync()
     assert tot["new_blocks"] == len(set(homes))
     assert tot["failed_inserts"] == len(homes) - len(set(homes))
+
+
+def test_refused_scan_leaves_the_map_usable(mrh, orc):
+    """A scan whose ray buffers no GPU holds is refused for lack of memory before it reads anything; the map
+    goes on as if it had not been called."""
+    import ctypes
+
+    announce("oversized scan refused")
+    rng = np.random.default_rng(6)
+    d = rng.normal(size=(3000, 3))
+    pts = (d / np.linalg.norm(d, axis=1, keepdims=True) * rng.uniform(1.0, 8.0, (3000, 1))).astype(np.float32)
+    cfg = dict(CFG, max_blocks=1 << 16, hash_slots=1 << 17)
+    g = mrh.Map(**cfg)
+    o = orc.OracleMap(**configs.oracle_kwargs(cfg))
+    dev, T = _dev(pts), np.eye(4)
+    for k in range(3):
+        st = mrh._lib.load().mrh_integrate_points(g._h, ctypes.c_void_p(dev.data_ptr()), ctypes.c_int64(1 << 33),
+                                                  T.ctypes.data_as(ctypes.c_void_p))
+        assert st == -2 and "memory" in mrh._lib.load().mrh_last_error(g._h).decode()
+        g.integrate_points(dev, T)
+        last, _ = g.sync()
+        assert last["observations"] == o.integrate_points(pts, T)["observations"]
+    compare_maps(gpu_sorted(g), o.extract(), excused=excused_keys(o), tau=cfg["tau"])
