@@ -78,11 +78,16 @@ mrh_status ensure_lidar(mrh_map* map, int64_t n) {
     DevMap& d = map->dm;
     mrh_status st = MRH_OK;
     bool changed = false;
-    auto alloc = [&](void* p, size_t bytes, const char* what) {  // p: the address of a pointer
-        if (st != MRH_OK) return;
-        st = check_hip(map, hipMalloc((void**)p, bytes), what);
-        if (st == MRH_OK) st = check_hip(map, hipMemsetAsync(*(void**)p, 0, bytes, map->stream), what);
+    auto alloc = [&](void* at, size_t bytes, const char* what) {  // at: the address of a pointer
+        void** p = (void**)at;
         changed = true;
+        if (st != MRH_OK || *p) return;  // (there since a call that ran out of memory further on)
+        st = check_hip(map, hipMalloc(p, bytes), what);
+        if (st != MRH_OK) *p = nullptr;
+        else if ((st = check_hip(map, hipMemsetAsync(*p, 0, bytes, map->stream), what)) != MRH_OK) {
+            (void)hipFree(*p);
+            *p = nullptr;
+        }
     };
     if (!map->lidar_ready) {
         alloc(&d.btouch, (size_t)d.max_blocks * 8, "touch masks");
