@@ -13,7 +13,7 @@
 // in LDS.  Which of its ancestors are split follows from their sums, which a first launch over the
 // image leaves per subtree: two launches and two reads of the image whatever the depth, where tables of
 // the whole image (36 B a pixel written twice and read by every level) took three and one per level.
-// Long thin images keep those tables (mrh_quadtree_build has the rule).
+// Long thin images and the longest ones keep those tables (mrh_quadtree_build has the rule).
 // With S_c and Q_c a node's sums of channel values and of their squares over its n pixels (exact
 // integers), n^2 times the channel variance is n Q_c - S_c^2, exact in 64 bits for images of up to
 // 2^23 pixels; the contrast is then formed in FP64.
@@ -253,7 +253,8 @@ __global__ __launch_bounds__(256) void k_qt_level(const uint32_t* __restrict__ S
 constexpr int kTileSide = 40;    // longest side of a subtree's root (640 x 480: 256 workgroups of 40 x 30)
 constexpr int kTilePitch = kTileSide + 1;
 constexpr int kTilePixels = kTileSide * kTileSide;
-constexpr int kTileDepth = 8;    // deepest subtree root
+constexpr int kTileDepth = 7;    // deepest subtree root
+constexpr int64_t kDeepPixels = 2500000;  // images from which subtree roots may lie that deep
 constexpr int kTileThreads = 512;
 
 // Sums of a node's channel values and squares.
@@ -613,10 +614,14 @@ mrh_status mrh_quadtree_build(mrh_quadtree* q, const uint8_t* rgb_dev, int32_t w
     const int32_t longer = std::max(width, height), shorter = std::min(width, height);
     const int tiles = tile_depth(longer);
     // Subtrees in LDS, unless the longer side asks for more subtree roots than the chip holds at once
-    // (256 at depth 4) and the shorter one leaves most of them nearly empty.  Whole builds, against the
-    // tables of the whole image: 640 x 480 43 us to 176, 640 x 10 33 to 80, 5120 x 640 431 to 564, but
-    // 5120 x 320 399 to 338 and 5120 x 160 384 to 241.
-    if (tiles <= 4 || (tiles <= kTileDepth && longer <= 8ll * shorter)) {
+    // (256 at depth 4) and the shorter one leaves most of them nearly empty, or there are so many
+    // (16384 at depth 7, four times as many one deeper) that they take longer than the tables, whose time goes
+    // with the pixels.  Whole builds, against the tables of the whole image: 640 x 480 69 us to 217,
+    // 641 x 480 (depth 5) 89 to 215, 1281 x 240 (6) 151 to 192, 2560 x 1440 186 to 571; depth 7: 2561 x 800 422 to
+    // 391, 3800 x 480 415 to 372, but 2561 x 1000 426 to 438, 3800 x 640 421 to 444, 5120 x 640 423 to 559;
+    // depth 8: 5121 x 800 1514 to 644, 5121 x 1600 1547 to 1242.
+    const bool deep_enough = tiles < kTileDepth || (tiles == kTileDepth && (int64_t)width * height >= kDeepPixels);
+    if (tiles <= 4 || (deep_enough && longer <= 8ll * shorter)) {
         hipLaunchKernelGGL(k_qt_sums, dim3(1u << (2 * tiles)), dim3(256), 0, s, rgb_dev, width, height, tiles, q->sums,
                            q->n_leaves);
         if (tiles > 4) hipLaunchKernelGGL(k_qt_reduce, dim3(1u << (2 * (tiles - 4))), dim3(256), 0, s, tiles, q->sums);

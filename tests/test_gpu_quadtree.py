@@ -86,3 +86,20 @@ def test_quadtree_subtrees(mrh, h, w, mn):
         # the contrast is an FP64 quotient of exact sums, rounded once to FP32
         assert np.allclose(gc[go], wc[oo], rtol=1e-6, atol=1e-6)
     qt.close()
+
+
+# (height, width, min size): on both sides of the line between the two forms where subtree roots lie at depth
+# 7 (2.5 million pixels), either side the longer, and beyond depth 7
+@pytest.mark.parametrize("h,w,mn", [(977, 2561, 6), (976, 2561, 6), (2561, 977, 6), (650, 5120, 6), (1000, 5121, 9)])
+def test_quadtree_large_images(mrh, h, w, mn):
+    announce(f"quadtree large {w}x{h}")
+    img = _image(np.random.default_rng(h + w), h, w, 64, 12.0)
+    qt = mrh.Quadtree(w, h)
+    want, wc, near = oracle.quadtree(img, 300.0, mn)
+    assert near == 0
+    leaves, con = qt.build(torch.from_numpy(img).cuda(), 300.0, mn)
+    got, gc = leaves.cpu().numpy(), con.cpu().numpy()
+    go, oo = np.lexsort(got.T[::-1]), np.lexsort(want.T[::-1])
+    assert np.array_equal(got[go], want[oo]), (len(got), len(want))
+    assert np.allclose(gc[go], wc[oo], rtol=1e-6, atol=1e-6)
+    qt.close()
