@@ -436,29 +436,29 @@ __global__ __launch_bounds__(kTileThreads) void k_qt_tree(const uint8_t* __restr
     __syncthreads();
     if (L.first_leaf < depth) return;
 
-    // summed-area tables: rows by shuffles (sums of a row of 40 fit 16 bits, two packed), then columns
+    // summed-area tables: rows by shuffles, then columns
 #pragma unroll
     for (int i = 0; i < kRows; ++i) {
         const int y = wave + i * kWaves;
-        uint32_t s01 = v[i][0] | v[i][1] << 16, s2 = v[i][2];
+        uint32_t s0 = v[i][0], s1 = v[i][1], s2 = v[i][2];
         uint32_t q0 = v[i][0] * v[i][0], q1 = v[i][1] * v[i][1], q2 = v[i][2] * v[i][2];
         for (int o = 1; o < kTileSide; o <<= 1) {
-            const uint32_t a = (uint32_t)__shfl_up((int)s01, o), b = (uint32_t)__shfl_up((int)s2, o);
+            const uint32_t a = (uint32_t)__shfl_up((int)s0, o), b = (uint32_t)__shfl_up((int)s1, o);
+            const uint32_t d = (uint32_t)__shfl_up((int)s2, o);
             const uint32_t e = (uint32_t)__shfl_up((int)q0, o), f = (uint32_t)__shfl_up((int)q1, o);
             const uint32_t g = (uint32_t)__shfl_up((int)q2, o);
-            if (lane >= o) s01 += a, s2 += b, q0 += e, q1 += f, q2 += g;
+            if (lane >= o) s0 += a, s1 += b, s2 += d, q0 += e, q1 += f, q2 += g;
         }
         if (lane < nd.w && y < nd.h) {
             const int at = (y + 1) * kTilePitch + lane + 1;
-            L.table[0][at] = s01 & 0xffffu;
-            L.table[1][at] = s01 >> 16;
+            L.table[0][at] = s0;
+            L.table[1][at] = s1;
             L.table[2][at] = s2;
             L.table[3][at] = q0;
             L.table[4][at] = q1;
             L.table[5][at] = q2;
         }
     }
-    static_assert(kTileSide * 255 < 1 << 16, "packed row sums");
     __syncthreads();
     if (t < 6 * kTilePitch) {
         const int plane = t / kTilePitch, x = t % kTilePitch;

@@ -103,3 +103,20 @@ def test_quadtree_large_images(mrh, h, w, mn):
     assert np.array_equal(got[go], want[oo]), (len(got), len(want))
     assert np.allclose(gc[go], wc[oo], rtol=1e-6, atol=1e-6)
     qt.close()
+
+
+@pytest.mark.parametrize("h,w", [(40, 40), (640, 640), (97, 203)])
+def test_quadtree_extreme_values(mrh, h, w):
+    """Channels of 0 and 255 only, the largest sums that a subtree holds."""
+    announce(f"quadtree of 0 and 255, {w}x{h}")
+    rng = np.random.default_rng(w)
+    for img in (np.full((h, w, 3), 255, np.uint8), np.where(rng.random((h, w, 3)) < 0.97, 255, 0).astype(np.uint8)):
+        qt = mrh.Quadtree(w, h)
+        want, wc, near = oracle.quadtree(img, 10.0, 1)
+        assert near == 0
+        leaves, con = qt.build(torch.from_numpy(img).cuda(), 10.0, 1)
+        got, gc = leaves.cpu().numpy(), con.cpu().numpy()
+        go, oo = np.lexsort(got.T[::-1]), np.lexsort(want.T[::-1])
+        assert np.array_equal(got[go], want[oo])
+        assert np.allclose(gc[go], wc[oo], rtol=1e-6, atol=1e-6)
+        qt.close()
