@@ -74,14 +74,16 @@ __global__ void k_reset(const DevMap* __restrict__ pm, uint32_t n_hash) {
 }
 
 // Rows of an extraction: the blocks in table order without those streamed out to the host store, and
-// the sum of the voxels before each.  Two launches, a workgroup per kExtractChunk ids: sums, then rows
-// (each workgroup adds up the sums before its own).  Against a copy of every descriptor to the host, a
+// the sum of the voxels before each.  Two launches over chunks of kExtractChunk ids, as far as blocks have been
+// handed out: sums, then rows (for each chunk the sums before it are added up).  Against a copy of every descriptor to the host, a
 // loop over them there and two uploads into new allocations.
 __device__ inline unsigned long long row_weight(uint32_t info) {  // rows << 40 | voxels
     if (info & kGoneBit) return 0ull;
     const int b = 3 * (3 - (int)((info >> kLevelShift) & 3u));
     return 1ull << 40 | ((info & kNoBlockBit) ? 0ull : 1ull << b);
 }
+
+__host__ __device__ inline uint32_t extract_chunks(uint32_t blocks) { return (blocks + kExtractChunk - 1) / kExtractChunk; }
 
 __device__ inline uint32_t block_count(const DevMap& m) {
     const uint32_t n = m.ctr->n_blocks;
@@ -90,72 +92,83 @@ __device__ inline uint32_t block_count(const DevMap& m) {
 
 __global__ __launch_bounds__(256) void k_extract_sums(const DevMap* __restrict__ pm, ExtractRow* __restrict__ rows) {
     const DevMap& m = *pm;
-    const uint32_t nb = block_count(m), id0 = blockIdx.x * kExtractChunk;
-    unsigned long long n = 0;
-#pragma unroll
-    for (uint32_t k = 0; k < kExtractChunk / 256; ++k) {
-        const uint32_t id = id0 + k * 256 + threadIdx.x;
-        n += id < nb ? row_weight(m.binfo[id]) : 0ull;
-    }
-    uint32_t r = (uint32_t)(n >> 40), v = (uint32_t)n;  // (a chunk has at most 2^20 voxels)
-    static_assert(kExtractChunk * 512ull < (1ull << 32), "chunk sums in 32 bits");
-    for (int o = 1; o < 64; o <<= 1) r += (uint32_t)__shfl_xor((int)r, o), v += (uint32_t)__shfl_xor((int)v, o);
+    const uint32_t nb = block_count(m);
     __shared__ uint32_t part[4][2];
-    if ((threadIdx.x & 63u) == 0) part[threadIdx.x >> 6][0] = r, part[threadIdx.x >> 6][1] = v;
-    __syncthreads();
-    if (threadIdx.x) return;
-    for (int w = 1; w < 4; ++w) r += part[w][0], v += part[w][1];
-    rows[m.max_blocks + blockIdx.x] = ExtractRow{(int64_t)v, r, 0u};
+    for (uint32_t chunk = blockIdx.x; chunk < extract_chunks(nb); chunk += gridDim.x) {
+        unsigned long long n = 0;
+#pragma unroll
+        for (uint32_t k = 0; k < kExtractChunk / 256; ++k) {
+            const uint32_t id = chunk * kExtractChunk + k * 256 + threadIdx.x;
+            n += id < nb ? row_weight(m.binfo[id]) : 0ull;
+        }
+        uint32_t r = (uint32_t)(n >> 40), v = (uint32_t)n;  // (a chunk has at most 2^20 voxels)
+        static_assert(kExtractChunk * 512ull < (1ull << 32), "chunk sums in 32 bits");
+        for (int o = 1; o < 64; o <<= 1) r += (uint32_t)__shfl_xor((int)r, o), v += (uint32_t)__shfl_xor((int)v, o);
+        if ((threadIdx.x & 63u) == 0) part[threadIdx.x >> 6][0] = r, part[threadIdx.x >> 6][1] = v;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < 4; ++w) r += part[w][0], v += part[w][1];
+            rows[m.max_blocks + chunk] = ExtractRow{(int64_t)v, r, 0u};
+        }
+        __syncthreads();
+    }
 }
 
-__global__ __launch_bounds__(256) void k_extract_rows(const DevMap* __restrict__ pm, ExtractRow* __restrict__ rows) {
+// total: where the number of rows and of voxels goes.
+__global__ __launch_bounds__(256) void k_extract_rows(const DevMap* __restrict__ pm, ExtractRow* __restrict__ rows,
+                                                      ExtractRow* __restrict__ total) {
     const DevMap& m = *pm;
-    const uint32_t nb = block_count(m), t = threadIdx.x, id0 = blockIdx.x * kExtractChunk + t * (kExtractChunk / 256);
+    const uint32_t nb = block_count(m), t = threadIdx.x, chunks = extract_chunks(nb);
     const ExtractRow* const sums = rows + m.max_blocks;
     __shared__ unsigned long long vbase[256];
     __shared__ uint32_t rbase[256];
-    // the chunks before this one, with this one's threads on top
-    unsigned long long v = 0;
-    uint32_t r = 0;
-    for (uint32_t i = t; i < blockIdx.x; i += 256) v += (unsigned long long)sums[i].off, r += sums[i].id;
-    vbase[t] = v;
-    rbase[t] = r;
-    __syncthreads();
-    for (uint32_t o = 128; o; o >>= 1) {
-        if (t < o) vbase[t] += vbase[t + o], rbase[t] += rbase[t + o];
+    if (nb == 0 && blockIdx.x == 0 && t == 0) *total = ExtractRow{0, 0u, 0u};
+    for (uint32_t chunk = blockIdx.x; chunk < chunks; chunk += gridDim.x) {
+        const uint32_t id0 = chunk * kExtractChunk + t * (kExtractChunk / 256);
+        // the chunks before this one, with this one's threads on top
+        unsigned long long v = 0;
+        uint32_t r = 0;
+        for (uint32_t i = t; i < chunk; i += 256) v += (unsigned long long)sums[i].off, r += sums[i].id;
+        vbase[t] = v;
+        rbase[t] = r;
         __syncthreads();
-    }
-    const unsigned long long v0 = vbase[0];
-    const uint32_t r0 = rbase[0];
-    uint32_t info[kExtractChunk / 256];
-    unsigned long long own = 0;
+        for (uint32_t o = 128; o; o >>= 1) {
+            if (t < o) vbase[t] += vbase[t + o], rbase[t] += rbase[t + o];
+            __syncthreads();
+        }
+        const unsigned long long v0 = vbase[0];
+        const uint32_t r0 = rbase[0];
+        uint32_t info[kExtractChunk / 256];
+        unsigned long long own = 0;
 #pragma unroll
-    for (uint32_t k = 0; k < kExtractChunk / 256; ++k) {
-        info[k] = id0 + k < nb ? m.binfo[id0 + k] : kGoneBit;
-        own += row_weight(info[k]);
-    }
-    __syncthreads();
-    vbase[t] = own & ((1ull << 40) - 1ull);
-    rbase[t] = (uint32_t)(own >> 40);
-    __syncthreads();
-    for (uint32_t o = 1; o < 256; o <<= 1) {
-        const unsigned long long a = t >= o ? vbase[t - o] : 0ull;
-        const uint32_t b = t >= o ? rbase[t - o] : 0u;
+        for (uint32_t k = 0; k < kExtractChunk / 256; ++k) {
+            info[k] = id0 + k < nb ? m.binfo[id0 + k] : kGoneBit;
+            own += row_weight(info[k]);
+        }
         __syncthreads();
-        vbase[t] += a;
-        rbase[t] += b;
+        vbase[t] = own & ((1ull << 40) - 1ull);
+        rbase[t] = (uint32_t)(own >> 40);
         __syncthreads();
-    }
-    v = v0 + (t ? vbase[t - 1] : 0ull);
-    r = r0 + (t ? rbase[t - 1] : 0u);
+        for (uint32_t o = 1; o < 256; o <<= 1) {
+            const unsigned long long a = t >= o ? vbase[t - o] : 0ull;
+            const uint32_t b = t >= o ? rbase[t - o] : 0u;
+            __syncthreads();
+            vbase[t] += a;
+            rbase[t] += b;
+            __syncthreads();
+        }
+        v = v0 + (t ? vbase[t - 1] : 0ull);
+        r = r0 + (t ? rbase[t - 1] : 0u);
 #pragma unroll
-    for (uint32_t k = 0; k < kExtractChunk / 256; ++k) {
-        const unsigned long long w = row_weight(info[k]);
-        if (w) rows[r] = ExtractRow{(int64_t)v, id0 + k, info[k]};
-        r += (uint32_t)(w >> 40);
-        v += w & ((1ull << 40) - 1ull);
+        for (uint32_t k = 0; k < kExtractChunk / 256; ++k) {
+            const unsigned long long w = row_weight(info[k]);
+            if (w) rows[r] = ExtractRow{(int64_t)v, id0 + k, info[k]};
+            r += (uint32_t)(w >> 40);
+            v += w & ((1ull << 40) - 1ull);
+        }
+        if (chunk == chunks - 1 && t == 255) *total = ExtractRow{(int64_t)v, r, 0u};
+        __syncthreads();
     }
-    if (blockIdx.x == gridDim.x - 1 && t == 255) rows[m.max_blocks + gridDim.x] = ExtractRow{(int64_t)v, r, 0u};
 }
 
 // Copy blocks out: keys, levels and (optionally) voxels from Morton to x-fastest order.  A workgroup takes
@@ -234,18 +247,18 @@ __global__ __launch_bounds__(256) void k_extract(const DevMap* __restrict__ pm, 
 }
 
 mrh_status scan_rows(mrh_map* m, const char* what, uint32_t& rows, int64_t& voxels) {
-    const uint32_t chunks = (m->dm.max_blocks + kExtractChunk - 1) / kExtractChunk;
+    const uint32_t chunks = extract_chunks(m->dm.max_blocks), grid = chunks < kExtractGrid ? chunks : kExtractGrid;
     mrh_status st = MRH_OK;
     if (!m->extract_rows)
         st = check_hip(m, hipMalloc((void**)&m->extract_rows, ((size_t)m->dm.max_blocks + chunks + 1) * sizeof(ExtractRow)), what);
     if (st != MRH_OK) return st;
-    hipLaunchKernelGGL(k_extract_sums, dim3(chunks), dim3(256), 0, m->stream, m->dmd, m->extract_rows);
-    hipLaunchKernelGGL(k_extract_rows, dim3(chunks), dim3(256), 0, m->stream, m->dmd, m->extract_rows);
+    ExtractRow* const end = m->extract_rows + m->dm.max_blocks + chunks;
+    hipLaunchKernelGGL(k_extract_sums, dim3(grid), dim3(256), 0, m->stream, m->dmd, m->extract_rows);
+    hipLaunchKernelGGL(k_extract_rows, dim3(grid), dim3(256), 0, m->stream, m->dmd, m->extract_rows, end);
     st = check_hip(m, hipGetLastError(), what);
     ExtractRow total{};
     if (st == MRH_OK)
-        st = check_hip(m, hipMemcpyAsync(&total, m->extract_rows + m->dm.max_blocks + chunks, sizeof(total), hipMemcpyDeviceToHost,
-                                         m->stream), what);
+        st = check_hip(m, hipMemcpyAsync(&total, end, sizeof(total), hipMemcpyDeviceToHost, m->stream), what);
     if (st == MRH_OK) st = check_hip(m, hipStreamSynchronize(m->stream), what);
     rows = total.id;
     voxels = total.off;

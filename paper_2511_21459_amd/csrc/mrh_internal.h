@@ -587,7 +587,8 @@ struct ExtractRow {
     int64_t off;
     uint32_t id, info;
 };
-constexpr uint32_t kExtractChunk = 2048;  // block ids per workgroup of the row scan
+constexpr uint32_t kExtractChunk = 2048;  // block ids a workgroup of the row scan takes at a time
+constexpr uint32_t kExtractGrid = 1024;   // workgroups of the row scan at most (of 2^21 ids without a second turn)
 constexpr uint32_t kExtractRows = 8;      // rows per workgroup of the copies
 
 // one profiled launch: kernel id and its bracketing events on the map's stream

@@ -236,3 +236,24 @@ def test_loaded_blocks_merge_by_their_variance(mrh, storage):
     got = {tuple(q): int(l) for q, l in zip(g.keys.tolist(), g.levels.tolist())}
     for q, l, lo in zip(keys.tolist(), levels.tolist(), low.tolist()):
         assert got[tuple(q)] == l + (1 if lo else 0), (q, l, lo)
+
+
+@pytest.mark.parametrize("n", [0, 1, 2048, 2049, 5000])
+def test_extract_from_a_large_table(mrh, n):
+    """Few blocks in a block table of 2^22: the row scan ends with the blocks that there are."""
+    announce(f"extract {n} blocks of a large table")
+    m = mrh.Map(voxel=0.05, levels=4, tau=0.15, max_blocks=1 << 22, heap_blocks=[16, 16, 8192, 8192])
+    k = np.arange(n)
+    keys = np.stack([k % 61, k // 61 % 61, k // 3721], 1).astype(np.int32) - 30
+    levels = (2 + (k % 3 == 0)).astype(np.uint8)
+    offs = np.concatenate([[0], np.cumsum((8 >> levels.astype(int)) ** 3)])
+    D = np.arange(offs[-1], dtype=np.float32)
+    if n:
+        assert m.load_blocks(keys, levels, D, np.ones(offs[-1], np.uint32), np.zeros(offs[-1], np.float32)) == n
+    assert m.counts() == (n, offs[-1])
+    e = {q: v.cpu().numpy() for q, v in m.extract().items()}
+    go, wo = np.lexsort(e["keys"].T), np.lexsort(keys.T)
+    assert np.array_equal(e["keys"][go], keys[wo]) and np.array_equal(e["levels"][go], levels[wo])
+    assert e["offsets"].shape == (n + 1,) and e["offsets"][-1] == offs[-1]
+    for g, w in zip(go, wo):
+        assert np.array_equal(e["D"][slice(*e["offsets"][g:g + 2])], D[slice(*offs[w:w + 2])])
