@@ -183,65 +183,67 @@ __global__ __launch_bounds__(256) void k_extract(const DevMap* __restrict__ pm, 
                                                  uint32_t* __restrict__ W, float* __restrict__ S2) {
     const DevMap& m = *pm;
     const int lane = threadIdx.x & 63, v = lane & 7, wave = (int)uniform(threadIdx.x >> 6);
-    const uint32_t row = blockIdx.x * kExtractRows + (lane >> 3);
     static_assert(kExtractRows * 8 == 64, "eight lanes per row");
-    ExtractRow e{0, 0u, kNoBlockBit};
-    if (row < nrows) e = rows[row];
-    if (wave == 0 && row < nrows) {
-        const int lvl = (int)((e.info >> kLevelShift) & 3u);
-        if (v == 0) {
-            if (keys) {
-                int32_t x, y, z;
-                unpack_key(m.bkey[e.id], x, y, z);
-                keys[3 * (size_t)row] = x;
-                keys[3 * (size_t)row + 1] = y;
-                keys[3 * (size_t)row + 2] = z;
+    for (uint32_t first = blockIdx.x * kExtractRows; first < nrows; first += gridDim.x * kExtractRows) {
+        const uint32_t row = first + (lane >> 3);
+        ExtractRow e{0, 0u, kNoBlockBit};
+        if (row < nrows) e = rows[row];
+        if (wave == 0 && row < nrows) {
+            const int lvl = (int)((e.info >> kLevelShift) & 3u);
+            if (v == 0) {
+                if (keys) {
+                    int32_t x, y, z;
+                    unpack_key(m.bkey[e.id], x, y, z);
+                    keys[3 * (size_t)row] = x;
+                    keys[3 * (size_t)row + 1] = y;
+                    keys[3 * (size_t)row + 2] = z;
+                }
+                if (levels) levels[row] = (e.info & kNoBlockBit) ? 0xFF : (uint8_t)lvl;
+                if (offsets) offsets[row] = e.off;
             }
-            if (levels) levels[row] = (e.info & kNoBlockBit) ? 0xFF : (uint8_t)lvl;
-            if (offsets) offsets[row] = e.off;
+            if (v == 1 && offsets && row == nrows - 1)
+                offsets[nrows] = e.off + (int64_t)(row_weight(e.info) & ((1ull << 40) - 1ull));
         }
-        if (v == 1 && offsets && row == nrows - 1)
-            offsets[nrows] = e.off + (int64_t)(row_weight(e.info) & ((1ull << 40) - 1ull));
-    }
-    if (!(D || W || S2)) return;
-    const bool block = !(e.info & kNoBlockBit);
-    const int lvl = (int)((e.info >> kLevelShift) & 3u);
-    auto out = [&](int64_t o, float d, uint32_t w, float s2) {
-        if (D) D[o] = d;
-        if (W) W[o] = w;
-        if (S2) S2[o] = s2;
-    };
-    // (the order of the eight voxels of a level-2 block is the same in both)
-    float d, s2;
-    uint32_t w;
-    if (wave == 0 && block && lvl == 2) {
-        Store<ST>::get(m, 2, (size_t)(e.info & kSlotMask) * 8 + v, d, w, s2);
-        out(e.off + v, d, w, s2);
-    } else if (wave == 0 && block && lvl == 3 && v == 0) {
-        Store<ST>::get(m, 3, (size_t)(e.info & kSlotMask), d, w, s2);
-        out(e.off, d, w, s2);
-    }
-    unsigned long long large = __ballot(block && lvl < 2 && v == 0);
-    for (int turn = 0; large; ++turn) {
-        const int src = __ffsll((long long)large) - 1;
-        large &= large - 1;
-        if ((turn & 3) != wave) continue;
-        const uint32_t info = (uint32_t)uniform(__shfl((int)e.info, src));
-        const int64_t off = (int64_t)((unsigned long long)(uint32_t)uniform(__shfl((int)(uint32_t)((unsigned long long)e.off >> 32), src)) << 32 |
-                                      (uint32_t)uniform(__shfl((int)(uint32_t)(unsigned long long)e.off, src)));
-        if (((info >> kLevelShift) & 3u) == 1u) {
-            const uint32_t p = spread3(lane & 3) | spread3((lane >> 2) & 3) << 1 | spread3(lane >> 4) << 2;
-            Store<ST>::get(m, 1, (size_t)(info & kSlotMask) * 64 + p, d, w, s2);
-            out(off + lane, d, w, s2);
-        } else {
-            const uint32_t p = spread3(lane & 7) | spread3(lane >> 3) << 1;
-            const size_t base = (size_t)(info & kSlotMask) * 512 + p;
-            float dd[8], ss[8];
-            uint32_t ww[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) Store<ST>::get(m, 0, base + (spread3(k) << 2), dd[k], ww[k], ss[k]);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) out(off + lane + 64 * k, dd[k], ww[k], ss[k]);
+        if (!(D || W || S2)) continue;
+        const bool block = !(e.info & kNoBlockBit);
+        const int lvl = (int)((e.info >> kLevelShift) & 3u);
+        auto out = [&](int64_t o, float d, uint32_t w, float s2) {
+            if (D) D[o] = d;
+            if (W) W[o] = w;
+            if (S2) S2[o] = s2;
+        };
+        // (the order of the eight voxels of a level-2 block is the same in both)
+        float d, s2;
+        uint32_t w;
+        if (wave == 0 && block && lvl == 2) {
+            Store<ST>::get(m, 2, (size_t)(e.info & kSlotMask) * 8 + v, d, w, s2);
+            out(e.off + v, d, w, s2);
+        } else if (wave == 0 && block && lvl == 3 && v == 0) {
+            Store<ST>::get(m, 3, (size_t)(e.info & kSlotMask), d, w, s2);
+            out(e.off, d, w, s2);
+        }
+        unsigned long long large = __ballot(block && lvl < 2 && v == 0);
+        for (int turn = 0; large; ++turn) {
+            const int src = __ffsll((long long)large) - 1;
+            large &= large - 1;
+            if ((turn & 3) != wave) continue;
+            const uint32_t info = (uint32_t)uniform(__shfl((int)e.info, src));
+            const int64_t off = (int64_t)((unsigned long long)(uint32_t)uniform(__shfl((int)(uint32_t)((unsigned long long)e.off >> 32), src)) << 32 |
+                                          (uint32_t)uniform(__shfl((int)(uint32_t)(unsigned long long)e.off, src)));
+            if (((info >> kLevelShift) & 3u) == 1u) {
+                const uint32_t p = spread3(lane & 3) | spread3((lane >> 2) & 3) << 1 | spread3(lane >> 4) << 2;
+                Store<ST>::get(m, 1, (size_t)(info & kSlotMask) * 64 + p, d, w, s2);
+                out(off + lane, d, w, s2);
+            } else {
+                const uint32_t p = spread3(lane & 7) | spread3(lane >> 3) << 1;
+                const size_t base = (size_t)(info & kSlotMask) * 512 + p;
+                float dd[8], ss[8];
+                uint32_t ww[8];
+    #pragma unroll
+                for (int k = 0; k < 8; ++k) Store<ST>::get(m, 0, base + (spread3(k) << 2), dd[k], ww[k], ss[k]);
+    #pragma unroll
+                for (int k = 0; k < 8; ++k) out(off + lane + 64 * k, dd[k], ww[k], ss[k]);
+            }
         }
     }
 }
@@ -498,7 +500,7 @@ mrh_status mrh_extract_blocks(mrh_map* map, int32_t* keys_dev, uint8_t* levels_d
         if (offsets_dev) return check_hip(map, hipMemcpy(offsets_dev, &nvox, 8, hipMemcpyHostToDevice), "extract");
         return MRH_OK;
     }
-    const dim3 grid((nout + kExtractRows - 1) / kExtractRows);
+    const dim3 grid(extract_grid(nout));
     auto run = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(256), 0, map->stream, map->dmd, map->extract_rows, nout, keys_dev, levels_dev,
                            offsets_dev, D_dev, W_dev, S2_dev);

@@ -589,7 +589,12 @@ struct ExtractRow {
 };
 constexpr uint32_t kExtractChunk = 2048;  // block ids a workgroup of the row scan takes at a time
 constexpr uint32_t kExtractGrid = 1024;   // workgroups of the row scan at most (of 2^21 ids without a second turn)
-constexpr uint32_t kExtractRows = 8;      // rows per workgroup of the copies
+constexpr uint32_t kExtractRows = 8;      // rows a workgroup of the copies takes at a time
+// Workgroups of the copies: a launch holds fewer than 2^32 threads, which 2^27 rows would need.
+inline uint32_t extract_grid(uint32_t rows) {
+    const uint32_t n = (rows + kExtractRows - 1) / kExtractRows;
+    return n < (1u << 22) ? n : 1u << 22;
+}
 
 // one profiled launch: kernel id and its bracketing events on the map's stream
 struct ProfRec {
