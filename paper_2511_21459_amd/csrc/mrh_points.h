@@ -854,12 +854,26 @@ __device__ inline TaskOut apply_new(const DevMap& m, uint32_t id, uint32_t info,
     return out;
 }
 
-// Blocks a task of level 0 or 1 holds.  A scan touches few of a block's lane groups (a ray about 5 of 64),
-// so a wave takes kApplyBlocks blocks and gives each touched group (level 1: voxel) a lane: the chain of
-// reads (queue entry, touch mask and sums, accumulators and state) is walked once for them all, where a
+// Blocks a task of level 0 or 1 holds at most.  A scan touches few of a block's lane groups (a ray about 5 of
+// 64), so a wave takes up to kApplyBlocks blocks and gives each touched group (level 1: voxel) a lane: the chain
+// of reads (queue entry, touch mask and sums, accumulators and state) is walked once for them all, where a
 // wave per block walked it for every block with most of its lanes idle (131072 points on a settled map:
 // 195 -> 153 us; bf16, 31 x 1023: 313 -> 241 us).
 constexpr int kApplyBlocks = 8;
+
+// Blocks per task: one until there are more blocks than kApplyWaves, then as many as keep the tasks below
+// that.  With fewer tasks a launch lasts as long as one wave goes through the groups of its blocks one after
+// the other: a scan of 8000 points without carving (1200 blocks of one level) 45 us with eight blocks per task, 14 with
+// one.  10 waves per CU, not the 16 that it holds: the merges of a wave share their atomics (2000 points without
+// carving on a street, second scan, 2900 blocks: 73 us with one block per task, 41 with two).  By the map's
+// own counts, in a batch too, so that a block's sums are added in one order.
+constexpr uint32_t kApplyWaves = 2560;
+__device__ inline uint32_t apply_blocks_per_task(const TaskCounts& c) {
+    const uint32_t n = c.n[0] + c.n[1];
+    uint32_t per = 1;
+    while (per < (uint32_t)kApplyBlocks && n > per * kApplyWaves) per *= 2;
+    return per;
+}
 
 struct ApplyLds {  // one wave's
     unsigned long long touched[kApplyBlocks];
@@ -884,10 +898,10 @@ __device__ inline int nth_bit(unsigned long long x, int k) {
 
 template <int ST, int LEVEL, bool WIDE>
 __device__ inline TaskOut apply_blocks(const DevMap& m, const u32x4 MRH_GLOBAL* list, uint32_t count, uint32_t group,
-                                       int par, DeferList* dl, ApplyLds& A) {
+                                       uint32_t per, int par, DeferList* dl, ApplyLds& A) {
     const int lane = lane_id();
-    const uint32_t bi = group * (uint32_t)kApplyBlocks + (uint32_t)lane;
-    const bool live = lane < kApplyBlocks && bi < count;
+    const uint32_t bi = group * per + (uint32_t)lane;
+    const bool live = (uint32_t)lane < per && bi < count;
     uint32_t id = 0, info = 0, bvc = 0;
     unsigned long long touched = 0ull;
     double bvs = 0.0;
@@ -1060,11 +1074,11 @@ __device__ inline TaskOut apply_packed(const DevMap& m, const u32x4 MRH_GLOBAL* 
     return out;
 }
 
-// A scan's update task space: [queued level-0 blocks | level-1 blocks, both in groups of kApplyBlocks |
+// A scan's update task space: [queued level-0 blocks | level-1 blocks, both in groups of apply_blocks_per_task |
 // level-2 blocks in groups of 8 | level-3 blocks in groups of 64] (new blocks are queued like the others).
 __device__ inline uint32_t points_task_count(const TaskCounts& c) {
-    return (c.n[0] + kApplyBlocks - 1) / kApplyBlocks + (c.n[1] + kApplyBlocks - 1) / kApplyBlocks + (c.n[2] + 7) / 8 +
-           (c.n[3] + 63) / 64;
+    const uint32_t per = apply_blocks_per_task(c);
+    return (c.n[0] + per - 1) / per + (c.n[1] + per - 1) / per + (c.n[2] + 7) / 8 + (c.n[3] + 63) / 64;
 }
 
 // One of its tasks.  Merges of level-0 / level-1 blocks are recorded in *dl, which has room for those of one
@@ -1073,10 +1087,10 @@ template <int ST, bool WIDE>
 __device__ inline TaskOut points_update_task(const DevMap& m, uint32_t t, const TaskCounts& c, int par, DeferList* dl,
                                              ApplyLds& A) {
     const uint32_t* n = c.n;
-    const uint32_t g0 = (n[0] + kApplyBlocks - 1) / kApplyBlocks, g1 = (n[1] + kApplyBlocks - 1) / kApplyBlocks;
-    if (t < g0) return apply_blocks<ST, 0, WIDE>(m, m.vis[0], n[0], t, par, dl, A);
+    const uint32_t per = apply_blocks_per_task(c), g0 = (n[0] + per - 1) / per, g1 = (n[1] + per - 1) / per;
+    if (t < g0) return apply_blocks<ST, 0, WIDE>(m, m.vis[0], n[0], t, per, par, dl, A);
     t -= g0;
-    if (t < g1) return apply_blocks<ST, 1, WIDE>(m, m.vis[1], n[1], t, par, dl, A);
+    if (t < g1) return apply_blocks<ST, 1, WIDE>(m, m.vis[1], n[1], t, per, par, dl, A);
     t -= g1;
     const uint32_t g2 = (n[2] + 7) / 8;
     const int level = t < g2 ? 2 : 3;

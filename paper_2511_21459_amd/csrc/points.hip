@@ -61,9 +61,14 @@ __global__ __launch_bounds__(256) void k_apply_points(const DevMap* __restrict__
 // Rays per workgroup of a scan's allocation and ray launches.  The ray launch's LDS tables gain from many rays,
 // but below some eight workgroups per CU a launch lasts as long as one of them.  Ray launch: 8000 rays 190 us by
 // 16, 146 by 4, 162 by 2; 31713 rays 366 by 16, 324 by 8, 349 by 4; 131072 rays 508 by 16, 522 by 8.
-// Allocation, mean of three scans: 8000 rays 63 us by 16, 49 by 4; 31713 rays 93 by 16, 85 by 8.  (A batch's
-// scans share the chip: always kRaysPerGroup.)
-static int32_t rays_per_group(int64_t n) { return n < (1 << 14) ? 4 : (n < (1 << 16) ? 8 : kRaysPerGroup); }
+// Allocation, mean of three scans: 8000 rays 63 us by 16, 49 by 4; 31713 rays 93 by 16, 85 by 8.  Without carving a
+// ray has a few blocks only, of which 16 rays just fill a wave: 8000 rays on a street 24 + 27 us (allocation
+// and rays of the first scan) by 4, 14 + 17 by 16; 31713 rays 33 + 50 by 8, 26 + 39 by 16.  (A batch's scans
+// share the chip: always kRaysPerGroup.)
+static int32_t rays_per_group(const mrh_map* map, int64_t n) {
+    if (!map->cfg.carve) return kRaysPerGroup;
+    return n < (1 << 14) ? 4 : (n < (1 << 16) ? 8 : kRaysPerGroup);
+}
 
 // Blocks a ray's walk can visit: the guard of the block walk bounds it by 4 + the sum over the
 // axes of the cells the segment spans (carving: up to max_range + tau long; otherwise 2 tau).
@@ -139,7 +144,7 @@ extern "C" mrh_status mrh_integrate_points(mrh_map* map, const float* xyz_dev, i
     if (!pose_from(T_ws, sp.P)) return set_error(map, MRH_ERR_INVALID_ARG, "non-finite pose");
     sp.xyz = global(xyz_dev);
     sp.n = n;
-    sp.rays = rays_per_group(n);
+    sp.rays = rays_per_group(map, n);
     mrh_status st = ensure_lidar(map, n);
     if (st != MRH_OK) return st;
     sp.parity = (int32_t)(map->frames & 1u);

@@ -208,3 +208,21 @@ def test_refused_scan_leaves_the_map_usable(mrh, orc):
         last, _ = g.sync()
         assert last["observations"] == o.integrate_points(pts, T)["observations"]
     compare_maps(gpu_sorted(g), o.extract(), excused=excused_keys(o), tau=cfg["tau"])
+
+
+@pytest.mark.parametrize("n", [2560, 2561, 5121, 10241])
+def test_blocks_per_task(mrh, orc, n):
+    """Scans that touch n blocks each, on both sides of the counts at which an update task takes more blocks: a
+    point in the middle of each, without carving; four scans, so that half of the blocks merge."""
+    announce(f"{n} blocks per scan")
+    cfg = dict(CFG, carve=False, var_thr=0.02 ** 2, max_blocks=1 << 15, hash_slots=1 << 16)
+    k = np.arange(n)
+    keys = np.stack([k % 25 - 12, k // 25 % 25 - 12, 4 + k // 625], 1)
+    rng = np.random.default_rng(n)
+    T = np.eye(4)
+    scans = []
+    for _ in range(4):
+        far = rng.normal(0.0, np.where(k % 2 == 0, 0.001, 0.05))  # along the ray: small and large variances
+        p = (keys + 0.5) * 0.4
+        scans.append(((p * (1.0 + np.clip(far, -0.05, 0.05) / np.linalg.norm(p, axis=1))[:, None]).astype(np.float32), T))
+    assert _scans_match(mrh, orc, cfg, scans) > n // 4
