@@ -385,7 +385,7 @@ mrh_status mrh_map_create(const mrh_config* cfg, void* stream, mrh_map** out) {
         alloc(&d.S2[n], nv * pb, "variance heap");
         if (c.color) alloc(&d.C[n], nv * 12, "colour heap");
     }
-    m->partials_cap = 1024;
+    m->partials_cap = 2048;
     alloc(&m->partials, (size_t)m->partials_cap * 6 * 8, "reduction partials");
     alloc(&m->pose_out, 6 * 8, "pose gradient");
     alloc(&m->count_dev, 8, "extraction counter");

@@ -343,6 +343,19 @@ __device__ inline int rank_in_mask(unsigned long long mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
 }
 
+// The position of the k-th set bit of x (k below its bit count).
+__device__ inline int nth_bit(unsigned long long x, int k) {
+    uint32_t lo = (uint32_t)x;
+    int pos = 0;
+    const int c = __popc(lo);
+    if (k >= c) k -= c, lo = (uint32_t)(x >> 32), pos = 32;
+    for (int w = 16; w > 0; w >>= 1) {
+        const int n = __popc(lo & ((1u << w) - 1u));
+        if (k >= n) k -= n, lo >>= w, pos += w;
+    }
+    return pos;
+}
+
 __device__ inline unsigned long long shfl_u64(unsigned long long v, int src) {
     const uint32_t lo = __shfl((int)(uint32_t)v, src), hi = __shfl((int)(uint32_t)(v >> 32), src);
     return ((unsigned long long)hi << 32) | lo;

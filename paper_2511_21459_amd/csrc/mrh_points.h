@@ -883,19 +883,6 @@ struct ApplyLds {  // one wave's
     uint32_t first[kApplyBlocks + 1];
 };
 
-// The position of the k-th set bit of x (k below its bit count).
-__device__ inline int nth_bit(unsigned long long x, int k) {
-    uint32_t lo = (uint32_t)x;
-    int pos = 0;
-    const int c = __popc(lo);
-    if (k >= c) k -= c, lo = (uint32_t)(x >> 32), pos = 32;
-    for (int w = 16; w > 0; w >>= 1) {
-        const int n = __popc(lo & ((1u << w) - 1u));
-        if (k >= n) k -= n, lo >>= w, pos += w;
-    }
-    return pos;
-}
-
 template <int ST, int LEVEL, bool WIDE>
 __device__ inline TaskOut apply_blocks(const DevMap& m, const u32x4 MRH_GLOBAL* list, uint32_t count, uint32_t group,
                                        uint32_t per, int par, DeferList* dl, ApplyLds& A) {

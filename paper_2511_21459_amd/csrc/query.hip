@@ -42,13 +42,8 @@ __device__ inline HashSlot block_slot(const DevMap& m, int32_t x, int32_t y, int
     return follow_slot(m, key, h, load_slot(m, h));
 }
 
-template <int ST, bool GRAD>
-__device__ inline QueryResult query_point(const DevMap& m, const double x[3], bool strict) {
-    QueryResult q;
-    q.valid = false;
-    q.sdf = 0.0;
-    q.grad[0] = q.grad[1] = q.grad[2] = 0.0;
-    const int c = lane_id() & 3;
+// The row of the point's block, NOBLOCK where it has none.
+__device__ inline uint32_t home_row(const DevMap& m, const double x[3]) {
     int32_t b[3];
     bool in_range = true;
     for (int k = 0; k < 3; ++k) {
@@ -56,10 +51,20 @@ __device__ inline QueryResult query_point(const DevMap& m, const double x[3], bo
         in_range = in_range && __builtin_fabs(fb) <= (double)kKeyLimit;
         b[k] = (int32_t)fb;
     }
+    return in_range ? block_slot(m, b[0], b[1], b[2]).info : kNoBlockBit;
+}
+
+template <int ST, bool GRAD>
+__device__ inline QueryResult query_point(const DevMap& m, const double x[3], uint32_t info, bool strict) {
+    QueryResult q;
+    q.valid = false;
+    q.sdf = 0.0;
+    q.grad[0] = q.grad[1] = q.grad[2] = 0.0;
+    const int c = lane_id() & 3;
     // uniform over the group, so its lanes leave together and the sums below see all 4
-    if (!in_range) return q;
-    const uint32_t info = block_slot(m, b[0], b[1], b[2]).info;
     if (info & kNoBlockBit) return q;
+    int32_t b[3];
+    for (int k = 0; k < 3; ++k) b[k] = (int32_t)__builtin_floor(x[k] * m.invB);
     const int n = (int)((info >> kLevelShift) & 3u), shift = 3 - n;
     // lattice cell, fractions, and this lane's corners: lattice points cell + (dx, dy, 0 and 1), each in
     // block cell >> shift (floor division by the block side)
@@ -145,6 +150,66 @@ __device__ inline void world_point(const QueryParams& qp, const float* pts, int6
 
 constexpr int kQueryPoints = 64;  // points per 256-thread workgroup
 
+// Batches of at least kQueryMany points: a wave first looks up the blocks of 64 points, a lane each, and then goes
+// on with those that have one, four lanes each (src, of the 64).  A batch that fills the chip is bound by VALU issue
+// or by the lines met, and four lanes that repeat a lookup cost what they save in a small one.  1M / 4M points on a
+// 1 cm room, us, one lane per point / four / this: off the map 17 / 23 / 16 and 48 / 72 / 41; over the map's box
+// 59 / 39 / 30 and 193 / 132 / 91; random on the map 142 / 75 / 77 and 539 / 276 / 283; with the adjoint in block
+// order 93 / 95 / 86 and 238 / 267 / 214, off the map 42 / 58 / 44 and 66 / 132 / 70.  32 points per wave: off the
+// map 17 and 47, over its box 32 and 94.  Below kQueryMany forward queries gain nothing from the lookup apart (262144
+// points: random on a street 33 us by it, 31 by four lanes; over a box 17 and 22; off the map 15 either way).  The
+// adjoint, whose fewer workgroups loop, has it from kAdjointMany points on: 131072 off the map 36 us by one lane
+// per point, 40 by four, 36 by it; over a street's box 46, 43 and 39; on the street 63, 50 and 55.
+constexpr int64_t kQueryMany = 1 << 19, kAdjointMany = 1 << 17;
+constexpr int kQueryWave = 64;
+
+template <typename F>
+__device__ inline void query_many(const DevMap& m, const QueryParams& qp, const float* __restrict__ pts, int64_t n, F&& point) {
+    const int lane = lane_id();
+    const int64_t stride = (int64_t)gridDim.x * 4 * kQueryWave;
+    for (int64_t first = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kQueryWave; first < n; first += stride) {
+        const bool on = first + lane < n;
+        double x[3] = {0.0, 0.0, 0.0};
+        uint32_t info = kNoBlockBit;
+        if (on) {
+            world_point(qp, pts, first + lane, x);
+            info = home_row(m, x);
+        }
+        const unsigned long long present = __ballot(!(info & kNoBlockBit));
+        if (on && (info & kNoBlockBit)) point(first + lane, x, kNoBlockBit, false);
+        const int count = __popcll(present);
+        for (int k = 0; k < count; k += kQueryWave / 4) {
+            const int at = k + (lane >> 2);
+            const int src = count == kQueryWave ? at : nth_bit(present, min(at, count - 1));
+            double xs[3];
+            for (int a = 0; a < 3; ++a) xs[a] = __shfl(x[a], src);
+            const uint32_t is = (uint32_t)__shfl((int)info, src);
+            if (at < count) point(first + src, xs, is, true);
+        }
+    }
+}
+
+template <int ST, bool GRAD>
+__global__ __launch_bounds__(256, 8) void k_query_many(const DevMap* __restrict__ pm, QueryParams qp, const float* __restrict__ pts,
+                                                       int64_t n, float* sdf, uint8_t* valid, float* grad) {
+    const DevMap& m = *pm;
+    const int c = lane_id() & 3;
+    query_many(m, qp, pts, n, [&](int64_t i, const double x[3], uint32_t info, bool present) {
+        if (!present) {
+            sdf[i] = 0.f;
+            valid[i] = 0;
+            if (GRAD) grad[3 * i] = grad[3 * i + 1] = grad[3 * i + 2] = 0.f;
+            return;
+        }
+        const QueryResult q = query_point<ST, GRAD>(m, x, info, qp.strict != 0);
+        if (c == 0) {
+            sdf[i] = (float)q.sdf;
+            valid[i] = q.valid ? 1 : 0;
+        }
+        if (GRAD && c < 3) grad[3 * i + c] = (float)(c == 0 ? q.grad[0] : c == 1 ? q.grad[1] : q.grad[2]);
+    });
+}
+
 template <int ST, bool GRAD>
 __global__ __launch_bounds__(256) void k_query(const DevMap* __restrict__ pm, QueryParams qp, const float* __restrict__ pts,
                                                int64_t n, float* sdf, uint8_t* valid, float* grad) {
@@ -154,7 +219,7 @@ __global__ __launch_bounds__(256) void k_query(const DevMap* __restrict__ pm, Qu
     for (int64_t i = (int64_t)blockIdx.x * kQueryPoints + (threadIdx.x >> 2); i < n; i += stride) {
         double x[3];
         world_point(qp, pts, i, x);
-        const QueryResult q = query_point<ST, GRAD>(m, x, qp.strict != 0);
+        const QueryResult q = query_point<ST, GRAD>(m, x, home_row(m, x), qp.strict != 0);
         if (c == 0) {
             sdf[i] = (float)q.sdf;
             valid[i] = q.valid ? 1 : 0;
@@ -165,19 +230,16 @@ __global__ __launch_bounds__(256) void k_query(const DevMap* __restrict__ pm, Qu
 
 // Backward: per point dL/dx = g_i * d sdf / dx; dL/dp = R^T dL/dx.  Of a point's pose terms lane 0 of the
 // group sums dL/dx and lane 1 x cross dL/dx; then per workgroup in a fixed order into FP64 partials.
-template <int ST>
+template <int ST, bool MANY>
 __global__ __launch_bounds__(256) void k_query_backward(const DevMap* __restrict__ pm, QueryParams qp, const float* __restrict__ pts,
                                                         int64_t n, const float* __restrict__ gsdf, float* gpts,
                                                         double* partials) {
     const DevMap& m = *pm;
     const int c = lane_id() & 3;
     double acc[3] = {0.0, 0.0, 0.0};
-    const int64_t stride = (int64_t)gridDim.x * kQueryPoints;
-    for (int64_t i = (int64_t)blockIdx.x * kQueryPoints + (threadIdx.x >> 2); i < n; i += stride) {
-        double x[3];
-        world_point(qp, pts, i, x);
+    auto add = [&](int64_t i, const double x[3], uint32_t info) {
         const float gi = gsdf[i];
-        const QueryResult q = query_point<ST, true>(m, x, qp.strict != 0);
+        const QueryResult q = query_point<ST, true>(m, x, info, qp.strict != 0);
         double g[3] = {0.0, 0.0, 0.0};
         if (q.valid) {
             const double gs = (double)gi;
@@ -190,6 +252,26 @@ __global__ __launch_bounds__(256) void k_query_backward(const DevMap* __restrict
         }
         const double t[3] = {x[1] * g[2] - x[2] * g[1], x[2] * g[0] - x[0] * g[2], x[0] * g[1] - x[1] * g[0]};
         for (int k = 0; k < 3; ++k) acc[k] += c == 0 ? g[k] : t[k];
+    };
+    if (MANY) {
+        uint32_t inf = 0u;  // axes on which a point without a block is not finite: x cross 0 is NaN then
+        query_many(m, qp, pts, n, [&](int64_t i, const double x[3], uint32_t info, bool present) {
+            if (present) {
+                add(i, x, info);
+                return;
+            }
+            gpts[3 * i] = gpts[3 * i + 1] = gpts[3 * i + 2] = 0.f;
+            for (int k = 0; k < 3; ++k) inf |= (__builtin_fabs(x[k]) < __builtin_inf() ? 0u : 1u) << k;
+        });
+        for (int k = 0; k < 3; ++k)
+            if (__any((inf & ~(1u << k)) != 0u) && c == 1) acc[k] = __builtin_nan("");
+    } else {
+        const int64_t stride = (int64_t)gridDim.x * kQueryPoints;
+        for (int64_t i = (int64_t)blockIdx.x * kQueryPoints + (threadIdx.x >> 2); i < n; i += stride) {
+            double x[3];
+            world_point(qp, pts, i, x);
+            add(i, x, home_row(m, x));
+        }
     }
     __shared__ double red[kQueryPoints][6];
     if (c < 2)
@@ -244,12 +326,20 @@ extern "C" mrh_status mrh_query_sdf(mrh_map* map, const float* pts_dev, int64_t 
     if (!pts_dev || !sdf_dev || !valid_dev) return MRH_ERR_INVALID_ARG;
     QueryParams qp;
     if (!make_params(T_wq, strict, qp)) return set_error(map, MRH_ERR_INVALID_ARG, "non-finite query pose");
-    const int64_t blocks = (n + kQueryPoints - 1) / kQueryPoints;
+    const int64_t per = n >= kQueryMany ? 4 * kQueryWave : kQueryPoints, blocks = (n + per - 1) / per;
     const unsigned grid = (unsigned)(blocks < 65536 ? blocks : 65536);
     launch(map, K_QUERY, [&] {
         auto go = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, map->stream, map->dmd, qp, pts_dev, n, sdf_dev, valid_dev, grad_dev);
         };
+        if (n >= kQueryMany) {
+            switch (map->cfg.storage) {
+                case MRH_STORE_F16: grad_dev ? go(k_query_many<MRH_STORE_F16, true>) : go(k_query_many<MRH_STORE_F16, false>); break;
+                case MRH_STORE_BF16: grad_dev ? go(k_query_many<MRH_STORE_BF16, true>) : go(k_query_many<MRH_STORE_BF16, false>); break;
+                default: grad_dev ? go(k_query_many<MRH_STORE_F32, true>) : go(k_query_many<MRH_STORE_F32, false>);
+            }
+            return;
+        }
         switch (map->cfg.storage) {
             case MRH_STORE_F16: grad_dev ? go(k_query<MRH_STORE_F16, true>) : go(k_query<MRH_STORE_F16, false>); break;
             case MRH_STORE_BF16: grad_dev ? go(k_query<MRH_STORE_BF16, true>) : go(k_query<MRH_STORE_BF16, false>); break;
@@ -268,13 +358,17 @@ extern "C" mrh_status mrh_query_sdf_backward(mrh_map* map, const float* pts_dev,
     if (!make_params(T_wq, strict, qp)) return set_error(map, MRH_ERR_INVALID_ARG, "non-finite query pose");
     for (int k = 0; k < 6; ++k) grad_pose_host[k] = 0.0;
     if (n == 0) return MRH_OK;
-    const int64_t blocks = (n + kQueryPoints - 1) / kQueryPoints;
+    const bool many = n >= kAdjointMany;
+    const int64_t per = many ? 4 * kQueryWave : kQueryPoints, blocks = (n + per - 1) / per;
     const int grid = (int)(blocks < map->partials_cap ? blocks : map->partials_cap);
     launch(map, K_QUERY_BACKWARD, [&] {
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, map->stream, map->dmd, qp, pts_dev, n, grad_sdf_dev, grad_pts_dev, map->partials);
+        };
         switch (map->cfg.storage) {
-            case MRH_STORE_F16: hipLaunchKernelGGL(k_query_backward<MRH_STORE_F16>, dim3(grid), dim3(256), 0, map->stream, map->dmd, qp, pts_dev, n, grad_sdf_dev, grad_pts_dev, map->partials); break;
-            case MRH_STORE_BF16: hipLaunchKernelGGL(k_query_backward<MRH_STORE_BF16>, dim3(grid), dim3(256), 0, map->stream, map->dmd, qp, pts_dev, n, grad_sdf_dev, grad_pts_dev, map->partials); break;
-            default: hipLaunchKernelGGL(k_query_backward<MRH_STORE_F32>, dim3(grid), dim3(256), 0, map->stream, map->dmd, qp, pts_dev, n, grad_sdf_dev, grad_pts_dev, map->partials);
+            case MRH_STORE_F16: many ? go(k_query_backward<MRH_STORE_F16, true>) : go(k_query_backward<MRH_STORE_F16, false>); break;
+            case MRH_STORE_BF16: many ? go(k_query_backward<MRH_STORE_BF16, true>) : go(k_query_backward<MRH_STORE_BF16, false>); break;
+            default: many ? go(k_query_backward<MRH_STORE_F32, true>) : go(k_query_backward<MRH_STORE_F32, false>);
         }
     });
     launch(map, K_REDUCE, [&] {

@@ -136,6 +136,63 @@ def test_query_group_edges(mrh, storage, strict):
                     assert torch.equal(a, b[:n]), (n, grad)
 
 
+@pytest.mark.parametrize("storage", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("strict", [False, True])
+def test_query_large_batches(mrh, storage, strict):
+    """A query of many points gives each what queries of few give it, at the sizes where the lookup of 64 points per
+    wave begins and ends, with waves whose points all have a block, some, one or none; the adjoint's pose gradient is
+    the same sum in another order (FP64, 6e5 terms: 1e-9 of the terms' absolute sum is far above its rounding)."""
+    announce(f"large query batches {storage} strict={strict}")
+    depths, cam, poses, _ = room_sequence(width=160, height=120, f=131.0, frames=[0, 5, 10, 15])
+    m = mrh.Map(**dict(configs.ROOM, max_blocks=1 << 15, hash_slots=1 << 16, storage=storage))
+    for k in range(len(depths)):
+        m.integrate_depth(_dev(depths[k]), cam.K, poses[k])
+    keys = m.extract(voxels=False)["keys"].cpu().numpy()
+    rng = np.random.default_rng(4)
+    size = (1 << 19) + 70001
+    pts = (keys[rng.integers(0, len(keys), size)] + rng.random((size, 3))) * 8 * configs.ROOM["voxel"]
+    share = np.repeat(rng.choice([0.0, 0.02, 0.5, 1.0], size // 64 + 1), 64)[:size]
+    pts[rng.random(size) < share] += 500.0
+    far = rng.integers(0, size, 50)
+    pts[far] = rng.choice([1e30, -3e7, 3e38], (50, 3))
+    pts, up = _dev(pts.astype(np.float32)), _dev(rng.standard_normal(size).astype(np.float32))
+    T = np.eye(4)
+    T[:2, :2] = [[0.8, -0.6], [0.6, 0.8]]
+    few = 100000
+    parts = [slice(a, min(a + few, size)) for a in range(0, size, few)]
+    for pose in (None, T):
+        apart = [m.query(pts[s].contiguous(), T=pose, strict=strict, with_grad=True) for s in parts]
+        want = [torch.cat(c) for c in zip(*apart)]
+        assert want[1].any() and not want[1].all()
+        for n in ((1 << 19) - 1, 1 << 19, (1 << 19) + 1, (1 << 19) + 65, size):
+            for grad in (False, True):
+                got = m.query(pts[:n].contiguous(), T=pose, strict=strict, with_grad=grad)
+                for a, b in zip(got, want):
+                    assert a is None or torch.equal(a, b[:n]), (n, grad)
+        gp, pg = [], []
+        for s in parts:
+            g, p6 = m.query_backward(pts[s].contiguous(), up[s].contiguous(), T=pose, strict=strict)
+            gp.append(g)
+            pg.append(np.asarray(p6))
+        gp = torch.cat(gp)
+        bound = float((gp.double().abs().sum(dim=1) * (1.0 + 2.0 * pts.double().abs().sum(dim=1))).sum())
+        g, p6 = m.query_backward(pts, up, T=pose, strict=strict)
+        assert torch.equal(g, gp)
+        assert np.abs(np.asarray(p6) - sum(pg)).max() <= 1e-9 * bound
+        # a point that is not finite: the pose terms that it enters by x cross dL/dx are NaN, as in small batches
+        odd = pts.clone()
+        for rows, value in ((slice(300, 301), (1.0, float("nan"), 2.0)), (slice(size - 1, size), (-float("inf"), 1.0, 2.0))):
+            odd[rows] = torch.tensor(value, device=odd.device)
+            for b, s in ((odd, slice(0, size)), (odd, slice(max(0, rows.start - 200), rows.stop))):
+                got = m.query(b[s].contiguous(), T=None, strict=strict)
+                assert not got[1][rows.start - s.start] and got[0][rows.start - s.start] == 0
+                bad = np.isnan(m.query_backward(b[s].contiguous(), up[s].contiguous(), T=None, strict=strict)[1])
+                axes = ~np.isfinite(odd[s].cpu().numpy()).all(axis=0)
+                assert list(bad) == [False] * 3 + [bool(axes[(k + 1) % 3] or axes[(k + 2) % 3]) for k in range(3)]
+        for n in ((1 << 17) - 1, 1 << 17, (1 << 17) + 1):
+            assert torch.equal(m.query_backward(pts[:n].contiguous(), up[:n].contiguous(), T=pose, strict=strict)[0], gp[:n]), n
+
+
 def _one_line(rng, n, lo, hi):
     """n points along one direction: every ray crosses the same voxels."""
     d = np.array([0.48, 0.6, 0.64])
