@@ -429,7 +429,7 @@ def points_region(T_ws, radius: float) -> "_lib.MrhRegion":
 
 
 class Batch:
-    """Many maps fused together: one frame per map per ``integrate`` call, at most four launches in
+    """Many maps fused together: one frame per map per ``integrate`` call, at most five launches in
     total, replayed from a captured HIP graph while the frame kinds and sizes stay the same."""
 
     def __init__(self, maps):

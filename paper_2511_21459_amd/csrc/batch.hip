@@ -180,9 +180,9 @@ __global__ __launch_bounds__(256) void k_batch_update(const DevMap* __restrict__
         c.n_new = uniform(c.n_new);
         if constexpr (KIND == MRH_FRAME_DEPTH) {
             const DepthFrame fr = *(const DepthFrame*)&ce[lo].df;
-            ts.add_uniform(depth_update_task<ST, false>(maps[lo], fr, nullptr, local, c));
+            ts.add(depth_update_task<ST, false>(maps[lo], fr, nullptr, local, c));
         } else {
-            ts.add_uniform(points_update_task<ST, WIDE>(maps[lo], local, c, ((const BatchEntry*)&ce[lo])->sp.parity, &dl, alds[wv]));
+            ts.add(points_update_task<ST, WIDE>(maps[lo], local, c, ((const BatchEntry*)&ce[lo])->sp.parity, &dl, alds[wv]));
         }
     }
     if (cur >= 0) {
@@ -239,7 +239,7 @@ static void enqueue_step(mrh_batch* b, hipStream_t s, uint32_t alloc_wgs, uint32
         else hipLaunchKernelGGL(k_batch_rays<false>, dim3(ray_wgs), dim3(256), 0, s, b->d_maps, b->d_ents, n);
         hipLaunchKernelGGL(k_batch_touch, dim3((unsigned)n * kBatchTouchWgs), dim3(256), 0, s, b->d_maps, b->d_ents, n);
     }
-    // at least one workgroup per map: workgroup i carries map i's update-side hand-off
+    // at least one workgroup per map, since each map's update-side hand-off takes duty_parts(grid / n) of them
     const dim3 ug((unsigned)(b->update_wgs > n ? b->update_wgs : n)), ub((unsigned)(64 * b->update_waves));
     auto update = [&](auto kind, auto w) {
         constexpr int K = decltype(kind)::value;

@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256) void k_alloc_depth(const DevMap* __restrict__ 
 
 // One wave per workgroup: tasks take from 1 us (hidden block) to 10 us or more and a launch has about two per
 // wave the chip holds, so the dispatcher hands a task to each wave that becomes free, where workgroups of four
-// waves and a stride left the last waves alone (640 x 480 room frames: 29.1 -> 27.0 us; 203 x 157: equal).
+// waves and a stride left the last waves alone (640 x 480 room frames: 29.1 -> 26.7 us, with the straight-line voxels; 203 x 157: equal).
 // 8192 workgroups: more than the tasks of most frames; the others take a second one.
 template <int ST, bool COLOR>
 __global__ __launch_bounds__(64) void k_integrate_depth(const DevMap* __restrict__ pm, DepthFrame f,
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(64) void k_integrate_depth(const DevMap* __restrict
     const uint32_t ntask = update_task_count(n);
     TaskStats ts;
     for (uint32_t t = wave; t < ntask; t += nwaves)
-        ts.add_uniform(depth_update_task<ST, COLOR>(m, f, rgb, t, n));
+        ts.add(depth_update_task<ST, COLOR>(m, f, rgb, t, n));
     flush_task_stats(m, ts, true);
 }
 

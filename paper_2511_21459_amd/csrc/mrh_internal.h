@@ -32,7 +32,6 @@ namespace mrh {
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
 
 // The atomics of the HIP headers (relaxed, device scope) on global pointers.
 using ::atomicAdd;
@@ -397,25 +396,6 @@ __device__ inline T group8_sum(T v) {
     v += dpp<kDppXor2>(v);
     return v + dpp<kDppHalfMirror>(v);
 }
-// The same for min / max (exact, so the order does not matter).
-template <typename T>
-__device__ inline T group8_min(T v) {
-    v = min(v, dpp<kDppXor1>(v));
-    v = min(v, dpp<kDppXor2>(v));
-    return min(v, dpp<kDppHalfMirror>(v));
-}
-template <typename T>
-__device__ inline T group8_max(T v) {
-    v = max(v, dpp<kDppXor1>(v));
-    v = max(v, dpp<kDppXor2>(v));
-    return max(v, dpp<kDppHalfMirror>(v));
-}
-__device__ inline double group8_fmin(double v) {
-    v = __builtin_fmin(v, dpp<kDppXor1>(v));
-    v = __builtin_fmin(v, dpp<kDppXor2>(v));
-    return __builtin_fmin(v, dpp<kDppHalfMirror>(v));
-}
-
 // Sum over each 16-lane row (group8_sum, then the row's other half by the row mirror).
 template <typename T>
 __device__ inline T row16_sum(T v) {
@@ -468,15 +448,8 @@ __device__ inline void stat_add(const DevMap& m, int s, unsigned long long v) {
     if (v) atomicAdd(&m.ctr->frame[(blockIdx.x + 7u * blockIdx.y) % kStripes][s], v);
 }
 
-// Morton (Z-order) position of voxel (i, j, k) inside a block of side 8 >> level, x lowest bit.
-__host__ __device__ inline int morton3(int i, int j, int k) {
-    int p = 0;
-    for (int b = 0; b < 3; ++b) p |= (((i >> b) & 1) << (3 * b)) | (((j >> b) & 1) << (3 * b + 1)) | (((k >> b) & 1) << (3 * b + 2));
-    return p;
-}
-
-// The bits of a coordinate below 8 at every third position: morton3(i, j, k) is
-// spread3(i) | spread3(j) << 1 | spread3(k) << 2.
+// The bits of a coordinate below 8 at every third position: the Morton (Z-order) position of voxel (i, j, k)
+// in its block is spread3(i) | spread3(j) << 1 | spread3(k) << 2.
 __host__ __device__ inline int spread3(int x) { return (x & 1) | ((x & 2) << 2) | ((x & 4) << 4); }
 
 __host__ __device__ inline void demorton3(int p, int& i, int& j, int& k) {

@@ -1,7 +1,7 @@
 // LiDAR fusion work units (Sec. 3.1 "3D Point Cloud", Eq. 1; Eq. 3 and Eq. 5; Sec. 3.2.1),
 // shared by the single-map kernels (points.hip) and the batched kernels (batch.hip).
 //
-//   points_alloc_chunk  16 rays: validity, segment [o, p + tau n] (carving) or the band
+//   points_alloc_chunk  4 to 16 rays: validity, segment [o, p + tau n] (carving) or the band
 //                       [p - tau n, p + tau n], walk over the block lattice,
 //                       insert, and the record of the hash slots of each ray's blocks in walk order
 //   points_ray_chunk    4 to 16 rays: their recorded (ray, block) pairs in parallel; inside each block a
@@ -108,8 +108,8 @@ constexpr int kAllocNew = 512;  // new blocks a workgroup registers together
 // place of a boundary in it is its index plus the boundaries of the other two axes before it, and the
 // block behind it follows from the same counts: every block is found on its own, one thread per block,
 // with no chain along the ray.  Walked step by step, a launch took as long as its longest ray, about
-// 250 blocks, whatever the number of rays: 8000 points 209 us, 131072 points 205 us (614 us into an empty
-// map); now 60, 92 and 241 us.
+// 250 blocks, whatever the number of rays: first, second and a later scan of 8000 points in a room 197, 92 and
+// 90 us, so 117, 15 and 11; of 131072 points 493, 131 and 131 us, so 272, 61 and 55.
 __device__ inline void points_alloc_chunk(const DevMap& m, const ScanParams& sp, uint32_t chunk) {
     __shared__ RayAxis axes[kAllocRaysPerGroup][3];
     __shared__ uint32_t sfirst[kAllocRaysPerGroup + 1];
@@ -614,8 +614,9 @@ __device__ inline void ray_fine_block(const DevMap& m, const double o[3], const 
 // front and levels 1 and 2 from the back.  Then full waves of waiting pairs of like length walk their
 // blocks.  Reads and atomics are kept apart because a wave's memory operations complete in order: a
 // read issued behind the walk's atomics, performed beyond the L2, waits for them (which is also why
-// the touched groups are gathered in LDS).  131072 points, with the queueing launch: 493 -> 335 us on a
-// settled map, 1718 -> 1220 us into an empty one (27 M atomics at 22 G/s, the rate that bounds it).
+// the touched groups are gathered in LDS).  First, second and a later scan of 131072 points in a room:
+// 1495, 891 and 270 us by the walk of each ray, so 1050, 496 and 145 (the first has 27 M atomics, and their
+// rate, about 25 G/s, bounds it).
 // The blocks of a ray beyond the recorded rcap_k are walked afterwards by one thread per ray, through
 // the same two steps.
 template <bool WIDE>
@@ -774,9 +775,8 @@ struct UnitOut {
 // The scan's observations of four voxels of level-0 blocks per lane (at[k], where on[k]) into their state, the
 // accumulators left at zero.  fresh: the state is empty and is written where no observation fell, too.  A
 // lane owns voxels, not groups of eight, so that the lanes of a group read and write its 32 and 64 bytes
-// together: with 16 bytes per lane and access the launch was bound by the L2's requests (100 M of them, 2.9 GB
-// of misses, for 131072 points into an empty map: 860 us, now 702 or 4.1 TB/s).  All reads of a step are
-// issued before any is used.
+// together: with 16 bytes per lane and access the launch was bound by the L2's requests (100 M of them for
+// 131072 points into an empty map: 860 us, and 702 so).  All reads of a step are issued before any is used.
 constexpr int kVoxelStep = 4;
 template <int ST, bool WIDE>
 __device__ inline void apply_voxels(const DevMap& m, const size_t at[kVoxelStep], const bool on[kVoxelStep], bool fresh,

@@ -67,7 +67,6 @@ struct Store;
 
 template <>
 struct Store<MRH_STORE_F32> {
-    static constexpr int kBytes = 12;
     __device__ static inline u32x2 MRH_GLOBAL* dw(const DevMap& m, int lvl) { return (u32x2 MRH_GLOBAL*)m.DW[lvl]; }
     __device__ static inline float MRH_GLOBAL* s2(const DevMap& m, int lvl) { return (float MRH_GLOBAL*)m.S2[lvl]; }
     // (the lanes' levels may differ)
@@ -114,7 +113,6 @@ struct Store<MRH_STORE_F32> {
 // shared by the two 16-bit formats: D codec and W codec differ, the variance plane is half
 template <int ST>
 struct Store16 {
-    static constexpr int kBytes = 6;
     __device__ static inline float decD(const DevMap& m, uint16_t b) {
         return (ST == MRH_STORE_F16 ? f16_to_f32(b) : bf16_to_f32(b)) * m.tau_f;
     }

@@ -428,17 +428,8 @@ struct TaskOut {
 // Statistics gathered by one wave over its tasks.
 struct TaskStats {
     unsigned long long obs = 0, fresh = 0, merge0 = 0, merge1 = 0, merge2 = 0, distinct = 0;
+    // the counts are wave-uniform and summed in scalar registers, of which the kernels have more to spare
     __device__ inline void add(const TaskOut& o) {
-        obs += o.obs;
-        fresh += o.fresh;
-        merge0 += o.merge0;
-        merge1 += o.merge1;
-        merge2 += o.merge2;
-        distinct += o.distinct;
-    }
-    // the same with the (wave-uniform) counts summed in scalar registers: for kernels that are
-    // short of vector registers but not of scalar ones
-    __device__ inline void add_uniform(const TaskOut& o) {
         obs += uniform(o.obs);
         fresh += uniform(o.fresh);
         merge0 += uniform(o.merge0);
@@ -563,7 +554,8 @@ __device__ inline void update_duties(const DevMap& m, int par, uint32_t part, ui
     }
 }
 
-// The part of a launch's hand-off that workgroup `local` of `count` runs, among the last kDutyParts.
+// How many of `count` workgroups share a hand-off.  In its launch exactly that many must call alloc_duties
+// or update_duties, with parts 0 .. below it: the last of them settles the counts (duty_done).
 __device__ inline uint32_t duty_parts(uint32_t count) { return count < kDutyParts ? count : kDutyParts; }
 
 // Queue block `id` on the update list of `level` (level < 0 queues nothing).  Called by every

@@ -49,7 +49,7 @@ __global__ __launch_bounds__(256) void k_apply_points(const DevMap* __restrict__
     unsigned long long m0 = 0, m1 = 0;
     TaskStats as;
     for (uint32_t t = wave; t < ntask; t += nwaves) {
-        as.add_uniform(points_update_task<ST, WIDE>(m, t, n, par, &dl, lds[wv]));
+        as.add(points_update_task<ST, WIDE>(m, t, n, par, &dl, lds[wv]));
         if (!dl.ready(kApplyBlocks)) run_deferred<ST>(m, dl, par, m0, m1);
     }
     run_deferred<ST>(m, dl, par, m0, m1);
