@@ -239,9 +239,9 @@ __global__ __launch_bounds__(256) void k_extract(const DevMap* __restrict__ pm, 
                 const size_t base = (size_t)(info & kSlotMask) * 512 + p;
                 float dd[8], ss[8];
                 uint32_t ww[8];
-    #pragma unroll
+#pragma unroll
                 for (int k = 0; k < 8; ++k) Store<ST>::get(m, 0, base + (spread3(k) << 2), dd[k], ww[k], ss[k]);
-    #pragma unroll
+#pragma unroll
                 for (int k = 0; k < 8; ++k) out(off + lane + 64 * k, dd[k], ww[k], ss[k]);
             }
         }
