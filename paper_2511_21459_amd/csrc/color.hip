@@ -48,13 +48,13 @@ __global__ __launch_bounds__(256) void k_extract_color(const DevMap* __restrict_
             } else {
                 const float MRH_GLOBAL* c = m.C[0] + 1536 * (size_t)(info & kSlotMask);
                 float f[24];
-    #pragma unroll
+#pragma unroll
                 for (int k = 0; k < 24; ++k) {
                     const int q = lane + 64 * k, x = q / 3;
                     const uint32_t p = spread3(x & 7) | spread3((x >> 3) & 7) << 1 | spread3(x >> 6) << 2;
                     f[k] = c[3 * p + (uint32_t)(q - 3 * x)];
                 }
-    #pragma unroll
+#pragma unroll
                 for (int k = 0; k < 24; ++k) o[64 * k] = f[k];
             }
         }
